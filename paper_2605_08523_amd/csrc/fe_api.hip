@@ -25,14 +25,15 @@ namespace {
 constexpr int64_t kStreamKMinN = 1536;   // workspaces for n >= this carry stream-K buffers
 
 // Schedule of the split-precision layer kernel (FE_SCHEDULE=dp|sk|sk2 overrides):
-//  0 data-parallel, 128 x 128 tiles, one workgroup per upper tile;
+//  0 data-parallel, one workgroup per upper tile (the tile by size: split_ring_tile);
 //  1 stream-K over 256 x 256 tiles, one workgroup per CU;
 //  2 stream-K over 128 x 128 tiles, two workgroups per CU (whole-tile rounds first when there
 //    are two or more rounds).
 // Order: a schedule forced by the tuner, FE_SCHEDULE, the tuned table (fe_autotune), then the
-// default: 2 when every stream-K workgroup gets at least eight K-blocks (else the partial-tile
-// traffic outweighs the balance: measured slower below N ~ 2000), otherwise 0. Only workspaces
-// sized for n >= kStreamKMinN carry the stream-K buffers.
+// default: 0 where all data-parallel tiles run at once (split_ring_tile has the figures), else 2
+// when every stream-K workgroup gets at least eight K-blocks (with fewer the partial-tile traffic
+// outweighs the balance), otherwise 0. Only workspaces sized for n >= kStreamKMinN carry the
+// stream-K buffers.
 // Schedules chosen by fe_autotune: (device, precision, size) -> schedule, process-wide. A
 // size uses the entry of the nearest tuned size within a factor sqrt(2).
 struct TunedEntry {
@@ -88,6 +89,7 @@ int use_streamk(int64_t n, const fe_workspace* ws, int prec) {
     if (env && env[0] == 's') return strcmp(env, "sk2") == 0 ? 2 : 1;
     const int tuned = tuned_schedule(ws->device, prec, n);
     if (tuned >= 0) return tuned;
+    if (fe::split_ring_tile(n, ws->n_cu)) return 0;
     const int64_t np = round_up(n, 128), T = np / 128, ntiles = T * (T + 1) / 2, nk = np / 64;
     const int64_t grid = 2 * (int64_t)ws->n_cu;
     const int64_t rounds = ntiles / grid;
@@ -187,12 +189,13 @@ int run_expansion(const double* H, int64_t n, int64_t ldh, double mu, double kT,
     } else if (split) {
         fe::SplitPlan plan{};
         plan.streamk = three ? 0 : use_streamk(n, ws, prec);   // three parts: data-parallel
+        plan.ring_tile = plan.streamk ? 0 : fe::split_ring_tile(n, ws->n_cu);
         plan.grid = plan.streamk == 2 ? 2 * ws->n_cu : ws->n_cu;
         plan.partial = ws->sk_partial;
         plan.own = ws->sk_partial ? ws->sk_partial + (size_t)ws->n_cu * 256 * 256 : nullptr;
         plan.flags = ws->sk_flags;
         plan.err = ws->sk_err;
-        const int tile = fe::split_tile_for(plan.streamk);
+        const int tile = plan.ring_tile ? plan.ring_tile : fe::split_tile_for(plan.streamk);
         const int64_t np = round_up(n, tile);
         if (np > ws->np_cap) return fail(FE_ERR_WORKSPACE, "padded size exceeds the workspace");
         SplitBufs b = carve_split(ws->slot[which], np, three);
@@ -849,6 +852,7 @@ extern "C" int fe_expand_density_noalloc(const double* H, int64_t n, int64_t ldh
     w.params = reinterpret_cast<fe::Params*>(base + kNoAllocParamsOff);
     w.bparts = reinterpret_cast<fe::BoundsPartial*>(base + kNoAllocBoundsOff);
     w.tparts = reinterpret_cast<fe::TracePartial*>(base + kNoAllocTracesOff);
+    FE_HIP(hipDeviceGetAttribute(&w.n_cu, hipDeviceAttributeMultiprocessorCount, dev));
     const bool corr = final_correction && (prec == FE_PREC_FP16X2 || prec == FE_PREC_BF16X2);
     return run_expansion(H, n, ldh, mu, kT, m, prec, 1.0, 0, D, d_is_fp64, ldd, trD, trD2, nullptr,
                          info, &w, static_cast<hipStream_t>(stream), 0, true, corr);

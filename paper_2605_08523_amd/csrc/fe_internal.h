@@ -103,7 +103,9 @@ struct LayerArgs {
 };
 // Schedule of the split-precision layer kernel.
 struct SplitPlan {
-    int streamk;          // 0: one workgroup per 128 x 128 upper tile; 1: persistent stream-K
+    int streamk;          // 0: one workgroup per upper tile; 1: persistent stream-K
+    int ring_tile;        // streamk = 0: tile of the one-round kernel (split_ring_tile), or 0 for the
+                          // 128 x 128 kernel of more rounds
     int grid;             // stream-K workgroups (one per CU)
     int groups;           // stream-K groups (8: one per XCD), set by the launcher
     int dp_tiles;         // leading tiles computed whole (data-parallel rounds), set by the launcher
@@ -117,6 +119,9 @@ struct SplitPlan {
     int* err;             // set to 1 if a bounded wait gave up
 };
 int split_tile_for(int streamk);
+// Tile of the data-parallel kernel whose workgroups all run at once at size n on n_cu compute
+// units: 64, 128, or 0 where the tiles need more than one round.
+int split_ring_tile(int64_t n, int n_cu);
 // The stream-K plan the launcher uses for a padded size np, schedule 1 or 2, at most grid
 // workgroups (host; see streamk_plan.h).
 SkGeometry split_sk_geometry(int64_t np, int streamk, int grid);

@@ -14,7 +14,9 @@
 //    traces. In the squared-affine form (FP16x2 default) the operand is the shifted state
 //    x + b/(2a), so b = 0 and X is neither read nor written.
 //  * Three schedules:
-//      data-parallel: one workgroup per upper tile (128 x 128, four 64 x 64 wave tiles);
+//      data-parallel: one workgroup per upper tile: 64 x 64 or 128 x 128 tiles with direct-to-LDS
+//        operand loads where all tiles run at once (split_ring_tile), else 128 x 128 (four
+//        64 x 64 wave tiles, register-staged);
 //      stream-K over 128 x 128 tiles, two persistent workgroups per CU: the (tile, K-block)
 //        iterations left after the whole-tile rounds are split evenly. A workgroup that stops
 //        inside a tile publishes its FP32 partial; the workgroup that finishes the tile adds the
@@ -40,7 +42,15 @@ using CfgSK2 = Cfg<128, 2, 2, 64, 128, 1>;   // stream-K over 128 x 128 tiles, t
 // Three-part BF16 split: six panels of 32-deep K-blocks in one LDS stage (61 KiB), so two
 // workgroups still fit per CU; data-parallel only.
 using CfgDP3 = Cfg<128, 2, 2, 32, 128, 1, 0, 3>;
-
+// One-round layers (k_layer_ring): 64 x 64 tiles of four 32 x 32 waves, two workgroups per CU, and
+// 128 x 128 tiles of eight 32 x 64 waves, one workgroup per CU. 64-deep K-blocks: a panel row is one
+// 128-byte line (32-deep blocks fetch every line twice: 4-8% slower); the three-part split's six
+// panels take 32-deep ones.
+using CfgR64 = Cfg<64, 2, 2, 64, 64, 2, 1>;
+using CfgR128 = Cfg<128, 4, 2, 64, 128, 2, 1>;
+using CfgR64x3 = Cfg<64, 2, 2, 32, 64, 3, 1, 3>;
+using CfgR128x3 = Cfg<128, 4, 2, 32, 128, 3, 1, 3>;
+static_assert(2 * CfgR64::LDS_BYTES <= 160 * 1024 && 2 * CfgR64x3::LDS_BYTES <= 160 * 1024, "two per CU");
 
 template <class C>
 __device__ inline void zero(Acc<C>& acc) {
@@ -69,6 +79,35 @@ k_layer_dp(LayerArgs p) {
         kloop<BF, C>(p.hi_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM, 0,
                      (int)(p.np / C::BK), acc, reinterpret_cast<uint16_t*>(smem));
     epilogue<BF, C>(p, acc, reinterpret_cast<float*>(smem), I, J, t);
+}
+
+// Data-parallel layer whose upper tiles all run at once: one workgroup per tile, operands straight to
+// LDS through the ring of stages (kloop_dma), and (64 x 64 tiles) the epilogue's X and A groups
+// loaded before the K loop. Bound by latency rather than by the MFMA rate: at n = 1001 a layer takes
+// 18 us, of which 2.2 are the launch, 4.3 the epilogue and 9.5 the K loop (its 64 K steps of MFMAs
+// alone 4.5, its loads alone 4.8: the LDS port carries both). The 64 x 64 tiles take the same sums in
+// the same order as k_layer_dp. The two-part 128 x 128 ones, whose sizes (n > 1984) ran stream-K
+// before, sum K in segments of 512, as that schedule's partial tiles did at n = 2048: one chain of
+// 2048 gave 1.45 times its error against FP64.
+template <bool BF, class C>
+__global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_layer_ring(LayerArgs p) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int T = (int)(p.np / C::BM);
+    const int t = xcd_tile(blockIdx.x, gridDim.x);
+    int I, J;
+    tile_coords(t, T, I, J);
+    constexpr bool kPre = EpiPre<C>::PER <= 4;
+    constexpr int kSeg = C::BM == 128 && C::NS == 2 ? 512 / C::BK : 0;
+    EpiPre<C> pre;
+    if constexpr (kPre) pre.load(p, I, J);
+    Acc<C> acc;
+    zero(acc);
+    kloop_dma<BF, C, kSeg>(p.hi_in, p.mid_in, p.lo_in, p.np, (int64_t)I * C::BM,
+                           (int64_t)J * C::BM, 0, (int)(p.np / C::BK), acc,
+                           reinterpret_cast<uint16_t*>(smem));
+    epilogue<BF, C, kPre ? 8 : 2, kPre>(p, acc, reinterpret_cast<float*>(smem), I, J, t, nullptr, 0,
+                                        0, false, &pre);
 }
 
 // Thread 0 waits until the workgroups of group g with indices jlo .. j-1 have published their
@@ -184,6 +223,17 @@ hipError_t launch_dp(const LayerArgs& a, hipStream_t s) {
 }
 
 template <bool BF, class C>
+hipError_t launch_ring(const LayerArgs& a, hipStream_t s) {
+    auto kern = k_layer_ring<BF, C>;
+    static bool done = false;
+    hipError_t e = set_lds(kern, C::LDS_BYTES, done);
+    if (e != hipSuccess) return e;
+    const int T = (int)(a.np / C::BM);
+    hipLaunchKernelGGL(kern, dim3(T * (T + 1) / 2), dim3(C::NT), C::LDS_BYTES, s, a);
+    return hipGetLastError();
+}
+
+template <bool BF, class C>
 hipError_t launch_sk(const LayerArgs& a, const SplitPlan& sk, hipStream_t s) {
     auto kern = k_layer_sk<BF, C>;
     static bool done = false;
@@ -218,6 +268,22 @@ hipError_t launch_sk(const LayerArgs& a, const SplitPlan& sk, hipStream_t s) {
 
 }  // namespace
 
+// Where the line lies (ms per density matrix, 26 layers, random dense; 256 CUs): two 64 x 64 tiles
+// fit a CU, so up to 512 of them run at once (n <= 1984): n = 1001 0.48 against 1.15 with 128 x 128
+// register-staged tiles, 1984 1.07 against 1.83 (stream-K) and 1.28 (128 x 128 ring); 528 tiles at
+// n = 2048 need a second round for 16 of them: 1.58 against 1.29 for the 128 x 128 ring, which takes
+// one round up to n = 2816 (2.13 against 2.62 for stream-K); at n = 2900 its second round makes
+// it 3.61 against 2.94.
+int split_ring_tile(int64_t n, int n_cu) {
+    auto tiles = [n](int64_t bm) {
+        const int64_t T = (n + bm - 1) / bm;
+        return T * (T + 1) / 2;
+    };
+    if (tiles(CfgR64::BM) <= 2 * (int64_t)n_cu) return CfgR64::BM;
+    if (tiles(CfgR128::BM) <= n_cu) return CfgR128::BM;
+    return 0;
+}
+
 int split_tile_for(int streamk) {
     static_assert(CfgDP3::BM == CfgDP::BM, "the three-part split runs the data-parallel tile");
     return streamk == 1 ? CfgSK::BM : streamk == 2 ? CfgSK2::BM : CfgDP::BM;
@@ -229,6 +295,18 @@ SkGeometry split_sk_geometry(int64_t np, int streamk, int grid) {
 }
 
 hipError_t launch_layer_split(const LayerArgs& a, int bf16, const SplitPlan& plan, hipStream_t s) {
+    if (plan.streamk == 0 && plan.ring_tile != 0) {
+        if (a.np % plan.ring_tile != 0) return hipErrorInvalidValue;
+        if (plan.ring_tile == CfgR64::BM)
+            return bf16 == 2 ? launch_ring<true, CfgR64x3>(a, s)
+                   : bf16    ? launch_ring<true, CfgR64>(a, s)
+                             : launch_ring<false, CfgR64>(a, s);
+        if (plan.ring_tile == CfgR128::BM)
+            return bf16 == 2 ? launch_ring<true, CfgR128x3>(a, s)
+                   : bf16    ? launch_ring<true, CfgR128>(a, s)
+                             : launch_ring<false, CfgR128>(a, s);
+        return hipErrorInvalidValue;
+    }
     if (bf16 == 2) {   // three-part BF16 split: data-parallel schedule only
         if (plan.streamk != 0) return hipErrorInvalidValue;
         return launch_dp<true, CfgDP3>(a, s);

@@ -166,9 +166,9 @@ struct Cfg {
     static_assert(WAVE_M % 32 == 0 && WAVE_N % 32 == 0, "wave tile");
     static_assert(BM % EC == 0 && EC % 32 == 0 && (EC * BM) % NT == 0, "epilogue chunk");
     static_assert(EC % 16 == 0 && LDY % 4 == 0, "vectorised epilogue");
-    static_assert(!DMA || (STAGES == 2 && BK >= 16 && BK <= 64 && (4 * BM * BK / 512) % (NT / 64) == 0),
+    static_assert(!DMA || (STAGES >= 2 && BK >= 32 && BK <= 64 && (2 * NS * BM * BK / 512) % (NT / 64) == 0),
                   "direct-to-LDS staging");
-    static_assert(NS == 2 || (NS == 3 && STAGES == 1 && !DMA), "three-part split: one register-staged stage");
+    static_assert(NS == 2 || (NS == 3 && (DMA || STAGES == 1)), "three-part split: register staging has one stage");
 };
 
 // N groups of (M MFMAs, one LDS read) for the scheduler.
@@ -188,23 +188,30 @@ struct Acc {
 
 // Direct-to-LDS form of the K loop (C::DMA): each lane's global_load_lds_dwordx4 moves one
 // 16-byte chunk, and the 64 chunks of one instruction land in 1 KiB of LDS in lane order. A stage
-// holds the four BM x BK operand panels (A hi, A lo, B hi, B lo) in unpadded rows; chunk c of row
+// holds the 2 NS BM x BK operand panels (A parts, then B parts) in unpadded rows; chunk c of row
 // r sits at position c ^ ((r / RP) % CPR) of its row (RP rows per 128 bytes), so the eight rows
-// that a quarter-wave's fragment read touches fall on distinct banks. Two stages: block kb + 1
-// is in flight while block kb is multiplied. The barrier is a bare s_barrier after an explicit
-// wait for this wave's own loads (a full __syncthreads would also drain everything else in
-// flight); the fragment reads of the next K step are interleaved with the current step's MFMAs.
-template <bool BF, class C>
-__device__ inline void kloop_dma(const uint16_t* __restrict__ hin, const uint16_t* __restrict__ lin,
-                                 int64_t np, int64_t I0, int64_t J0, int kb0, int kb1, Acc<C>& acc,
-                                 uint16_t* smem) {
+// that a quarter-wave's fragment read touches fall on distinct banks. The stages form a ring:
+// while block kb is multiplied, the next STAGES - 1 blocks are in flight, so a short K loop whose
+// operands come from beyond the L2 (another XCD wrote them) pays that latency once and not per
+// block. SEG > 0: the blocks are summed in segments of SEG, each from zero, and the segments' sums
+// added (a long K loop then rounds like the stream-K schedules' partial sums, not like one
+// chain). The barrier is a bare s_barrier after an explicit wait for this wave's own loads of block
+// kb (a full __syncthreads would also drain everything else in flight) and for its fragment reads
+// of block kb - 1, whose stage is refilled right after it. Blocks, K steps and products are taken
+// in the order of the register-staged loops, so an element's sum does not depend on the form.
+template <bool BF, class C, int SEG = 0>
+__device__ inline void kloop_dma(const uint16_t* __restrict__ hin, const uint16_t* __restrict__ min,
+                                 const uint16_t* __restrict__ lin, int64_t np, int64_t I0,
+                                 int64_t J0, int kb0, int kb1, Acc<C>& acc, uint16_t* smem) {
     typedef __attribute__((address_space(3))) void lds_void;
     typedef const __attribute__((address_space(1))) void global_void;
+    constexpr int NS = C::NS, S = C::STAGES;
     constexpr int CPR = C::BK / 8, RP = 8 / CPR > 0 ? 8 / CPR : 1, RPI = 64 / CPR;
     constexpr int IPA = C::BM / RPI;                      // 1-KiB instructions per panel and stage
-    constexpr int NW = C::NT / 64, IPW = 4 * IPA / NW;    // per wave and stage
-    constexpr int PANEL = C::BM * C::BK, STAGE = 4 * PANEL;
+    constexpr int NW = C::NT / 64, IPW = 2 * NS * IPA / NW;   // per wave and stage
+    constexpr int PANEL = C::BM * C::BK, STAGE = 2 * NS * PANEL;
     static_assert((RPI / RP) % CPR == 0, "a lane's chunk position is the same in every instruction");
+    static_assert(2 * NS * IPA % NW == 0 && IPW * (S - 1) < 64, "in-flight loads fit the wait counter");
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = tid >> 6;
@@ -218,92 +225,137 @@ __device__ inline void kloop_dma(const uint16_t* __restrict__ hin, const uint16_
     int dst[IPW];
 #pragma unroll
     for (int q = 0; q < IPW; ++q) {
-        const int gi = wave_u + q * NW, a = gi / IPA, blk = gi % IPA;
-        src[q] = ((a & 1) ? lin : hin) + ((a < 2 ? I0 : J0) + blk * RPI) * np;
+        const int gi = wave_u + q * NW, a = gi / IPA, blk = gi % IPA, part = a % NS;
+        const uint16_t* base = part == 0 ? hin : (NS == 3 && part == 1) ? min : lin;
+        src[q] = base + ((a < NS ? I0 : J0) + blk * RPI) * np;
         dst[q] = a * PANEL + blk * RPI * C::BK;
     }
-    auto issue = [&](int kb, uint16_t* stage) {
+    auto issue = [&](int kb, uint16_t* stage, int q0, int q1) {
         const int64_t k0 = (int64_t)kb * C::BK;
 #pragma unroll
-        for (int q = 0; q < IPW; ++q)
+        for (int q = q0; q < q1; ++q)
             __builtin_amdgcn_global_load_lds((global_void*)(src[q] + k0 + lane_off),
                                              (lds_void*)(stage + dst[q]), 16, 0, 0);
     };
     const int frag_row = lane & 31, frag_c = lane >> 5;
     struct Frag {
-        u32x4 ah[C::MB], al[C::MB], bh[C::NB], bl[C::NB];
+        u32x4 a[C::MB][NS], b[C::NB][NS];
     };
     auto ld = [&](const uint16_t* stage, int ks, Frag& f) {
 #pragma unroll
         for (int mb = 0; mb < C::MB; ++mb) {
             const int r = wm * C::WAVE_M + mb * 32 + frag_row;
             const int o = r * C::BK + swz(r, ks * 2 + frag_c) * 8;
-            f.ah[mb] = *reinterpret_cast<const u32x4*>(stage + o);
-            f.al[mb] = *reinterpret_cast<const u32x4*>(stage + PANEL + o);
+#pragma unroll
+            for (int t = 0; t < NS; ++t) f.a[mb][t] = *reinterpret_cast<const u32x4*>(stage + t * PANEL + o);
         }
 #pragma unroll
         for (int nb = 0; nb < C::NB; ++nb) {
             const int r = wn * C::WAVE_N + nb * 32 + frag_row;
             const int o = r * C::BK + swz(r, ks * 2 + frag_c) * 8;
-            f.bh[nb] = *reinterpret_cast<const u32x4*>(stage + 2 * PANEL + o);
-            f.bl[nb] = *reinterpret_cast<const u32x4*>(stage + 3 * PANEL + o);
+#pragma unroll
+            for (int t = 0; t < NS; ++t)
+                f.b[nb][t] = *reinterpret_cast<const u32x4*>(stage + (NS + t) * PANEL + o);
         }
     };
     auto mm = [&](const Frag& f) {
 #pragma unroll
         for (int mb = 0; mb < C::MB; ++mb) {
-            const u32x4 ahs = scale_hi<BF>(f.ah[mb]);
+            if constexpr (NS == 3) {
 #pragma unroll
-            for (int nb = 0; nb < C::NB; ++nb)
-                acc.v[mb][nb] = mfma3<BF>(ahs, f.ah[mb], f.al[mb], f.bh[nb], f.bl[nb], acc.v[mb][nb]);
+                for (int nb = 0; nb < C::NB; ++nb) acc.v[mb][nb] = mfma6(f.a[mb], f.b[nb], acc.v[mb][nb]);
+            } else {
+                const u32x4 ahs = scale_hi<BF>(f.a[mb][0]);
+#pragma unroll
+                for (int nb = 0; nb < C::NB; ++nb)
+                    acc.v[mb][nb] = mfma3<BF>(ahs, f.a[mb][0], f.a[mb][1], f.b[nb][0], f.b[nb][1],
+                                              acc.v[mb][nb]);
+            }
         }
     };
-    // Scheduling of one step: the hi scaling first, then each fragment read of the next step
-    // between MFMAs of this one.
-    constexpr int NDS = 2 * (C::MB + C::NB), NMF = 3 * C::MB * C::NB;
+    // Scheduling of one step: this step's share of the loads that refill the free stage, the hi
+    // scaling, then the fragment reads of the next step, spread between this step's MFMAs where it
+    // has enough of them, else ahead of them.
+    constexpr int KS = C::BK / 16;
+    static_assert(KS % 2 == 0, "two fragment sets");
+    constexpr int NDS = NS * (C::MB + C::NB), NMF = (NS == 3 ? 6 : 3) * C::MB * C::NB;
     constexpr int PER = NMF >= 2 * NDS ? 2 : 1;   // MFMAs between two fragment reads
-    static_assert(NMF >= PER * NDS, "interleave pattern");
     auto pattern = [&](bool reads) {
-        __builtin_amdgcn_sched_group_barrier(0x002, 4 * C::MB, 0);
-        if (reads) {
-            sgb_interleave<NDS, PER>();
-            __builtin_amdgcn_sched_group_barrier(0x008, NMF - PER * NDS, 0);
-        } else {
+        if constexpr (NMF >= PER * NDS) {
+            __builtin_amdgcn_sched_group_barrier(0x002, 4 * C::MB, 0);
+            if (reads) {
+                sgb_interleave<NDS, PER>();
+                __builtin_amdgcn_sched_group_barrier(0x008, NMF - PER * NDS, 0);
+            } else {
+                __builtin_amdgcn_sched_group_barrier(0x008, NMF, 0);
+            }
+        } else if (reads) {
+            __builtin_amdgcn_sched_group_barrier(0x100, NDS, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 4 * C::MB, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, NMF, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    constexpr int KS = C::BK / 16;
-    static_assert(KS % 2 == 0, "two fragment sets");
-    auto compute = [&](const uint16_t* stage) {
+    // Multiplies the block in `stage`; fill: block `kbf` is loaded into `free` meanwhile, a part of
+    // its loads with each K step (issued in one piece they would hold every wave of the workgroup
+    // at the same point while the load path takes them, the MFMA pipes idle).
+    constexpr int FS = S == 2 ? (KS + 1) / 2 : KS;   // steps that carry loads (S = 2: the early ones)
+    auto compute = [&](const uint16_t* stage, bool fill, int kbf, uint16_t* free) {
         Frag f0, f1;
         ld(stage, 0, f0);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int ks = 0; ks < KS; ks += 2) {
-            ld(stage, ks + 1, f1);
-            mm(f0);
-            pattern(true);
-            if (ks + 2 < KS) {
-                ld(stage, ks + 2, f0);
-                mm(f1);
-                pattern(true);
-            } else {
-                mm(f1);
-                pattern(false);
-            }
+        for (int ks = 0; ks < KS; ++ks) {
+            if (ks < FS && fill) issue(kbf, free, ks * IPW / FS, (ks + 1) * IPW / FS);
+            __builtin_amdgcn_sched_barrier(0);
+            Frag& cur = ks & 1 ? f1 : f0;
+            Frag& nxt = ks & 1 ? f0 : f1;
+            if (ks + 1 < KS) ld(stage, ks + 1, nxt);
+            mm(cur);
+            pattern(ks + 1 < KS);
         }
     };
-    if (kb0 < kb1) issue(kb0, smem);
-    for (int kb = kb0; kb < kb1; ++kb) {
-        uint16_t* cur = smem + ((kb - kb0) & 1) * STAGE;
-        uint16_t* nxt = smem + (((kb - kb0) & 1) ^ 1) * STAGE;
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's chunks of block kb landed
+    const int nk = kb1 - kb0;
+#pragma unroll
+    for (int q = 0; q < S - 1; ++q)
+        if (q < nk) issue(kb0 + q, smem + q * STAGE, 0, IPW);
+    // lgkmcnt(0) and vmcnt(n) with n = the loads of the blocks after this one (6-bit counter)
+    constexpr int kAhead = IPW * (S - 2);
+    constexpr int kWait = 0x0070 | (kAhead & 15) | ((kAhead >> 4) << 14);
+    int slot = 0;
+    Acc<C> sum;
+    if constexpr (SEG > 0) sum = acc;
+    for (int i = 0; i < nk; ++i) {
+        if constexpr (SEG > 0) {
+            if (i % SEG == 0) {
+#pragma unroll
+                for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+                    for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+                        for (int j = 0; j < 16; ++j) {
+                            if (i > 0) sum.v[mb][nb][j] += acc.v[mb][nb][j];
+                            acc.v[mb][nb][j] = 0.0f;
+                        }
+            }
+        }
+        // this wave's chunks of block i landed (the last S - 2 blocks drain everything)
+        if (i + S - 2 < nk) __builtin_amdgcn_s_waitcnt(kWait);
+        else __builtin_amdgcn_s_waitcnt(0x0070);
         asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();          // ... and every wave's; nxt is no longer read
+        __builtin_amdgcn_s_barrier();          // ... and every wave's; block i - 1's stage is free
         asm volatile("" ::: "memory");
-        if (kb + 1 < kb1) issue(kb + 1, nxt);
-        compute(cur);
+        const int free = slot == 0 ? S - 1 : slot - 1;
+        compute(smem + slot * STAGE, i + S - 1 < nk, kb0 + i + S - 1, smem + free * STAGE);
+        slot = slot == S - 1 ? 0 : slot + 1;
+    }
+    if constexpr (SEG > 0) {
+#pragma unroll
+        for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) acc.v[mb][nb][j] += sum.v[mb][nb][j];
     }
     asm volatile("" ::: "memory");
     __syncthreads();
@@ -318,7 +370,7 @@ __device__ inline void kloop(const uint16_t* __restrict__ hin, const uint16_t* _
                              int64_t np, int64_t I0, int64_t J0, int kb0, int kb1, Acc<C>& acc,
                              uint16_t* smem) {
     if constexpr (C::DMA) {
-        kloop_dma<BF, C>(hin, lin, np, I0, J0, kb0, kb1, acc, smem);
+        kloop_dma<BF, C>(hin, nullptr, lin, np, I0, J0, kb0, kb1, acc, smem);
         return;
     }
     int tid = threadIdx.x;
@@ -462,6 +514,10 @@ __device__ inline void kloop3(const uint16_t* __restrict__ hin, const uint16_t* 
                               const uint16_t* __restrict__ lin, int64_t np, int64_t I0, int64_t J0,
                               int kb0, int kb1, Acc<C>& acc, uint16_t* smem) {
     static_assert(C::NS == 3, "three-part split");
+    if constexpr (C::DMA) {
+        kloop_dma<true, C>(hin, min, lin, np, I0, J0, kb0, kb1, acc, smem);
+        return;
+    }
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = tid >> 6;
@@ -617,6 +673,38 @@ __device__ inline floatx4 load4_coherent(__amdgpu_buffer_rsrc_t rs, int off) {
     return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kCoherentAux));
 }
 
+// The X and A groups of a tile that each thread's epilogue uses, loaded before the K loop: the layer
+// reads them from where the previous one left them, usually beyond this XCD's L2, and a short K
+// loop's epilogue would wait for that latency again. For tiles whose epilogue runs in one chunk.
+template <class C>
+struct EpiPre {
+    static constexpr int G = C::BM / 4, PER = C::EC * G / C::NT;
+    floatx4 x[PER], a[PER];
+    // Every address lies in the padded matrices, whose padding the rescale wrote; groups in the
+    // padding are loaded too and not used. a is loaded (and later read) only where the layer
+    // updates or outputs A.
+    __device__ inline void load(const LayerArgs& p, int I, int J) {
+        static_assert(C::EC == C::BM, "one epilogue chunk per tile");
+        const int64_t o = ((int64_t)I * C::BM) * p.np + (int64_t)J * C::BM;
+        const bool load_a = p.last != 0 || p.d_old != 0.0f || p.d_new != 0.0f;
+        auto at = [&](const float* m, int u) {
+            const int e = threadIdx.x + u * C::NT;
+            return *reinterpret_cast<const floatx4*>(m + o + (int64_t)(e / G) * p.np + (e % G) * 4);
+        };
+        if (p.affine == 0) {
+#pragma unroll
+            for (int u = 0; u < PER; ++u) x[u] = at(p.X, u);
+        } else {
+#pragma unroll
+            for (int u = 0; u < PER; ++u) x[u] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        if (load_a) {
+#pragma unroll
+            for (int u = 0; u < PER; ++u) a[u] = at(p.A, u);
+        }
+    }
+};
+
 // One chunk (tile rows R0 .. R0+EC-1) of the fused epilogue of tile (I, J), I <= J:
 //   Y = X^2 (from sY, or from the row-major BM x BM tile Y0 in memory if Y0 is set) plus the
 //   partial tiles parts[0..nparts-1] (part_stride floats apart, written by other workgroups and
@@ -634,11 +722,12 @@ __device__ inline floatx4 load4_coherent(__amdgpu_buffer_rsrc_t rs, int off) {
 //   (zero off the diagonal): X stays block diagonal, and the real block never sees a padded
 //   value. (Groups that straddle n are computed whole: their padded entries come out zero.)
 // Ends with a barrier (sY is free again).
-template <bool BF, class C, int UMAX>
+// pre (PRE): the tile's X and A groups, loaded before the K loop (EpiPre; one chunk per tile).
+template <bool BF, class C, int UMAX, bool PRE = false>
 __device__ inline void epi_chunk(const LayerArgs& p, float* sY, int R0, int I, int J,
                                  const float* __restrict__ Y0, const float* __restrict__ parts,
                                  size_t part_stride, int nparts, double& tr, double& sq,
-                                 bool poisoned) {
+                                 bool poisoned, const EpiPre<C>* pre = nullptr) {
     const int tid = threadIdx.x;
     const int64_t np = p.np;
     const int64_t I0 = (int64_t)I * C::BM, J0 = (int64_t)J * C::BM;
@@ -681,9 +770,14 @@ __device__ inline void epi_chunk(const LayerArgs& p, float* sY, int R0, int I, i
                          : *reinterpret_cast<const floatx4*>(sY + rl * C::LDY + c);
             if (nparts > 0)
                 bt.p[u] = load4_coherent(make_rsrc(parts, part_bytes), loc * (int)sizeof(float));
-            const floatx4 z{0.0f, 0.0f, 0.0f, 0.0f};
-            bt.x[u] = (use_x && live) ? *reinterpret_cast<const floatx4*>(X + gi) : z;
-            bt.a[u] = (load_a && live) ? *reinterpret_cast<const floatx4*>(A + gi) : z;
+            if constexpr (PRE) {
+                bt.x[u] = pre->x[b0 + u];
+                bt.a[u] = pre->a[b0 + u];
+            } else {
+                const floatx4 z{0.0f, 0.0f, 0.0f, 0.0f};
+                bt.x[u] = (use_x && live) ? *reinterpret_cast<const floatx4*>(X + gi) : z;
+                bt.a[u] = (load_a && live) ? *reinterpret_cast<const floatx4*>(A + gi) : z;
+            }
         }
     };
     auto finish_batch = [&](int b0, Batch& bt) {
@@ -852,10 +946,11 @@ __device__ inline void write_traces(const LayerArgs& p, double tr, double sq, fl
 // Fused epilogue of tile (I, J), I <= J, from the accumulators (which hold s X^2), plus optional
 // partial tiles of other workgroups (see epi_chunk). The accumulators go through sY EC rows at a
 // time. UMAX bounds the groups whose loads a thread keeps in flight (register budget).
-template <bool BF, class C, int UMAX = 8>
+template <bool BF, class C, int UMAX = 8, bool PRE = false>
 __device__ inline void epilogue(const LayerArgs& p, const Acc<C>& acc, float* sY, int I, int J,
                                 int tile_index, const float* __restrict__ parts = nullptr,
-                                size_t part_stride = 0, int nparts = 0, bool poisoned = false) {
+                                size_t part_stride = 0, int nparts = 0, bool poisoned = false,
+                                const EpiPre<C>* pre = nullptr) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / C::WN, wn = wave % C::WN;
     const float inv_s = BF ? 1.0f : (1.0f / 2048.0f);
@@ -880,8 +975,8 @@ __device__ inline void epilogue(const LayerArgs& p, const Acc<C>& acc, float* sY
             }
         }
         __syncthreads();
-        epi_chunk<BF, C, UMAX>(p, sY, R0, I, J, nullptr, parts, part_stride, nparts, tr, sq,
-                               poisoned);
+        epi_chunk<BF, C, UMAX, PRE>(p, sY, R0, I, J, nullptr, parts, part_stride, nparts, tr, sq,
+                                    poisoned, pre);
     }
     if (p.last) write_traces<C>(p, tr, sq, sY, tile_index);
 }

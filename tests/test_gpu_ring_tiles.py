@@ -1,0 +1,48 @@
+"""One-round data-parallel layers (64 x 64 and 128 x 128 tiles, direct-to-LDS operand ring) at the
+edges of their tiles and of the sizes they are chosen for (n <= 1984 and n <= 2816 on 256 compute
+units): they take the same products in the same order as the batch's register-staged 128 x 128
+kernel, so D is bitwise that of a batch of one. The traces are FP64 sums of the same values in
+another order: n^2 additions of at most 1 each, 2^-53 relative each. The two-part 128 x 128 tiles
+add their products in segments of 512 along K: against FP64 their D is no further off than the
+batch kernel's one chain."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def api():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_08523_amd import api as _api
+    _api.lib()
+    return _api
+
+
+@pytest.mark.parametrize("prec", ["fp16x2", "bf16x2", "bf16x3"])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 191, 449, 1983, 1985, 2816, 2817])
+def test_bitwise_equal_to_the_batch_kernel(api, paper_model, monkeypatch, n, prec):
+    monkeypatch.setenv("FE_SCHEDULE", "dp")   # n = 2817 takes the kernel of more rounds
+    print(f"case n={n} {prec}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    H = torch.randn((n, n), dtype=torch.float64, device="cuda", generator=g)
+    H = (H + H.T) / (2.0 * n ** 0.5)
+    D, tr, tr2, _ = api.expand_density(H, 0.05, 0.1, paper_model, prec=prec, ws=api.Workspace(n + 1))
+    plan = api.BatchPlan([dict(H=H, mu=0.05, kT=0.1)], paper_model, prec=prec)
+    plan.launch()
+    torch.cuda.synchronize()
+    if 1984 < n <= 2816 and prec != "bf16x3":
+        f, v = torch.linalg.eigh(H)
+        ref = (v * torch.sigmoid((0.05 - f) / 0.1)) @ v.T
+        e = [float(torch.linalg.norm(x.double() - ref)) for x in (D, plan.D[0])]
+        print(f"n={n} {prec} |dD|_F ring {e[0]:.3e} batch {e[1]:.3e}", flush=True)
+        assert torch.equal(D, D.T) and e[0] <= e[1]
+        plan.close()
+        return
+    assert torch.equal(D, plan.D[0])
+    tol = 2.0 ** -53 * n * n
+    assert abs(float(tr) - float(plan.tr[0, 0])) <= tol * n
+    assert abs(float(tr2) - float(plan.tr[0, 1])) <= tol * n
+    plan.close()
