@@ -269,13 +269,12 @@ int run_expansion(const double* H, int64_t n, int64_t ldh, double mu, double kT,
             wa.P = P; wa.partials = tp;
             wa.f64_epi = 1;
             wa.d_last = d_old[i];
-            const int Tw = (int)(np / fe::wide_tile());
-            npart = Tw * (Tw + 1) / 2;
+            npart = fe::wide_tiles(np);
             if (npart > fe::kMaxTiles) return fail(FE_ERR_WORKSPACE, "too many tiles");
             FE_HIP(fe::launch_layer_f32(wa, s));
         }
     } else {
-        // FP64 beyond the one-workgroup size, or FP32: 64 x 64 tiled MFMA layers on X itself
+        // FP64 beyond the one-workgroup size, or FP32: tiled MFMA layers on X itself
         const bool f64 = prec == FE_PREC_FP64;
         const int tile = fe::wide_tile();
         const int64_t np = round_up(n, tile);
@@ -290,8 +289,7 @@ int run_expansion(const double* H, int64_t n, int64_t ldh, double mu, double kT,
             ra.X32 = static_cast<float*>(b.X[0]); ra.A32 = static_cast<float*>(b.A); ra.mode = 1;
         }
         FE_HIP(fe::launch_rescale(ra, s));
-        const int T = (int)(np / tile);
-        npart = T * (T + 1) / 2;
+        npart = fe::wide_tiles(np);
         if (npart > fe::kMaxTiles) return fail(FE_ERR_WORKSPACE, "too many tiles");
         for (int i = 0; i < m->L; ++i) {
             fe::WideArgs wa{};

@@ -146,7 +146,7 @@ struct SmallArgs {
 };
 hipError_t launch_small_f64(const SmallArgs& a, hipStream_t s);
 
-// FP32 / FP64 tiled MFMA kernels (64 x 64 tiles) in two forms:
+// FP32 / FP64 tiled MFMA kernels in two forms:
 //  layer form (plain = 0): one layer of the recursion on X itself (operands = the full symmetric
 //    X_in, ping-pong with X_out), upper tiles only, fused epilogue as in the split kernel;
 //  product form (plain = 1): C = X_in B_in^T for row-major np x np operands over all tiles, written
@@ -167,7 +167,9 @@ struct WideArgs {
     int f64_epi;            // last layer of the FP32 kernel as a correction layer: FP64 epilogue,
     double d_last;          //   D = A + d_last X + (a Y + b X + c I) in FP64, not rounded to FP32
 };
-int wide_tile();
+int wide_tile();                    // padding unit of np
+int wide_bm(int64_t np);            // tile of the layer kernel at padded size np
+int wide_tiles(int64_t np);         // its upper tiles (trace partials of a last layer)
 // X[i][j] = X[j][i] for i > j (np x np FP32, np a multiple of wide_tile()).
 hipError_t launch_mirror_upper_f32(float* X, int64_t np, hipStream_t s);
 hipError_t launch_layer_f32(const WideArgs& a, hipStream_t s);

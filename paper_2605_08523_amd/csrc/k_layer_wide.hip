@@ -1,261 +1,403 @@
 // FP32 and FP64 layer kernels of the recursion X <- a X^2 + b X + c I, A <- A + d X
 // (Eq. mlsp2), and the plain product C = L R^T used by the coefficient trainer.
 //
-// 64 x 64 output tiles, four waves of 32 x 32; FP32 uses v_mfma_f32_32x32x2f32 (one 32 x 32
-// block per wave), FP64 uses v_mfma_f64_16x16x4f64 (2 x 2 blocks per wave). The operands of
-// tile (I, J) are the row panels I and J (X is symmetric, so column panel J = row panel J^T).
-// Register prefetch of the next K block overlaps the MFMAs on the current one. The layer form
-// computes only upper tiles and writes each tile and its mirror through an LDS-staged epilogue.
+// One workgroup of four waves per BM x BM output tile (BM = 32 or 64; a wave holds 1 or 2 x 2 blocks
+// of 16 x 16), v_mfma_f32_16x16x4f32 or v_mfma_f64_16x16x4f64. The operands of tile (I, J) are the
+// row panels I and J (X is symmetric, so column panel J = row panel J^T). They go straight from
+// global memory to LDS (one 128-byte line of every panel row per K block) through a ring of stages.
+// The layer form computes only upper tiles and writes each tile and its mirror through an
+// LDS-staged epilogue, whose X and A groups are loaded before the K loop; waves whose block lies in
+// the padding or strictly below the diagonal skip the products.
+//
+// Why 16 x 16 blocks: both types are bound by the MFMA rate, and a layer of ordinary size has few
+// blocks per SIMD (n = 1500: 4656 of 16 x 16 on 1024 SIMDs), so the time follows the largest count on
+// one SIMD. In FP32 the MFMA adds its products one by one in ascending k (measured: 16x16x4 and
+// 32x32x2 chains and a scalar fmaf chain agree bitwise), so the block shape does not change a bit.
+// Measured (us per layer; before: 64 x 64 tiles of four 32 x 32 waves, one LDS buffer): FP32 n = 256
+// 6.0 (16.7), 1500 43 (81; the MFMA rate alone 23), FP64 n = 256 7.1 (25), 1000 31 (78; 14).
+#include <type_traits>
+
 #include "fe_internal.h"
+#include "split_common.h"
 
 namespace fe {
 namespace {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef double double4v __attribute__((ext_vector_type(4)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 template <typename T>
 struct Mfma;
 
-// v_mfma_f32_32x32x2f32: lane l supplies A[l % 32][l / 32] and B[l / 32][l % 32];
-// acc[j] of lane l holds D[8 (j/4) + 4 (l/32) + j%4][l % 32].
+// v_mfma_f32_16x16x4f32: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16];
+// acc[i] of lane l holds D[4 (l / 16) + i][l % 16].
 template <>
 struct Mfma<float> {
-    static constexpr int BLK = 32, KSTEP = 2, NACC = 16;
-    using acc_t = floatx16;
-    __device__ static acc_t zero() {
-        acc_t z;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) z[j] = 0.0f;
-        return z;
+    using vec = floatx4;
+    __device__ static vec mma(float a, float b, vec c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
     }
-    __device__ static acc_t mma(float a, float b, acc_t c) {
-        return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-    }
-    __device__ static int arow(int lane) { return lane & 31; }
-    __device__ static int akk(int lane) { return lane >> 5; }
-    __device__ static int crow(int lane, int j) { return 8 * (j >> 2) + 4 * (lane >> 5) + (j & 3); }
-    __device__ static int ccol(int lane) { return lane & 31; }
+    __device__ static int crow(int lane, int i) { return 4 * (lane >> 4) + i; }
 };
 
-// v_mfma_f64_16x16x4f64: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16];
-// acc[i] of lane l holds D[4 i + l / 16][l % 16].
+// v_mfma_f64_16x16x4f64: the same operands; acc[i] of lane l holds D[4 i + l / 16][l % 16].
 template <>
 struct Mfma<double> {
-    static constexpr int BLK = 16, KSTEP = 4, NACC = 4;
-    using acc_t = double4v;
-    __device__ static acc_t zero() { return (acc_t){0.0, 0.0, 0.0, 0.0}; }
-    __device__ static acc_t mma(double a, double b, acc_t c) {
+    using vec = doublex4;
+    __device__ static vec mma(double a, double b, vec c) {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
     }
-    __device__ static int arow(int lane) { return lane & 15; }
-    __device__ static int akk(int lane) { return lane >> 4; }
-    __device__ static int crow(int lane, int j) { return 4 * j + (lane >> 4); }
-    __device__ static int ccol(int lane) { return lane & 15; }
+    __device__ static int crow(int lane, int i) { return 4 * i + (lane >> 4); }
 };
 
-constexpr int BM = 64;        // tile
-constexpr int NT = 256;       // 4 waves, 2 x 2 of 32 x 32
+constexpr int kPad = 64;      // padding unit of the matrices (a multiple of every tile)
+constexpr int NT = 256;       // 4 waves, 2 x 2
+
+template <typename T, int BM>
+struct WCfg {
+    static constexpr int BK = 128 / (int)sizeof(T);        // one line of every panel row
+    static constexpr int NB = BM / 32;                     // 16 x 16 blocks per wave side
+    static constexpr int S = 4;                            // ring stages
+    static constexpr int PANEL = BM * 128, STAGE = 2 * PANEL;   // bytes
+    static constexpr int IPW = 2 * (BM / 8) / 4;           // 1-KiB loads per wave and stage
+    static constexpr int LDY = BM + 4;                     // epilogue staging row (elements)
+    static constexpr int G = BM / 4, PER = BM * G / NT;    // four-column groups: per row, per thread
+    static constexpr size_t EPI = (size_t)BM * LDY * sizeof(double);
+    static constexpr size_t LDS = (size_t)S * STAGE > EPI ? (size_t)S * STAGE : EPI;
+};
 
 __device__ inline double wave_sum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
 
+// Four elements at the element type's own alignment (the trainer's callers may pass such arrays).
 template <typename T>
+struct Unaligned;
+template <>
+struct Unaligned<float> {
+    typedef floatx4 vec __attribute__((aligned(4)));
+};
+template <>
+struct Unaligned<double> {
+    typedef doublex4 vec __attribute__((aligned(8)));
+};
+
+// ALIGNED: every matrix starts on 16 bytes (rows then do too). Otherwise the operands go through
+// registers into the same LDS places, element by element.
+template <typename T, int BM, bool ALIGNED>
 __global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
     using M = Mfma<T>;
-    constexpr int BK = 16;                       // K per LDS stage
-    constexpr int LDK = BK + 1;                  // odd row stride: conflict-free column reads
-    constexpr int NBW = 32 / M::BLK;             // MFMA blocks per wave side
-    constexpr int LDY = BM + 1;
-    __shared__ T sA[BM * LDK], sB[BM * LDK];
-    __shared__ T sY[BM * LDY];
-    __shared__ double red[8];
+    using W = WCfg<T, BM>;
+    using vec = typename M::vec;
+    using gvec = typename std::conditional<ALIGNED, vec, typename Unaligned<T>::vec>::type;
+    typedef __attribute__((address_space(3))) void lds_void;
+    constexpr int NB = W::NB, S = W::S, BK = W::BK;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int64_t np = p.np;
+    const int64_t np = p.np, n = p.n;
     const int T_ = (int)(np / BM);
+    const int t = split::xcd_tile(blockIdx.x, gridDim.x);
     int I, J;
     if (p.plain) {
-        I = blockIdx.x / T_;
-        J = blockIdx.x % T_;
+        I = t / T_;
+        J = t % T_;
     } else {
-        int rem = blockIdx.x, i = 0;
-        while (rem >= T_ - i) {
-            rem -= T_ - i;
-            ++i;
-        }
-        I = i;
-        J = i + rem;
+        split::tile_coords(t, T_, I, J);
     }
     const bool diag = !p.plain && I == J;
     const int64_t I0 = (int64_t)I * BM, J0 = (int64_t)J * BM;
     const T* __restrict__ Lm = static_cast<const T*>(p.X_in);
     const T* __restrict__ Rm = p.plain ? static_cast<const T*>(p.B_in) : Lm;
+    T* __restrict__ A = static_cast<T*>(p.A);
+    const bool last = p.last != 0, ent = p.entropy != 0;
+    const T dn = (T)p.d_next;
+    const bool use_a = !p.plain && (last || dn != (T)0);
 
-    // global -> LDS: 64 rows x 16 K of each panel = 1024 elements, 4 per thread
-    constexpr int PER = BM * BK / NT;
-    T ra[PER], rb[PER];
-    auto gload = [&](int kb) {
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int e = tid + q * NT, row = e / BK, k = e % BK;
-            ra[q] = Lm[(I0 + row) * np + (int64_t)kb * BK + k];
-            rb[q] = Rm[(J0 + row) * np + (int64_t)kb * BK + k];
-        }
+    // the epilogue's groups (all inside the padded matrices)
+    vec xg[W::PER], ag[W::PER];
+    auto group = [&](int u) {
+        const int e = tid + u * NT;
+        return (I0 + e / W::G) * np + J0 + (e % W::G) * 4;
     };
-    auto sstore = [&]() {
+    if (!p.plain) {
 #pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int e = tid + q * NT, row = e / BK, k = e % BK;
-            sA[row * LDK + k] = ra[q];
-            sB[row * LDK + k] = rb[q];
-        }
-    };
-
-    typename M::acc_t acc[NBW][NBW];
+        for (int u = 0; u < W::PER; ++u) xg[u] = *reinterpret_cast<const gvec*>(Lm + group(u));
+    }
+    if (use_a) {
 #pragma unroll
-    for (int x = 0; x < NBW; ++x)
-#pragma unroll
-        for (int y = 0; y < NBW; ++y) acc[x][y] = M::zero();
-
-    const int nk = (int)(np / BK);
-    gload(0);
-    sstore();
-    __syncthreads();
-    for (int kb = 0; kb < nk; ++kb) {
-        if (kb + 1 < nk) gload(kb + 1);
-#pragma unroll
-        for (int k0 = 0; k0 < BK; k0 += M::KSTEP) {
-            T av[NBW], bv[NBW];
-#pragma unroll
-            for (int x = 0; x < NBW; ++x) {
-                av[x] = sA[(wm * 32 + x * M::BLK + M::arow(lane)) * LDK + k0 + M::akk(lane)];
-                bv[x] = sB[(wn * 32 + x * M::BLK + M::arow(lane)) * LDK + k0 + M::akk(lane)];
-            }
-#pragma unroll
-            for (int x = 0; x < NBW; ++x)
-#pragma unroll
-                for (int y = 0; y < NBW; ++y) acc[x][y] = M::mma(av[x], bv[y], acc[x][y]);
-        }
-        __syncthreads();
-        if (kb + 1 < nk) {
-            sstore();
-            __syncthreads();
-        }
+        for (int u = 0; u < W::PER; ++u) ag[u] = *reinterpret_cast<const gvec*>(A + group(u));
     }
 
-    // stage the 64 x 64 product tile in LDS
+    // Ring of stages: chunk c (16 bytes) of panel row r sits at chunk c ^ (r % 8) of its 128-byte LDS
+    // row, so the rows that a fragment read touches spread over the banks. Load q of this wave
+    // covers panel rows 8 g .. 8 g + 7, g = wave + 4 q (left panel, then right). Nothing in the loop
+    // needs vector arithmetic (MFMAs do not run beside it: four vector instructions per MFMA took
+    // 8 of its 15 ns here): a load's address is the lane's fixed offset plus a scalar one, a
+    // fragment's LDS address a fixed register plus the stage's constant (the stages are unrolled).
+    const int64_t row_bytes = np * (int64_t)sizeof(T);
+    const uint32_t lane_off = (uint32_t)((lane >> 3) * row_bytes + (((lane & 7) ^ (lane >> 3)) << 4));
+    const __amdgpu_buffer_rsrc_t rs[2] = {
+        split::make_rsrc(Lm + I0 * np, (uint32_t)(BM * row_bytes)),
+        split::make_rsrc(Rm + J0 * np, (uint32_t)(BM * row_bytes))};
+    auto issue = [&](int kb, int stage) {
 #pragma unroll
-    for (int x = 0; x < NBW; ++x)
+        for (int q = 0; q < W::IPW; ++q) {
+            const int right = q >= W::IPW / 2, blk = wave + 4 * (q % (W::IPW / 2));
+            unsigned char* l = smem + stage * W::STAGE + right * W::PANEL + blk * 1024;
+            const uint32_t soff = (uint32_t)(blk * 8 * row_bytes) + (uint32_t)kb * 128;
+            if constexpr (ALIGNED) {
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs[right], (lds_void*)l, 16, (int)lane_off,
+                                                         (int)soff, 0, 0);
+            } else {
+                const T* g = reinterpret_cast<const T*>(
+                    reinterpret_cast<const char*>(right ? Rm + J0 * np : Lm + I0 * np) + soff + lane_off);
+                T v[16 / sizeof(T)];
 #pragma unroll
-        for (int y = 0; y < NBW; ++y)
+                for (int k = 0; k < (int)(16 / sizeof(T)); ++k) v[k] = g[k];
 #pragma unroll
-            for (int j = 0; j < M::NACC; ++j) {
-                const int r = wm * 32 + x * M::BLK + M::crow(lane, j);
-                const int c = wn * 32 + y * M::BLK + M::ccol(lane);
-                sY[r * LDY + c] = acc[x][y][j];
+                for (int k = 0; k < (int)(16 / sizeof(T)); ++k)
+                    reinterpret_cast<T*>(l + lane * 16)[k] = v[k];
             }
+        }
+    };
+    // A block whose rows or columns are all padding, or that lies strictly below the diagonal, is
+    // not stored: its wave skips the products.
+    const bool work = p.plain || (I0 + wm * NB * 16 < n && J0 + wn * NB * 16 < n && !(diag && wm > wn));
+    const int fr = lane & 15, fk = lane >> 4;
+    constexpr int KS = BK / 4;
+    typedef __attribute__((address_space(3))) const unsigned char lds_char;
+    lds_char* const lds0 = (lds_char*)smem;
+    uint32_t oa[KS], ob[KS];   // byte offsets of element (row fr, k = 4 s + fk) of this wave's blocks
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        constexpr int PC = 16 / (int)sizeof(T);   // elements per chunk
+        const int k = 4 * s + fk;
+        const uint32_t o = fr * 128 + (((k / PC) ^ (fr & 7)) << 4) + (k % PC) * (int)sizeof(T);
+        oa[s] = o + wm * NB * 2048;
+        ob[s] = o + wn * NB * 2048 + W::PANEL;
+        asm volatile("" : "+v"(oa[s]), "+v"(ob[s]));   // kept, not recomputed in the loop
+    }
+    vec acc[NB][NB];
+#pragma unroll
+    for (int x = 0; x < NB; ++x)
+#pragma unroll
+        for (int y = 0; y < NB; ++y) acc[x][y] = vec{0, 0, 0, 0};
+    const int nk = (int)((n + BK - 1) / BK);   // beyond n both operands are zero
+    struct Frag {
+        T a[KS][NB], b[KS][NB];
+    };
+    auto read = [&](int stage, Frag& f) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int x = 0; x < NB; ++x) {
+                typedef __attribute__((address_space(3))) const T lds_T;
+                f.a[s][x] = *(lds_T*)(lds0 + oa[s] + stage * W::STAGE + x * 2048);
+                f.b[s][x] = *(lds_T*)(lds0 + ob[s] + stage * W::STAGE + x * 2048);
+            }
+    };
+    auto multiply = [&](const Frag& f) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int x = 0; x < NB; ++x)
+#pragma unroll
+                for (int y = 0; y < NB; ++y) acc[x][y] = M::mma(f.a[s][x], f.b[s][y], acc[x][y]);
+    };
+    // Block i in stage u. First waits until this wave's loads of block i + 1 have landed (those of the
+    // S - 2 blocks after it may be in flight) and its fragment reads of block i are done, and joins
+    // the other waves: block i + 1 is whole and block i's stage is free. Then the next block's
+    // fragments are read and the free stage is refilled while this block is multiplied, so that a wave
+    // alone on its SIMD keeps the MFMA pipe busy. full: the blocks up to i + S exist (no conditions).
+    auto step = [&](auto wk, auto full, int i, int u, const Frag& cur, Frag& nxt) {
+        if (full || i + 1 < nk) {
+            if (full || i + S - 1 < nk) __builtin_amdgcn_s_waitcnt(0x0070 | (W::IPW * (S - 2)));
+            else __builtin_amdgcn_s_waitcnt(0x0070);   // lgkmcnt(0), vmcnt(loads of later blocks)
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (full || i + S < nk) issue(i + S, u);
+            if constexpr (wk) read((u + 1) % S, nxt);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (wk) multiply(cur);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto loop = [&](auto wk) {
+        constexpr std::true_type yes{};
+        constexpr std::false_type no{};
+        Frag f0, f1;
+        if constexpr (wk) read(0, f0);
+        int i = 0;
+        for (; i + 2 * S - 1 < nk; i += S) {
+            step(wk, yes, i, 0, f0, f1);
+            step(wk, yes, i + 1, 1, f1, f0);
+            step(wk, yes, i + 2, 2, f0, f1);
+            step(wk, yes, i + 3, 3, f1, f0);
+        }
+        for (; i < nk; i += S) {
+            step(wk, no, i, 0, f0, f1);
+            if (i + 1 < nk) step(wk, no, i + 1, 1, f1, f0);
+            if (i + 2 < nk) step(wk, no, i + 2, 2, f0, f1);
+            if (i + 3 < nk) step(wk, no, i + 3, 3, f1, f0);
+        }
+    };
+#pragma unroll
+    for (int b = 0; b < S; ++b)
+        if (b < nk) issue(b, b);
+    static_assert(S == 4 && W::IPW * (S - 1) < 16, "four stages unrolled, four-bit wait count");
+    if (S - 1 < nk) __builtin_amdgcn_s_waitcnt(0x0070 | (W::IPW * (S - 1)));
+    else __builtin_amdgcn_s_waitcnt(0x0070);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (work) loop(std::true_type{});
+    else loop(std::false_type{});
+    asm volatile("" ::: "memory");
     __syncthreads();
 
+    // the product tile goes through LDS to four-column groups in registers
+    T* sY = reinterpret_cast<T*>(smem);
+#pragma unroll
+    for (int x = 0; x < NB; ++x)
+#pragma unroll
+        for (int y = 0; y < NB; ++y)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                sY[((wm * NB + x) * 16 + M::crow(lane, j)) * W::LDY + (wn * NB + y) * 16 + fr] = acc[x][y][j];
+    __syncthreads();
+    vec yg[W::PER];
+#pragma unroll
+    for (int u = 0; u < W::PER; ++u) {
+        const int e = tid + u * NT;
+        yg[u] = *reinterpret_cast<const vec*>(sY + (e / W::G) * W::LDY + (e % W::G) * 4);
+    }
     if (p.plain) {
         T* C = static_cast<T*>(p.X_out);
-        for (int e = tid; e < BM * BM; e += NT) {
-            const int r = e / BM, c = e % BM;
-            C[(I0 + r) * np + J0 + c] = sY[r * LDY + c];
+#pragma unroll
+        for (int u = 0; u < W::PER; ++u) *reinterpret_cast<gvec*>(C + group(u)) = yg[u];
+        return;
+    }
+
+    const T ca = (T)p.a, cb = (T)p.b, cc = (T)p.c;
+    if (!last) {
+        T* __restrict__ Xo = static_cast<T*>(p.X_out);
+#pragma unroll
+        for (int u = 0; u < W::PER; ++u) {
+            const int e = tid + u * NT, r = e / W::G, c = (e % W::G) * 4;
+            const int64_t gr = I0 + r, gc = J0 + c, gi = gr * np + gc;
+            vec xn, an;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const T v = ca * yg[u][k] + cb * xg[u][k] + (gr == gc + k ? cc : (T)0);
+                xn[k] = gr < n && gc + k < n ? v : (T)0;   // the padding stays zero
+                if (use_a) an[k] = ag[u][k] + dn * xn[k];
+            }
+            if (!diag || c >= r) {
+                if (use_a) *reinterpret_cast<gvec*>(A + gi) = an;
+                *reinterpret_cast<gvec*>(Xo + gi) = xn;
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (c + k < r) continue;
+                    if (use_a) A[gi + k] = an[k];
+                    Xo[gi + k] = xn[k];
+                }
+            }
+            *reinterpret_cast<vec*>(sY + r * W::LDY + c) = xn;
+        }
+        __syncthreads();
+        // Mirror: output row J0 + c, columns I0 + r .. r + 3 hold x(r .. r + 3, c).
+#pragma unroll
+        for (int u = 0; u < W::PER; ++u) {
+            const int e = tid + u * NT, c = e / W::G, r = (e % W::G) * 4;
+            if (diag && r >= c) continue;   // nothing strictly below the diagonal
+            vec v;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = sY[(r + k) * W::LDY + c];
+            T* o = Xo + (J0 + c) * np + I0 + r;
+            if (!diag || r + 3 < c) {
+                *reinterpret_cast<gvec*>(o) = v;
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (r + k < c) o[k] = v[k];
+            }
         }
         return;
     }
 
-    const T ca = (T)p.a, cb = (T)p.b, cc = (T)p.c, dn = (T)p.d_next;
-    const bool last = p.last != 0, ent = p.entropy != 0;
-    const int flip = (last && !ent) ? p.P->flipped : 0;
-    const bool f64e = last && p.f64_epi;   // FP64 epilogue of a correction layer (T = float)
-    const int64_t n = p.n;
-    T* __restrict__ Xo = static_cast<T*>(p.X_out);
-    T* __restrict__ A = static_cast<T*>(p.A);
-    // Last-layer value at upper position gi (row gr, column gc) from the product y:
-    // D = A + d_last X + (a y + b X + c delta), in FP64 for the correction layer (then not
-    // rounded: the layer's D is formed in FP64 from FP32 products and FP32 state), else in T.
-    auto last_value = [&](T y, int64_t gi, int64_t gr, int64_t gc) -> double {
-        double v;
-        if (f64e) {
-            const double x = (double)Lm[gi];
-            v = (double)A[gi] + p.d_last * x + (p.a * (double)y + p.b * x + (gr == gc ? p.c : 0.0));
-        } else {
-            const T xn = ca * y + cb * Lm[gi] + (gr == gc ? cc : (T)0);
-            v = (double)A[gi] + (double)xn;
-        }
-        if (flip) v = (gr == gc ? 1.0 : 0.0) - v;
-        // FP32 mode carries FP32 values (so the tile and its mirror hold the same number)
-        return (ent || sizeof(T) == 8 || f64e) ? v : (double)(float)v;
-    };
+    // Last layer: D = A + X' (I - D if flipped), or U = A + X' traced only (entropy). With f64_epi
+    // (T = float) D = A + d_last X + (a y + b X + c delta) in FP64, not rounded.
+    const int flip = !ent ? p.P->flipped : 0;
+    const bool f64e = p.f64_epi != 0;
+    const bool write = !(ent || p.out_mode == 2);
+    double* sD = reinterpret_cast<double*>(smem);
     double tr = 0.0, sq = 0.0;
-    for (int e = tid; e < BM * BM; e += NT) {
-        const int r = e / BM, c = e % BM;
-        if (diag && r > c) continue;
-        const int64_t gr = I0 + r, gc = J0 + c, gi = gr * np + gc;
-        const T y = sY[r * LDY + c];
-        if (!last) {
-            const T xn = ca * y + cb * Lm[gi] + (gr == gc ? cc : (T)0);
-            if (dn != (T)0) A[gi] += dn * xn;
-            Xo[gi] = xn;
-            sY[r * LDY + c] = xn;
-        } else {
-            const double vo = last_value(y, gi, gr, gc);
-            if (gr < n && gc < n) {
-                if (gr == gc) tr += vo;
-                sq += (gr == gc ? 1.0 : 2.0) * vo * vo;
-                if (!ent) {
-                    if (p.out_mode == 0)
-                        reinterpret_cast<float*>(p.D)[gr * p.ldd + gc] = (float)vo;
-                    else if (p.out_mode == 1)
-                        reinterpret_cast<double*>(p.D)[gr * p.ldd + gc] = vo;
-                }
+    auto put = [&](int64_t row, int64_t col, double v) {
+        if (p.out_mode == 0) reinterpret_cast<float*>(p.D)[row * p.ldd + col] = (float)v;
+        else reinterpret_cast<double*>(p.D)[row * p.ldd + col] = v;
+    };
+    __syncthreads();   // every thread's y is in registers: the staging now holds doubles
+#pragma unroll
+    for (int u = 0; u < W::PER; ++u) {
+        const int e = tid + u * NT, r = e / W::G, c = (e % W::G) * 4;
+        const int64_t gr = I0 + r;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t gc = J0 + c + k;
+            const T y = yg[u][k], x = xg[u][k], a = ag[u][k];
+            double v;
+            if (f64e) {
+                v = (double)a + p.d_last * (double)x +
+                    (p.a * (double)y + p.b * (double)x + (gr == gc ? p.c : 0.0));
+            } else {
+                const T xn = ca * y + cb * x + (gr == gc ? cc : (T)0);
+                v = (double)a + (double)xn;
             }
-            if (!f64e) sY[r * LDY + c] = (T)vo;   // the correction layer keeps y and recomputes
+            if (flip) v = (gr == gc ? 1.0 : 0.0) - v;
+            // FP32 mode carries FP32 values (so the tile and its mirror hold the same number)
+            if (!(ent || sizeof(T) == 8 || f64e)) v = (double)(float)v;
+            if ((!diag || c + k >= r) && gr < n && gc < n) {
+                if (gr == gc) tr += v;
+                sq += (gr == gc ? 1.0 : 2.0) * v * v;
+                if (write) put(gr, gc, v);
+            }
+            sD[r * W::LDY + c + k] = v;
         }
     }
     __syncthreads();
-    if (!(last && (ent || p.out_mode == 2))) {
-        for (int e = tid; e < BM * BM; e += NT) {
-            const int r = e % BM, c = e / BM;
-            if (diag && !(r < c)) continue;
-            const T v = sY[r * LDY + c];
-            const int64_t orow = J0 + c, ocol = I0 + r;
-            if (!last) {
-                Xo[orow * np + ocol] = v;
-            } else if (orow < n && ocol < n) {
-                // the mirror of an FP64 correction value is recomputed from the same operands,
-                // so D stays exactly symmetric
-                const double vo = f64e ? last_value(v, (I0 + r) * np + J0 + c, I0 + r, J0 + c)
-                                       : (double)v;
-                if (p.out_mode == 0)
-                    reinterpret_cast<float*>(p.D)[orow * p.ldd + ocol] = (float)vo;
-                else
-                    reinterpret_cast<double*>(p.D)[orow * p.ldd + ocol] = vo;
+    if (write) {
+#pragma unroll
+        for (int u = 0; u < W::PER; ++u) {
+            const int e = tid + u * NT, c = e / W::G, r = (e % W::G) * 4;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (diag && !(r + k < c)) continue;
+                if (J0 + c < n && I0 + r + k < n) put(J0 + c, I0 + r + k, sD[(r + k) * W::LDY + c]);
             }
         }
     }
-    if (last) {
-        tr = wave_sum(tr);
-        sq = wave_sum(sq);
-        if (lane == 0) {
-            red[2 * wave] = tr;
-            red[2 * wave + 1] = sq;
+    __syncthreads();
+    tr = wave_sum(tr);
+    sq = wave_sum(sq);
+    if (lane == 0) {
+        sD[2 * wave] = tr;
+        sD[2 * wave + 1] = sq;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        double tt = 0.0, ss = 0.0;
+        for (int w = 0; w < 4; ++w) {
+            tt += sD[2 * w];
+            ss += sD[2 * w + 1];
         }
-        __syncthreads();
-        if (tid == 0) {
-            double t = 0.0, s = 0.0;
-            for (int w = 0; w < 4; ++w) {
-                t += red[2 * w];
-                s += red[2 * w + 1];
-            }
-            p.partials[blockIdx.x].tr = t;
-            p.partials[blockIdx.x].sq = s;
-        }
+        p.partials[t].tr = tt;
+        p.partials[t].sq = ss;
     }
 }
 
@@ -263,6 +405,7 @@ __global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
 // i > j), through 64 x 64 LDS tiles: workgroup (I, J), I >= J, reads the upper tile (J, I) row by
 // row and writes its transpose into the lower tile (I, J); diagonal tiles copy within the tile.
 __global__ void __launch_bounds__(256) k_mirror_upper(float* X, int64_t np) {
+    constexpr int BM = kPad;
     __shared__ float t[BM][BM + 1];
     int rem = blockIdx.x, i = 0;
     const int T_ = (int)(np / BM);
@@ -283,23 +426,43 @@ __global__ void __launch_bounds__(256) k_mirror_upper(float* X, int64_t np) {
     }
 }
 
+template <typename T, int BM, bool ALIGNED>
+hipError_t launch_t(const WideArgs& a, hipStream_t s) {
+    auto kern = k_wide<T, BM, ALIGNED>;
+    constexpr size_t lds = WCfg<T, BM>::LDS;
+    static_assert(lds <= 64 * 1024, "no attribute needed for the dynamic LDS");
+    const int T_ = (int)(a.np / BM);
+    hipLaunchKernelGGL(kern, dim3(a.plain ? T_ * T_ : T_ * (T_ + 1) / 2), dim3(NT), lds, s, a);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch(const WideArgs& a, hipStream_t s) {
-    if (a.np % BM != 0) return hipErrorInvalidValue;
-    const int T_ = (int)(a.np / BM);
-    const int grid = a.plain ? T_ * T_ : T_ * (T_ + 1) / 2;
-    hipLaunchKernelGGL(k_wide<T>, dim3(grid), dim3(NT), 0, s, a);
-    return hipGetLastError();
+    if (a.np % kPad != 0 || a.n < 1 || a.n > a.np) return hipErrorInvalidValue;
+    const uintptr_t m = reinterpret_cast<uintptr_t>(a.X_in) | reinterpret_cast<uintptr_t>(a.B_in) |
+                        reinterpret_cast<uintptr_t>(a.X_out) | reinterpret_cast<uintptr_t>(a.A);
+    if (m % 16 != 0)
+        return wide_bm(a.np) == 32 ? launch_t<T, 32, false>(a, s) : launch_t<T, 64, false>(a, s);
+    return wide_bm(a.np) == 32 ? launch_t<T, 32, true>(a, s) : launch_t<T, 64, true>(a, s);
 }
 
 }  // namespace
 
-int wide_tile() { return BM; }
+int wide_tile() { return kPad; }
+// Where the line lies (us per layer, 32 x 32 against 64 x 64 tiles): FP32 n = 1500 43 / 60, 4096
+// 596 / 635, 5000 1321 / 1224, 8192 5024 / 4586; FP64 n = 1000 31 / 49, 4096 1197 / 1250, 5000
+// 2629 / 2276, 8192 10334 / 9147: small tiles spread few blocks over the SIMDs, large ones halve the
+// operand traffic.
+int wide_bm(int64_t np) { return np <= 4096 ? 32 : 64; }
+int wide_tiles(int64_t np) {
+    const int T_ = (int)(np / wide_bm(np));
+    return T_ * (T_ + 1) / 2;
+}
 hipError_t launch_layer_f32(const WideArgs& a, hipStream_t s) { return launch<float>(a, s); }
 hipError_t launch_layer_f64(const WideArgs& a, hipStream_t s) { return launch<double>(a, s); }
 hipError_t launch_mirror_upper_f32(float* X, int64_t np, hipStream_t s) {
-    if (np % BM != 0) return hipErrorInvalidValue;
-    const int T_ = (int)(np / BM);
+    if (np % kPad != 0) return hipErrorInvalidValue;
+    const int T_ = (int)(np / kPad);
     hipLaunchKernelGGL(k_mirror_upper, dim3(T_ * (T_ + 1) / 2), dim3(256), 0, s, X, np);
     return hipGetLastError();
 }
