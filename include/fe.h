@@ -365,10 +365,11 @@ int fe_matrix_forward(float* hist, int64_t n, const double* theta, int32_t L, fl
                       void* stream);
 
 /* Backward of fe_matrix_forward: given G = dLoss/dP (device n x n float32, symmetric), writes
- * grad (device float64 L x 4) = dLoss/dtheta: per layer one FP32 MFMA product
- * M = Xb_{i+1} X_i and an elementwise pass Xb_i = a_i (M + M^T) + b_i Xb_{i+1} + d_i G with the
- * coefficient gradients <M, X_i>, <Xb_{i+1}, X_i>, Tr Xb_{i+1}, <G, X_i> reduced in FP64.
- * work: device float32 3 n^2; part: device float64 4 * nblocks (nblocks >= 1 reduction blocks). */
+ * grad (device float64 L x 4) = dLoss/dtheta: per layer one pass that forms the FP32 MFMA product
+ * M = Xb_{i+1} X_i with its transpose, Xb_i = a_i (M + M^T) + b_i Xb_{i+1} + d_i G and the
+ * coefficient gradients <M, X_i>, <Xb_{i+1}, X_i>, Tr Xb_{i+1}, <G, X_i> summed in FP64.
+ * work: device float32 3 n^2 (adjoints and partial sums); part: device float64 4 * nblocks
+ * (nblocks >= 1), not read or written. */
 int fe_matrix_backward(const float* hist, int64_t n, const double* theta, int32_t L,
                        const float* G, float* work, double* part, int32_t nblocks,
                        double* grad, void* stream);

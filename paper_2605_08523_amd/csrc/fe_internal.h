@@ -146,24 +146,19 @@ struct SmallArgs {
 };
 hipError_t launch_small_f64(const SmallArgs& a, hipStream_t s);
 
-// FP32 / FP64 tiled MFMA kernels in two forms:
-//  layer form (plain = 0): one layer of the recursion on X itself (operands = the full symmetric
-//    X_in, ping-pong with X_out), upper tiles only, fused epilogue as in the split kernel;
-//  product form (plain = 1): C = X_in B_in^T for row-major np x np operands over all tiles, written
-//    row-major to X_out (used by the trainer's backward pass, where B_in = X is symmetric).
+// FP32 / FP64 tiled MFMA kernel: one layer of the recursion on X itself (operands = the full symmetric
+// X_in, ping-pong with X_out), upper tiles only, fused epilogue as in the split kernel.
 struct WideArgs {
     int64_t np, n;
-    const void* X_in;       // layer: full symmetric X; product: left operand
-    const void* B_in;       // product: right operand (rows)
-    void* X_out;            // layer: next X (full); product: C
-    void* A;                // accumulator, upper triangle (layer form)
+    const void* X_in;       // full symmetric X
+    void* X_out;            // next X (full)
+    void* A;                // accumulator, upper triangle
     double a, b, c, d_next;
     int last, out_mode, entropy;
     void* D;
     int64_t ldd;
     const Params* P;
     TracePartial* partials;
-    int plain;
     int f64_epi;            // last layer of the FP32 kernel as a correction layer: FP64 epilogue,
     double d_last;          //   D = A + d_last X + (a Y + b X + c I) in FP64, not rounded to FP32
 };
@@ -255,16 +250,19 @@ struct MatTheta {
     double v[4 * kScalarMaxL];
 };
 struct BwdArgs {
-    const float* M;         // Xb_{i+1} X_i
     const float* Xb;        // Xb_{i+1}
     const float* X;         // X_i
     const float* G;         // dLoss/dP
     float* Xb_out;          // Xb_i
     float ca, cb, cd;       // a_i, b_i, d_i
-    int64_t n;
-    double* part;           // per-block partial sums, nblocks x 4
+    int64_t n;              // a multiple of 64
+    double* part;           // per-tile partial sums, wide_bwd_tiles(n) x 4
 };
-hipError_t launch_bwd_elem(const BwdArgs& a, int nblocks, double* grad4, hipStream_t s);
+// One layer of the backward pass, and after all L of them the sums of the layers' partials
+// (part: L x tiles x 4) in a fixed order into grad (L x 4).
+int wide_bwd_tiles(int64_t n);
+hipError_t launch_layer_bwd(const BwdArgs& a, hipStream_t s);
+hipError_t launch_bwd_reduce(const double* part, int tiles, int L, double* grad, hipStream_t s);
 // G = P - Dref (FP32; G may be NULL) and *sumsq = sum (P - Dref)^2 in FP64 over `total` entries
 // (nblocks partial sums in part, reduced in a fixed order).
 hipError_t launch_mat_residual(const float* P, const double* Dref, int64_t total, float* G,

@@ -660,23 +660,23 @@ int fe_matrix_backward(const float* hist, int64_t n, const double* theta, int32_
     if (nblocks < 1) return fail(FE_ERR_ARG, "nblocks must be >= 1");
     hipStream_t s = static_cast<hipStream_t>(stream);
     const size_t nn = (size_t)n * n;
-    float* Xb = work;            // adjoint of X_{i+1}
-    float* Xb2 = work + nn;      // adjoint of X_i
-    float* M = work + 2 * nn;    // Xb_{i+1} X_i
-    FE_HIP(hipMemcpyAsync(Xb, G, sizeof(float) * nn, hipMemcpyDeviceToDevice, s));
+    // the adjoints ping-pong in the first two thirds of work; the last third holds the layers' FP64
+    // partial sums, aligned to 8 bytes: L <= 96 layers of (n/32)(n/32 + 1)/2 tiles x 4 doubles,
+    // 9,224 of its 16,384 bytes at n = 64 and a smaller share beyond
+    const float* Xb = G;
+    float* next = work;
+    const int tiles = fe::wide_bwd_tiles(n);
+    double* sums = reinterpret_cast<double*>((reinterpret_cast<uintptr_t>(work + 2 * nn) + 7) / 8 * 8);
     for (int i = L - 1; i >= 0; --i) {
-        const float* Xi = hist + (size_t)i * nn;
-        fe::WideArgs wa{};
-        wa.np = n; wa.n = n; wa.plain = 1;
-        wa.X_in = Xb; wa.B_in = Xi; wa.X_out = M;
-        FE_HIP(fe::launch_layer_f32(wa, s));
         fe::BwdArgs ba{};
-        ba.M = M; ba.Xb = Xb; ba.X = Xi; ba.G = G; ba.Xb_out = Xb2;
+        ba.Xb = Xb; ba.X = hist + (size_t)i * nn; ba.G = G; ba.Xb_out = next;
         ba.ca = (float)theta[4 * i]; ba.cb = (float)theta[4 * i + 1]; ba.cd = (float)theta[4 * i + 3];
-        ba.n = n; ba.part = part;
-        FE_HIP(fe::launch_bwd_elem(ba, nblocks, grad + 4 * i, s));
-        std::swap(Xb, Xb2);
+        ba.n = n; ba.part = sums + (size_t)i * tiles * 4;
+        FE_HIP(fe::launch_layer_bwd(ba, s));
+        Xb = next;
+        next = next == work ? work + nn : work;
     }
+    FE_HIP(fe::launch_bwd_reduce(sums, tiles, L, grad, s));
     return FE_OK;
 }
 

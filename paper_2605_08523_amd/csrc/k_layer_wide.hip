@@ -1,5 +1,5 @@
 // FP32 and FP64 layer kernels of the recursion X <- a X^2 + b X + c I, A <- A + d X
-// (Eq. mlsp2), and the plain product C = L R^T used by the coefficient trainer.
+// (Eq. mlsp2), and the backward layer of the coefficient trainer.
 //
 // One workgroup of four waves per BM x BM output tile (BM = 32 or 64; a wave holds 1 or 2 x 2 blocks
 // of 16 x 16), v_mfma_f32_16x16x4f32 or v_mfma_f64_16x16x4f64. The operands of tile (I, J) are the
@@ -53,13 +53,15 @@ struct Mfma<double> {
 constexpr int kPad = 64;      // padding unit of the matrices (a multiple of every tile)
 constexpr int NT = 256;       // 4 waves, 2 x 2
 
-template <typename T, int BM>
+// NPR: products per tile (two operand panels each).
+template <typename T, int BM, int NPR = 1>
 struct WCfg {
     static constexpr int BK = 128 / (int)sizeof(T);        // one line of every panel row
     static constexpr int NB = BM / 32;                     // 16 x 16 blocks per wave side
     static constexpr int S = 4;                            // ring stages
-    static constexpr int PANEL = BM * 128, STAGE = 2 * PANEL;   // bytes
-    static constexpr int IPW = 2 * (BM / 8) / 4;           // 1-KiB loads per wave and stage
+    static constexpr int PANEL = BM * 128, STAGE = 2 * NPR * PANEL;   // bytes
+    static constexpr int IPP = BM / 32;                    // 1-KiB loads per wave, panel and stage
+    static constexpr int IPW = 2 * NPR * IPP;              // ... per wave and stage
     static constexpr int LDY = BM + 4;                     // epilogue staging row (elements)
     static constexpr int G = BM / 4, PER = BM * G / NT;    // four-column groups: per row, per thread
     static constexpr size_t EPI = (size_t)BM * LDY * sizeof(double);
@@ -83,78 +85,48 @@ struct Unaligned<double> {
     typedef doublex4 vec __attribute__((aligned(8)));
 };
 
-// ALIGNED: every matrix starts on 16 bytes (rows then do too). Otherwise the operands go through
-// registers into the same LDS places, element by element.
-template <typename T, int BM, bool ALIGNED>
-__global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
+// acc[p] += L_p R_p^T over nk K blocks for NPR products at once, from the BM-row panels at Lp[p] and
+// Rp[p] of np-wide matrices: products per element in ascending k. work (the same for all lanes of a
+// wave): this wave's blocks are wanted. ALIGNED: the panels start on 16 bytes (rows then do too);
+// otherwise the operands go through registers into the same LDS places, element by element. Ends
+// with a barrier.
+//
+// Ring of stages: chunk c (16 bytes) of panel row r sits at chunk c ^ (r % 8) of its 128-byte LDS row,
+// so the rows that a fragment read touches spread over the banks. Nothing in the loop needs vector
+// arithmetic (MFMAs do not run beside it: four vector instructions per MFMA took 8 of its 15 ns
+// here): a load's address is the lane's fixed offset plus a scalar one, a fragment's LDS address a
+// fixed register plus the stage's constant (the stages are unrolled).
+template <typename T, int BM, bool ALIGNED, int NPR>
+__device__ __attribute__((always_inline)) inline void wide_products(
+    const T* const (&Lp)[NPR], const T* const (&Rp)[NPR], int64_t np, int nk, bool work,
+    unsigned char* smem,
+    typename Mfma<T>::vec (&acc)[NPR][WCfg<T, BM>::NB][WCfg<T, BM>::NB]) {
     using M = Mfma<T>;
-    using W = WCfg<T, BM>;
-    using vec = typename M::vec;
-    using gvec = typename std::conditional<ALIGNED, vec, typename Unaligned<T>::vec>::type;
+    using W = WCfg<T, BM, NPR>;
     typedef __attribute__((address_space(3))) void lds_void;
     constexpr int NB = W::NB, S = W::S, BK = W::BK;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int64_t np = p.np, n = p.n;
-    const int T_ = (int)(np / BM);
-    const int t = split::xcd_tile(blockIdx.x, gridDim.x);
-    int I, J;
-    if (p.plain) {
-        I = t / T_;
-        J = t % T_;
-    } else {
-        split::tile_coords(t, T_, I, J);
-    }
-    const bool diag = !p.plain && I == J;
-    const int64_t I0 = (int64_t)I * BM, J0 = (int64_t)J * BM;
-    const T* __restrict__ Lm = static_cast<const T*>(p.X_in);
-    const T* __restrict__ Rm = p.plain ? static_cast<const T*>(p.B_in) : Lm;
-    T* __restrict__ A = static_cast<T*>(p.A);
-    const bool last = p.last != 0, ent = p.entropy != 0;
-    const T dn = (T)p.d_next;
-    const bool use_a = !p.plain && (last || dn != (T)0);
-
-    // the epilogue's groups (all inside the padded matrices)
-    vec xg[W::PER], ag[W::PER];
-    auto group = [&](int u) {
-        const int e = tid + u * NT;
-        return (I0 + e / W::G) * np + J0 + (e % W::G) * 4;
-    };
-    if (!p.plain) {
-#pragma unroll
-        for (int u = 0; u < W::PER; ++u) xg[u] = *reinterpret_cast<const gvec*>(Lm + group(u));
-    }
-    if (use_a) {
-#pragma unroll
-        for (int u = 0; u < W::PER; ++u) ag[u] = *reinterpret_cast<const gvec*>(A + group(u));
-    }
-
-    // Ring of stages: chunk c (16 bytes) of panel row r sits at chunk c ^ (r % 8) of its 128-byte LDS
-    // row, so the rows that a fragment read touches spread over the banks. Load q of this wave
-    // covers panel rows 8 g .. 8 g + 7, g = wave + 4 q (left panel, then right). Nothing in the loop
-    // needs vector arithmetic (MFMAs do not run beside it: four vector instructions per MFMA took
-    // 8 of its 15 ns here): a load's address is the lane's fixed offset plus a scalar one, a
-    // fragment's LDS address a fixed register plus the stage's constant (the stages are unrolled).
     const int64_t row_bytes = np * (int64_t)sizeof(T);
     const uint32_t lane_off = (uint32_t)((lane >> 3) * row_bytes + (((lane & 7) ^ (lane >> 3)) << 4));
-    const __amdgpu_buffer_rsrc_t rs[2] = {
-        split::make_rsrc(Lm + I0 * np, (uint32_t)(BM * row_bytes)),
-        split::make_rsrc(Rm + J0 * np, (uint32_t)(BM * row_bytes))};
+    __amdgpu_buffer_rsrc_t rs[2 * NPR];
+#pragma unroll
+    for (int p = 0; p < 2 * NPR; ++p)
+        rs[p] = split::make_rsrc(p & 1 ? Rp[p >> 1] : Lp[p >> 1], (uint32_t)(BM * row_bytes));
     auto issue = [&](int kb, int stage) {
 #pragma unroll
         for (int q = 0; q < W::IPW; ++q) {
-            const int right = q >= W::IPW / 2, blk = wave + 4 * (q % (W::IPW / 2));
-            unsigned char* l = smem + stage * W::STAGE + right * W::PANEL + blk * 1024;
+            const int panel = q / W::IPP, blk = wave + 4 * (q % W::IPP);
+            unsigned char* l = smem + stage * W::STAGE + panel * W::PANEL + blk * 1024;
             const uint32_t soff = (uint32_t)(blk * 8 * row_bytes) + (uint32_t)kb * 128;
             if constexpr (ALIGNED) {
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs[right], (lds_void*)l, 16, (int)lane_off,
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs[panel], (lds_void*)l, 16, (int)lane_off,
                                                          (int)soff, 0, 0);
             } else {
                 const T* g = reinterpret_cast<const T*>(
-                    reinterpret_cast<const char*>(right ? Rm + J0 * np : Lm + I0 * np) + soff + lane_off);
+                    reinterpret_cast<const char*>(panel & 1 ? Rp[panel >> 1] : Lp[panel >> 1]) + soff +
+                    lane_off);
                 T v[16 / sizeof(T)];
 #pragma unroll
                 for (int k = 0; k < (int)(16 / sizeof(T)); ++k) v[k] = g[k];
@@ -164,9 +136,6 @@ __global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
             }
         }
     };
-    // A block whose rows or columns are all padding, or that lies strictly below the diagonal, is
-    // not stored: its wave skips the products.
-    const bool work = p.plain || (I0 + wm * NB * 16 < n && J0 + wn * NB * 16 < n && !(diag && wm > wn));
     const int fr = lane & 15, fk = lane >> 4;
     constexpr int KS = BK / 4;
     typedef __attribute__((address_space(3))) const unsigned char lds_char;
@@ -181,32 +150,32 @@ __global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
         ob[s] = o + wn * NB * 2048 + W::PANEL;
         asm volatile("" : "+v"(oa[s]), "+v"(ob[s]));   // kept, not recomputed in the loop
     }
-    vec acc[NB][NB];
-#pragma unroll
-    for (int x = 0; x < NB; ++x)
-#pragma unroll
-        for (int y = 0; y < NB; ++y) acc[x][y] = vec{0, 0, 0, 0};
-    const int nk = (int)((n + BK - 1) / BK);   // beyond n both operands are zero
     struct Frag {
-        T a[KS][NB], b[KS][NB];
+        T a[NPR][KS][NB], b[NPR][KS][NB];
     };
     auto read = [&](int stage, Frag& f) {
 #pragma unroll
-        for (int s = 0; s < KS; ++s)
+        for (int p = 0; p < NPR; ++p)
 #pragma unroll
-            for (int x = 0; x < NB; ++x) {
-                typedef __attribute__((address_space(3))) const T lds_T;
-                f.a[s][x] = *(lds_T*)(lds0 + oa[s] + stage * W::STAGE + x * 2048);
-                f.b[s][x] = *(lds_T*)(lds0 + ob[s] + stage * W::STAGE + x * 2048);
-            }
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int x = 0; x < NB; ++x) {
+                    typedef __attribute__((address_space(3))) const T lds_T;
+                    const int o = stage * W::STAGE + p * 2 * W::PANEL + x * 2048;
+                    f.a[p][s][x] = *(lds_T*)(lds0 + oa[s] + o);
+                    f.b[p][s][x] = *(lds_T*)(lds0 + ob[s] + o);
+                }
     };
     auto multiply = [&](const Frag& f) {
 #pragma unroll
         for (int s = 0; s < KS; ++s)
 #pragma unroll
-            for (int x = 0; x < NB; ++x)
+            for (int p = 0; p < NPR; ++p)
 #pragma unroll
-                for (int y = 0; y < NB; ++y) acc[x][y] = M::mma(f.a[s][x], f.b[s][y], acc[x][y]);
+                for (int x = 0; x < NB; ++x)
+#pragma unroll
+                    for (int y = 0; y < NB; ++y)
+                        acc[p][x][y] = M::mma(f.a[p][s][x], f.b[p][s][y], acc[p][x][y]);
     };
     // Block i in stage u. First waits until this wave's loads of block i + 1 have landed (those of the
     // S - 2 blocks after it may be in flight) and its fragment reads of block i are done, and joins
@@ -259,6 +228,56 @@ __global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
     else loop(std::false_type{});
     asm volatile("" ::: "memory");
     __syncthreads();
+}
+
+template <typename T, int BM, bool ALIGNED>
+__global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
+    using M = Mfma<T>;
+    using W = WCfg<T, BM>;
+    using vec = typename M::vec;
+    using gvec = typename std::conditional<ALIGNED, vec, typename Unaligned<T>::vec>::type;
+    constexpr int NB = W::NB;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1, fr = lane & 15;
+    const int64_t np = p.np, n = p.n;
+    const int T_ = (int)(np / BM);
+    const int t = split::xcd_tile(blockIdx.x, gridDim.x);
+    int I, J;
+    split::tile_coords(t, T_, I, J);
+    const bool diag = I == J;
+    const int64_t I0 = (int64_t)I * BM, J0 = (int64_t)J * BM;
+    const T* __restrict__ X = static_cast<const T*>(p.X_in);
+    T* __restrict__ A = static_cast<T*>(p.A);
+    const bool last = p.last != 0, ent = p.entropy != 0;
+    const T dn = (T)p.d_next;
+    const bool use_a = last || dn != (T)0;
+
+    // the epilogue's groups (all inside the padded matrices)
+    vec xg[W::PER], ag[W::PER];
+    auto group = [&](int u) {
+        const int e = tid + u * NT;
+        return (I0 + e / W::G) * np + J0 + (e % W::G) * 4;
+    };
+#pragma unroll
+    for (int u = 0; u < W::PER; ++u) xg[u] = *reinterpret_cast<const gvec*>(X + group(u));
+    if (use_a) {
+#pragma unroll
+        for (int u = 0; u < W::PER; ++u) ag[u] = *reinterpret_cast<const gvec*>(A + group(u));
+    }
+    // A block whose rows or columns are all padding, or that lies strictly below the diagonal, is
+    // not stored: its wave skips the products. Beyond n both operands are zero.
+    const bool work = I0 + wm * NB * 16 < n && J0 + wn * NB * 16 < n && !(diag && wm > wn);
+    vec acc[1][NB][NB];
+#pragma unroll
+    for (int x = 0; x < NB; ++x)
+#pragma unroll
+        for (int y = 0; y < NB; ++y) acc[0][x][y] = vec{0, 0, 0, 0};
+    const T* const lp[1] = {X + I0 * np};
+    const T* const rp[1] = {X + J0 * np};
+    wide_products<T, BM, ALIGNED, 1>(lp, rp, np, (int)((n + W::BK - 1) / W::BK), work, smem, acc);
 
     // the product tile goes through LDS to four-column groups in registers
     T* sY = reinterpret_cast<T*>(smem);
@@ -268,19 +287,13 @@ __global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
         for (int y = 0; y < NB; ++y)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                sY[((wm * NB + x) * 16 + M::crow(lane, j)) * W::LDY + (wn * NB + y) * 16 + fr] = acc[x][y][j];
+                sY[((wm * NB + x) * 16 + M::crow(lane, j)) * W::LDY + (wn * NB + y) * 16 + fr] = acc[0][x][y][j];
     __syncthreads();
     vec yg[W::PER];
 #pragma unroll
     for (int u = 0; u < W::PER; ++u) {
         const int e = tid + u * NT;
         yg[u] = *reinterpret_cast<const vec*>(sY + (e / W::G) * W::LDY + (e % W::G) * 4);
-    }
-    if (p.plain) {
-        T* C = static_cast<T*>(p.X_out);
-#pragma unroll
-        for (int u = 0; u < W::PER; ++u) *reinterpret_cast<gvec*>(C + group(u)) = yg[u];
-        return;
     }
 
     const T ca = (T)p.a, cb = (T)p.b, cc = (T)p.c;
@@ -401,6 +414,86 @@ __global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
     }
 }
 
+// Backward of one layer of the FP32 matrix recursion in one pass over the upper tiles (I, J): with
+// M = Xb X (Xb the adjoint of this layer's output, X its input),
+//   Xb_out = a (M + M^T) + b Xb + d G,
+// and the tile's FP64 sums of <M, X>, <Xb, X>, Tr Xb and <G, X> (the layer's coefficient gradients).
+// The tile needs M at (i, j) and at (j, i): two products over the same K blocks, Xb_I X_J^T and
+// X_I Xb_J^T, so that no M goes through memory and no transposed pass follows. n = 256: 8 us per
+// layer against 43 for the separate product, elementwise pass and one-thread reduction.
+template <bool ALIGNED>
+__global__ void __launch_bounds__(NT) k_wide_bwd(BwdArgs p) {
+    constexpr int BM = 32;
+    using M = Mfma<float>;
+    using W = WCfg<float, BM, 2>;
+    using gvec = typename std::conditional<ALIGNED, floatx4, Unaligned<float>::vec>::type;
+    static_assert(W::PER == 1 && W::NB == 1, "one group per thread");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1, fr = lane & 15;
+    const int64_t np = p.n;
+    const int t = split::xcd_tile(blockIdx.x, gridDim.x);
+    int I, J;
+    split::tile_coords(t, (int)(np / BM), I, J);
+    const bool diag = I == J;
+    const int64_t I0 = (int64_t)I * BM, J0 = (int64_t)J * BM;
+    // element groups: (I0 + r, J0 + c ..) of the tile and (J0 + r, I0 + c ..) of its mirror
+    const int r = tid / W::G, c = (tid % W::G) * 4;
+    const int64_t gu = (I0 + r) * np + J0 + c, gl = (J0 + r) * np + I0 + c;
+    auto load = [](const float* m, int64_t o) -> floatx4 { return *reinterpret_cast<const gvec*>(m + o); };
+    const floatx4 xu = load(p.X, gu), bu = load(p.Xb, gu), qu = load(p.G, gu);
+    const floatx4 xl = load(p.X, gl), bl = load(p.Xb, gl), ql = load(p.G, gl);
+
+    floatx4 acc[2][1][1] = {{{floatx4{0, 0, 0, 0}}}, {{floatx4{0, 0, 0, 0}}}};
+    const float* const lp[2] = {p.Xb + I0 * np, p.X + I0 * np};
+    const float* const rp[2] = {p.X + J0 * np, p.Xb + J0 * np};
+    wide_products<float, BM, ALIGNED, 2>(lp, rp, np, (int)(np / W::BK), true, smem, acc);
+
+    float* s0 = reinterpret_cast<float*>(smem);   // M at (i, j)
+    float* s1 = s0 + BM * W::LDY;                 // M at (j, i), stored at (i, j)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int o = (wm * 16 + M::crow(lane, j)) * W::LDY + wn * 16 + fr;
+        s0[o] = acc[0][0][0][j];
+        s1[o] = acc[1][0][0][j];
+    }
+    __syncthreads();
+    double sa = 0.0, sb = 0.0, sc = 0.0, sd = 0.0;
+    auto half = [&](int64_t o, auto m_at, auto mt_at, const floatx4& x, const floatx4& xb,
+                    const floatx4& g, int64_t row, int64_t col) {
+        floatx4 out;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float m = m_at(k), mt = mt_at(k);
+            sa += (double)m * x[k];
+            sb += (double)xb[k] * x[k];
+            if (row == col + k) sc += xb[k];
+            sd += (double)g[k] * x[k];
+            out[k] = fmaf(p.cd, g[k], fmaf(p.ca, m + mt, p.cb * xb[k]));
+        }
+        *reinterpret_cast<gvec*>(p.Xb_out + o) = out;
+    };
+    half(gu, [&](int k) { return s0[r * W::LDY + c + k]; }, [&](int k) { return s1[r * W::LDY + c + k]; },
+         xu, bu, qu, I0 + r, J0 + c);
+    if (!diag)
+        half(gl, [&](int k) { return s1[(c + k) * W::LDY + r]; },
+             [&](int k) { return s0[(c + k) * W::LDY + r]; }, xl, bl, ql, J0 + r, I0 + c);
+    sa = wave_sum(sa);
+    sb = wave_sum(sb);
+    sc = wave_sum(sc);
+    sd = wave_sum(sd);
+    __syncthreads();
+    double* red = reinterpret_cast<double*>(smem);
+    if (lane == 0) {
+        red[4 * wave] = sa;
+        red[4 * wave + 1] = sb;
+        red[4 * wave + 2] = sc;
+        red[4 * wave + 3] = sd;
+    }
+    __syncthreads();
+    if (tid < 4) p.part[(size_t)t * 4 + tid] = (red[tid] + red[4 + tid]) + (red[8 + tid] + red[12 + tid]);
+}
+
 // Lower triangle of an np x np FP32 matrix from its upper triangle (X[i][j] = X[j][i] for
 // i > j), through 64 x 64 LDS tiles: workgroup (I, J), I >= J, reads the upper tile (J, I) row by
 // row and writes its transpose into the lower tile (I, J); diagonal tiles copy within the tile.
@@ -432,15 +525,15 @@ hipError_t launch_t(const WideArgs& a, hipStream_t s) {
     constexpr size_t lds = WCfg<T, BM>::LDS;
     static_assert(lds <= 64 * 1024, "no attribute needed for the dynamic LDS");
     const int T_ = (int)(a.np / BM);
-    hipLaunchKernelGGL(kern, dim3(a.plain ? T_ * T_ : T_ * (T_ + 1) / 2), dim3(NT), lds, s, a);
+    hipLaunchKernelGGL(kern, dim3(T_ * (T_ + 1) / 2), dim3(NT), lds, s, a);
     return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch(const WideArgs& a, hipStream_t s) {
     if (a.np % kPad != 0 || a.n < 1 || a.n > a.np) return hipErrorInvalidValue;
-    const uintptr_t m = reinterpret_cast<uintptr_t>(a.X_in) | reinterpret_cast<uintptr_t>(a.B_in) |
-                        reinterpret_cast<uintptr_t>(a.X_out) | reinterpret_cast<uintptr_t>(a.A);
+    const uintptr_t m = reinterpret_cast<uintptr_t>(a.X_in) | reinterpret_cast<uintptr_t>(a.X_out) |
+                        reinterpret_cast<uintptr_t>(a.A);
     if (m % 16 != 0)
         return wide_bm(a.np) == 32 ? launch_t<T, 32, false>(a, s) : launch_t<T, 64, false>(a, s);
     return wide_bm(a.np) == 32 ? launch_t<T, 32, true>(a, s) : launch_t<T, 64, true>(a, s);
@@ -460,6 +553,21 @@ int wide_tiles(int64_t np) {
 }
 hipError_t launch_layer_f32(const WideArgs& a, hipStream_t s) { return launch<float>(a, s); }
 hipError_t launch_layer_f64(const WideArgs& a, hipStream_t s) { return launch<double>(a, s); }
+int wide_bwd_tiles(int64_t n) {
+    const int T_ = (int)(n / 32);
+    return T_ * (T_ + 1) / 2;
+}
+hipError_t launch_layer_bwd(const BwdArgs& a, hipStream_t s) {
+    if (a.n < kPad || a.n % kPad != 0) return hipErrorInvalidValue;
+    const uintptr_t m = reinterpret_cast<uintptr_t>(a.X) | reinterpret_cast<uintptr_t>(a.Xb) |
+                        reinterpret_cast<uintptr_t>(a.G) | reinterpret_cast<uintptr_t>(a.Xb_out);
+    constexpr size_t lds = WCfg<float, 32, 2>::LDS;
+    static_assert(lds <= 64 * 1024, "no attribute needed for the dynamic LDS");
+    const dim3 grid(wide_bwd_tiles(a.n));
+    if (m % 16 != 0) hipLaunchKernelGGL(k_wide_bwd<false>, grid, dim3(NT), lds, s, a);
+    else hipLaunchKernelGGL(k_wide_bwd<true>, grid, dim3(NT), lds, s, a);
+    return hipGetLastError();
+}
 hipError_t launch_mirror_upper_f32(float* X, int64_t np, hipStream_t s) {
     if (np % kPad != 0) return hipErrorInvalidValue;
     const int T_ = (int)(np / kPad);

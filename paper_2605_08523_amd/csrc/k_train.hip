@@ -3,7 +3,7 @@
 //    and its output layer), the residuals against the target values and the Jacobian with
 //    respect to the 4L coefficients by reverse-mode differentiation, FP64, one lane per point;
 //  * Gram products J^T J and J^T v for the Levenberg-Marquardt normal equations;
-//  * the elementwise part of the backward pass of the FP32 matrix recursion.
+//  * the reduction of the backward pass's coefficient gradients (its layers: k_layer_wide.hip).
 #include <math.h>
 
 #include "fe_internal.h"
@@ -119,45 +119,21 @@ k_gram(const double* JT, const double* v, int P, int n, double* G, double* g) {
     if (threadIdx.x == 0) *dst = red[0];
 }
 
-// Backward of one layer of the FP32 matrix recursion, given M = Xb_{i+1} X_i:
-//   grad a_i = <M, X_i>, grad b_i = <Xb_{i+1}, X_i>, grad c_i = tr Xb_{i+1}, grad d_i = <G, X_i>,
-//   Xb_i = a_i (M + M^T) + b_i Xb_{i+1} + d_i G.
-// Partial sums per block (FP64) are reduced in a fixed order by k_bwd_reduce.
+// Coefficient gradients of layer blockIdx.x: its tiles' partial sums, four threads' strides apart, in
+// a fixed order.
 __global__ void __launch_bounds__(256)
-k_bwd_elem(BwdArgs a) {
-    const int64_t n = a.n;
-    const int64_t total = n * n;
-    double sa = 0.0, sb = 0.0, sc = 0.0, sd = 0.0;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-        const int64_t i = e / n, j = e - i * n;
-        const float m = a.M[e], mt = a.M[j * n + i];
-        const float xb = a.Xb[e], x = a.X[e], gg = a.G[e];
-        sa += (double)m * x;
-        sb += (double)xb * x;
-        if (i == j) sc += xb;
-        sd += (double)gg * x;
-        a.Xb_out[e] = a.ca * (m + mt) + a.cb * xb + a.cd * gg;
-    }
-    __shared__ double red[4][256];
-    red[0][threadIdx.x] = sa;
-    red[1][threadIdx.x] = sb;
-    red[2][threadIdx.x] = sc;
-    red[3][threadIdx.x] = sd;
+k_bwd_reduce(const double* part, int tiles, double* grad) {
+    const double* q = part + (size_t)blockIdx.x * tiles * 4;
+    __shared__ double red[256];
+    double s = 0.0;
+    for (int e = threadIdx.x; e < tiles * 4; e += 256) s += q[e];   // e % 4 = threadIdx.x % 4
+    red[threadIdx.x] = s;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int c = 0; c < 4; ++c) red[c][threadIdx.x] += red[c][threadIdx.x + w];
+    for (int w = 128; w >= 4; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x < 4) a.part[(size_t)blockIdx.x * 4 + threadIdx.x] = red[threadIdx.x][0];
-}
-
-__global__ void __launch_bounds__(64)
-k_bwd_reduce(const double* part, int nblocks, double* grad4) {
-    if (threadIdx.x >= 4) return;
-    double s = 0.0;
-    for (int b = 0; b < nblocks; ++b) s += part[(size_t)b * 4 + threadIdx.x];
-    grad4[threadIdx.x] = s;
+    if (threadIdx.x < 4) grad[(size_t)blockIdx.x * 4 + threadIdx.x] = red[threadIdx.x];
 }
 
 // P = A + X_L from the forward history (A = sum_i d_i X_i), and G-weighted output pieces.
@@ -222,9 +198,8 @@ hipError_t launch_gram(const double* JT, const double* v, int P, int n, double* 
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_elem(const BwdArgs& a, int nblocks, double* grad4, hipStream_t s) {
-    hipLaunchKernelGGL(k_bwd_elem, dim3(nblocks), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_bwd_reduce, dim3(1), dim3(64), 0, s, a.part, nblocks, grad4);
+hipError_t launch_bwd_reduce(const double* part, int tiles, int L, double* grad, hipStream_t s) {
+    hipLaunchKernelGGL(k_bwd_reduce, dim3(L), dim3(256), 0, s, part, tiles, grad);
     return hipGetLastError();
 }
 
