@@ -89,25 +89,35 @@ k_layer_dp(LayerArgs p) {
 // the same order as k_layer_dp. The two-part 128 x 128 ones, whose sizes (n > 1984) ran stream-K
 // before, sum K in segments of 512, as that schedule's partial tiles did at n = 2048: one chain of
 // 2048 gave 1.45 times its error against FP64.
+template <bool BF, class C, int AUX>
+__device__ __attribute__((always_inline)) inline void ring_tile(const LayerArgs& p, int t,
+                                                                unsigned char* smem, bool poisoned) {
+    int I, J;
+    tile_coords(t, (int)(p.np / C::BM), I, J);
+    constexpr bool kPre = EpiPre<C>::PER <= 4;
+    constexpr int kSeg = C::BM == 128 && C::NS == 2 ? 512 / C::BK : 0;
+    EpiPre<C> pre;
+    if constexpr (kPre) pre.template load<AUX>(p, I, J);
+    Acc<C> acc;
+    zero(acc);
+    kloop_dma<BF, C, kSeg, AUX>(p.hi_in, p.mid_in, p.lo_in, p.np, (int64_t)I * C::BM,
+                                (int64_t)J * C::BM, 0, (int)(p.np / C::BK), acc,
+                                reinterpret_cast<uint16_t*>(smem));
+    if constexpr (C::BM == 64) {
+        if (!p.last && !p.affine) {
+            epilogue_mid64<BF, C>(p, acc, reinterpret_cast<float*>(smem), I, J, poisoned, pre);
+            return;
+        }
+    }
+    epilogue<BF, C, kPre ? 8 : 2, kPre>(p, acc, reinterpret_cast<float*>(smem), I, J, t, nullptr, 0,
+                                        0, poisoned, &pre);
+}
+
 template <bool BF, class C>
 __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_layer_ring(LayerArgs p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int T = (int)(p.np / C::BM);
-    const int t = xcd_tile(blockIdx.x, gridDim.x);
-    int I, J;
-    tile_coords(t, T, I, J);
-    constexpr bool kPre = EpiPre<C>::PER <= 4;
-    constexpr int kSeg = C::BM == 128 && C::NS == 2 ? 512 / C::BK : 0;
-    EpiPre<C> pre;
-    if constexpr (kPre) pre.load(p, I, J);
-    Acc<C> acc;
-    zero(acc);
-    kloop_dma<BF, C, kSeg>(p.hi_in, p.mid_in, p.lo_in, p.np, (int64_t)I * C::BM,
-                           (int64_t)J * C::BM, 0, (int)(p.np / C::BK), acc,
-                           reinterpret_cast<uint16_t*>(smem));
-    epilogue<BF, C, kPre ? 8 : 2, kPre>(p, acc, reinterpret_cast<float*>(smem), I, J, t, nullptr, 0,
-                                        0, false, &pre);
+    ring_tile<BF, C, 0>(p, xcd_tile(blockIdx.x, gridDim.x), smem, false);
 }
 
 // Thread 0 waits until the workgroups of group g with indices jlo .. j-1 have published their

@@ -3,6 +3,8 @@
 // epilogue of one upper-triangle tile.
 #pragma once
 
+#include <type_traits>
+
 #include "fe_internal.h"
 
 namespace fe {
@@ -21,8 +23,8 @@ template <bool BF>
 __device__ inline void split16(float x, uint16_t& h, uint16_t& l) {
     if constexpr (!BF) {
         const _Float16 hh = (_Float16)x;
-        const float r = x - (float)hh;
-        const _Float16 ll = (_Float16)(r * 2048.0f);
+        // (x - hi) 2^11, exact in FP32, as one mixed-precision fused multiply-add
+        const _Float16 ll = (_Float16)fmaf(-(float)hh, 2048.0f, x * 2048.0f);
         h = __builtin_bit_cast(uint16_t, hh);
         l = __builtin_bit_cast(uint16_t, ll);
     } else {
@@ -186,77 +188,103 @@ struct Acc {
     floatx16 v[C::MB][C::NB];
 };
 
-// Direct-to-LDS form of the K loop (C::DMA): each lane's global_load_lds_dwordx4 moves one
-// 16-byte chunk, and the 64 chunks of one instruction land in 1 KiB of LDS in lane order. A stage
-// holds the 2 NS BM x BK operand panels (A parts, then B parts) in unpadded rows; chunk c of row
-// r sits at position c ^ ((r / RP) % CPR) of its row (RP rows per 128 bytes), so the eight rows
-// that a quarter-wave's fragment read touches fall on distinct banks. The stages form a ring:
-// while block kb is multiplied, the next STAGES - 1 blocks are in flight, so a short K loop whose
-// operands come from beyond the L2 (another XCD wrote them) pays that latency once and not per
-// block. SEG > 0: the blocks are summed in segments of SEG, each from zero, and the segments' sums
-// added (a long K loop then rounds like the stream-K schedules' partial sums, not like one
-// chain). The barrier is a bare s_barrier after an explicit wait for this wave's own loads of block
-// kb (a full __syncthreads would also drain everything else in flight) and for its fragment reads
-// of block kb - 1, whose stage is refilled right after it. Blocks, K steps and products are taken
-// in the order of the register-staged loops, so an element's sum does not depend on the form.
-template <bool BF, class C, int SEG = 0>
-__device__ inline void kloop_dma(const uint16_t* __restrict__ hin, const uint16_t* __restrict__ min,
-                                 const uint16_t* __restrict__ lin, int64_t np, int64_t I0,
-                                 int64_t J0, int kb0, int kb1, Acc<C>& acc, uint16_t* smem) {
+// Buffer resource over [base, base + bytes) for raw buffer accesses (lanes outside the range
+// read zero and drop their stores).
+__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes,
+                                             0x00020000);
+}
+
+// Direct-to-LDS form of the K loop (C::DMA): each lane's buffer_load_dwordx4 ... lds moves one 16-byte
+// chunk, and the 64 chunks of one instruction land in 1 KiB of LDS in lane order. A stage holds the
+// 2 NS BM x BK operand panels (A parts, then B parts) in unpadded rows; chunk c of row r sits at
+// position c ^ ((r / RP) % CPR) of its row (RP rows per 128 bytes), so the eight rows that a
+// quarter-wave's fragment read touches fall on distinct banks. The stages form a ring: while block
+// kb is multiplied, the next STAGES - 1 blocks are in flight, so a short K loop whose operands come
+// from beyond the L2 (another XCD wrote them) pays that latency once and not per block. A wave alone
+// on its SIMD pays for every instruction between its MFMAs, so the loop has few: the loads' addresses
+// are one lane offset plus a scalar, the fragments' a fixed register plus a constant (the stages are
+// unrolled), and each step's fragments are read during the step before, across the block boundary
+// too. The barrier there is a bare s_barrier after an explicit wait for this wave's own loads of the
+// next block (a full __syncthreads would also drain everything else in flight) and its fragment
+// reads of the current one, whose stage is refilled after it. AUX: cache policy of the operand
+// loads. SEG > 0: the blocks are summed in segments of SEG, each from zero, and the segments' sums
+// added (a long K loop then rounds like the stream-K schedules' partial sums, not like one chain).
+// Blocks, K steps and products are taken in the order of the register-staged loops, so an element's
+// sum (SEG = 0) does not depend on the form. Ends with a barrier.
+template <bool BF, class C, int SEG = 0, int AUX = 0>
+__device__ __attribute__((always_inline)) inline void kloop_dma(
+    const uint16_t* __restrict__ hin, const uint16_t* __restrict__ min,
+    const uint16_t* __restrict__ lin, int64_t np, int64_t I0, int64_t J0, int kb0, int kb1,
+    Acc<C>& acc, uint16_t* smem) {
     typedef __attribute__((address_space(3))) void lds_void;
-    typedef const __attribute__((address_space(1))) void global_void;
+    typedef __attribute__((address_space(3))) const unsigned char lds_char;
+    typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
     constexpr int NS = C::NS, S = C::STAGES;
-    constexpr int CPR = C::BK / 8, RP = 8 / CPR > 0 ? 8 / CPR : 1, RPI = 64 / CPR;
-    constexpr int IPA = C::BM / RPI;                      // 1-KiB instructions per panel and stage
-    constexpr int NW = C::NT / 64, IPW = 2 * NS * IPA / NW;   // per wave and stage
-    constexpr int PANEL = C::BM * C::BK, STAGE = 2 * NS * PANEL;
-    static_assert((RPI / RP) % CPR == 0, "a lane's chunk position is the same in every instruction");
-    static_assert(2 * NS * IPA % NW == 0 && IPW * (S - 1) < 64, "in-flight loads fit the wait counter");
+    constexpr int CPR = C::BK / 8, RP = 8 / CPR, RPI = 64 / CPR;
+    constexpr int IPA = C::BM / RPI;                          // 1-KiB loads per panel and stage
+    constexpr int NW = C::NT / 64, IPW = 2 * NS * IPA / NW;   // loads per wave and stage
+    constexpr int ROW = 2 * C::BK, PANEL = C::BM * ROW, STAGE = 2 * NS * PANEL;   // bytes
+    static_assert(IPA % NW == 0, "a wave's load q is in panel NW q / IPA");
+    static_assert((RPI / RP) % CPR == 0 && 32 / RP % CPR == 0, "chunk positions depend on the lane only");
+    static_assert(IPW * (S - 1) < 64, "in-flight loads fit the wait counter");
+    static_assert(SEG % S == 0, "segments are whole turns of the ring");
     int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    const int lane = tid & 63, wave = tid >> 6;
+    asm volatile("" : "+v"(tid));   // keep address arithmetic inside a caller's persistent loop
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / C::WN, wn = wave % C::WN;
-    auto swz = [](int r, int c) { return c ^ ((r / RP) % CPR); };
-    // Instruction q of this wave covers panel a, rows blk * RPI .. + RPI - 1: a wave-uniform base
-    // (scalar registers) plus the lane's offset, the same for every q.
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const uint32_t lane_off = (uint32_t)((lane / CPR) * np + swz(lane / CPR, lane % CPR) * 8);
-    const uint16_t* src[IPW];
-    int dst[IPW];
+    const uint32_t row_bytes = (uint32_t)(2 * np);
+    const uint32_t lane_off =
+        (lane / CPR) * row_bytes + (((lane % CPR) ^ ((lane / CPR / RP) % CPR)) << 4);
+    __amdgpu_buffer_rsrc_t rs[2 * NS];
 #pragma unroll
-    for (int q = 0; q < IPW; ++q) {
-        const int gi = wave_u + q * NW, a = gi / IPA, blk = gi % IPA, part = a % NS;
+    for (int a = 0; a < 2 * NS; ++a) {
+        const int part = a % NS;
         const uint16_t* base = part == 0 ? hin : (NS == 3 && part == 1) ? min : lin;
-        src[q] = base + ((a < NS ? I0 : J0) + blk * RPI) * np;
-        dst[q] = a * PANEL + blk * RPI * C::BK;
+        rs[a] = make_rsrc(base + (a < NS ? I0 : J0) * np, C::BM * row_bytes);
     }
-    auto issue = [&](int kb, uint16_t* stage, int q0, int q1) {
-        const int64_t k0 = (int64_t)kb * C::BK;
+    auto issue = [&](int kb, int stage, int q0, int q1) {
 #pragma unroll
-        for (int q = q0; q < q1; ++q)
-            __builtin_amdgcn_global_load_lds((global_void*)(src[q] + k0 + lane_off),
-                                             (lds_void*)(stage + dst[q]), 16, 0, 0);
+        for (int q = q0; q < q1; ++q) {
+            const int a = NW * q / IPA, blk = wave + NW * q % IPA;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rs[a], (lds_void*)((unsigned char*)smem + stage * STAGE + a * PANEL + blk * 1024), 16,
+                (int)lane_off, (int)(blk * RPI * row_bytes + (uint32_t)kb * ROW), 0, AUX);
+        }
     };
-    const int frag_row = lane & 31, frag_c = lane >> 5;
+    constexpr int KS = C::BK / 16;
+    static_assert(KS % 2 == 0, "two fragment sets");
+    // byte offsets of this lane's 16 bytes of K step ks in the wave's first A and B row block; one
+    // register per 64 KiB of stages (the reach of an LDS instruction's constant)
+    constexpr int SPG = 65536 / STAGE < 1 ? 1 : 65536 / STAGE, GR = (S + SPG - 1) / SPG;
+    uint32_t oa[GR][KS], ob[GR][KS];
+#pragma unroll
+    for (int g = 0; g < GR; ++g)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int r = lane & 31;
+            const uint32_t o = r * ROW + (((ks * 2 + (lane >> 5)) ^ ((r / RP) % CPR)) << 4) + g * SPG * STAGE;
+            oa[g][ks] = o + wm * C::WAVE_M * ROW;
+            ob[g][ks] = o + wn * C::WAVE_N * ROW + NS * PANEL;
+            asm volatile("" : "+v"(oa[g][ks]), "+v"(ob[g][ks]));
+        }
+    lds_char* const lds0 = (lds_char*)smem;
     struct Frag {
         u32x4 a[C::MB][NS], b[C::NB][NS];
     };
-    auto ld = [&](const uint16_t* stage, int ks, Frag& f) {
+    auto ld = [&](int stage, int ks, Frag& f) {
+        const int g = stage / SPG, so = stage % SPG * STAGE;
 #pragma unroll
-        for (int mb = 0; mb < C::MB; ++mb) {
-            const int r = wm * C::WAVE_M + mb * 32 + frag_row;
-            const int o = r * C::BK + swz(r, ks * 2 + frag_c) * 8;
-#pragma unroll
-            for (int t = 0; t < NS; ++t) f.a[mb][t] = *reinterpret_cast<const u32x4*>(stage + t * PANEL + o);
-        }
-#pragma unroll
-        for (int nb = 0; nb < C::NB; ++nb) {
-            const int r = wn * C::WAVE_N + nb * 32 + frag_row;
-            const int o = r * C::BK + swz(r, ks * 2 + frag_c) * 8;
+        for (int mb = 0; mb < C::MB; ++mb)
 #pragma unroll
             for (int t = 0; t < NS; ++t)
-                f.b[nb][t] = *reinterpret_cast<const u32x4*>(stage + (NS + t) * PANEL + o);
-        }
+                f.a[mb][t] = *(lds_u32x4*)(lds0 + oa[g][ks] + so + t * PANEL + mb * 32 * ROW);
+#pragma unroll
+        for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+            for (int t = 0; t < NS; ++t)
+                f.b[nb][t] = *(lds_u32x4*)(lds0 + ob[g][ks] + so + t * PANEL + nb * 32 * ROW);
     };
     auto mm = [&](const Frag& f) {
 #pragma unroll
@@ -273,11 +301,8 @@ __device__ inline void kloop_dma(const uint16_t* __restrict__ hin, const uint16_
             }
         }
     };
-    // Scheduling of one step: this step's share of the loads that refill the free stage, the hi
-    // scaling, then the fragment reads of the next step, spread between this step's MFMAs where it
-    // has enough of them, else ahead of them.
-    constexpr int KS = C::BK / 16;
-    static_assert(KS % 2 == 0, "two fragment sets");
+    // Scheduling of one step: the fragment reads of the next step, spread between this step's MFMAs
+    // where it has enough of them, else ahead of them.
     constexpr int NDS = NS * (C::MB + C::NB), NMF = (NS == 3 ? 6 : 3) * C::MB * C::NB;
     constexpr int PER = NMF >= 2 * NDS ? 2 : 1;   // MFMAs between two fragment reads
     auto pattern = [&](bool reads) {
@@ -296,66 +321,124 @@ __device__ inline void kloop_dma(const uint16_t* __restrict__ hin, const uint16_
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    // Multiplies the block in `stage`; fill: block `kbf` is loaded into `free` meanwhile, a part of
-    // its loads with each K step (issued in one piece they would hold every wave of the workgroup
-    // at the same point while the load path takes them, the MFMA pipes idle).
-    constexpr int FS = S == 2 ? (KS + 1) / 2 : KS;   // steps that carry loads (S = 2: the early ones)
-    auto compute = [&](const uint16_t* stage, bool fill, int kbf, uint16_t* free) {
-        Frag f0, f1;
-        ld(stage, 0, f0);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            if (ks < FS && fill) issue(kbf, free, ks * IPW / FS, (ks + 1) * IPW / FS);
-            __builtin_amdgcn_sched_barrier(0);
-            Frag& cur = ks & 1 ? f1 : f0;
-            Frag& nxt = ks & 1 ? f0 : f1;
-            if (ks + 1 < KS) ld(stage, ks + 1, nxt);
-            mm(cur);
-            pattern(ks + 1 < KS);
-        }
-    };
     const int nk = kb1 - kb0;
-#pragma unroll
-    for (int q = 0; q < S - 1; ++q)
-        if (q < nk) issue(kb0 + q, smem + q * STAGE, 0, IPW);
-    // lgkmcnt(0) and vmcnt(n) with n = the loads of the blocks after this one (6-bit counter)
+    Frag f0, f1;
+    // Block i in stage u. kCross: before its last step this wave's loads of block i + 1 have landed
+    // (those of the S - 2 blocks after it may be in flight), every wave's have, and block i's stage
+    // is free: block i + S then goes there, the loads spread over this step and the next block's
+    // (S = 2: the next block's first, for their way is the shortest). Wave tiles whose accumulators
+    // leave no room for fragments across the boundary arrive at the block's start instead.
+    // full: the blocks up to i + S exist (no conditions).
+    constexpr bool kCross = C::MB * C::NB <= 4;
     constexpr int kAhead = IPW * (S - 2);
-    constexpr int kWait = 0x0070 | (kAhead & 15) | ((kAhead >> 4) << 14);
-    int slot = 0;
-    Acc<C> sum;
-    if constexpr (SEG > 0) sum = acc;
-    for (int i = 0; i < nk; ++i) {
-        if constexpr (SEG > 0) {
-            if (i % SEG == 0) {
-#pragma unroll
-                for (int mb = 0; mb < C::MB; ++mb)
-#pragma unroll
-                    for (int nb = 0; nb < C::NB; ++nb)
-#pragma unroll
-                        for (int j = 0; j < 16; ++j) {
-                            if (i > 0) sum.v[mb][nb][j] += acc.v[mb][nb][j];
-                            acc.v[mb][nb][j] = 0.0f;
-                        }
-            }
-        }
-        // this wave's chunks of block i landed (the last S - 2 blocks drain everything)
-        if (i + S - 2 < nk) __builtin_amdgcn_s_waitcnt(kWait);
+    constexpr int kWait = 0x0070 | (kAhead & 15) | ((kAhead >> 4) << 14);   // lgkmcnt(0), vmcnt(kAhead)
+    constexpr int FS = !kCross ? 1 : S == 2 ? 2 : KS;   // steps that carry loads
+    auto arrive = [&](bool later) {
+        if (later) __builtin_amdgcn_s_waitcnt(kWait);
         else __builtin_amdgcn_s_waitcnt(0x0070);
         asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();          // ... and every wave's; block i - 1's stage is free
+        __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        const int free = slot == 0 ? S - 1 : slot - 1;
-        compute(smem + slot * STAGE, i + S - 1 < nk, kb0 + i + S - 1, smem + free * STAGE);
-        slot = slot == S - 1 ? 0 : slot + 1;
+    };
+    auto block = [&](auto full, int i, int u) {
+        if constexpr (!kCross) {
+            arrive(full || i + S - 2 < nk);
+            if (full || i + S - 1 < nk) issue(kb0 + i + S - 1, (u + S - 1) % S, 0, IPW);
+            ld(u, 0, f0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            Frag& cur = ks & 1 ? f1 : f0;
+            Frag& nxt = ks & 1 ? f0 : f1;
+            if (ks + 1 < KS) {
+                ld(u, ks + 1, nxt);
+                mm(cur);
+                pattern(true);
+                // the rest of block i - 1 + S, whose first loads followed block i - 1's last step
+                if constexpr (kCross)
+                    if (ks + 1 < FS && (full || i - 1 + S < nk))
+                        issue(kb0 + i - 1 + S, (u + S - 1) % S, (ks + 1) * IPW / FS, (ks + 2) * IPW / FS);
+            } else if (kCross && (full || i + 1 < nk)) {
+                arrive(full || i + S - 1 < nk);
+                ld((u + 1) % S, 0, nxt);
+                mm(cur);
+                pattern(true);
+                if (full || i + S < nk) issue(kb0 + i + S, u, 0, IPW / FS);
+            } else {
+                mm(cur);
+                pattern(false);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    auto turn = [&](auto full, int i) {
+        block(full, i, 0);
+        if (full || i + 1 < nk) block(full, i + 1, 1);
+        if constexpr (S > 2)
+            if (full || i + 2 < nk) block(full, i + 2, 2);
+        if constexpr (S > 3)
+            if (full || i + 3 < nk) block(full, i + 3, 3);
+        static_assert(S >= 2 && S <= 4, "stages unrolled");
+    };
+    // the blocks in flight at the start: kCross all but the part of block S - 1 that block 0 issues
+#pragma unroll
+    for (int q = 0; q < S - 1; ++q)
+        if (q < nk) issue(kb0 + q, q, 0, IPW);
+    if constexpr (kCross) {
+        if (S - 1 < nk) {
+            issue(kb0 + S - 1, S - 1, 0, IPW / FS);
+            constexpr int w = IPW * (S - 2) + IPW / FS;
+            __builtin_amdgcn_s_waitcnt(0x0070 | (w & 15) | ((w >> 4) << 14));
+        } else {
+            __builtin_amdgcn_s_waitcnt(0x0070);
+        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        ld(0, 0, f0);
+        __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (SEG > 0) {
+    // whole turns of the ring whose loads all exist, then the rest
+    int i = 0;
+    if constexpr (SEG == 0) {
+        for (; i + 2 * S - 1 < nk; i += S) turn(yes, i);
+        for (; i < nk; i += S) turn(no, i);
+    } else {
+        Acc<C> sum;
+        auto flush = [&](bool fresh) {
 #pragma unroll
-        for (int mb = 0; mb < C::MB; ++mb)
+            for (int mb = 0; mb < C::MB; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < C::NB; ++nb)
+                for (int nb = 0; nb < C::NB; ++nb)
 #pragma unroll
-                for (int j = 0; j < 16; ++j) acc.v[mb][nb][j] += sum.v[mb][nb][j];
+                    for (int j = 0; j < 16; ++j) {
+                        sum.v[mb][nb][j] = fresh ? acc.v[mb][nb][j] : sum.v[mb][nb][j] + acc.v[mb][nb][j];
+                        acc.v[mb][nb][j] = 0.0f;
+                    }
+        };
+        int seg = SEG;   // end of the current segment
+        bool fresh = true;
+        while (i < nk) {
+            const int end = seg < nk ? seg : nk;
+            for (; i < end && i + 2 * S - 1 < nk; i += S) turn(yes, i);
+            for (; i < end; i += S) turn(no, i);
+            if (i < nk) {
+                flush(fresh);
+                fresh = false;
+                seg += SEG;
+            }
+        }
+        if (!fresh) {
+#pragma unroll
+            for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) acc.v[mb][nb][j] += sum.v[mb][nb][j];
+        }
     }
     asm volatile("" ::: "memory");
     __syncthreads();
@@ -660,12 +743,6 @@ __device__ inline float load_coherent(const float* p) {
     return __hip_atomic_load(const_cast<float*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Buffer resource over [base, base + bytes) for raw buffer accesses (lanes outside the range
-// read zero and drop their stores).
-__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes,
-                                             0x00020000);
-}
 constexpr int kCoherentAux = 16;   // cache policy sc1: device-coherent access
 
 // Four consecutive floats at byte offset off of a buffer, read device-coherently (16 bytes).
@@ -675,35 +752,155 @@ __device__ inline floatx4 load4_coherent(__amdgpu_buffer_rsrc_t rs, int off) {
 
 // The X and A groups of a tile that each thread's epilogue uses, loaded before the K loop: the layer
 // reads them from where the previous one left them, usually beyond this XCD's L2, and a short K
-// loop's epilogue would wait for that latency again. For tiles whose epilogue runs in one chunk.
+// loop's epilogue would wait for that latency again. For tiles whose epilogue runs in one chunk of a
+// matrix below 4 GiB. Every address lies in the padded matrices, whose padding the rescale wrote;
+// a is loaded (and later read) only where the layer updates or outputs A. AUX: cache policy.
 template <class C>
 struct EpiPre {
-    static constexpr int G = C::BM / 4, PER = C::EC * G / C::NT;
+    static constexpr int G = C::BM / 4, PER = C::EC * G / C::NT, RPG = C::NT / G;   // rows per group step
     floatx4 x[PER], a[PER];
-    // Every address lies in the padded matrices, whose padding the rescale wrote; groups in the
-    // padding are loaded too and not used. a is loaded (and later read) only where the layer
-    // updates or outputs A.
+    template <int AUX = 0>
     __device__ inline void load(const LayerArgs& p, int I, int J) {
         static_assert(C::EC == C::BM, "one epilogue chunk per tile");
-        const int64_t o = ((int64_t)I * C::BM) * p.np + (int64_t)J * C::BM;
-        const bool load_a = p.last != 0 || p.d_old != 0.0f || p.d_new != 0.0f;
-        auto at = [&](const float* m, int u) {
-            const int e = threadIdx.x + u * C::NT;
-            return *reinterpret_cast<const floatx4*>(m + o + (int64_t)(e / G) * p.np + (e % G) * 4);
+        const uint32_t np = (uint32_t)p.np, bytes = np * np * 4;
+        const int voff = (int)((threadIdx.x / G) * np * 4 + (threadIdx.x % G) * 16);
+        const uint32_t base = ((uint32_t)I * C::BM * np + (uint32_t)J * C::BM) * 4;
+        auto at = [&](__amdgpu_buffer_rsrc_t rs, int u) {
+            return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                   rs, voff, (int)(base + u * RPG * np * 4), AUX));
         };
         if (p.affine == 0) {
+            const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.X, bytes);
 #pragma unroll
-            for (int u = 0; u < PER; ++u) x[u] = at(p.X, u);
+            for (int u = 0; u < PER; ++u) x[u] = at(rs, u);
         } else {
 #pragma unroll
             for (int u = 0; u < PER; ++u) x[u] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
         }
-        if (load_a) {
+        if (p.last != 0 || p.d_old != 0.0f || p.d_new != 0.0f) {
+            const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.A, bytes);
 #pragma unroll
-            for (int u = 0; u < PER; ++u) a[u] = at(p.A, u);
+            for (int u = 0; u < PER; ++u) a[u] = at(rs, u);
         }
     }
 };
+
+// The epilogue of a 64 x 64 tile in the direct layer form, all layers but the last: the same values
+// as epi_chunk in a third of its instructions, which a workgroup alone on its CU waits for one by
+// one (us per density matrix with a launch per layer, 26 layers, against epi_chunk: n = 128 159 / 213,
+// 256 189 / 246, 1001 427 / 469).
+// Addresses are one lane offset plus scalars; the parts split once travel through LDS for the mirror
+// tile; 1/s is folded into a (a power of two); a diagonal tile writes both triangles of X, A and
+// the operands itself, its lower elements from the transposed product (so they equal the upper ones
+// bit for bit). The padding comes out zero. LDS: 16-byte groups of row r at group g ^ (r / 4).
+template <bool BF, class C>
+__device__ inline void epilogue_mid64(const LayerArgs& p, const Acc<C>& acc, float* sY, int I, int J,
+                                      bool poisoned, const EpiPre<C>& pre) {
+    static_assert(C::BM == 64 && C::NT == 256 && C::MB == 1 && C::NB == 1, "four waves of 32 x 32");
+    constexpr int G = 16, PER = 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int rt = tid / G, g = tid % G;   // this thread's row step and group
+    const uint32_t np = (uint32_t)p.np;
+    const int I0 = I * 64, J0 = J * 64;
+    const bool diag = I == J;
+    auto at = [](int r, int c) { return r * 64 + (((c >> 2) ^ (r >> 2)) << 2) + (c & 3); };
+    {
+        const int rb = (wave / C::WN) * 32 + 4 * (lane >> 5), c = (wave % C::WN) * 32 + (lane & 31);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) sY[at(rb + 8 * (j >> 2) + (j & 3), c)] = acc.v[0][0][j];
+    }
+    const float ca = poisoned ? __builtin_nanf("") : p.a * (BF ? 1.0f : 1.0f / 2048.0f);
+    const float cb = p.b, cc = p.c, dold = p.d_old, dnew = p.d_new;
+    const bool upd = dold != 0.0f || dnew != 0.0f;
+    const int vx = (int)(rt * np * 4 + g * 16), vh = (int)(rt * np * 2 + g * 8);
+    const uint32_t bu = (uint32_t)I0 * np + J0, bl = (uint32_t)J0 * np + I0;   // tile, mirror
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.X, np * np * 4), ra = make_rsrc(p.A, np * np * 4);
+    const __amdgpu_buffer_rsrc_t rh = make_rsrc(p.hi_out, np * np * 2),
+                                 rl = make_rsrc(p.lo_out, np * np * 2),
+                                 rm = make_rsrc(C::NS == 3 ? p.mid_out : p.hi_out, np * np * 2);
+    auto put = [&](__amdgpu_buffer_rsrc_t rs, u32x2 v, uint32_t base, int u) {
+        __builtin_amdgcn_raw_buffer_store_b64(v, rs, vh, (int)((base + u * 16 * np) * 2), 0);
+    };
+    __syncthreads();
+    u32x4 w[PER], w3[PER];   // hi | lo << 16 (three parts: hi | mid << 16, and lo)
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int r = rt + 16 * u, c = g * 4;
+        floatx4 y = *reinterpret_cast<const floatx4*>(sY + at(r, c));
+        if (diag) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (c + k < r) y[k] = sY[at(c + k, r)];
+        }
+        floatx4 xn;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool one = diag && r == c + k && I0 + r < p.n;
+            xn[k] = fmaf(ca, y[k], fmaf(cb, pre.x[u][k], one ? cc : 0.0f));
+        }
+        // 16-byte stores take no scalar offset: with one, the compiler lets a vector instruction
+        // overwrite the data registers right behind the store, and under back-pressure (two such
+        // workgroups on one CU) the store picked up the new value of the first
+        const int so = vx + (int)((bu + u * 16 * np) * 4);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, xn), rx, so, 0, 0);
+        if (upd) {
+            floatx4 an;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) an[k] = fmaf(dnew, xn[k], fmaf(dold, pre.x[u][k], pre.a[u][k]));
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, an), ra, so, 0, 0);
+        }
+        u32x2 h, m, l;
+        if constexpr (C::NS == 3) {
+            split4x3(xn, h, m, l);
+            put(rm, m, bu, u);
+        } else {
+            split4<BF>(xn, h, l);
+            m = l;
+        }
+        put(rh, h, bu, u);
+        put(rl, l, bu, u);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t hk = k & 1 ? h[k >> 1] >> 16 : h[k >> 1] & 0xffffu;
+            w[u][k] = hk | (k & 1 ? m[k >> 1] & 0xffff0000u : m[k >> 1] << 16);
+            if constexpr (C::NS == 3) w3[u][k] = k & 1 ? l[k >> 1] >> 16 : l[k >> 1] & 0xffffu;
+        }
+    }
+    if (diag) {
+        __syncthreads();
+        return;
+    }
+    uint32_t* sW = reinterpret_cast<uint32_t*>(sY);
+    __syncthreads();   // every product is read: the parts take its place
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int o = at(rt + 16 * u, g * 4);
+        *reinterpret_cast<u32x4*>(sW + o) = w[u];
+        if constexpr (C::NS == 3) *reinterpret_cast<u32x4*>(sW + 4096 + o) = w3[u];
+    }
+    __syncthreads();
+    // Mirror: output row J0 + c, columns I0 + 4 g .. 4 g + 3
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int c = rt + 16 * u;
+        uint32_t v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = sW[at(4 * g + k, c)];
+        const u32x2 h{(v[0] & 0xffffu) | (v[1] << 16), (v[2] & 0xffffu) | (v[3] << 16)};
+        const u32x2 m{(v[0] >> 16) | (v[1] & 0xffff0000u), (v[2] >> 16) | (v[3] & 0xffff0000u)};
+        put(rh, h, bl, u);
+        if constexpr (C::NS == 3) {
+            put(rm, m, bl, u);
+            uint32_t q[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) q[k] = sW[4096 + at(4 * g + k, c)];
+            put(rl, u32x2{q[0] | (q[1] << 16), q[2] | (q[3] << 16)}, bl, u);
+        } else {
+            put(rl, m, bl, u);
+        }
+    }
+    __syncthreads();
+}
 
 // One chunk (tile rows R0 .. R0+EC-1) of the fused epilogue of tile (I, J), I <= J:
 //   Y = X^2 (from sY, or from the row-major BM x BM tile Y0 in memory if Y0 is set) plus the
