@@ -507,7 +507,8 @@ int fe_streamk_segments(int64_t np, int32_t schedule, int32_t grid, int32_t w, i
                         int32_t* segs, int32_t cap, int32_t* count);
 
 /* Test hook for failure handling (process-wide): while enabled, every stream-K wait of the layer
- * kernel waits for a flag value that no workgroup writes and gives up after a short bounded spin,
+ * kernel, and every wait of the launch that runs all layers of a small matrix, waits for a flag
+ * value that no workgroup writes and gives up after a short bounded spin,
  * as a wait that timed out would. Every kernel still exits normally; the tiles finished after a
  * give-up are NaN, the traces NaN, and the rescale info status FE_ERR_HIP. */
 int fe_debug_streamk_giveup(int32_t enable);

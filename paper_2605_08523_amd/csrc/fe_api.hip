@@ -63,6 +63,10 @@ hipEvent_t layer_event(int k) {
     if (k + 1 > g_ev_used) g_ev_used = k + 1;
     return g_ev[k];
 }
+bool layer_events_on() {
+    std::lock_guard<std::mutex> lk(g_ev_mu);
+    return g_ev_on;
+}
 constexpr uint32_t kNeverEpoch = 0xFFFFFFFFu;   // no launch publishes this value
 thread_local int t_forced_schedule = -1;   // set by the tuner around its timing runs
 
@@ -95,6 +99,17 @@ int use_streamk(int64_t n, const fe_workspace* ws, int prec) {
     const int64_t rounds = ntiles / grid;
     const int64_t nsk = rounds >= 2 ? ntiles - (rounds - 1) * grid : ntiles;
     return nsk * nk >= 8 * grid ? 2 : 0;
+}
+
+// Control words and limits of a resident launch over L layers (resident.h).
+fe::ResidentArgs resident_args(fe_workspace* ws, int which, int L) {
+    fe::ResidentArgs R{};
+    R.ctl = ws->ctl + which * fe::kResInts;
+    R.L = L;
+    const bool giveup = g_sk_giveup.load() != 0;
+    R.spin_limit = giveup ? 64 : (1 << 23);   // ~0.6 us per poll: ~5 s
+    R.need_offset = giveup ? (1 << 30) : 0;
+    return R;
 }
 
 // Slot carving for the precision modes (np x np elements each). three: the middle parts of the
@@ -167,7 +182,8 @@ int run_expansion(const double* H, int64_t n, int64_t ldh, double mu, double kT,
     fe::Params* P = ws->params + which;
     fe::BoundsPartial* bp = ws->bparts + (size_t)which * fe::kMaxBoundsBlocks;
     fe::TracePartial* tp = ws->tparts + (size_t)which * fe::kMaxTiles;
-    FE_HIP(fe::launch_bounds_params(H, n, ldh, mu, kT, m->beta0, m->mu0, bp, P, s));
+    int32_t* ctl = ws->ctl + which * fe::kResInts;
+    FE_HIP(fe::launch_bounds_params(H, n, ldh, mu, kT, m->beta0, m->mu0, bp, P, ctl, s));
 
     int npart = 1;
     if (prec == FE_PREC_FP64 && round_up(n, 16) <= fe::small_f64_max_np()) {
@@ -220,6 +236,24 @@ int run_expansion(const double* H, int64_t n, int64_t ldh, double mu, double kT,
         float d_old[kMaxLayers], d_new[kMaxLayers];
         pair_accumulator_terms(m->L, dval, d_old, d_new);
         const int nsplit = corr ? m->L - 1 : m->L;   // layers on the 16-bit split
+        // Small sizes in one launch; timed layers need launches of their own.
+        if (plan.ring_tile && !corr && !af.ok && m->L <= fe::kResMaxL && !layer_events_on() &&
+            fe::split_resident(n, ws->n_cu)) {
+            fe::LayerArgs la{};
+            la.np = np; la.n = n; la.X = b.X; la.A = b.A;
+            la.out_mode = out_mode; la.entropy = entropy; la.D = D; la.ldd = ldd;
+            la.P = P; la.partials = tp;
+            fe::ResidentSplit rs{};
+            for (int k = 0; k < 2; ++k) {
+                rs.hi[k] = b.hi[k]; rs.lo[k] = b.lo[k]; rs.mid[k] = b.mid[k];
+            }
+            for (int i = 0; i < m->L; ++i)
+                rs.c[i] = {(float)th[4 * i], (float)th[4 * i + 1], (float)th[4 * i + 2], d_old[i], d_new[i]};
+            FE_HIP(fe::launch_layers_resident(la, bf, rs, resident_args(ws, which, m->L), s));
+            FE_HIP(fe::launch_reduce_partials(tp, npart, trD, trD2, S, P, ctl + fe::kResErr, s));
+            if (info) return read_info(ws, which, s, info);
+            return FE_OK;
+        }
         if (hipEvent_t ev = layer_event(0)) {
             std::lock_guard<std::mutex> lk(g_ev_mu);
             g_ev_used = 1;
@@ -334,8 +368,13 @@ int fe_workspace_create(int64_t max_n, int32_t max_batch, int64_t batch_elems, f
     if (e == hipSuccess)
         e = hipMalloc(reinterpret_cast<void**>(&ws->tparts), 2 * (size_t)fe::kMaxTiles * sizeof(fe::TracePartial));
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&ws->newton), 2 * sizeof(double));
-    if (e == hipSuccess)
-        e = hipMalloc(reinterpret_cast<void**>(&ws->dots), (fe::kMaxDotBlocks + 3) * sizeof(double));
+    if (e == hipSuccess) {
+        // the control words of resident launches follow the dot partials, on lines of their own
+        const size_t dots = round_up((fe::kMaxDotBlocks + 3) * (int64_t)sizeof(double), 128);
+        e = hipMalloc(reinterpret_cast<void**>(&ws->dots), dots + 2 * fe::kResInts * sizeof(int32_t));
+        if (e == hipSuccess)
+            ws->ctl = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(ws->dots) + dots);
+    }
     if (e == hipSuccess) e = hipDeviceGetAttribute(&ws->n_cu, hipDeviceAttributeMultiprocessorCount, ws->device);
     if (e == hipSuccess && max_n >= kStreamKMinN) {
         e = hipMalloc(reinterpret_cast<void**>(&ws->sk_partial), 2 * (size_t)ws->n_cu * 256 * 256 * sizeof(float));
@@ -392,7 +431,8 @@ int fe_rescale(const double* H, int64_t n, int64_t ldh, double mu, double kT, co
     if (rc) return rc;
     if (X0 && ldx < n) return fail(FE_ERR_ARG, "ldx < n");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    FE_HIP(fe::launch_bounds_params(H, n, ldh, mu, kT, m->beta0, m->mu0, ws->bparts, ws->params, s));
+    FE_HIP(fe::launch_bounds_params(H, n, ldh, mu, kT, m->beta0, m->mu0, ws->bparts, ws->params,
+                                    nullptr, s));
     if (X0) {
         const int64_t np = round_up(n, 16);
         WideBufs b = carve_wide(ws->slot[0], np, sizeof(float));
@@ -436,7 +476,8 @@ int fe_expand_density_filling(const double* H, int64_t n, int64_t ldh, double n_
     if (!(tol > 0.0) || max_iter < 1) return fail(FE_ERR_ARG, "tol must be > 0 and max_iter >= 1");
 
     // Bracket: Tr D increases with mu, from ~0 below the Gershgorin interval to ~n above it.
-    FE_HIP(fe::launch_bounds_params(H, n, ldh, 0.0, kT, m->beta0, m->mu0, ws->bparts, ws->params, s));
+    FE_HIP(fe::launch_bounds_params(H, n, ldh, 0.0, kT, m->beta0, m->mu0, ws->bparts, ws->params,
+                                    nullptr, s));
     FE_HIP(hipStreamSynchronize(s));
     fe::Params p;
     FE_HIP(hipMemcpy(&p, ws->params, sizeof(p), hipMemcpyDeviceToHost));
@@ -496,7 +537,7 @@ int fe_model_select(const double* H, int64_t n, int64_t ldh, double mu, double k
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     FE_HIP(fe::launch_bounds_params(H, n, ldh, mu, kT, bank[0].beta0, bank[0].mu0, ws->bparts,
-                                    ws->params, s));
+                                    ws->params, nullptr, s));
     FE_HIP(hipStreamSynchronize(s));
     fe::Params p;
     FE_HIP(hipMemcpy(&p, ws->params, sizeof(p), hipMemcpyDeviceToHost));
@@ -777,9 +818,10 @@ constexpr size_t kNoAllocParamsOff = 0;
 constexpr size_t kNoAllocBoundsOff = 256;
 constexpr size_t kNoAllocTracesOff =
     kNoAllocBoundsOff + ((fe::kMaxBoundsBlocks * sizeof(fe::BoundsPartial) + 255) / 256) * 256;
+constexpr size_t kNoAllocCtlOff = kNoAllocTracesOff + (size_t)fe::kMaxTiles * sizeof(fe::TracePartial);
 static_assert(2 * sizeof(fe::Params) <= kNoAllocBoundsOff, "parameter block");
-static_assert(kNoAllocTracesOff + (size_t)fe::kMaxTiles * sizeof(fe::TracePartial) <= kNoAllocHeadBytes,
-              "partials block");
+static_assert(kNoAllocCtlOff % 128 == 0 && kNoAllocCtlOff + fe::kResInts * 4 <= kNoAllocHeadBytes,
+              "partials and control words");
 
 }  // namespace
 
@@ -850,6 +892,7 @@ extern "C" int fe_expand_density_noalloc(const double* H, int64_t n, int64_t ldh
     w.params = reinterpret_cast<fe::Params*>(base + kNoAllocParamsOff);
     w.bparts = reinterpret_cast<fe::BoundsPartial*>(base + kNoAllocBoundsOff);
     w.tparts = reinterpret_cast<fe::TracePartial*>(base + kNoAllocTracesOff);
+    w.ctl = reinterpret_cast<int32_t*>(base + kNoAllocCtlOff);
     FE_HIP(hipDeviceGetAttribute(&w.n_cu, hipDeviceAttributeMultiprocessorCount, dev));
     const bool corr = final_correction && (prec == FE_PREC_FP16X2 || prec == FE_PREC_BF16X2);
     return run_expansion(H, n, ldh, mu, kT, m, prec, 1.0, 0, D, d_is_fp64, ldd, trD, trD2, nullptr,

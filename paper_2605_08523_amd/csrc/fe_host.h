@@ -25,6 +25,7 @@ struct fe_workspace {
     uint32_t* sk_flags = nullptr;                 // stream-K flags [n_cu]
     int* sk_err = nullptr;                        // stream-K wait failure flag
     uint32_t epoch = 0;                           // last stream-K launch epoch
+    int32_t* ctl = nullptr;                       // [2 * kResInts] a slot's resident-launch control words (in dots)
     double* newton = nullptr;                     // [2] traces of the current chemical-potential iterate
     double* dots = nullptr;                       // [kMaxDotBlocks + 3] Frobenius-product partials, S, trD
     // batch capacity

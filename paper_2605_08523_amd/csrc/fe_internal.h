@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "fe.h"
+#include "resident.h"
 #include "streamk_plan.h"
 
 namespace fe {
@@ -40,10 +41,11 @@ constexpr int kMaxTiles = 1 << 16;
 
 // ---- launchers (one per translation unit; all asynchronous on `s`) ------------------------
 
-// Gershgorin bounds and the rescale parameters of Sec. IV.1 into *P.
+// Gershgorin bounds and the rescale parameters of Sec. IV.1 into *P; ctl (or NULL): the control
+// words of a resident launch that follows, set to zero.
 hipError_t launch_bounds_params(const double* H, int64_t n, int64_t ldh, double mu, double kT,
                                 double beta0, double mu0, BoundsPartial* partials, Params* P,
-                                hipStream_t s);
+                                int32_t* ctl, hipStream_t s);
 
 // X0 = scale H + shift I into the working copies of a padded np x np matrix. Entries outside
 // n x n are zero. `alpha` rescales towards mu0 for the entropy input:
@@ -122,9 +124,21 @@ int split_tile_for(int streamk);
 // Tile of the data-parallel kernel whose workgroups all run at once at size n on n_cu compute
 // units: 64, 128, or 0 where the tiles need more than one round.
 int split_ring_tile(int64_t n, int n_cu);
+// Whether its 64 x 64 tiles fit one XCD's compute units, one on each (launch_layers_resident).
+bool split_resident(int64_t n, int n_cu);
 // The stream-K plan the launcher uses for a padded size np, schedule 1 or 2, at most grid
 // workgroups (host; see streamk_plan.h).
 SkGeometry split_sk_geometry(int64_t np, int streamk, int grid);
+// All layers in one launch on 64 x 64 tiles (resident.h; direct layer form): a's operand pointers and
+// coefficients are replaced per layer by T's. R.ntiles is set here.
+struct ResidentSplit {
+    uint16_t *hi[2], *lo[2], *mid[2];
+    struct Coef {
+        float a, b, c, d_old, d_new;
+    } c[kResMaxL];
+};
+hipError_t launch_layers_resident(const LayerArgs& a, int bf16, const ResidentSplit& T,
+                                  ResidentArgs R, hipStream_t s);
 // bf16: 0 FP16x2, 1 BF16x2, 2 three-part BF16 (data-parallel plan only; LayerArgs mid_* set).
 hipError_t launch_layer_split(const LayerArgs& a, int bf16, const SplitPlan& plan, hipStream_t s);
 

@@ -94,7 +94,7 @@ int fe_expand_density_variant(const double* H, int64_t n, int64_t ldh, double mu
     float* parts = reinterpret_cast<float*>(lo + e);
 
     fe::Params* P = ws->params;
-    FE_HIP(fe::launch_bounds_params(H, n, ldh, mu, kT, m->beta0, m->mu0, ws->bparts, P, s));
+    FE_HIP(fe::launch_bounds_params(H, n, ldh, mu, kT, m->beta0, m->mu0, ws->bparts, P, nullptr, s));
     // x_0 in FP32 (the rescale's accumulator output is pointed at the same slot with weight 1)
     float* x0 = slot[0];
     fe::RescaleArgs ra{};

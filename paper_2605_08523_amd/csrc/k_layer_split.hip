@@ -28,6 +28,7 @@
 //        accumulators per lane also stay in registers through the wait and the epilogue.
 //    A workgroup only ever waits for workgroups with smaller ids, which were dispatched earlier,
 //    and every wait is bounded.
+#include "resident.h"
 #include "split_common.h"
 #include "streamk_plan.h"
 
@@ -118,6 +119,34 @@ __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2
 k_layer_ring(LayerArgs p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     ring_tile<BF, C, 0>(p, xcd_tile(blockIdx.x, gridDim.x), smem, false);
+}
+
+// All layers of a small matrix in one launch (resident.h), by the same tile code. us per density matrix
+// (26 layers, with ~17 for the prologue's launches) against a launch per layer: n = 64 120 / 158,
+// 256 157 / 189, 384 202 / 228; with more tiles than the XCD has CUs two workgroups share one and
+// the gain is gone (n = 512, 36 tiles: 294 / 269).
+template <bool BF, class C>
+__global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_layer_resident(LayerArgs base, ResidentSplit T, ResidentArgs R) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    resident_items(R, [&](int layer, int tile, bool gave_up) {
+        LayerArgs p = base;
+        const int in = layer & 1;
+        p.hi_in = T.hi[in];
+        p.lo_in = T.lo[in];
+        p.mid_in = T.mid[in];
+        p.hi_out = T.hi[in ^ 1];
+        p.lo_out = T.lo[in ^ 1];
+        p.mid_out = T.mid[in ^ 1];
+        const ResidentSplit::Coef& c = T.c[layer];
+        p.a = c.a;
+        p.b = c.b;
+        p.c = c.c;
+        p.d_old = c.d_old;
+        p.d_new = c.d_new;
+        p.last = layer == R.L - 1;
+        ring_tile<BF, C, kCoherentLoad>(p, tile, smem, gave_up);
+    });
 }
 
 // Thread 0 waits until the workgroups of group g with indices jlo .. j-1 have published their
@@ -244,6 +273,17 @@ hipError_t launch_ring(const LayerArgs& a, hipStream_t s) {
 }
 
 template <bool BF, class C>
+hipError_t launch_resident(const LayerArgs& a, const ResidentSplit& T, const ResidentArgs& R,
+                           hipStream_t s) {
+    auto kern = k_layer_resident<BF, C>;
+    static bool done = false;
+    hipError_t e = set_lds(kern, C::LDS_BYTES, done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(8 * R.ntiles), dim3(C::NT), C::LDS_BYTES, s, a, T, R);
+    return hipGetLastError();
+}
+
+template <bool BF, class C>
 hipError_t launch_sk(const LayerArgs& a, const SplitPlan& sk, hipStream_t s) {
     auto kern = k_layer_sk<BF, C>;
     static bool done = false;
@@ -294,6 +334,11 @@ int split_ring_tile(int64_t n, int n_cu) {
     return 0;
 }
 
+bool split_resident(int64_t n, int n_cu) {
+    const int64_t T = (n + CfgR64::BM - 1) / CfgR64::BM;
+    return 8 * (T * (T + 1) / 2) <= n_cu;
+}
+
 int split_tile_for(int streamk) {
     static_assert(CfgDP3::BM == CfgDP::BM, "the three-part split runs the data-parallel tile");
     return streamk == 1 ? CfgSK::BM : streamk == 2 ? CfgSK2::BM : CfgDP::BM;
@@ -302,6 +347,17 @@ int split_tile_for(int streamk) {
 SkGeometry split_sk_geometry(int64_t np, int streamk, int grid) {
     if (streamk == 1) return sk_plan(np, CfgSK::BM, CfgSK::BK, grid, CfgSK::MB * CfgSK::NB <= 4);
     return sk_plan(np, CfgSK2::BM, CfgSK2::BK, grid, CfgSK2::MB * CfgSK2::NB <= 4);
+}
+
+hipError_t launch_layers_resident(const LayerArgs& a, int bf16, const ResidentSplit& T,
+                                  ResidentArgs R, hipStream_t s) {
+    const int T_ = (int)(a.np / CfgR64::BM);
+    if (a.np % CfgR64::BM != 0 || R.L < 1 || R.L > kResMaxL || !R.ctl || a.affine)
+        return hipErrorInvalidValue;
+    R.ntiles = T_ * (T_ + 1) / 2;
+    return bf16 == 2 ? launch_resident<true, CfgR64x3>(a, T, R, s)
+           : bf16    ? launch_resident<true, CfgR64>(a, T, R, s)
+                     : launch_resident<false, CfgR64>(a, T, R, s);
 }
 
 hipError_t launch_layer_split(const LayerArgs& a, int bf16, const SplitPlan& plan, hipStream_t s) {

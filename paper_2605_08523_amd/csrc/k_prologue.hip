@@ -77,7 +77,9 @@ k_gershgorin(const double* __restrict__ H, int64_t n, int64_t ldh, BoundsPartial
 // Reduce the partial bounds and compute the rescale of Sec. IV.1 in FP64 on the device.
 __global__ void __launch_bounds__(256)
 k_params(const BoundsPartial* partials, int count, double mu, double kT, double beta0, double mu0,
-         Params* P) {
+         Params* P, int32_t* ctl) {
+    static_assert(kResInts <= 256, "one word per thread");
+    if (ctl && threadIdx.x < kResInts) ctl[threadIdx.x] = 0;
     double lo = INFINITY, hi = -INFINITY;
     int bad = 0;
     for (int k = threadIdx.x; k < count; k += blockDim.x) {
@@ -308,13 +310,13 @@ __global__ void __launch_bounds__(256) k_fill_symmetric(double* H, int64_t n, ui
 
 hipError_t launch_bounds_params(const double* H, int64_t n, int64_t ldh, double mu, double kT,
                                 double beta0, double mu0, BoundsPartial* partials, Params* P,
-                                hipStream_t s) {
+                                int32_t* ctl, hipStream_t s) {
     int64_t blocks = (n + 3) / 4;
     if (blocks > kMaxBoundsBlocks) blocks = kMaxBoundsBlocks;
     hipLaunchKernelGGL(k_gershgorin, dim3((unsigned)blocks), dim3(kBoundsThreads), 0, s, H, n, ldh,
                        partials);
     hipLaunchKernelGGL(k_params, dim3(1), dim3(256), 0, s, partials, (int)blocks, mu, kT, beta0,
-                       mu0, P);
+                       mu0, P, ctl);
     return hipGetLastError();
 }
 
