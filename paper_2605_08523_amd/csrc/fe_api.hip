@@ -12,10 +12,6 @@
 
 #include "fe_internal.h"
 
-namespace fe {
-int small_f64_max_np();
-}  // namespace fe
-
 #include "fe_host.h"
 
 using namespace fehost;
@@ -23,6 +19,7 @@ using namespace fehost;
 namespace {
 
 constexpr int64_t kStreamKMinN = 1536;   // workspaces for n >= this carry stream-K buffers
+constexpr int64_t kSmallN64 = 128;       // FP64 up to this size takes at most kResMaxL layers
 
 // Schedule of the split-precision layer kernel (FE_SCHEDULE=dp|sk|sk2 overrides):
 //  0 data-parallel, one workgroup per upper tile (the tile by size: split_ring_tile);
@@ -183,26 +180,27 @@ int run_expansion(const double* H, int64_t n, int64_t ldh, double mu, double kT,
     fe::BoundsPartial* bp = ws->bparts + (size_t)which * fe::kMaxBoundsBlocks;
     fe::TracePartial* tp = ws->tparts + (size_t)which * fe::kMaxTiles;
     int32_t* ctl = ws->ctl + which * fe::kResInts;
+    if (prec == FE_PREC_FP64 && n <= kSmallN64 && m->L > fe::kResMaxL)
+        return fail(FE_ERR_ARG, "too many layers for the small FP64 path");
+    if (!split && n <= fe::small_max_n(prec == FE_PREC_FP64) && m->L <= fe::kSmallMaxL) {
+        fe::SmallArgs sa{};
+        sa.H = H; sa.n = n; sa.ldh = ldh;
+        sa.mu = mu; sa.kT = kT; sa.beta0 = m->beta0; sa.mu0 = m->mu0; sa.alpha = alpha;
+        for (int i = 0; i < m->L; ++i) {
+            for (int k = 0; k < 3; ++k) sa.theta[4 * i + k] = th[4 * i + k];
+            sa.theta[4 * i + 3] = dval(i);
+        }
+        sa.L = m->L; sa.out_mode = out_mode; sa.entropy = entropy;
+        sa.D = D; sa.ldd = ldd; sa.P = P;
+        sa.trD = trD; sa.trD2 = trD2; sa.S = S;
+        FE_HIP(fe::launch_small(sa, prec == FE_PREC_FP64, s));
+        if (info) return read_info(ws, which, s, info);
+        return FE_OK;
+    }
     FE_HIP(fe::launch_bounds_params(H, n, ldh, mu, kT, m->beta0, m->mu0, bp, P, ctl, s));
 
     int npart = 1;
-    if (prec == FE_PREC_FP64 && round_up(n, 16) <= fe::small_f64_max_np()) {
-        const int64_t np = round_up(n, 16);
-        WideBufs b = carve_wide(ws->slot[which], np, sizeof(double));
-        fe::RescaleArgs ra{};
-        ra.H = H; ra.n = n; ra.ldh = ldh; ra.np = np; ra.P = P;
-        ra.alpha = alpha; ra.mu0 = m->mu0; ra.d0 = 0.0;
-        ra.X64 = static_cast<double*>(b.X[0]); ra.A64 = static_cast<double*>(b.A);
-        ra.mode = 2;
-        FE_HIP(fe::launch_rescale(ra, s));
-        if (m->L > fe::kSmallMaxL) return fail(FE_ERR_ARG, "too many layers for the small FP64 path");
-        fe::SmallArgs sa{};
-        sa.n = n; sa.np = np; sa.X0 = static_cast<double*>(b.X[0]); sa.L = m->L;
-        memcpy(sa.theta, th, sizeof(double) * 4 * m->L);
-        sa.d0 = dval(0); sa.out_mode = out_mode; sa.entropy = entropy; sa.D = D; sa.ldd = ldd;
-        sa.P = P; sa.partials = tp;
-        FE_HIP(fe::launch_small_f64(sa, s));
-    } else if (split) {
+    if (split) {
         fe::SplitPlan plan{};
         plan.streamk = three ? 0 : use_streamk(n, ws, prec);   // three parts: data-parallel
         plan.ring_tile = plan.streamk ? 0 : fe::split_ring_tile(n, ws->n_cu);
@@ -308,7 +306,7 @@ int run_expansion(const double* H, int64_t n, int64_t ldh, double mu, double kT,
             FE_HIP(fe::launch_layer_f32(wa, s));
         }
     } else {
-        // FP64 beyond the one-workgroup size, or FP32: tiled MFMA layers on X itself
+        // FP64 or FP32: tiled MFMA layers on X itself
         const bool f64 = prec == FE_PREC_FP64;
         const int tile = fe::wide_tile();
         const int64_t np = round_up(n, tile);
@@ -325,6 +323,22 @@ int run_expansion(const double* H, int64_t n, int64_t ldh, double mu, double kT,
         FE_HIP(fe::launch_rescale(ra, s));
         npart = fe::wide_tiles(np);
         if (npart > fe::kMaxTiles) return fail(FE_ERR_WORKSPACE, "too many tiles");
+        if (m->L <= fe::kResMaxL && fe::wide_resident(np, ws->n_cu)) {
+            fe::WideArgs wa{};
+            wa.np = np; wa.n = n; wa.A = b.A;
+            wa.out_mode = out_mode; wa.entropy = entropy; wa.D = D; wa.ldd = ldd;
+            wa.P = P; wa.partials = tp;
+            fe::ResidentWide rw{};
+            rw.X[0] = b.X[0]; rw.X[1] = b.X[1];
+            for (int i = 0; i < m->L; ++i) {
+                for (int k = 0; k < 3; ++k) rw.theta[4 * i + k] = th[4 * i + k];
+                rw.theta[4 * i + 3] = dval(i);
+            }
+            FE_HIP(fe::launch_layers_wide_resident(wa, f64, rw, resident_args(ws, which, m->L), s));
+            FE_HIP(fe::launch_reduce_partials(tp, npart, trD, trD2, S, P, ctl + fe::kResErr, s));
+            if (info) return read_info(ws, which, s, info);
+            return FE_OK;
+        }
         for (int i = 0; i < m->L; ++i) {
             fe::WideArgs wa{};
             wa.np = np; wa.n = n;
@@ -851,10 +865,6 @@ int noalloc_scratch(int dev, unsigned char** out) {
 // Bytes of the padded matrices run_expansion carves from a slot for one density expansion of
 // size n in precision prec on the data-parallel schedule.
 size_t expansion_slot_bytes(int64_t n, int prec) {
-    if (prec == FE_PREC_FP64 && round_up(n, 16) <= fe::small_f64_max_np()) {
-        const size_t np = (size_t)round_up(n, 16);
-        return 3 * np * np * sizeof(double);
-    }
     if (prec == FE_PREC_FP16X2 || prec == FE_PREC_BF16X2) {
         const size_t np = (size_t)round_up(n, fe::split_tile_for(0));
         return 2 * np * np * sizeof(float) + 4 * np * np * sizeof(uint16_t);

@@ -142,23 +142,24 @@ hipError_t launch_layers_resident(const LayerArgs& a, int bf16, const ResidentSp
 // bf16: 0 FP16x2, 1 BF16x2, 2 three-part BF16 (data-parallel plan only; LayerArgs mid_* set).
 hipError_t launch_layer_split(const LayerArgs& a, int bf16, const SplitPlan& plan, hipStream_t s);
 
-// Whole recursion for np <= 128 in FP64 inside one workgroup's LDS. The coefficients travel
-// by value with the launch.
+// A whole FP64 (f64) or FP32 expansion of n <= small_max_n(f64) in one launch: bounds, *P, all layers,
+// D and the traces. us per density matrix with 26 layers, against the launch per step and all layers
+// resident: FP64 n = 16 21 / 76, 48 46 / 89, 64 80 / 91, 80 139 / 100; FP32 64 38 / 82, 80 54 / 92. (Past
+// 80 an upper block per wave no longer fits one workgroup.)
 constexpr int kSmallMaxL = 96;
+constexpr int small_max_n(bool f64) { return f64 ? 64 : 80; }
 struct SmallArgs {
-    int64_t n, np;
-    const double* X0;       // np x np FP64 start matrix (full)
-    double theta[4 * kSmallMaxL];
-    int L;
-    double d0;
-    int out_mode;           // 0 = D float32, 1 = D float64, 2 = traces only
-    int entropy;
+    const double* H;
+    int64_t n, ldh;
+    double mu, kT, beta0, mu0, alpha;
+    double theta[4 * kSmallMaxL];   // a, b, c and the accumulator weight d (after the skip rule) per layer
+    int L, out_mode, entropy;       // out_mode: 0 = D float32, 1 = D float64, 2 = traces only
     void* D;
     int64_t ldd;
-    const Params* P;
-    TracePartial* partials; // one entry
+    Params* P;
+    double *trD, *trD2, *S;         // device, each may be NULL
 };
-hipError_t launch_small_f64(const SmallArgs& a, hipStream_t s);
+hipError_t launch_small(const SmallArgs& a, bool f64, hipStream_t s);
 
 // FP32 / FP64 tiled MFMA kernel: one layer of the recursion on X itself (operands = the full symmetric
 // X_in, ping-pong with X_out), upper tiles only, fused epilogue as in the split kernel.
@@ -181,6 +182,15 @@ int wide_bm(int64_t np);            // tile of the layer kernel at padded size n
 int wide_tiles(int64_t np);         // its upper tiles (trace partials of a last layer)
 // X[i][j] = X[j][i] for i > j (np x np FP32, np a multiple of wide_tile()).
 hipError_t launch_mirror_upper_f32(float* X, int64_t np, hipStream_t s);
+// All layers in one launch (resident.h): a's X_in, X_out, coefficients and last flag are replaced per
+// layer by L's (theta: R.L x 4). R.ntiles is set here.
+struct ResidentWide {
+    void* X[2];
+    double theta[4 * kResMaxL];   // a, b, c and the accumulator weight d (after the skip rule) per layer
+};
+bool wide_resident(int64_t np, int n_cu);   // whether its tiles fit one XCD's compute units
+hipError_t launch_layers_wide_resident(const WideArgs& a, bool f64, const ResidentWide& L,
+                                       ResidentArgs R, hipStream_t s);
 hipError_t launch_layer_f32(const WideArgs& a, hipStream_t s);
 hipError_t launch_layer_f64(const WideArgs& a, hipStream_t s);
 

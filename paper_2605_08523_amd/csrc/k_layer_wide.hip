@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "fe_internal.h"
+#include "resident.h"
 #include "split_common.h"
 
 namespace fe {
@@ -98,14 +99,14 @@ struct Unaligned<double> {
 // Rp[p] of np-wide matrices: products per element in ascending k. work (the same for all lanes of a
 // wave): this wave's blocks are wanted. ALIGNED: the panels start on 16 bytes (rows then do too);
 // otherwise the operands go through registers into the same LDS places, element by element. Ends
-// with a barrier.
+// with a barrier. AUX: cache policy of the loads.
 //
 // Ring of stages: chunk c (16 bytes) of panel row r sits at chunk c ^ (r % 8) of its 128-byte LDS row,
 // so the rows that a fragment read touches spread over the banks. Nothing in the loop needs vector
 // arithmetic (MFMAs do not run beside it: four vector instructions per MFMA took 8 of its 15 ns
 // here): a load's address is the lane's fixed offset plus a scalar one, a fragment's LDS address a
 // fixed register plus the stage's constant (the stages are unrolled).
-template <typename T, int BM, bool ALIGNED, int NPR>
+template <typename T, int BM, bool ALIGNED, int NPR, int AUX = 0>
 __device__ __attribute__((always_inline)) inline void wide_products(
     const T* const (&Lp)[NPR], const T* const (&Rp)[NPR], int64_t np, int nk, bool work,
     unsigned char* smem,
@@ -131,7 +132,7 @@ __device__ __attribute__((always_inline)) inline void wide_products(
             const uint32_t soff = (uint32_t)(blk * 8 * row_bytes) + (uint32_t)kb * 128;
             if constexpr (ALIGNED) {
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rs[panel], (lds_void*)l, 16, (int)lane_off,
-                                                         (int)soff, 0, 0);
+                                                         (int)soff, 0, AUX);
             } else {
                 const T* g = reinterpret_cast<const T*>(
                     reinterpret_cast<const char*>(panel & 1 ? Rp[panel >> 1] : Lp[panel >> 1]) + soff +
@@ -239,21 +240,23 @@ __device__ __attribute__((always_inline)) inline void wide_products(
     __syncthreads();
 }
 
-template <typename T, int BM, bool ALIGNED>
-__global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
+// Upper tile t of one layer. AUX: cache policy of the loads (kCoherentLoad: a matrix of less than
+// 4 GiB that other workgroups of this XCD wrote in the same launch). poisoned: outputs are NaN.
+template <typename T, int BM, bool ALIGNED, int AUX>
+__device__ __attribute__((always_inline)) inline void wide_tile_layer(const WideArgs& p, int t,
+                                                                      unsigned char* smem,
+                                                                      bool poisoned) {
     using M = Mfma<T>;
     using W = WCfg<T, BM>;
     using vec = typename M::vec;
     using gvec = typename std::conditional<ALIGNED, vec, typename Unaligned<T>::vec>::type;
     constexpr int NB = W::NB;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1, fr = lane & 15;
     const int64_t np = p.np, n = p.n;
     const int T_ = (int)(np / BM);
-    const int t = split::xcd_tile(blockIdx.x, gridDim.x);
     int I, J;
     split::tile_coords(t, T_, I, J);
     const bool diag = I == J;
@@ -270,11 +273,26 @@ __global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
         const int e = tid + u * NT;
         return (I0 + e / W::G) * np + J0 + (e % W::G) * 4;
     };
+    auto load = [&](const T* m, int u) -> vec {
+        if constexpr (AUX == 0) {
+            return *reinterpret_cast<const gvec*>(m + group(u));
+        } else {
+            const __amdgpu_buffer_rsrc_t rs = split::make_rsrc(m, (uint32_t)(np * np * sizeof(T)));
+            const int o = (int)(group(u) * sizeof(T));
+            split::u32x4 v[sizeof(T) / 4];
 #pragma unroll
-    for (int u = 0; u < W::PER; ++u) xg[u] = *reinterpret_cast<const gvec*>(X + group(u));
+            for (int q = 0; q < (int)(sizeof(T) / 4); ++q)
+                v[q] = __builtin_amdgcn_raw_buffer_load_b128(rs, o + 16 * q, 0, AUX);
+            vec r;
+            __builtin_memcpy(&r, v, sizeof(r));
+            return r;
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < W::PER; ++u) xg[u] = load(X, u);
     if (use_a) {
 #pragma unroll
-        for (int u = 0; u < W::PER; ++u) ag[u] = *reinterpret_cast<const gvec*>(A + group(u));
+        for (int u = 0; u < W::PER; ++u) ag[u] = load(A, u);
     }
     // A block whose rows or columns are all padding, or that lies strictly below the diagonal, is
     // not stored: its wave skips the products. Beyond n both operands are zero.
@@ -286,7 +304,7 @@ __global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
         for (int y = 0; y < NB; ++y) acc[0][x][y] = vec{0, 0, 0, 0};
     const T* const lp[1] = {X + I0 * np};
     const T* const rp[1] = {X + J0 * np};
-    wide_products<T, BM, ALIGNED, 1>(lp, rp, np, (int)((n + W::BK - 1) / W::BK), work, smem, acc);
+    wide_products<T, BM, ALIGNED, 1, AUX>(lp, rp, np, (int)((n + W::BK - 1) / W::BK), work, smem, acc);
 
     // the product tile goes through LDS to four-column groups in registers
     T* sY = reinterpret_cast<T*>(smem);
@@ -305,7 +323,7 @@ __global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
         yg[u] = *reinterpret_cast<const vec*>(sY + (e / W::G) * W::LDY + (e % W::G) * 4);
     }
 
-    const T ca = (T)p.a, cb = (T)p.b, cc = (T)p.c;
+    const T ca = poisoned ? (T)__builtin_nan("") : (T)p.a, cb = (T)p.b, cc = (T)p.c;
     if (!last) {
         T* __restrict__ Xo = static_cast<T*>(p.X_out);
 #pragma unroll
@@ -421,6 +439,32 @@ __global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
         p.partials[t].tr = tt;
         p.partials[t].sq = ss;
     }
+}
+
+template <typename T, int BM, bool ALIGNED>
+__global__ void __launch_bounds__(NT) k_wide(WideArgs p) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    wide_tile_layer<T, BM, ALIGNED, 0>(p, split::xcd_tile(blockIdx.x, gridDim.x), smem, false);
+}
+
+// All layers of a small matrix in one launch (resident.h), by the same tile code. us per density matrix
+// (26 layers) against a launch per layer: FP64 n = 64 97 / 113, 128 117 / 137, 192 145 / 158 and, with
+// more tiles than the XCD has CUs, 256 235 / 180; FP32 64 85 / 104, 192 120 / 137, 256 161 / 145.
+// (One workgroup with the matrix in its LDS: n = 128 FP64 503.)
+template <typename T>
+__global__ void __launch_bounds__(NT) k_wide_resident(WideArgs base, ResidentWide L, ResidentArgs R) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    resident_items(R, [&](int layer, int tile, bool gave_up) {
+        WideArgs p = base;
+        p.X_in = L.X[layer & 1];
+        p.X_out = L.X[(layer & 1) ^ 1];
+        p.a = L.theta[4 * layer];
+        p.b = L.theta[4 * layer + 1];
+        p.c = L.theta[4 * layer + 2];
+        p.last = layer + 1 == R.L;
+        p.d_next = p.last ? 0.0 : L.theta[4 * layer + 7];
+        wide_tile_layer<T, 32, true, kCoherentLoad>(p, tile, smem, gave_up);
+    });
 }
 
 // Backward of one layer of the FP32 matrix recursion in one pass over the upper tiles (I, J): with
@@ -562,6 +606,21 @@ int wide_tiles(int64_t np) {
 }
 hipError_t launch_layer_f32(const WideArgs& a, hipStream_t s) { return launch<float>(a, s); }
 hipError_t launch_layer_f64(const WideArgs& a, hipStream_t s) { return launch<double>(a, s); }
+bool wide_resident(int64_t np, int n_cu) {
+    const int64_t T = np / 32;
+    return np % kPad == 0 && 8 * (T * (T + 1) / 2) <= n_cu;
+}
+hipError_t launch_layers_wide_resident(const WideArgs& a, bool f64, const ResidentWide& L,
+                                       ResidentArgs R, hipStream_t s) {
+    if (a.np % kPad != 0 || a.n < 1 || a.n > a.np || R.L < 1 || R.L > kResMaxL || !R.ctl)
+        return hipErrorInvalidValue;
+    const int T_ = (int)(a.np / 32);
+    R.ntiles = T_ * (T_ + 1) / 2;
+    const dim3 grid(8 * R.ntiles);
+    if (f64) hipLaunchKernelGGL(k_wide_resident<double>, grid, dim3(NT), (WCfg<double, 32>::LDS), s, a, L, R);
+    else hipLaunchKernelGGL(k_wide_resident<float>, grid, dim3(NT), (WCfg<float, 32>::LDS), s, a, L, R);
+    return hipGetLastError();
+}
 int wide_bwd_tiles(int64_t n) {
     const int T_ = (int)(n / 32);
     return T_ * (T_ + 1) / 2;

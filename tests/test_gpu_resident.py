@@ -1,9 +1,14 @@
-"""Small matrices with all layers in one launch (n <= 448 for the 16-bit splits on 256 compute
-units), at the edges of their tiles and of the sizes they are chosen for. They take the tile code of
-the launches per layer, so D is bitwise that of a batch of one, call after call. A
-wait that gives up is reported as for stream-K."""
+"""Small matrices with all layers in one launch (n <= 448 for the 16-bit splits, n <= 192 for FP32 and
+FP64 on 256 compute units; from the bounds to the traces in one workgroup for n <= 64 in FP64 and 80 in
+FP32), at the edges of their tiles and of the sizes they are chosen for. The
+splits take the tile code of the launches per layer, so D is bitwise that of a batch of one, call
+after call; FP32 and FP64 are held to the oracle's recursion by the rounding of their chains of n
+products over 26 layers. A wait that gives up is reported as for stream-K."""
+import numpy as np
 import pytest
 
+from oracle import fermi as F
+from oracle import recursion as R
 from paper_2605_08523_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -35,7 +40,34 @@ def test_split_bitwise_and_repeatable(api, paper_model, n, prec):
     ws.close()
 
 
-@pytest.mark.parametrize("n,prec", [(128, "fp16x2")])
+@pytest.mark.parametrize("prec,tol", [("fp32", 1e-5), ("fp64", 1e-11)])
+@pytest.mark.parametrize("n", [1, 16, 17, 48, 64, 65, 80, 81, 128, 129, 192, 193])
+def test_wide_against_the_oracle(api, paper_model, n, prec, tol):
+    print(f"case n={n} {prec}", flush=True)
+    Hh = W.random_dense(n, 90 + n)
+    H = torch.from_numpy(Hh).cuda()
+    m = paper_model
+    ref, _ = R.mlsp2_density(Hh, 0.05, 0.1, m.theta, m.beta0, m.mu0)
+    ws = api.Workspace(n)
+    out = torch.float64 if prec == "fp64" else torch.float32
+    first = None
+    for _ in range(10):
+        D, tr, tr2, info = api.expand_density(H, 0.05, 0.1, m, prec=prec, ws=ws, out_dtype=out,
+                                              want_info=True)
+        torch.cuda.synchronize()
+        first = D.clone() if first is None else first
+        assert torch.equal(D, first) and torch.equal(D, D.T)
+    lo, hi = F.gershgorin(Hh)
+    assert abs(info["emin"] - lo) <= 1e-14 * n and abs(info["emax"] - hi) <= 1e-14 * n
+    d = D.double().cpu().numpy()
+    assert np.linalg.norm(d - ref) / max(1.0, np.linalg.norm(ref)) <= tol
+    # D's elements leave in its type, the trace is summed from the FP64 / FP32 layer values
+    assert abs(float(tr) - np.trace(ref)) <= tol * n
+    assert abs(float(tr2) - np.sum(ref * ref)) <= 2 * tol * n
+    ws.close()
+
+
+@pytest.mark.parametrize("n,prec", [(128, "fp16x2"), (128, "fp64")])
 def test_giveup_is_reported(api, paper_model, n, prec):
     print(f"case giveup n={n} {prec}", flush=True)
     H = torch.from_numpy(W.random_dense(n, 5)).cuda()
