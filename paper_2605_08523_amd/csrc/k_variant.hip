@@ -21,6 +21,12 @@ namespace {
 
 using namespace split;
 using CfgQ = Cfg<128, 2, 2, 64, 128, 1>;
+// Sizes whose tiles all run at once (split_ring_tile): the operand ring of the MLSP2 layers, the same
+// products in the same order. us per Skip-SP2 expansion (22 squarings and their combines), 128 x 128
+// register-staged tiles / ring: n = 512 645 / 573, 1000 1021 / 595, 1728 1516 / 890, 2197 1863 / 1307,
+// 2744 2297 / 1828. With more tiles than compute units (n = 3375) two staged workgroups per CU stay.
+using CfgQ64 = Cfg<64, 2, 2, 64, 64, 2, 1>;
+using CfgQ128 = Cfg<128, 4, 2, 64, 128, 2, 1>;
 
 template <bool BF, class C>
 __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -392,9 +398,25 @@ hipError_t set_lds_once(Kern kern, size_t bytes, bool& done) {
     return e;
 }
 
+template <bool BF, class C>
+hipError_t launch_square_ring(const uint16_t* hi, const uint16_t* lo, int64_t np, float* out,
+                              hipStream_t s) {
+    auto kern = k_square<BF, C>;
+    static bool done = false;
+    hipError_t e = set_lds_once(kern, C::LDS_BYTES, done);
+    if (e != hipSuccess) return e;
+    const int T = (int)(np / C::BM);
+    hipLaunchKernelGGL(kern, dim3(T * (T + 1) / 2), dim3(C::NT), C::LDS_BYTES, s, hi, lo, np, out);
+    return hipGetLastError();
+}
+
 template <bool BF>
 hipError_t launch_square_t(const uint16_t* hi, const uint16_t* lo, int64_t np, float* out,
                            int slots, float* parts, hipStream_t s) {
+    switch (split_ring_tile(np, slots / 2)) {
+        case 64: return launch_square_ring<BF, CfgQ64>(hi, lo, np, out, s);
+        case 128: return launch_square_ring<BF, CfgQ128>(hi, lo, np, out, s);
+    }
     using C = CfgQ;
     auto kern = k_square<BF, C>;
     auto kpart = k_square_part<BF, C>;
