@@ -104,11 +104,10 @@ __device__ __attribute__((always_inline)) inline void ring_tile(const LayerArgs&
     kloop_dma<BF, C, kSeg, AUX>(p.hi_in, p.mid_in, p.lo_in, p.np, (int64_t)I * C::BM,
                                 (int64_t)J * C::BM, 0, (int)(p.np / C::BK), acc,
                                 reinterpret_cast<uint16_t*>(smem));
-    if constexpr (C::BM == 64) {
-        if (!p.last && !p.affine) {
-            epilogue_mid64<BF, C>(p, acc, reinterpret_cast<float*>(smem), I, J, poisoned, pre);
-            return;
-        }
+    if (!p.last && !p.affine) {
+        epilogue_mid<BF, C, AUX>(p, acc, reinterpret_cast<float*>(smem), I, J, poisoned,
+                                 kPre ? &pre : nullptr);
+        return;
     }
     epilogue<BF, C, kPre ? 8 : 2, kPre>(p, acc, reinterpret_cast<float*>(smem), I, J, t, nullptr, 0,
                                         0, poisoned, &pre);

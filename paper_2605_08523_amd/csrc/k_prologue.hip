@@ -150,13 +150,20 @@ __device__ inline void rescale_quad(const RescaleArgs& a, double scale, double s
         return;
     }
     const float d0f = (float)a.d0;
-    split::floatx4 xf, af;
+    split::floatx4 xf, xm, af;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        xf[k] = (float)x[k];
-        af[k] = d0f * xf[k];
+    for (int k = 0; k < 4; ++k) xf[k] = xm[k] = (float)x[k];
+    if (a.mode == 0 && i > j0 && (i ^ j0) < 128 && i < a.n) {
+        // Below the diagonal of a 128-wide diagonal block X and A mirror what lies above it (H may be
+        // symmetric only to rounding): the layers update both from the symmetric product. The
+        // operands keep H's own elements.
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (j0 + k < i) xm[k] = (float)(a.alpha * (scale * a.H[(j0 + k) * a.ldh + i]));
     }
-    *reinterpret_cast<split::floatx4*>(a.X32 + e0) = xf;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) af[k] = d0f * xm[k];
+    *reinterpret_cast<split::floatx4*>(a.X32 + e0) = xm;
     *reinterpret_cast<split::floatx4*>(a.A32 + e0) = af;
     if (a.mode != 0) return;
     uint16_t h[4], l[4], md[4];

@@ -785,30 +785,38 @@ struct EpiPre {
     }
 };
 
-// The epilogue of a 64 x 64 tile in the direct layer form, all layers but the last: the same values
-// as epi_chunk in a third of its instructions, which a workgroup alone on its CU waits for one by
-// one (us per density matrix with a launch per layer, 26 layers, against epi_chunk: n = 128 159 / 213,
+// The epilogue of a tile in the direct layer form, all layers but the last: the same values as epi_chunk
+// in a third of its instructions, which a workgroup alone on its CU waits for one by one (us per
+// density matrix with a launch per layer, 26 layers, against epi_chunk: n = 128 159 / 213,
 // 256 189 / 246, 1001 427 / 469).
-// Addresses are one lane offset plus scalars; the parts split once travel through LDS for the mirror
-// tile; 1/s is folded into a (a power of two); a diagonal tile writes both triangles of X, A and
-// the operands itself, its lower elements from the transposed product (so they equal the upper ones
-// bit for bit). The padding comes out zero. LDS: 16-byte groups of row r at group g ^ (r / 4).
-template <bool BF, class C>
-__device__ inline void epilogue_mid64(const LayerArgs& p, const Acc<C>& acc, float* sY, int I, int J,
-                                      bool poisoned, const EpiPre<C>& pre) {
-    static_assert(C::BM == 64 && C::NT == 256 && C::MB == 1 && C::NB == 1, "four waves of 32 x 32");
-    constexpr int G = 16, PER = 4;
+// Addresses are one lane offset plus scalars; the parts split once travel through LDS, in the place of
+// the product they came from, for the mirror tile; 1/s is folded into a (a power of two); a diagonal
+// tile writes both triangles of X, A and the operands itself, its lower elements from the transposed
+// product (the rescale made X and A symmetric there, so they equal the upper ones bit for bit). The
+// padding comes out zero. LDS: 16-byte groups of row r at group g ^ (r / 4) (modulo the row). pre: the
+// tile's X and A groups, or NULL: loaded here, UB groups at a time. AUX: cache policy of those loads.
+template <bool BF, class C, int AUX = 0, int UB = 4>
+__device__ __attribute__((always_inline)) inline void epilogue_mid(const LayerArgs& p, const Acc<C>& acc,
+                                                                   float* sY, int I, int J,
+                                                                   bool poisoned,
+                                                                   const EpiPre<C>* pre) {
+    constexpr int BM = C::BM, G = BM / 4, RPG = C::NT / G, PER = BM / RPG;
+    static_assert(PER % UB == 0, "whole batches of groups");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int rt = tid / G, g = tid % G;   // this thread's row step and group
     const uint32_t np = (uint32_t)p.np;
-    const int I0 = I * 64, J0 = J * 64;
+    const int I0 = I * BM, J0 = J * BM;
     const bool diag = I == J;
-    auto at = [](int r, int c) { return r * 64 + (((c >> 2) ^ (r >> 2)) << 2) + (c & 3); };
-    {
-        const int rb = (wave / C::WN) * 32 + 4 * (lane >> 5), c = (wave % C::WN) * 32 + (lane & 31);
+    auto at = [](int r, int c) { return r * BM + (((c >> 2) ^ ((r >> 2) & (G - 1))) << 2) + (c & 3); };
 #pragma unroll
-        for (int j = 0; j < 16; ++j) sY[at(rb + 8 * (j >> 2) + (j & 3), c)] = acc.v[0][0][j];
-    }
+    for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < C::NB; ++nb) {
+            const int rb = (wave / C::WN) * C::WAVE_M + mb * 32 + 4 * (lane >> 5);
+            const int c = (wave % C::WN) * C::WAVE_N + nb * 32 + (lane & 31);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) sY[at(rb + 8 * (j >> 2) + (j & 3), c)] = acc.v[mb][nb][j];
+        }
     const float ca = poisoned ? __builtin_nanf("") : p.a * (BF ? 1.0f : 1.0f / 2048.0f);
     const float cb = p.b, cc = p.c, dold = p.d_old, dnew = p.d_new;
     const bool upd = dold != 0.0f || dnew != 0.0f;
@@ -819,70 +827,84 @@ __device__ inline void epilogue_mid64(const LayerArgs& p, const Acc<C>& acc, flo
                                  rl = make_rsrc(p.lo_out, np * np * 2),
                                  rm = make_rsrc(C::NS == 3 ? p.mid_out : p.hi_out, np * np * 2);
     auto put = [&](__amdgpu_buffer_rsrc_t rs, u32x2 v, uint32_t base, int u) {
-        __builtin_amdgcn_raw_buffer_store_b64(v, rs, vh, (int)((base + u * 16 * np) * 2), 0);
+        __builtin_amdgcn_raw_buffer_store_b64(v, rs, vh, (int)((base + u * RPG * np) * 2), 0);
     };
-    __syncthreads();
-    u32x4 w[PER], w3[PER];   // hi | lo << 16 (three parts: hi | mid << 16, and lo)
+    floatx4 xg[UB], ag[UB];
+    auto fetch = [&](int u0) {
+        if (pre) return;
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int r = rt + 16 * u, c = g * 4;
-        floatx4 y = *reinterpret_cast<const floatx4*>(sY + at(r, c));
-        if (diag) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (c + k < r) y[k] = sY[at(c + k, r)];
-        }
-        floatx4 xn;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const bool one = diag && r == c + k && I0 + r < p.n;
-            xn[k] = fmaf(ca, y[k], fmaf(cb, pre.x[u][k], one ? cc : 0.0f));
-        }
-        // 16-byte stores take no scalar offset: with one, the compiler lets a vector instruction
-        // overwrite the data registers right behind the store, and under back-pressure (two such
-        // workgroups on one CU) the store picked up the new value of the first
-        const int so = vx + (int)((bu + u * 16 * np) * 4);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, xn), rx, so, 0, 0);
+        for (int u = 0; u < UB; ++u)
+            xg[u] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                    rx, vx, (int)((bu + (u0 + u) * RPG * np) * 4), AUX));
         if (upd) {
-            floatx4 an;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) an[k] = fmaf(dnew, xn[k], fmaf(dold, pre.x[u][k], pre.a[u][k]));
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, an), ra, so, 0, 0);
+            for (int u = 0; u < UB; ++u)
+                ag[u] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                        ra, vx, (int)((bu + (u0 + u) * RPG * np) * 4), AUX));
         }
-        u32x2 h, m, l;
-        if constexpr (C::NS == 3) {
-            split4x3(xn, h, m, l);
-            put(rm, m, bu, u);
-        } else {
-            split4<BF>(xn, h, l);
-            m = l;
-        }
-        put(rh, h, bu, u);
-        put(rl, l, bu, u);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t hk = k & 1 ? h[k >> 1] >> 16 : h[k >> 1] & 0xffffu;
-            w[u][k] = hk | (k & 1 ? m[k >> 1] & 0xffff0000u : m[k >> 1] << 16);
-            if constexpr (C::NS == 3) w3[u][k] = k & 1 ? l[k >> 1] >> 16 : l[k >> 1] & 0xffffu;
-        }
-    }
-    if (diag) {
-        __syncthreads();
-        return;
-    }
+    };
+    fetch(0);
     uint32_t* sW = reinterpret_cast<uint32_t*>(sY);
-    __syncthreads();   // every product is read: the parts take its place
+    __syncthreads();
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int o = at(rt + 16 * u, g * 4);
-        *reinterpret_cast<u32x4*>(sW + o) = w[u];
-        if constexpr (C::NS == 3) *reinterpret_cast<u32x4*>(sW + 4096 + o) = w3[u];
+    for (int u0 = 0; u0 < PER; u0 += UB) {
+        if (u0 > 0) fetch(u0);
+#pragma unroll
+        for (int v = 0; v < UB; ++v) {
+            const int u = u0 + v, r = rt + RPG * u, c = g * 4;
+            const floatx4 x = pre ? pre->x[u] : xg[v], a = pre ? pre->a[u] : ag[v];
+            floatx4 y = *reinterpret_cast<const floatx4*>(sY + at(r, c));
+            if (diag) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (c + k < r) y[k] = sY[at(c + k, r)];
+            }
+            floatx4 xn;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const bool one = diag && r == c + k && I0 + r < p.n;
+                xn[k] = fmaf(ca, y[k], fmaf(cb, x[k], one ? cc : 0.0f));
+            }
+            // 16-byte stores take no scalar offset: with one, the compiler lets a vector instruction
+            // overwrite the data registers right behind the store, and under back-pressure (two such
+            // workgroups on one CU) the store picked up the new value of the first
+            const int so = vx + (int)((bu + u * RPG * np) * 4);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, xn), rx, so, 0, 0);
+            if (upd) {
+                floatx4 an;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) an[k] = fmaf(dnew, xn[k], fmaf(dold, x[k], a[k]));
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, an), ra, so, 0, 0);
+            }
+            u32x2 h, m, l;
+            if constexpr (C::NS == 3) {
+                split4x3(xn, h, m, l);
+                put(rm, m, bu, u);
+            } else {
+                split4<BF>(xn, h, l);
+                m = l;
+            }
+            put(rh, h, bu, u);
+            put(rl, l, bu, u);
+            if (!diag) {   // hi | lo << 16 (three parts: hi | mid << 16, and lo) for the mirror
+                u32x4 w, w3;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t hk = k & 1 ? h[k >> 1] >> 16 : h[k >> 1] & 0xffffu;
+                    w[k] = hk | (k & 1 ? m[k >> 1] & 0xffff0000u : m[k >> 1] << 16);
+                    if constexpr (C::NS == 3) w3[k] = k & 1 ? l[k >> 1] >> 16 : l[k >> 1] & 0xffffu;
+                }
+                *reinterpret_cast<u32x4*>(sW + at(r, c)) = w;
+                if constexpr (C::NS == 3) *reinterpret_cast<u32x4*>(sW + BM * BM + at(r, c)) = w3;
+            }
+        }
     }
     __syncthreads();
+    if (diag) return;
     // Mirror: output row J0 + c, columns I0 + 4 g .. 4 g + 3
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-        const int c = rt + 16 * u;
+        const int c = rt + RPG * u;
         uint32_t v[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] = sW[at(4 * g + k, c)];
@@ -893,7 +915,7 @@ __device__ inline void epilogue_mid64(const LayerArgs& p, const Acc<C>& acc, flo
             put(rm, m, bl, u);
             uint32_t q[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) q[k] = sW[4096 + at(4 * g + k, c)];
+            for (int k = 0; k < 4; ++k) q[k] = sW[BM * BM + at(4 * g + k, c)];
             put(rl, u32x2{q[0] | (q[1] << 16), q[2] | (q[3] << 16)}, bl, u);
         } else {
             put(rl, m, bl, u);
