@@ -245,15 +245,16 @@ int fe_batch_plan_create_bank(const fe_batch_item* items, int32_t count, const f
 int fe_batch_plan_launch(fe_batch_plan* plan, void* stream);
 
 /* Rebuilds the plan (layout, tables, captured graph) with layer tiles of `tile` x `tile`, tile
- * 128 (the default: the single-matrix kernel's tiles) or 64 (32 x 32 per wave: less padding for
- * small matrices, more LDS traffic per flop). Results differ from the other tile size at most by
- * the order of FP32 sums. Waits for the device first (a launch of the plan may be in flight), then
+ * 128 or 64 (less padding for small matrices, more LDS traffic per flop). A new plan's tile is 128,
+ * and until one of this function and the autotuner is called its kernel takes the 128 x 128 tiles in
+ * 64 x 64 pieces where the sizes make that less work. Results differ from the other tile size at
+ * most by the order of FP32 sums. Waits for the device first (a launch of the plan may be in flight), then
  * replaces the captured graph; on failure the plan is left empty and its launches fail. */
 int fe_batch_plan_retile(fe_batch_plan* plan, int32_t tile);
 
-/* How a plan runs the layers of a pass. FE_BATCH_LAUNCH_QUEUE (the default for batches whose
- * first layer holds at least two 128 x 128 tiles per compute unit; smaller batches, bound by their
- * chain of layers, default to FE_BATCH_LAUNCH_LAYERS): every layer of every matrix in one launch: each matrix's (tile, layer) work items sit in the queue of one XCD in
+/* How a plan runs the layers of a pass. FE_BATCH_LAUNCH_QUEUE (the default for batches of at least
+ * 12 matrices, and for those whose first layer holds at least two 128 x 128 tiles per compute unit;
+ * others, which would leave XCDs idle, default to FE_BATCH_LAUNCH_LAYERS): every layer of every matrix in one launch: each matrix's (tile, layer) work items sit in the queue of one XCD in
  * layer-major order; a workgroup takes the next item of its XCD's queue and starts it once the
  * matrix has completed its previous layer (bounded waits; the XCD is read from the hardware, so
  * the L2 that holds the matrix is the one its readers use). It needs the device to deal

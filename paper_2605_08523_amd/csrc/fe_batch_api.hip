@@ -24,6 +24,7 @@ struct fe_batch_plan {
     uint64_t gen = 0;       // workspace layout generation this plan was built for
     int count = 0;
     int tile = 128;         // tile size of the layer kernel (128 or 64)
+    bool by_size = true;    // 128 not asked for: tiles in 64 x 64 pieces where that is less work
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     fe_workspace* ws = nullptr;
@@ -352,10 +353,34 @@ void release_plan(fe_batch_plan* plan) {
     plan->queues = nullptr;
 }
 
-// Builds and captures `plan` for its stored inputs with layer tiles of `tile` (128 or 64): item i
+// Tile of the layer kernel of a plan that leaves it open. Small matrices waste much of their 128 x 128
+// tiles; a 64 x 64 tile takes about 1.33 times as long per element (its operand panels pass through
+// LDS twice as often). us per batch with 128 / 64 tiles, and their ratio of work: 60 matrices of
+// n 64 ... 768 1367 / 1513 (1.19), 30 of 16 ... 768 630 / 730 (1.22), 8 of 128 ... 768 634 / 771 (1.25);
+// 60 of 128 ... 384 719 / 672 (1.36), 12 of 128 ... 512 400 / 372 (1.37), 30 of 64 ... 256 311 / 228 (1.38).
+// The work table of the queue launch (16 bytes per item) bounds it: at most 64 MiB with 64 x 64 tiles.
+int tile_by_size(const std::vector<fe_batch_item>& items, int max_L) {
+    double w128 = 0.0, w64 = 0.0, tiles64 = 0.0;
+    for (const fe_batch_item& it : items) {
+        const double n = (double)it.n, T = (double)((it.n + 127) / 128), t = (double)((it.n + 63) / 64);
+        w128 += 0.5 * T * (T + 1.0) * 4.0 * n;
+        w64 += 0.5 * t * (t + 1.0) * n;
+        tiles64 += T * (2.0 * T + 1.0);
+    }
+    return w128 > 1.3 * w64 && tiles64 * max_L <= (double)(1 << 22) ? 64 : 128;
+}
+
+// Builds and captures `plan` for its stored inputs with layer tiles of `want` (128 or 64): item i
 // runs model dens[model[i]] (and ent[model[i]] for the entropy pass when ent is non-empty).
-int build_plan(fe_batch_plan* plan, int tile) {
+int build_plan(fe_batch_plan* plan, int want) {
     release_plan(plan);
+    int tile = want;
+    if (want == 128 && plan->by_size) {
+        int max_L = 1;
+        for (const fe_model& m : plan->dens) max_L = std::max(max_L, (int)m.L);
+        for (const fe_model& m : plan->ent) max_L = std::max(max_L, (int)m.L);
+        tile = tile_by_size(plan->items, max_L);
+    }
     const fe_batch_item* items = plan->items.data();
     const int count = plan->count;
     const std::vector<int>& model = plan->model;
@@ -444,7 +469,7 @@ int build_plan(fe_batch_plan* plan, int tile) {
     const std::vector<LayerLaunch> ll_d = launches_of(km_d);
     const std::vector<LayerLaunch> ll_e = launches_of(km_e);
 
-    plan->tile = tile;
+    plan->tile = want;
     // device tables: [density coef | L | d0 | shift0 | entropy ...], 256-byte aligned parts
     auto al = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t cd = al(td.coef.size() * 4), ld = al(td.L.size() * 4), dd = al(td.d0.size() * 4);
@@ -512,11 +537,10 @@ int build_plan(fe_batch_plan* plan, int tile) {
             v.q.qoff = reinterpret_cast<const int32_t*>(qb + qoff_off);
             v.q.nq = nq;
             v.q.ticket = counters;
-            v.q.done = counters + nq;
-            v.q.err = counters + nq + count;
+            v.q.done = counters + fe::kQueueLine * nq;
+            v.q.err = counters + fe::kQueueLine * ((int64_t)nq + count);
             const bool giveup = g_queue_giveup.load() != 0;
-            // 1 << 20 polls, each after up to 16 x 512 clocks of sleep: ~5 s
-            v.q.spin_limit = giveup ? 64 : (1 << 20);
+            v.q.spin_limit = giveup ? 64 : (1 << 23);   // ~0.6 us per poll: ~5 s
             v.q.need_offset = giveup ? (1 << 30) : 0;
             v.grid = longest * nq;
         };
@@ -550,7 +574,7 @@ int build_plan(fe_batch_plan* plan, int tile) {
     return rc;
 }
 
-// A new plan holding copies of its inputs, built with 128 x 128 layer tiles.
+// A new plan holding copies of its inputs, built in the default form.
 int create_plan(const fe_batch_item* items, int count, const std::vector<int>& model,
                 const std::vector<const fe_model*>& dens, const std::vector<const fe_model*>& ent,
                 double alpha, int32_t prec, int32_t* status, fe_workspace* ws,
@@ -573,9 +597,9 @@ int create_plan(const fe_batch_item* items, int count, const std::vector<int>& m
     plan->prec = prec;
     plan->status = status;
     // Default launch form: the queue launch when the first layer alone holds at least one 128 x 128
-    // tile per resident workgroup slot (two per CU); a smaller batch is bound by its chain of
-    // layers, where the per-layer launches hand each layer over faster (measured: 64 matrices of
-    // N <= 300, 0.63 against 1.0 ms; 256 of N <= 384, 2.09 against 1.84 ms the other way round).
+    // tile per resident workgroup slot (two per CU), or from 12 matrices on. With fewer, XCDs stay idle
+    // that a launch per layer would use (us, queue / per layer: 30 matrices of n 64 ... 256 217 / 247,
+    // 60 of 128 ... 384 653 / 933, 12 of 128 ... 512 290 / 313, 6 of 16 ... 160 199 / 179).
     {
         int64_t tiles = 0;
         for (int i = 0; i < count; ++i) {
@@ -586,7 +610,7 @@ int create_plan(const fe_batch_item* items, int count, const std::vector<int>& m
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             cus = 256;
-        plan->launch = tiles >= 2 * (int64_t)cus ? FE_BATCH_LAUNCH_QUEUE : FE_BATCH_LAUNCH_LAYERS;
+        plan->launch = tiles >= 2 * (int64_t)cus || 2 * count >= 3 * kXcds ? FE_BATCH_LAUNCH_QUEUE : FE_BATCH_LAUNCH_LAYERS;
         plan->default_launch = plan->launch;
     }
     const int rc = build_plan(plan, 128);
@@ -700,6 +724,7 @@ int fe_batch_plan_retile(fe_batch_plan* plan, int32_t tile) {
     if (tile == 64 && plan->prec == FE_PREC_BF16X3)
         return fail(FE_ERR_ARG, "the three-part BF16 split runs 128 x 128 tiles only");
     FE_HIP(hipDeviceSynchronize());   // a launch of the old graph may still be reading its tables
+    plan->by_size = false;
     return build_plan(plan, tile);
 }
 
@@ -737,6 +762,7 @@ int fe_batch_plan_autotune(fe_batch_plan* plan, void* stream, int32_t* tile, dou
         double ms;
     };
     std::vector<Cand> cands;
+    plan->by_size = false;
     for (int t : {128, 64}) {
         if (t == 64 && plan->prec == FE_PREC_BF16X3) continue;
         if (queue_ok) cands.push_back({t, FE_BATCH_LAUNCH_QUEUE, NAN});

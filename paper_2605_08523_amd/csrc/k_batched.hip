@@ -9,26 +9,24 @@
 #include <vector>
 
 #include "batch_queue.h"
+#include "resident.h"
 #include "split_common.h"
 
 namespace fe {
 namespace {
 
 using namespace split;
-// 128 x 128 tiles over eight waves of 32 x 64 (four waves per SIMD with two workgroups per CU):
-// each workgroup's K loop here is short (2 to 12 blocks) and waits on its loads more than on the
-// MFMA pipes, so more waves per CU hide more of that latency (1.08x over four waves of 64 x 64
-// on the batch of 1024); the epilogue keeps two groups of loads in flight per thread (register
-// budget of four waves per SIMD).
-using CfgB = Cfg<128, 4, 2, 64, 128, 1>;
-constexpr int kBatchEpiGroups = 2;
-// 64 x 64 tiles (32 x 32 per wave): less padding for small N. Three waves per SIMD (the 128 x 128
-// tile: four): at four its code spills ~10 registers, and three run small-matrix batches 4-6%
-// faster.
-using CfgB64 = Cfg<64, 2, 2, 32, 64, 1>;
-// Three-part BF16 split: the same 128 x 128 tile and eight waves, six panels of 32-deep K-blocks
-// in one LDS stage.
-using CfgB3 = Cfg<128, 4, 2, 32, 128, 1, 0, 3>;
+// The tiles of the single-matrix one-round layers, bitwise the same: 128 x 128 (eight waves, one
+// workgroup per CU) and 64 x 64 (four waves, two per CU), operands through a direct-to-LDS ring. ms per
+// batch, register-staged tiles / ring: 60 matrices of n 64 ... 768 1.72 / 1.37 (128 x 128); 30 of
+// 64 ... 256 0.69 / 0.23 (64 x 64), 60 of 128 ... 384 and 40 layers 1.80 (128 x 128) / 0.67 (64 x 64).
+using CfgB = Cfg<128, 4, 2, 64, 128, 2, 1>;
+using CfgB64 = Cfg<64, 2, 2, 64, 64, 2, 1>;
+// Three-part BF16 split: six panels of 32-deep K-blocks per stage.
+using CfgB3 = Cfg<128, 4, 2, 32, 128, 3, 1, 3>;
+using CfgB3x64 = Cfg<64, 2, 2, 32, 64, 3, 1, 3>;
+template <class C>
+constexpr int kPerCu = C::LDS_BYTES > 80 * 1024 ? 1 : 2;   // workgroups per CU
 
 __device__ inline double wsum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -166,17 +164,21 @@ k_batch_rescale(const BatchMat* mats, int count, const Params* P, double alpha, 
                 x[k] = alpha * v + (i == j ? (1.0 - alpha) * mu0 : 0.0);
             }
         }
-        floatx4 xf, af;
+        floatx4 xf, xm, af;
         uint16_t h[4], l[4], md[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             xf[k] = (float)x[k];
-            af[k] = d0 * xf[k];
+            xm[k] = xf[k];
+            // below the diagonal of a diagonal tile X and A mirror what lies above it (rescale_quad)
+            if (j0 + k < i && (i ^ j0) < 128 && i < m.n)
+                xm[k] = (float)(alpha * (scale * m.H[(j0 + k) * m.ldh + i]));
+            af[k] = d0 * xm[k];
             const float xs = i == j0 + k ? (float)(x[k] + s0) : xf[k];
             if (three) split3(xs, h[k], md[k], l[k]);
             else split16<BF>(xs, h[k], l[k]);
         }
-        *reinterpret_cast<floatx4*>(m.X + e0) = xf;
+        *reinterpret_cast<floatx4*>(m.X + e0) = xm;
         *reinterpret_cast<floatx4*>(m.A + e0) = af;
         auto pack = [](const uint16_t* v) {
             return u32x2{(uint32_t)v[0] | ((uint32_t)v[1] << 16), (uint32_t)v[2] | ((uint32_t)v[3] << 16)};
@@ -204,7 +206,7 @@ k_batch_rescale(const BatchMat* mats, int count, const Params* P, double alpha, 
 // no-alias arguments: its atomics precede these loads, and only with the arguments' no-alias
 // guarantee does the compiler know them unwritten and load them into scalar registers (else the
 // descriptors take vector registers throughout the tile's code, which then spills).
-template <bool BF, class C>
+template <bool BF, class C, int AUX>
 __device__ __attribute__((always_inline)) inline void batch_tile(
     const BatchLayerArgs& q, const BatchMat* __restrict__ mats, const int32_t* __restrict__ Ls,
     const float* __restrict__ coef, int lo, int t, int layer, bool poisoned, unsigned char* smem) {
@@ -240,23 +242,25 @@ __device__ __attribute__((always_inline)) inline void batch_tile(
     p.P = q.P + lo;
     p.partials = q.partials + m.tile0;
     Acc<C> acc;
-#pragma unroll
-    for (int mb = 0; mb < C::MB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < C::NB; ++nb)
-#pragma unroll
-            for (int j = 0; j < 16; ++j) acc.v[mb][nb][j] = 0.0f;
+    zero(acc);
     // K-blocks wholly in the padding add only zero products to the real block (X is block
     // diagonal there), and the padded part of the tile is not stored: they are skipped.
     const int kend = (int)((p.n + C::BK - 1) / C::BK);
-    if constexpr (C::NS == 3)
-        kloop3<C>(p.hi_in, p.mid_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM, 0, kend,
-                  acc, reinterpret_cast<uint16_t*>(smem));
-    else
-        kloop<BF, C>(p.hi_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM, 0, kend, acc,
-                     reinterpret_cast<uint16_t*>(smem));
-    epilogue<BF, C, C::BM == 128 ? kBatchEpiGroups : 8>(p, acc, reinterpret_cast<float*>(smem), I, J,
-                                                        t, nullptr, 0, 0, poisoned);
+    float* const sY = reinterpret_cast<float*>(smem);
+    constexpr bool kPre = EpiPre<C>::PER <= 4;
+    EpiPre<C> pre;
+    if constexpr (kPre) pre.template load<AUX>(p, I, J);
+    kloop_dma<BF, C, 0, AUX>(p.hi_in, p.mid_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM,
+                             0, kend, acc, reinterpret_cast<uint16_t*>(smem));
+    if (!p.last && !p.affine) {
+        epilogue_mid<BF, C, AUX, kPre ? 4 : 2>(p, acc, sY, I, J, poisoned, kPre ? &pre : nullptr);
+        return;
+    }
+    if constexpr (AUX != 0 && !kPre) {   // plain loads follow: no stale line in this CU's L1
+        asm volatile("buffer_inv sc1\n\ts_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
+    epilogue<BF, C, kPre ? 8 : 2, kPre>(p, acc, sY, I, J, t, nullptr, 0, 0, poisoned, &pre);
 }
 
 // One layer for every upper tile of every matrix. Workgroup g takes the (matrix, tile) of its slot
@@ -266,7 +270,7 @@ __device__ __attribute__((always_inline)) inline void batch_tile(
 // a map it finds its matrix by binary search over the tile prefix sums.
 template <bool BF, class C>
 __global__ void __launch_bounds__(C::NT)
-__attribute__((amdgpu_waves_per_eu(C::BM == 128 ? 4 : 3, C::BM == 128 ? 4 : 3)))
+__attribute__((amdgpu_waves_per_eu(2, 2)))
 k_batch_layer(BatchLayerArgs q) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int g = blockIdx.x;
@@ -286,75 +290,76 @@ k_batch_layer(BatchLayerArgs q) {
         t = g - q.mats[lo].tile0;
     }
     if (q.layer >= q.cf.L[q.mats[lo].model]) return;   // not launched for such matrices
-    batch_tile<BF, C>(q, q.mats, q.cf.L, q.cf.coef, lo, t, q.layer, false, smem);
+    batch_tile<BF, C, 0>(q, q.mats, q.cf.L, q.cf.coef, lo, t, q.layer, false, smem);
 }
 
 // Every layer of every matrix of a pass in one launch (the queue protocol is described with
-// BatchQueue): each workgroup takes the next ticket of its XCD's queue, waits until the item's
-// matrix has completed its previous layer, computes the item, and once every wave's stores of it
-// have completed counts it done. The wait is bounded: one that gives up marks the matrix and
-// raises the abort flag, after which no wait blocks; such an item is computed with NaN outputs.
-// Workgroups beyond their queue's length leave at once.
+// BatchQueue): each workgroup takes tickets of its XCD's queue until that is exhausted; it waits until
+// the item's matrix has completed its previous layer, computes the item, and once every wave's stores of
+// it have completed counts it done. The wait is bounded: one that gives up marks the matrix and raises
+// the abort flag, after which no wait blocks; such an item is computed with NaN outputs.
 template <bool BF, class C>
 __global__ void __launch_bounds__(C::NT)
-__attribute__((amdgpu_waves_per_eu(C::BM == 128 ? 4 : 3, C::BM == 128 ? 4 : 3)))
+__attribute__((amdgpu_waves_per_eu(2, 2)))
 k_batch_queue(BatchLayerArgs q, BatchQueue Q, const BatchMat* __restrict__ mats,
               const int32_t* __restrict__ Ls, const float* __restrict__ coef) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ int4 s_item;
     __shared__ int s_gave_up;
-    if (threadIdx.x == 0) {
-        int x;
-        asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(x));
-        int4 it = make_int4(-1, 0, 0, 0);   // none: no queue for this XCD (the completion check
-                                            // reports the matrices), or the queue is exhausted
-        if (x < Q.nq) {
-            const int q0 = Q.qoff[x], total = Q.qoff[x + 1] - q0;
-            const int k = __hip_atomic_fetch_add(Q.ticket + x, 1, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-            if (k < total) it = Q.items[q0 + k];
-        }
-        int gave_up = 0;
-        if (it.x >= 0) {
-            int32_t* const abort_flag = Q.err + q.count;
-            int spins = 0, backoff = 1;
-            const int need = it.w + Q.need_offset;
-            while (__hip_atomic_load(Q.done + it.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
-                   need) {
-                if (++spins > Q.spin_limit ||
-                    __hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-                    __hip_atomic_store(Q.err + it.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    gave_up = 1;
-                    break;
+    int x;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(x));
+    if (x >= Q.nq) return;   // no queue for this XCD (the completion check reports the matrices)
+    const int q0 = Q.qoff[x], total = Q.qoff[x + 1] - q0;
+    // the next item: (-1, ...) once the queue is exhausted
+    auto take = [&]() {
+        const int k = __hip_atomic_fetch_add(Q.ticket + x * kQueueLine, 1, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+        return k < total ? Q.items[q0 + k] : make_int4(-1, 0, 0, 0);
+    };
+    int4 it = make_int4(-1, 0, 0, 0);
+    if (threadIdx.x == 0) it = take();
+    for (;;) {
+        if (threadIdx.x == 0) {
+            int gave_up = 0;
+            if (it.x >= 0) {
+                int32_t* const abort_flag = Q.err + q.count;
+                int spins = 0;
+                const int need = it.w + Q.need_offset;
+                while (__hip_atomic_load(Q.done + it.x * kQueueLine, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT) < need) {
+                    if (++spins > Q.spin_limit ||
+                        (spins % 16 == 0 && __hip_atomic_load(abort_flag, __ATOMIC_RELAXED,
+                                                              __HIP_MEMORY_SCOPE_AGENT))) {
+                        __hip_atomic_store(Q.err + it.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        __hip_atomic_store(abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        gave_up = 1;
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(4);
                 }
-                // Back off (up to ~16 x 512 clocks between polls): where most workgroups wait
-                // (small batches), tight polling of a few counters slows the producers' updates.
-                for (int k = 0; k < backoff; ++k) __builtin_amdgcn_s_sleep(8);
-                if (backoff < 16) backoff *= 2;
             }
+            s_item = it;
+            s_gave_up = gave_up;
+            // nothing of the above is in flight beside the item's counted loads
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
-        s_item = it;
-        s_gave_up = gave_up;
+        __syncthreads();
+        const int mat = __builtin_amdgcn_readfirstlane(s_item.x);
+        if (mat < 0) return;   // the queue is exhausted; whole workgroup leaves
+        const int t = __builtin_amdgcn_readfirstlane(s_item.y);
+        const int layer = __builtin_amdgcn_readfirstlane(s_item.z);
+        const bool gave_up = __builtin_amdgcn_readfirstlane(s_gave_up) != 0;
+        batch_tile<BF, C, kCoherentLoad>(q, mats, Ls, coef, mat, t, layer, gave_up, smem);
+        // This wave's stores of the item have completed (in the XCD's L2). The memory clobber keeps
+        // the compiler from sinking any of them below the wait.
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            __hip_atomic_fetch_add(Q.done + mat * kQueueLine, 1, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            it = take();
+        }
     }
-    // Lines of the matrix that this CU's L1 holds from before its producers' stores are stale:
-    // wave 0 invalidates the L1 and waits for that before the barrier, after which every wave
-    // loads. The invalidate takes agent scope: the workgroup-scope one leaves the L1 alone when a
-    // workgroup's waves share one CU (measured: it does not stop stale reads here).
-    if (threadIdx.x < 64) asm volatile("buffer_inv sc1\n\ts_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    const int mat = __builtin_amdgcn_readfirstlane(s_item.x);
-    if (mat < 0) return;   // nothing to do; whole workgroup leaves
-    const int t = __builtin_amdgcn_readfirstlane(s_item.y);
-    const int layer = __builtin_amdgcn_readfirstlane(s_item.z);
-    const bool gave_up = __builtin_amdgcn_readfirstlane(s_gave_up) != 0;
-    batch_tile<BF, C>(q, mats, Ls, coef, mat, t, layer, gave_up, smem);
-    // This wave's stores of the item have completed (in the XCD's L2). The memory clobber keeps
-    // the compiler from sinking any of them below the wait.
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0)
-        __hip_atomic_fetch_add(Q.done + mat, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // XCD of workgroup b (one wave each), for the check that the queue launch's assumptions hold.
@@ -377,7 +382,7 @@ k_batch_queue_check(const BatchMat* mats, int count, BatchQueue Q, BatchCoef cf,
     const BatchMat& m = mats[b];
     const int64_t T = m.np / tile;
     const int64_t want = (int64_t)cf.L[m.model] * (T * (T + 1) / 2);
-    if ((Q.done[b] != want || Q.err[b] != 0) && P[b].status >= 0) P[b].status = FE_ERR_HIP;
+    if ((Q.done[(int64_t)b * kQueueLine] != want || Q.err[b] != 0) && P[b].status >= 0) P[b].status = FE_ERR_HIP;
 }
 
 // Per-matrix fixed-order reduction of the tile traces into Tr, sum of squares, and S (entropy).
@@ -447,14 +452,14 @@ hipError_t launch_layer_t(const BatchLayerArgs& q, int grid, hipStream_t s) {
 hipError_t launch_batch_layer(const BatchLayerArgs& q, int grid, int bf16, int tile,
                               hipStream_t s) {
     if (grid < 1) return hipErrorInvalidValue;
-    if (bf16 == 2)   // three-part BF16 split: 128 x 128 tiles only
-        return tile == 128 ? launch_layer_t<true, CfgB3>(q, grid, s) : hipErrorInvalidValue;
     if (tile == 64)
-        return bf16 ? launch_layer_t<true, CfgB64>(q, grid, s)
-                    : launch_layer_t<false, CfgB64>(q, grid, s);
+        return bf16 == 2 ? launch_layer_t<true, CfgB3x64>(q, grid, s)
+               : bf16    ? launch_layer_t<true, CfgB64>(q, grid, s)
+                         : launch_layer_t<false, CfgB64>(q, grid, s);
     if (tile != 128) return hipErrorInvalidValue;
-    return bf16 ? launch_layer_t<true, CfgB>(q, grid, s)
-                : launch_layer_t<false, CfgB>(q, grid, s);
+    return bf16 == 2 ? launch_layer_t<true, CfgB3>(q, grid, s)
+           : bf16    ? launch_layer_t<true, CfgB>(q, grid, s)
+                     : launch_layer_t<false, CfgB>(q, grid, s);
 }
 
 template <bool BF, class C>
@@ -468,6 +473,13 @@ hipError_t queue_t(const BatchLayerArgs& q, const BatchQueue& Q, int64_t grid, h
         if (e != hipSuccess) return e;
         done = true;
     }
+    // as many workgroups as run at once (the same number on every XCD)
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    const int64_t slots = std::max((int64_t)Q.nq, (int64_t)kPerCu<C> * cus / Q.nq * Q.nq);
+    if (grid > slots) grid = slots;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s, q, Q, q.mats,
                        q.cf.L, q.cf.coef);
     return hipGetLastError();
@@ -483,11 +495,14 @@ hipError_t launch_batch_queue_reset(const BatchQueue& Q, int count, hipStream_t 
 hipError_t launch_batch_queue(const BatchLayerArgs& q, const BatchQueue& Q, int64_t grid, int bf16,
                               int tile, hipStream_t s) {
     if (grid < 1 || grid > 0x7fffffff) return hipErrorInvalidValue;
-    if (bf16 == 2) return tile == 128 ? queue_t<true, CfgB3>(q, Q, grid, s) : hipErrorInvalidValue;
     if (tile == 64)
-        return bf16 ? queue_t<true, CfgB64>(q, Q, grid, s) : queue_t<false, CfgB64>(q, Q, grid, s);
+        return bf16 == 2 ? queue_t<true, CfgB3x64>(q, Q, grid, s)
+               : bf16    ? queue_t<true, CfgB64>(q, Q, grid, s)
+                         : queue_t<false, CfgB64>(q, Q, grid, s);
     if (tile != 128) return hipErrorInvalidValue;
-    return bf16 ? queue_t<true, CfgB>(q, Q, grid, s) : queue_t<false, CfgB>(q, Q, grid, s);
+    return bf16 == 2 ? queue_t<true, CfgB3>(q, Q, grid, s)
+           : bf16    ? queue_t<true, CfgB>(q, Q, grid, s)
+                     : queue_t<false, CfgB>(q, Q, grid, s);
 }
 
 hipError_t batch_queue_probe(int nq, bool* ok) {

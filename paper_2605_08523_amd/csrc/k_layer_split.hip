@@ -53,16 +53,6 @@ using CfgR64x3 = Cfg<64, 2, 2, 32, 64, 3, 1, 3>;
 using CfgR128x3 = Cfg<128, 4, 2, 32, 128, 3, 1, 3>;
 static_assert(2 * CfgR64::LDS_BYTES <= 160 * 1024 && 2 * CfgR64x3::LDS_BYTES <= 160 * 1024, "two per CU");
 
-template <class C>
-__device__ inline void zero(Acc<C>& acc) {
-#pragma unroll
-    for (int mb = 0; mb < C::MB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < C::NB; ++nb)
-#pragma unroll
-            for (int j = 0; j < 16; ++j) acc.v[mb][nb][j] = 0.0f;
-}
-
 template <bool BF, class C>
 __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_layer_dp(LayerArgs p) {

@@ -195,6 +195,24 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t by
                                              0x00020000);
 }
 
+// This thread's index, opaque to the optimiser: in a persistent loop the offsets formed from it stay
+// where they are used instead of being kept in registers (then spilled) around the loop.
+__device__ inline int opaque_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+template <class C>
+__device__ inline void zero(Acc<C>& acc) {
+#pragma unroll
+    for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc.v[mb][nb][j] = 0.0f;
+}
+
 // Direct-to-LDS form of the K loop (C::DMA): each lane's buffer_load_dwordx4 ... lds moves one 16-byte
 // chunk, and the 64 chunks of one instruction land in 1 KiB of LDS in lane order. A stage holds the
 // 2 NS BM x BK operand panels (A parts, then B parts) in unpadded rows; chunk c of row r sits at
@@ -763,7 +781,8 @@ struct EpiPre {
     __device__ inline void load(const LayerArgs& p, int I, int J) {
         static_assert(C::EC == C::BM, "one epilogue chunk per tile");
         const uint32_t np = (uint32_t)p.np, bytes = np * np * 4;
-        const int voff = (int)((threadIdx.x / G) * np * 4 + (threadIdx.x % G) * 16);
+        const int tid = opaque_tid();
+        const int voff = (int)((tid / G) * np * 4 + (tid % G) * 16);
         const uint32_t base = ((uint32_t)I * C::BM * np + (uint32_t)J * C::BM) * 4;
         auto at = [&](__amdgpu_buffer_rsrc_t rs, int u) {
             return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(
@@ -802,7 +821,7 @@ __device__ __attribute__((always_inline)) inline void epilogue_mid(const LayerAr
                                                                    const EpiPre<C>* pre) {
     constexpr int BM = C::BM, G = BM / 4, RPG = C::NT / G, PER = BM / RPG;
     static_assert(PER % UB == 0, "whole batches of groups");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = opaque_tid(), lane = tid & 63, wave = tid >> 6;
     const int rt = tid / G, g = tid % G;   // this thread's row step and group
     const uint32_t np = (uint32_t)p.np;
     const int I0 = I * BM, J0 = J * BM;
@@ -947,7 +966,7 @@ __device__ inline void epi_chunk(const LayerArgs& p, float* sY, int R0, int I, i
                                  const float* __restrict__ Y0, const float* __restrict__ parts,
                                  size_t part_stride, int nparts, double& tr, double& sq,
                                  bool poisoned, const EpiPre<C>* pre = nullptr) {
-    const int tid = threadIdx.x;
+    const int tid = opaque_tid();
     const int64_t np = p.np;
     const int64_t I0 = (int64_t)I * C::BM, J0 = (int64_t)J * C::BM;
     const bool diag = (I == J);
@@ -1170,7 +1189,7 @@ __device__ inline void epilogue(const LayerArgs& p, const Acc<C>& acc, float* sY
                                 int tile_index, const float* __restrict__ parts = nullptr,
                                 size_t part_stride = 0, int nparts = 0, bool poisoned = false,
                                 const EpiPre<C>* pre = nullptr) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = opaque_tid(), lane = tid & 63, wave = tid >> 6;
     const int wm = wave / C::WN, wn = wave % C::WN;
     const float inv_s = BF ? 1.0f : (1.0f / 2048.0f);
     double tr = 0.0, sq = 0.0;
