@@ -227,7 +227,7 @@ struct LayerLaunch {
 int enqueue_pass(fe_workspace* ws, int count, int64_t max_np, const fe::BatchCoef& cf,
                  const std::vector<LayerLaunch>& launches, const QueueLaunch* queue, double alpha,
                  int entropy, int bf, int tile, int32_t* status, hipStream_t s) {
-    if (!entropy) FE_HIP(fe::launch_batch_bounds(ws->bmats, count, ws->bparams, s));
+    if (!entropy) FE_HIP(fe::launch_batch_bounds(ws->bmats, count, max_np, ws->bparams, s));
     FE_HIP(fe::launch_batch_rescale(ws->bmats, count, max_np, ws->bparams, alpha, cf, bf, s));
     if (queue) {
         fe::BatchLayerArgs q{};
@@ -690,7 +690,7 @@ int fe_batch_plan_create_bank(const fe_batch_item* items, int32_t count, const f
     ++ws->batch_gen;
     FE_HIP(hipDeviceSynchronize());
     FE_HIP(hipMemcpy(ws->bmats, mats.data(), sizeof(fe::BatchMat) * count, hipMemcpyHostToDevice));
-    FE_HIP(fe::launch_batch_bounds(ws->bmats, count, ws->bparams, nullptr));
+    FE_HIP(fe::launch_batch_bounds(ws->bmats, count, max_np, ws->bparams, nullptr));
     std::vector<fe::Params> P(count);
     FE_HIP(hipMemcpy(P.data(), ws->bparams, sizeof(fe::Params) * count, hipMemcpyDeviceToHost));
     std::vector<int> model(count, 0);

@@ -240,7 +240,8 @@ struct BatchLayerArgs {
 };
 constexpr int kBatchPad = 128;   // batch matrices are padded to a multiple of this
 // Bounds and rescale parameters of every matrix with its own (beta0, mu0).
-hipError_t launch_batch_bounds(const BatchMat* mats, int count, Params* P, hipStream_t s);
+hipError_t launch_batch_bounds(const BatchMat* mats, int count, int64_t max_n, Params* P,
+                               hipStream_t s);
 // bf16 (here and below): 0 FP16x2, 1 BF16x2, 2 three-part BF16 (BatchMat mid[] set).
 hipError_t launch_batch_rescale(const BatchMat* mats, int count, int64_t max_np, const Params* P,
                                 double alpha, BatchCoef cf, int bf16, hipStream_t s);

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "batch_queue.h"
+#include "rescale_params.h"
 #include "resident.h"
 #include "split_common.h"
 
@@ -41,20 +42,25 @@ __device__ inline double wmax(double v) {
     return v;
 }
 
-// One workgroup of 16 waves per matrix: Gershgorin bounds (one wave per row, each row summed in
-// the same order as the single-matrix prologue, so both give the same bounds) and the rescale
-// parameters of Sec. IV.1.
+// Gershgorin bounds of kBoundsWaves rows (chunk blockIdx.x) of matrix blockIdx.y, one wave per row, each
+// row summed in the same order as the single-matrix prologue, so both give the same bounds. The
+// chunks' partials go where the rescale writes X later (np >= 128, so they fit). us for 60 matrices of
+// n 64 ... 768: 28 (one workgroup per matrix, bound by its largest: 156).
 constexpr int kBoundsWaves = 16;
+__host__ __device__ inline int bounds_chunks(int64_t n) {
+    return (int)((n + kBoundsWaves - 1) / kBoundsWaves);
+}
 __global__ void __launch_bounds__(kBoundsWaves * 64)
-k_batch_bounds(const BatchMat* mats, int count, Params* P) {
-    const int b = blockIdx.x;
+k_batch_bounds(const BatchMat* mats, int count) {
+    const int b = blockIdx.y;
     if (b >= count) return;
     const BatchMat m = mats[b];
-    const double beta0 = m.beta0, mu0 = m.mu0;
+    if ((int)blockIdx.x >= bounds_chunks(m.n)) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double lo = INFINITY, hi = -INFINITY;
     int bad = 0;
-    for (int64_t i = wave; i < m.n; i += kBoundsWaves) {
+    const int64_t i = (int64_t)blockIdx.x * kBoundsWaves + wave;
+    if (i < m.n) {
         const double* row = m.H + i * m.ldh;
         double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
         int64_t j = lane;
@@ -68,7 +74,7 @@ k_batch_bounds(const BatchMat* mats, int count, Params* P) {
         const double s = wsum((s0 + s1) + (s2 + s3));
         const double d = row[i];
         const double r = s - fabs(d);
-        if (!isfinite(s)) bad = 1;
+        bad = !isfinite(s);
         lo = fmin(lo, d - r);
         hi = fmax(hi, d + r);
     }
@@ -86,52 +92,35 @@ k_batch_bounds(const BatchMat* mats, int count, Params* P) {
         hi = fmax(hi, shi[w]);
         bad |= sbad[w];
     }
-    const double mu = m.mu, kT = m.kT;
-    Params p;
-    p.emin = lo;
-    p.emax = hi;
-    p.flipped = p.clamped = p.degenerate = 0;
-    p.status = FE_OK;
-    const double width = hi - lo;
-    if (bad || !isfinite(lo) || !isfinite(hi)) {
-        p.status = FE_ERR_NONFINITE;
-        p.mu_p = p.beta_p = p.beta_max = p.scale = p.shift = NAN;
-    } else if (!(kT > 0.0)) {
+    reinterpret_cast<BoundsPartial*>(m.X)[blockIdx.x] = BoundsPartial{lo, hi, bad, 0};
+}
+
+// The rescale parameters of Sec. IV.1, one wave per matrix.
+__global__ void __launch_bounds__(64)
+k_batch_params(const BatchMat* mats, int count, Params* P) {
+    const int b = blockIdx.x;
+    if (b >= count) return;
+    const BatchMat m = mats[b];
+    const int chunks = bounds_chunks(m.n);
+    const BoundsPartial* parts = reinterpret_cast<const BoundsPartial*>(m.X);
+    double lo = INFINITY, hi = -INFINITY;
+    int bad = 0;
+    for (int k = threadIdx.x; k < chunks; k += 64) {
+        lo = fmin(lo, parts[k].lo);
+        hi = fmax(hi, parts[k].hi);
+        bad |= parts[k].nonfinite;
+    }
+    lo = wmin(lo);
+    hi = wmax(hi);
+    bad = __any(bad);
+    if (threadIdx.x != 0) return;
+    Params p = rescale_params(lo, hi, bad, m.mu, m.kT, m.beta0, m.mu0);
+    if (p.status != FE_ERR_NONFINITE && !(m.kT > 0.0)) {
+        p = Params{};
+        p.emin = lo;
+        p.emax = hi;
         p.status = FE_ERR_DOMAIN;
         p.mu_p = p.beta_p = p.beta_max = p.scale = p.shift = NAN;
-    } else if (width <= 1e-300 * fmax(1.0, fabs(hi))) {
-        double y = mu0 + (mu - lo) / (kT * beta0);
-        p.degenerate = 1;
-        if (!(y >= 0.0 && y <= 1.0)) {
-            p.clamped = 1;
-            y = fmin(1.0, fmax(0.0, y));
-        }
-        p.mu_p = NAN;
-        p.beta_p = INFINITY;
-        p.beta_max = NAN;
-        p.scale = 0.0;
-        p.shift = y;
-    } else if (!(lo < mu && mu < hi)) {
-        p.status = FE_ERR_DOMAIN;
-        p.mu_p = p.beta_p = p.beta_max = p.scale = p.shift = NAN;
-    } else {
-        double mu_p = (hi - mu) / width;
-        double beta_p = width / kT;
-        const int flip = mu_p > 0.5;
-        if (flip) mu_p = 1.0 - mu_p;
-        const double bmax = fmin(mu0 / mu_p, (1.0 - mu0) / (1.0 - mu_p)) * beta0;
-        if (beta_p > bmax) {
-            beta_p = bmax;
-            p.clamped = 1;
-            p.status = FE_WARN_BETA_CLAMPED;
-        }
-        const double r = beta_p / beta0;
-        p.scale = flip ? r / width : -r / width;
-        p.shift = flip ? r * (-lo / width - mu_p) + mu0 : r * (hi / width - mu_p) + mu0;
-        p.mu_p = mu_p;
-        p.beta_p = beta_p;
-        p.beta_max = bmax;
-        p.flipped = flip;
     }
     P[b] = p;
 }
@@ -415,8 +404,14 @@ k_batch_reduce(const BatchMat* mats, int count, const TracePartial* partials, co
 
 }  // namespace
 
-hipError_t launch_batch_bounds(const BatchMat* mats, int count, Params* P, hipStream_t s) {
-    hipLaunchKernelGGL(k_batch_bounds, dim3(count), dim3(kBoundsWaves * 64), 0, s, mats, count, P);
+hipError_t launch_batch_bounds(const BatchMat* mats, int count, int64_t max_n, Params* P,
+                               hipStream_t s) {
+    for (int b0 = 0; b0 < count; b0 += 65535) {   // the y extent of a grid
+        const int k = std::min(count - b0, 65535);
+        hipLaunchKernelGGL(k_batch_bounds, dim3(bounds_chunks(max_n), k), dim3(kBoundsWaves * 64), 0, s,
+                           mats + b0, k);
+    }
+    hipLaunchKernelGGL(k_batch_params, dim3(count), dim3(64), 0, s, mats, count, P);
     return hipGetLastError();
 }
 
