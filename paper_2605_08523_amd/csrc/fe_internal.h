@@ -124,6 +124,10 @@ int split_tile_for(int streamk);
 // Tile of the data-parallel kernel whose workgroups all run at once at size n on n_cu compute
 // units: 64, 128, or 0 where the tiles need more than one round.
 int split_ring_tile(int64_t n, int n_cu);
+// Schedule (SplitPlan::streamk) of the two-part layers of larger sizes, and the workgroups per CU of
+// schedule 2.
+int split_schedule(int64_t n, int n_cu);
+int split_sk2_per_cu(int64_t n);
 // Whether its 64 x 64 tiles fit one XCD's compute units, one on each (launch_layers_resident).
 bool split_resident(int64_t n, int n_cu);
 // The stream-K plan the launcher uses for a padded size np, schedule 1 or 2, at most grid

@@ -11,17 +11,17 @@
 //  * The epilogue is fused (see split_common.h): Y goes through LDS, one row-major pass applies
 //    a Y + b X + c delta_ij, updates A and writes the next hi/lo (and, in the direct form, the FP32
 //    master X); a transposed pass writes the mirror tile. The last layer writes D and FP64
-//    traces. In the squared-affine form (FP16x2 default) the operand is the shifted state
+//    traces. In the squared-affine form (FE_FORM=affine) the operand is the shifted state
 //    x + b/(2a), so b = 0 and X is neither read nor written.
 //  * Three schedules:
 //      data-parallel: one workgroup per upper tile: 64 x 64 or 128 x 128 tiles with direct-to-LDS
 //        operand loads where all tiles run at once (split_ring_tile), else 128 x 128 (four
 //        64 x 64 wave tiles, register-staged);
-//      stream-K over 128 x 128 tiles, two persistent workgroups per CU: the (tile, K-block)
-//        iterations left after the whole-tile rounds are split evenly. A workgroup that stops
-//        inside a tile publishes its FP32 partial; the workgroup that finishes the tile adds the
-//        earlier workgroups' partials in a fixed order in its epilogue (accumulators stay in
-//        registers);
+//      stream-K over 128 x 128 tiles, persistent workgroups (one per CU on the one-round ring; beyond
+//        the Infinity Cache two, register-staged): the (tile, K-block) iterations left after the
+//        whole-tile rounds are split evenly. A workgroup that stops inside a tile publishes its
+//        FP32 partial; the workgroup that finishes the tile adds the earlier workgroups' partials
+//        in a fixed order in its epilogue (accumulators stay in registers);
 //      stream-K over 256 x 256 tiles (eight 128 x 64 wave tiles, two LDS stages filled by
 //        direct global-to-LDS loads, fragment reads interleaved with the MFMAs), one
 //        workgroup per CU: the same; its K loop holds no prefetch registers, so the 128
@@ -35,11 +35,14 @@
 namespace fe {
 namespace {
 
+constexpr int64_t kInfinityCache = (int64_t)256 << 20;
+
 using namespace split;
 
 using CfgDP = Cfg<128, 2, 2, 64, 128, 1>;
 using CfgSK = Cfg<256, 2, 4, 32, 128, 2, 1>;   // direct-to-LDS operand staging
-using CfgSK2 = Cfg<128, 2, 2, 64, 128, 1>;   // stream-K over 128 x 128 tiles, two workgroups per CU
+using CfgSK2 = Cfg<128, 4, 2, 64, 128, 2, 1>;   // stream-K over 128 x 128 tiles, the one-round layers' ring
+using CfgSK2x2 = Cfg<128, 2, 2, 64, 128, 1>;    // ... for operands beyond the Infinity Cache (split_sk2_per_cu)
 // Three-part BF16 split: six panels of 32-deep K-blocks in one LDS stage (61 KiB), so two
 // workgroups still fit per CU; data-parallel only.
 using CfgDP3 = Cfg<128, 2, 2, 32, 128, 1, 0, 3>;
@@ -81,19 +84,25 @@ k_layer_dp(LayerArgs p) {
 // before, sum K in segments of 512, as that schedule's partial tiles did at n = 2048: one chain of
 // 2048 gave 1.45 times its error against FP64.
 template <bool BF, class C, int AUX>
+__device__ __attribute__((always_inline)) inline void ring_products(const LayerArgs& p, int I, int J,
+                                                                    int kb0, int kb1, Acc<C>& acc,
+                                                                    unsigned char* smem) {
+    constexpr int kSeg = C::BM == 128 && C::NS == 2 ? 512 / C::BK : 0;
+    kloop_dma<BF, C, kSeg, AUX>(p.hi_in, p.mid_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM,
+                                kb0, kb1, acc, reinterpret_cast<uint16_t*>(smem));
+}
+
+template <bool BF, class C, int AUX>
 __device__ __attribute__((always_inline)) inline void ring_tile(const LayerArgs& p, int t,
                                                                 unsigned char* smem, bool poisoned) {
     int I, J;
     tile_coords(t, (int)(p.np / C::BM), I, J);
     constexpr bool kPre = EpiPre<C>::PER <= 4;
-    constexpr int kSeg = C::BM == 128 && C::NS == 2 ? 512 / C::BK : 0;
     EpiPre<C> pre;
     if constexpr (kPre) pre.template load<AUX>(p, I, J);
     Acc<C> acc;
     zero(acc);
-    kloop_dma<BF, C, kSeg, AUX>(p.hi_in, p.mid_in, p.lo_in, p.np, (int64_t)I * C::BM,
-                                (int64_t)J * C::BM, 0, (int)(p.np / C::BK), acc,
-                                reinterpret_cast<uint16_t*>(smem));
+    ring_products<BF, C, AUX>(p, I, J, 0, (int)(p.np / C::BK), acc, smem);
     if (!p.last && !p.affine) {
         epilogue_mid<BF, C, AUX>(p, acc, reinterpret_cast<float*>(smem), I, J, poisoned,
                                  kPre ? &pre : nullptr);
@@ -205,8 +214,11 @@ k_layer_sk(LayerArgs p, SplitPlan sk) {
         const float* parts = sk.partial + (size_t)(g + NG * jlo) * TILE;
         Acc<C> acc;
         zero(acc);
-        kloop<BF, C>(p.hi_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM, kb0, kb1, acc,
-                     reinterpret_cast<uint16_t*>(smem));
+        if constexpr (C::DMA)
+            ring_products<BF, C, 0>(p, I, J, kb0, kb1, acc, smem);
+        else
+            kloop<BF, C>(p.hi_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM, kb0, kb1, acc,
+                         reinterpret_cast<uint16_t*>(smem));
         if (pass == 0) {
             // Publication: every wave waits until its device-coherent stores of the partial
             // have completed, then one flag store (device-coherent too) announces the tile.
@@ -220,6 +232,13 @@ k_layer_sk(LayerArgs p, SplitPlan sk) {
                                    __HIP_MEMORY_SCOPE_AGENT);
         } else if constexpr (kRegEpi) {
             const bool gave_up = wait_published(sk, g, NG, jlo, w);
+            if constexpr (C::BM == 128 && C::DMA) {
+                if (!p.last && !p.affine && (I != J || jlo == j)) {
+                    epilogue_mid<BF, C>(p, acc, sY, I, J, gave_up, nullptr, parts, (size_t)NG * TILE,
+                                        j - jlo);
+                    return;
+                }
+            }
             epilogue<BF, C, 1>(p, acc, sY, I, J, t, parts, (size_t)NG * TILE, j - jlo, gave_up);
         } else {
             store_tile<BF, C, false>(acc, own);
@@ -249,6 +268,16 @@ hipError_t launch_dp(const LayerArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(kern, dim3(T * (T + 1) / 2), dim3(C::NT), C::LDS_BYTES, s, a);
     return hipGetLastError();
 }
+
+// The kernel that runs tiles [0, dp_tiles) of a stream-K layer whole.
+template <bool BF, class C, bool DMA = C::DMA != 0>
+struct WholeTiles {
+    static constexpr auto kernel = k_layer_ring<BF, C>;
+};
+template <bool BF, class C>
+struct WholeTiles<BF, C, false> {
+    static constexpr auto kernel = k_layer_dp<BF, C>;
+};
 
 template <bool BF, class C>
 hipError_t launch_ring(const LayerArgs& a, hipStream_t s) {
@@ -292,7 +321,7 @@ hipError_t launch_sk(const LayerArgs& a, const SplitPlan& sk, hipStream_t s) {
     if (plan.grid < 1) return hipErrorInvalidValue;
     if constexpr (reg_epi) {
         if (plan.dp_tiles > 0) {
-            auto dkern = k_layer_dp<BF, C>;
+            auto dkern = WholeTiles<BF, C>::kernel;
             static bool ddone = false;
             e = set_lds(dkern, C::LDS_BYTES, ddone);
             if (e != hipSuccess) return e;
@@ -326,6 +355,33 @@ int split_ring_tile(int64_t n, int n_cu) {
 bool split_resident(int64_t n, int n_cu) {
     const int64_t T = (n + CfgR64::BM - 1) / CfgR64::BM;
     return 8 * (T * (T + 1) / 2) <= n_cu;
+}
+
+int split_sk2_per_cu(int64_t n) {
+    static_assert(CfgSK2::BM == CfgSK2x2::BM && CfgSK2::BK == CfgSK2x2::BK, "one geometry");
+    return 4 * n * n >= kInfinityCache ? 2 : 1;
+}
+
+// ms per density matrix (26 layers): before (stream-K, 128 x 128 register-staged tiles, two workgroups
+// per CU) / 128 x 128 ring / 256 x 256, random dense and banded: n = 3000 4.4 / 3.9 / 5.7 (banded), 4096
+// 6.3 / 5.8 / 6.5 and 8.5 / 7.8 / 8.6, 4500 9.2 / 8.3 / 8.4 and 12.9 / 11.6 / 11.0, 5000 12.8 / 11.0 / 10.9
+// and 18.8 / 15.1 / 14.1, 5500 17.8 / 15.1 / 12.9 and 26.5 / 22.0 / 16.3, 6000 19.2 / 17.8 / 18.5 and
+// 24.7 / 24.5 / 25.0, 6500 25.3 / 22.1 / 21.6, 7000 29.1 / 28.4 / 27.0 and 36.4 / 38.1 / 34.9, 7600
+// 39.9 / 37.9 / 33.9: the 256 x 256 tiles pass half the operands through LDS, but need three quarters
+// of the CUs in their first round, and lose where they start a second one. From n = 8192 the
+// operands (4 n^2 bytes) no longer fit the 256 MiB Infinity Cache, and an XCD that works on 8 x 8
+// tiles at a time fetches fewer panels per tile than one with 8 x 4: banded 8192 57.3 / 58.5 / 60.7,
+// 10000 106 / 116 / 131. From eight whole rounds on the uneven last one costs less than the partial
+// tiles: stream-K / data-parallel 12000 150 / 146 and 201 / 182, 16384 463 / 441 (10000, six rounds:
+// 106 / 111).
+int split_schedule(int64_t n, int n_cu) {
+    auto tiles = [n](int64_t bm) {
+        const int64_t T = (n + bm - 1) / bm;
+        return T * (T + 1) / 2;
+    };
+    if (split_sk2_per_cu(n) == 2) return tiles(128) >= 16 * (int64_t)n_cu ? 0 : 2;
+    const int64_t t = tiles(256);
+    return 4 * t >= 3 * (int64_t)n_cu && (t <= n_cu || 4 * t >= 5 * (int64_t)n_cu) ? 1 : 2;
 }
 
 int split_tile_for(int streamk) {
@@ -368,6 +424,8 @@ hipError_t launch_layer_split(const LayerArgs& a, int bf16, const SplitPlan& pla
     }
     if (plan.streamk == 1)
         return bf16 ? launch_sk<true, CfgSK>(a, plan, s) : launch_sk<false, CfgSK>(a, plan, s);
+    if (plan.streamk == 2 && split_sk2_per_cu(a.n) == 2)
+        return bf16 ? launch_sk<true, CfgSK2x2>(a, plan, s) : launch_sk<false, CfgSK2x2>(a, plan, s);
     if (plan.streamk == 2)
         return bf16 ? launch_sk<true, CfgSK2>(a, plan, s) : launch_sk<false, CfgSK2>(a, plan, s);
     return bf16 ? launch_dp<true>(a, s) : launch_dp<false>(a, s);

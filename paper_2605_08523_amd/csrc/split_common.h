@@ -814,11 +814,15 @@ struct EpiPre {
 // product (the rescale made X and A symmetric there, so they equal the upper ones bit for bit). The
 // padding comes out zero. LDS: 16-byte groups of row r at group g ^ (r / 4) (modulo the row). pre: the
 // tile's X and A groups, or NULL: loaded here, UB groups at a time. AUX: cache policy of those loads.
+// parts: nparts partial tiles of other workgroups as in epi_chunk (not for a diagonal tile).
 template <bool BF, class C, int AUX = 0, int UB = 4>
 __device__ __attribute__((always_inline)) inline void epilogue_mid(const LayerArgs& p, const Acc<C>& acc,
                                                                    float* sY, int I, int J,
                                                                    bool poisoned,
-                                                                   const EpiPre<C>* pre) {
+                                                                   const EpiPre<C>* pre,
+                                                                   const float* __restrict__ parts = nullptr,
+                                                                   size_t part_stride = 0,
+                                                                   int nparts = 0) {
     constexpr int BM = C::BM, G = BM / 4, RPG = C::NT / G, PER = BM / RPG;
     static_assert(PER % UB == 0, "whole batches of groups");
     const int tid = opaque_tid(), lane = tid & 63, wave = tid >> 6;
@@ -873,6 +877,12 @@ __device__ __attribute__((always_inline)) inline void epilogue_mid(const LayerAr
             const int u = u0 + v, r = rt + RPG * u, c = g * 4;
             const floatx4 x = pre ? pre->x[u] : xg[v], a = pre ? pre->a[u] : ag[v];
             floatx4 y = *reinterpret_cast<const floatx4*>(sY + at(r, c));
+            for (int q = 0; q < nparts; ++q) {
+                const floatx4 z = load4_coherent(make_rsrc(parts + (size_t)q * part_stride, BM * BM * 4),
+                                                 (r * BM + c) * 4);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) y[k] = fmaf(z[k], BF ? 1.0f : 2048.0f, y[k]);
+            }
             if (diag) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
