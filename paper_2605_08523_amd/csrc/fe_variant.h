@@ -54,6 +54,11 @@ SquareSplit square_split(int ntiles, int nk, int slots);
 constexpr int64_t kSquarePartTile = 128 * 128;   // floats per partial tile
 hipError_t launch_square(const uint16_t* hi, const uint16_t* lo, int64_t np, float* out, int bf16,
                          int slots, float* parts, hipStream_t s);
+// That and the combine a after it in one launch, where the tiles run at once (split_ring_tile(np, n_cu)
+// is not 0): x takes the place of a.term[tx] and a.acc_src and is stored in x_out unless NULL; a.hi and
+// a.lo are other buffers than hi and lo; not the first or last combine.
+hipError_t launch_square_combine(const uint16_t* hi, const uint16_t* lo, const CombineArgs& a, int tx,
+                                 float* x_out, int n_cu, hipStream_t s);
 
 // Scalar Skip-SP2 / Max-SP2 model at n device points and, if JT is not null, its Jacobian
 // transposed (JT[p][k], coefficient p in the layout of fe_qmodel). coef is a device array.

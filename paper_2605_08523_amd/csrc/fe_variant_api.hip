@@ -110,6 +110,26 @@ int fe_expand_density_variant(const double* H, int64_t n, int64_t ldh, double mu
         a.n = n; a.np = np; a.bf16 = bf; a.hi = hi; a.lo = lo; a.P = P;
         return a;
     };
+    // Where the tiles run at once a squaring and the next layer's combine are one launch, and the operands
+    // alternate between two buffers; the second lies where the squaring's partial tiles would be (a
+    // round of slots, so two tiles per CU: at least as large).
+    const bool fused = fe::split_ring_tile(np, slots / 2) != 0 &&
+                       2 * e * sizeof(uint16_t) <= (size_t)slots * fe::kSquarePartTile * sizeof(float);
+    uint16_t* const ops[2] = {hi, reinterpret_cast<uint16_t*>(parts)};
+    // Layer i's combine, and the squaring of its operand into x_dst if nothing follows in one launch.
+    // tx: the combine's term that layer i - 1's squaring gives; keep: a later layer reads that x.
+    auto layer = [&](int i, fe::CombineArgs& a, int tx, bool keep, float* x_src, float* x_dst) -> int {
+        if (fused && i > 0) {
+            const uint16_t* in = ops[(i - 1) & 1];
+            a.hi = ops[i & 1];
+            a.lo = a.hi + e;
+            FE_HIP(fe::launch_square_combine(in, in + e, a, tx, keep ? x_src : nullptr, slots / 2, s));
+        } else {
+            FE_HIP(fe::launch_combine(a, s));
+        }
+        if (!fused || i + 1 == L) FE_HIP(fe::launch_square(a.hi, a.lo, np, x_dst, bf, slots, parts, s));
+        return FE_OK;
+    };
     fe::CombineArgs fin = base();
     if (m->arch == FE_ARCH_MAX) {
         int off = 0;
@@ -121,8 +141,8 @@ int fe_expand_density_variant(const double* H, int64_t n, int64_t ldh, double mu
                 a.term[j] = slot[j];
                 a.w[j] = (float)c[off + 1 + j];
             }
-            FE_HIP(fe::launch_combine(a, s));
-            FE_HIP(fe::launch_square(hi, lo, np, slot[i + 1], bf, slots, parts, s));
+            rc = layer(i, a, i, true, slot[i], slot[i + 1]);
+            if (rc) return rc;
             off += i + 2;
         }
         fin.diag = (float)c[off];
@@ -158,8 +178,8 @@ int fe_expand_density_variant(const double* H, int64_t n, int64_t ldh, double mu
             }
             a.acc_src = ring[i % k];
             a.acc_first = i == 0;
-            FE_HIP(fe::launch_combine(a, s));
-            FE_HIP(fe::launch_square(hi, lo, np, ring[(i + 1) % k], bf, slots, parts, s));
+            rc = layer(i, a, 0, k > 1, ring[i % k], ring[(i + 1) % k]);
+            if (rc) return rc;
         }
         double d = 0.0;
         for (int l = 0; l < K; ++l) d += a0[l];

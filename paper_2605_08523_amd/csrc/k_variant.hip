@@ -65,6 +65,121 @@ k_square(const uint16_t* __restrict__ hi, const uint16_t* __restrict__ lo, int64
         }
 }
 
+// A squaring and the combine that follows it in one kernel (one-round tiles only): the tile's x = Z^2
+// goes from the accumulators through LDS into the combine of a (term tx and acc_src are x), whose
+// operand z goes to hi_out/lo_out, another buffer than the one that the other tiles still read. x
+// itself is written to x_out unless NULL (no later layer reads it). The values are k_square's and
+// k_combine's. It saves a launch and x's way through memory: us per Skip-SP2 expansion, two kernels /
+// one: n = 1728 890 / 717, 2197 1307 / 1195, 2744 1828 / 1591; Max-SP2 1728 1021 / 864, 2744 2409 / 2164.
+template <bool BF, class C>
+__global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_square_combine(const uint16_t* __restrict__ hi, const uint16_t* __restrict__ lo, CombineArgs a, int tx,
+                 float* __restrict__ x_out) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int BM = C::BM, G = BM / 4, RPG = C::NT / G, PER = BM / RPG;
+    const int64_t np = a.np;
+    int I, J;
+    tile_coords(xcd_tile(blockIdx.x, gridDim.x), (int)(np / BM), I, J);
+    Acc<C> acc;
+    zero(acc);
+    const int64_t I0 = (int64_t)I * BM, J0 = (int64_t)J * BM;
+    kloop<BF, C>(hi, lo, np, I0, J0, 0, (int)(np / C::BK), acc, reinterpret_cast<uint16_t*>(smem));
+    // LDS as in epilogue_mid: 16-byte groups of row r at group g ^ (r / 4)
+    auto at = [](int r, int c) { return r * BM + (((c >> 2) ^ ((r >> 2) & (G - 1))) << 2) + (c & 3); };
+    float* const sY = reinterpret_cast<float*>(smem);
+    uint32_t* const sW = reinterpret_cast<uint32_t*>(smem);
+    const int tid = opaque_tid(), lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+    for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < C::NB; ++nb) {
+            const int rb = (wave / C::WN) * C::WAVE_M + mb * 32 + 4 * (lane >> 5);
+            const int c = (wave % C::WN) * C::WAVE_N + nb * 32 + (lane & 31);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) sY[at(rb + 8 * (j >> 2) + (j & 3), c)] = acc.v[mb][nb][j];
+        }
+    __syncthreads();
+    const float inv_s = BF ? 1.0f : (1.0f / 2048.0f);
+    const bool diag = I == J;
+    const int rt = tid / G, c = (tid % G) * 4;
+#pragma unroll 2
+    for (int u = 0; u < PER; ++u) {
+        const int r = rt + RPG * u;
+        if (diag && c + 3 < r) continue;   // entirely below the diagonal
+        const int64_t gr = I0 + r, gi = gr * np + J0 + c;
+        floatx4 x = *reinterpret_cast<const floatx4*>(sY + at(r, c)), z;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            x[k] *= inv_s;
+            z[k] = (gr == J0 + c + k) ? a.diag : 0.0f;
+        }
+        if (x_out) *reinterpret_cast<floatx4*>(x_out + gi) = x;
+        auto add = [&](float w, const floatx4& v) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) z[k] = fmaf(w, v[k], z[k]);
+        };
+        int t = 0;
+        for (; t + 4 <= a.nterm; t += 4) {   // the group's loads before its FMAs
+            floatx4 v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                v[q] = t + q == tx ? x : *reinterpret_cast<const floatx4*>(a.term[t + q] + gi);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) add(a.w[t + q], v[q]);
+        }
+        for (; t < a.nterm; ++t) add(a.w[t], t == tx ? x : *reinterpret_cast<const floatx4*>(a.term[t] + gi));
+        for (int l = 0; l < a.nacc; ++l) {
+            floatx4 v = *reinterpret_cast<const floatx4*>(a.acc[l] + gi);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = fmaf(a.g[l], x[k], v[k]);
+            *reinterpret_cast<floatx4*>(a.acc[l] + gi) = v;
+        }
+        u32x2 h, l;
+        split4<BF>(z, h, l);
+        u32x4 w;   // hi | lo << 16 for the mirror
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            w[k] = (k & 1 ? h[k >> 1] >> 16 : h[k >> 1] & 0xffffu) |
+                   (k & 1 ? l[k >> 1] & 0xffff0000u : l[k >> 1] << 16);
+        *reinterpret_cast<u32x4*>(sW + at(r, c)) = w;
+        if (!diag || c >= r) {
+            *reinterpret_cast<u32x2*>(a.hi + gi) = h;
+            *reinterpret_cast<u32x2*>(a.lo + gi) = l;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (c + k < r) continue;
+                a.hi[gi + k] = (uint16_t)w[k];
+                a.lo[gi + k] = (uint16_t)(w[k] >> 16);
+            }
+        }
+    }
+    __syncthreads();
+    // Mirror: output row J0 + m, columns I0 + c .. c + 3 hold z(c .. c + 3, m).
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int m = rt + RPG * u;
+        if (diag && c >= m) continue;   // the mirror of a diagonal tile is its strict lower part
+        uint32_t v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = sW[at(c + k, m)];
+        const int64_t oi = (J0 + m) * np + I0 + c;
+        if (!diag || c + 3 < m) {
+            *reinterpret_cast<u32x2*>(a.hi + oi) = u32x2{(v[0] & 0xffffu) | (v[1] << 16),
+                                                         (v[2] & 0xffffu) | (v[3] << 16)};
+            *reinterpret_cast<u32x2*>(a.lo + oi) = u32x2{(v[0] >> 16) | (v[1] & 0xffff0000u),
+                                                         (v[2] >> 16) | (v[3] & 0xffff0000u)};
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (c + k >= m) continue;
+                a.hi[oi + k] = (uint16_t)v[k];
+                a.lo[oi + k] = (uint16_t)(v[k] >> 16);
+            }
+        }
+    }
+}
+
 // The tiles left after the whole rounds of the data-parallel launch (a partial round would
 // leave most CUs idle): tile tile0 + w / nsplit, K-blocks of segment w % nsplit, its FP32 partial
 // (row-major 128 x 128) to parts[w]; k_square_reduce adds the nsplit partials of each tile in
@@ -134,7 +249,6 @@ k_square_reduce(int64_t np, int tile0, int nsplit, const float* __restrict__ par
 }
 
 constexpr int kCT = 64;   // combine tile
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 __device__ inline void tile_of(int t, int T, int& I, int& J) {
     I = 0;
@@ -410,6 +524,18 @@ hipError_t launch_square_ring(const uint16_t* hi, const uint16_t* lo, int64_t np
     return hipGetLastError();
 }
 
+template <bool BF, class C>
+hipError_t launch_square_combine_t(const uint16_t* hi, const uint16_t* lo, const CombineArgs& a, int tx,
+                                   float* x_out, hipStream_t s) {
+    auto kern = k_square_combine<BF, C>;
+    static bool done = false;
+    hipError_t e = set_lds_once(kern, C::LDS_BYTES, done);
+    if (e != hipSuccess) return e;
+    const int T = (int)(a.np / C::BM);
+    hipLaunchKernelGGL(kern, dim3(T * (T + 1) / 2), dim3(C::NT), C::LDS_BYTES, s, hi, lo, a, tx, x_out);
+    return hipGetLastError();
+}
+
 template <bool BF>
 hipError_t launch_square_t(const uint16_t* hi, const uint16_t* lo, int64_t np, float* out,
                            int slots, float* parts, hipStream_t s) {
@@ -475,6 +601,20 @@ hipError_t launch_square(const uint16_t* hi, const uint16_t* lo, int64_t np, flo
     if (np % CfgQ::BM != 0) return hipErrorInvalidValue;
     return bf16 ? launch_square_t<true>(hi, lo, np, out, slots, parts, s)
                 : launch_square_t<false>(hi, lo, np, out, slots, parts, s);
+}
+
+hipError_t launch_square_combine(const uint16_t* hi, const uint16_t* lo, const CombineArgs& a, int tx,
+                                 float* x_out, int n_cu, hipStream_t s) {
+    if (a.np % CfgQ::BM != 0 || a.out || a.acc_first || a.nterm < 1 || a.nterm > kCombineMaxTerms ||
+        a.nacc < 0 || a.nacc > kCombineMaxAcc || hi == a.hi || lo == a.lo)
+        return hipErrorInvalidValue;
+    switch (split_ring_tile(a.np, n_cu)) {
+        case 64: return a.bf16 ? launch_square_combine_t<true, CfgQ64>(hi, lo, a, tx, x_out, s)
+                               : launch_square_combine_t<false, CfgQ64>(hi, lo, a, tx, x_out, s);
+        case 128: return a.bf16 ? launch_square_combine_t<true, CfgQ128>(hi, lo, a, tx, x_out, s)
+                                : launch_square_combine_t<false, CfgQ128>(hi, lo, a, tx, x_out, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_variant_eval(const VariantEvalArgs& a, hipStream_t s) {
