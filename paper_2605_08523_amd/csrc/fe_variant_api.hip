@@ -35,17 +35,6 @@ int64_t variant_bytes(int64_t np, const fe_qmodel* m, int slots) {
            (int64_t)slots * fe::kSquarePartTile * (int64_t)sizeof(float);
 }
 
-// Largest |operand| over the unit interval of the model coordinate (4097 points).
-double variant_range(const fe_qmodel* m) {
-    double zm = 0.0;
-    for (int i = 0; i <= 4096; ++i) {
-        double z = 0.0;
-        (void)qmodel_value(m->arch, m->L, m->k, m->K, m->coef, i / 4096.0, &z);
-        zm = fmax(zm, z);
-    }
-    return zm;
-}
-
 }  // namespace
 
 extern "C" {

@@ -23,8 +23,9 @@ using namespace split;
 using CfgQ = Cfg<128, 2, 2, 64, 128, 1>;
 // Sizes whose tiles all run at once (split_ring_tile): the operand ring of the MLSP2 layers, the same
 // products in the same order. us per Skip-SP2 expansion (22 squarings and their combines), 128 x 128
-// register-staged tiles / ring: n = 512 645 / 573, 1000 1021 / 595, 1728 1516 / 890, 2197 1863 / 1307,
-// 2744 2297 / 1828. With more tiles than compute units (n = 3375) two staged workgroups per CU stay.
+// register-staged tiles / ring / ring and the combine in one launch: n = 1000 1021 / 595 / 413, 1728
+// 1516 / 890 / 680, 2197 1863 / 1307 / 1154, 2744 2297 / 1828 / 1554. With more tiles than compute
+// units (n = 3375: 3525) two staged workgroups per CU stay.
 using CfgQ64 = Cfg<64, 2, 2, 64, 64, 2, 1>;
 using CfgQ128 = Cfg<128, 4, 2, 64, 128, 2, 1>;
 
@@ -69,8 +70,8 @@ k_square(const uint16_t* __restrict__ hi, const uint16_t* __restrict__ lo, int64
 // goes from the accumulators through LDS into the combine of a (term tx and acc_src are x), whose
 // operand z goes to hi_out/lo_out, another buffer than the one that the other tiles still read. x
 // itself is written to x_out unless NULL (no later layer reads it). The values are k_square's and
-// k_combine's. It saves a launch and x's way through memory: us per Skip-SP2 expansion, two kernels /
-// one: n = 1728 890 / 717, 2197 1307 / 1195, 2744 1828 / 1591; Max-SP2 1728 1021 / 864, 2744 2409 / 2164.
+// k_combine's. It saves a launch and x's way through memory; us per Max-SP2 expansion, two launches / one:
+// n = 1728 1021 / 831, 2744 2409 / 2139 (Skip-SP2 above).
 template <bool BF, class C>
 __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_square_combine(const uint16_t* __restrict__ hi, const uint16_t* __restrict__ lo, CombineArgs a, int tx,
