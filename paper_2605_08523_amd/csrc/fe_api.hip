@@ -148,7 +148,7 @@ int run_expansion(const double* H, int64_t n, int64_t ldh, double mu, double kT,
                   int prec, double alpha, int entropy, void* D, int d_is_fp64, int64_t ldd,
                   double* trD, double* trD2, double* S, fe_rescale_info* info, fe_workspace* ws,
                   hipStream_t s, int which, bool noalloc = false,
-                  bool final_correction = false) {
+                  bool final_correction = false, bool bounds_known = false) {
     int rc = check_common(H, n, ldh, mu, kT, ws);
     if (rc) return rc;
     rc = check_model(m, entropy ? "entropy model" : "model");
@@ -192,7 +192,8 @@ int run_expansion(const double* H, int64_t n, int64_t ldh, double mu, double kT,
         if (info) return read_info(ws, which, s, info);
         return FE_OK;
     }
-    FE_HIP(fe::launch_bounds_params(H, n, ldh, mu, kT, m->beta0, m->mu0, bp, P, ctl, s));
+    FE_HIP(fe::launch_bounds_params(bounds_known ? nullptr : H, n, ldh, mu, kT, m->beta0, m->mu0, bp, P,
+                                    ctl, s));
 
     int npart = 1;
     if (split) {
@@ -499,6 +500,7 @@ int fe_expand_density_filling(const double* H, int64_t n, int64_t ldh, double n_
     double mu = isfinite(mu_init) ? mu_init : 0.5 * (lo + hi);
     if (!(mu > lo && mu < hi)) return fail(FE_ERR_DOMAIN, "mu_init lies outside the Gershgorin bounds of H");
 
+    // The bracket's bounds are those of every iterate (the same H, and slot 0's partials).
     // Newton on Tr D(mu) = n_occ with d Tr D / d mu = (Tr D - sum D_ij^2) / kT (Sec. IV.3), kept
     // inside the shrinking bracket: a step that leaves it, or a vanishing derivative (mu in a
     // gap at low temperature), is replaced by bisection.
@@ -507,7 +509,7 @@ int fe_expand_density_filling(const double* H, int64_t n, int64_t ldh, double n_
     bool converged = false;
     for (int it = 1; it <= max_iter; ++it) {
         rc = run_expansion(H, n, ldh, mu, kT, m, prec, 1.0, 0, D, d_is_fp64, ldd, ws->newton,
-                           ws->newton + 1, nullptr, &inf, ws, s, 0);
+                           ws->newton + 1, nullptr, &inf, ws, s, 0, false, false, true);
         if (rc < 0) return rc;
         FE_HIP(hipMemcpy(t, ws->newton, sizeof(t), hipMemcpyDeviceToHost));
         *mu_out = mu;

@@ -42,7 +42,7 @@ constexpr int kMaxTiles = 1 << 16;
 // ---- launchers (one per translation unit; all asynchronous on `s`) ------------------------
 
 // Gershgorin bounds and the rescale parameters of Sec. IV.1 into *P; ctl (or NULL): the control
-// words of a resident launch that follows, set to zero.
+// words of a resident launch that follows, set to zero. H NULL: partials already hold the bounds.
 hipError_t launch_bounds_params(const double* H, int64_t n, int64_t ldh, double mu, double kT,
                                 double beta0, double mu0, BoundsPartial* partials, Params* P,
                                 int32_t* ctl, hipStream_t s);

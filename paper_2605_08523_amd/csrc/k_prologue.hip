@@ -272,8 +272,9 @@ hipError_t launch_bounds_params(const double* H, int64_t n, int64_t ldh, double 
                                 int32_t* ctl, hipStream_t s) {
     int64_t blocks = (n + 3) / 4;
     if (blocks > kMaxBoundsBlocks) blocks = kMaxBoundsBlocks;
-    hipLaunchKernelGGL(k_gershgorin, dim3((unsigned)blocks), dim3(kBoundsThreads), 0, s, H, n, ldh,
-                       partials);
+    if (H)
+        hipLaunchKernelGGL(k_gershgorin, dim3((unsigned)blocks), dim3(kBoundsThreads), 0, s, H, n, ldh,
+                           partials);
     hipLaunchKernelGGL(k_params, dim3(1), dim3(256), 0, s, partials, (int)blocks, mu, kT, beta0,
                        mu0, P, ctl);
     return hipGetLastError();
