@@ -46,15 +46,24 @@ using CfgSK2x2 = Cfg<128, 2, 2, 64, 128, 1>;    // ... for operands beyond the I
 // Three-part BF16 split: six panels of 32-deep K-blocks in one LDS stage (61 KiB), so two
 // workgroups still fit per CU; data-parallel only.
 using CfgDP3 = Cfg<128, 2, 2, 32, 128, 1, 0, 3>;
-// One-round layers (k_layer_ring): 64 x 64 tiles of four 32 x 32 waves, two workgroups per CU, and
-// 128 x 128 tiles of eight 32 x 64 waves, one workgroup per CU. 64-deep K-blocks: a panel row is one
-// 128-byte line (32-deep blocks fetch every line twice: 4-8% slower); the three-part split's six
-// panels take 32-deep ones.
+// One-round layers (k_layer_ring): 64 x 64 tiles of four 32 x 32 waves, two workgroups per CU, or one
+// per CU with a deeper ring (lone tiles); 128 x 128 tiles of eight 32 x 64 waves, one workgroup per CU.
+// 64-deep K-blocks: a panel row is one 128-byte line (32-deep blocks fetch every line twice: 4-8%
+// slower); two workgroups of the three-part split's six panels only have room for 32-deep ones.
+// Lone tiles wait for their loads with nothing beside them: us per density matrix (26 layers) with two
+// stages / three, n = 449 267 / 249, 700 340 / 299, 1001 420 / 356, 1408 565 / 468 (four: 245, 311, 350,
+// 478); three parts, 32-deep / 64-deep blocks, 700 373 / 362, 1001 484 / 414, 1400 743 / 627.
 using CfgR64 = Cfg<64, 2, 2, 64, 64, 2, 1>;
-using CfgR128 = Cfg<128, 4, 2, 64, 128, 2, 1>;
 using CfgR64x3 = Cfg<64, 2, 2, 32, 64, 3, 1, 3>;
+using CfgL64 = Cfg<64, 2, 2, 64, 64, 3, 1>;
+using CfgL64x3 = Cfg<64, 2, 2, 64, 64, 3, 1, 3>;
+using CfgR128 = Cfg<128, 4, 2, 64, 128, 2, 1>;
 using CfgR128x3 = Cfg<128, 4, 2, 32, 128, 3, 1, 3>;
 static_assert(2 * CfgR64::LDS_BYTES <= 160 * 1024 && 2 * CfgR64x3::LDS_BYTES <= 160 * 1024, "two per CU");
+// All layers in one launch (k_layer_resident): two stages hold the few blocks of a panel (n = 256 157 us
+// with two, 174 with three; three parts 188 against 195 with three 32-deep ones, n = 448 272 / 308).
+using CfgS64 = CfgR64;
+using CfgS64x3 = Cfg<64, 2, 2, 64, 64, 2, 1, 3>;
 
 template <bool BF, class C>
 __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -338,10 +347,10 @@ hipError_t launch_sk(const LayerArgs& a, const SplitPlan& sk, hipStream_t s) {
 
 // Where the line lies (ms per density matrix, 26 layers, random dense; 256 CUs): two 64 x 64 tiles
 // fit a CU, so up to 512 of them run at once (n <= 1984): n = 1001 0.48 against 1.15 with 128 x 128
-// register-staged tiles, 1984 1.07 against 1.83 (stream-K) and 1.28 (128 x 128 ring); 528 tiles at
-// n = 2048 need a second round for 16 of them: 1.58 against 1.29 for the 128 x 128 ring, which takes
-// one round up to n = 2816 (2.13 against 2.62 for stream-K); at n = 2900 its second round makes
-// it 3.61 against 2.94.
+// register-staged tiles (0.36 since), 1984 1.07 against 1.83 (stream-K) and 1.28 (128 x 128 ring; 0.93
+// since); 528 tiles at n = 2048 need a second round for 16 of them: 1.58 against 1.29 for the 128 x 128
+// ring (1.09 since), which takes one round up to n = 2816 (2.13 against 2.62 for stream-K, 1.89 since); at
+// n = 2900 its second round makes it 3.61 against 2.94 (stream-K on the ring: 2.63).
 int split_ring_tile(int64_t n, int n_cu) {
     auto tiles = [n](int64_t bm) {
         const int64_t T = (n + bm - 1) / bm;
@@ -400,14 +409,19 @@ hipError_t launch_layers_resident(const LayerArgs& a, int bf16, const ResidentSp
     if (a.np % CfgR64::BM != 0 || R.L < 1 || R.L > kResMaxL || !R.ctl || a.affine)
         return hipErrorInvalidValue;
     R.ntiles = T_ * (T_ + 1) / 2;
-    return bf16 == 2 ? launch_resident<true, CfgR64x3>(a, T, R, s)
-           : bf16    ? launch_resident<true, CfgR64>(a, T, R, s)
-                     : launch_resident<false, CfgR64>(a, T, R, s);
+    return bf16 == 2 ? launch_resident<true, CfgS64x3>(a, T, R, s)
+           : bf16    ? launch_resident<true, CfgS64>(a, T, R, s)
+                     : launch_resident<false, CfgS64>(a, T, R, s);
 }
 
 hipError_t launch_layer_split(const LayerArgs& a, int bf16, const SplitPlan& plan, hipStream_t s) {
     if (plan.streamk == 0 && plan.ring_tile != 0) {
         if (a.np % plan.ring_tile != 0) return hipErrorInvalidValue;
+        const int64_t T = a.np / plan.ring_tile;
+        if (plan.ring_tile == CfgL64::BM && T * (T + 1) / 2 <= plan.grid)   // at most one per CU
+            return bf16 == 2 ? launch_ring<true, CfgL64x3>(a, s)
+                   : bf16    ? launch_ring<true, CfgL64>(a, s)
+                             : launch_ring<false, CfgL64>(a, s);
         if (plan.ring_tile == CfgR64::BM)
             return bf16 == 2 ? launch_ring<true, CfgR64x3>(a, s)
                    : bf16    ? launch_ring<true, CfgR64>(a, s)

@@ -23,10 +23,11 @@ using namespace split;
 using CfgQ = Cfg<128, 2, 2, 64, 128, 1>;
 // Sizes whose tiles all run at once (split_ring_tile): the operand ring of the MLSP2 layers, the same
 // products in the same order. us per Skip-SP2 expansion (22 squarings and their combines), 128 x 128
-// register-staged tiles / ring / ring and the combine in one launch: n = 1000 1021 / 595 / 413, 1728
+// register-staged tiles / ring / ring and the combine in one launch: n = 1000 1021 / 595 / 364, 1728
 // 1516 / 890 / 680, 2197 1863 / 1307 / 1154, 2744 2297 / 1828 / 1554. With more tiles than compute
 // units (n = 3375: 3525) two staged workgroups per CU stay.
 using CfgQ64 = Cfg<64, 2, 2, 64, 64, 2, 1>;
+using CfgQ64L = Cfg<64, 2, 2, 64, 64, 3, 1>;   // at most one workgroup per CU: a deeper ring
 using CfgQ128 = Cfg<128, 4, 2, 64, 128, 2, 1>;
 
 template <bool BF, class C>
@@ -513,6 +514,11 @@ hipError_t set_lds_once(Kern kern, size_t bytes, bool& done) {
     return e;
 }
 
+bool lone_tiles(int64_t np, int n_cu) {
+    const int64_t T = np / CfgQ64::BM;
+    return T * (T + 1) / 2 <= n_cu;
+}
+
 template <bool BF, class C>
 hipError_t launch_square_ring(const uint16_t* hi, const uint16_t* lo, int64_t np, float* out,
                               hipStream_t s) {
@@ -541,7 +547,9 @@ template <bool BF>
 hipError_t launch_square_t(const uint16_t* hi, const uint16_t* lo, int64_t np, float* out,
                            int slots, float* parts, hipStream_t s) {
     switch (split_ring_tile(np, slots / 2)) {
-        case 64: return launch_square_ring<BF, CfgQ64>(hi, lo, np, out, s);
+        case 64:
+            return lone_tiles(np, slots / 2) ? launch_square_ring<BF, CfgQ64L>(hi, lo, np, out, s)
+                                             : launch_square_ring<BF, CfgQ64>(hi, lo, np, out, s);
         case 128: return launch_square_ring<BF, CfgQ128>(hi, lo, np, out, s);
     }
     using C = CfgQ;
@@ -610,8 +618,12 @@ hipError_t launch_square_combine(const uint16_t* hi, const uint16_t* lo, const C
         a.nacc < 0 || a.nacc > kCombineMaxAcc || hi == a.hi || lo == a.lo)
         return hipErrorInvalidValue;
     switch (split_ring_tile(a.np, n_cu)) {
-        case 64: return a.bf16 ? launch_square_combine_t<true, CfgQ64>(hi, lo, a, tx, x_out, s)
-                               : launch_square_combine_t<false, CfgQ64>(hi, lo, a, tx, x_out, s);
+        case 64:
+            if (lone_tiles(a.np, n_cu))
+                return a.bf16 ? launch_square_combine_t<true, CfgQ64L>(hi, lo, a, tx, x_out, s)
+                              : launch_square_combine_t<false, CfgQ64L>(hi, lo, a, tx, x_out, s);
+            return a.bf16 ? launch_square_combine_t<true, CfgQ64>(hi, lo, a, tx, x_out, s)
+                          : launch_square_combine_t<false, CfgQ64>(hi, lo, a, tx, x_out, s);
         case 128: return a.bf16 ? launch_square_combine_t<true, CfgQ128>(hi, lo, a, tx, x_out, s)
                                 : launch_square_combine_t<false, CfgQ128>(hi, lo, a, tx, x_out, s);
     }
