@@ -14,7 +14,7 @@
 // one SIMD. In FP32 the MFMA adds its products one by one in ascending k (measured: 16x16x4 and
 // 32x32x2 chains and a scalar fmaf chain agree bitwise), so the block shape does not change a bit.
 // Measured (us per layer; before: 64 x 64 tiles of four 32 x 32 waves, one LDS buffer): FP32 n = 256
-// 6.0 (16.7), 1500 43 (81; the MFMA rate alone 23), FP64 n = 256 7.1 (25), 1000 31 (78; 14).
+// 5.3 (16.7), 1500 37 (81; the MFMA rate alone 23), FP64 n = 256 6.6 (25), 1000 29 (78; 14).
 #include <type_traits>
 
 #include "fe_internal.h"
@@ -124,9 +124,9 @@ __device__ __attribute__((always_inline)) inline void wide_products(
 #pragma unroll
     for (int p = 0; p < 2 * NPR; ++p)
         rs[p] = split::make_rsrc(p & 1 ? Rp[p >> 1] : Lp[p >> 1], (uint32_t)(BM * row_bytes));
-    auto issue = [&](int kb, int stage) {
+    auto issue = [&](int kb, int stage, int q0, int q1) {
 #pragma unroll
-        for (int q = 0; q < W::IPW; ++q) {
+        for (int q = q0; q < q1; ++q) {
             const int panel = q / W::IPP, blk = wave + 4 * (q % W::IPP);
             unsigned char* l = smem + stage * W::STAGE + panel * W::PANEL + blk * 1024;
             const uint32_t soff = (uint32_t)(blk * 8 * row_bytes) + (uint32_t)kb * 128;
@@ -148,6 +148,8 @@ __device__ __attribute__((always_inline)) inline void wide_products(
     };
     const int fr = lane & 15, fk = lane >> 4;
     constexpr int KS = BK / 4;
+    static_assert(W::IPW <= KS, "a load of the next stage behind each K step");
+    constexpr bool kAhead = AUX != 0;   // few blocks (a resident launch): all reads at once
     typedef __attribute__((address_space(3))) const unsigned char lds_char;
     lds_char* const lds0 = (lds_char*)smem;
     uint32_t oa[KS], ob[KS];   // byte offsets of element (row fr, k = 4 s + fk) of this wave's blocks
@@ -163,35 +165,34 @@ __device__ __attribute__((always_inline)) inline void wide_products(
     struct Frag {
         T a[NPR][KS][NB], b[NPR][KS][NB];
     };
-    auto read = [&](int stage, Frag& f) {
+    auto read = [&](int stage, int s, Frag& f) {
 #pragma unroll
         for (int p = 0; p < NPR; ++p)
 #pragma unroll
-            for (int s = 0; s < KS; ++s)
-#pragma unroll
-                for (int x = 0; x < NB; ++x) {
-                    typedef __attribute__((address_space(3))) const T lds_T;
-                    const int o = stage * W::STAGE + p * 2 * W::PANEL + x * 2048;
-                    f.a[p][s][x] = *(lds_T*)(lds0 + oa[s] + o);
-                    f.b[p][s][x] = *(lds_T*)(lds0 + ob[s] + o);
-                }
+            for (int x = 0; x < NB; ++x) {
+                typedef __attribute__((address_space(3))) const T lds_T;
+                const int o = stage * W::STAGE + p * 2 * W::PANEL + x * 2048;
+                f.a[p][s][x] = *(lds_T*)(lds0 + oa[s] + o);
+                f.b[p][s][x] = *(lds_T*)(lds0 + ob[s] + o);
+            }
     };
-    auto multiply = [&](const Frag& f) {
+    auto multiply = [&](int s, const Frag& f) {
 #pragma unroll
-        for (int s = 0; s < KS; ++s)
+        for (int p = 0; p < NPR; ++p)
 #pragma unroll
-            for (int p = 0; p < NPR; ++p)
+            for (int x = 0; x < NB; ++x)
 #pragma unroll
-                for (int x = 0; x < NB; ++x)
-#pragma unroll
-                    for (int y = 0; y < NB; ++y)
-                        acc[p][x][y] = M::mma(f.a[p][s][x], f.b[p][s][y], acc[p][x][y]);
+                for (int y = 0; y < NB; ++y)
+                    acc[p][x][y] = M::mma(f.a[p][s][x], f.b[p][s][y], acc[p][x][y]);
     };
     // Block i in stage u. First waits until this wave's loads of block i + 1 have landed (those of the
     // S - 2 blocks after it may be in flight) and its fragment reads of block i are done, and joins
-    // the other waves: block i + 1 is whole and block i's stage is free. Then the next block's
-    // fragments are read and the free stage is refilled while this block is multiplied, so that a wave
-    // alone on its SIMD keeps the MFMA pipe busy. full: the blocks up to i + S exist (no conditions).
+    // the other waves: block i + 1 is whole and block i's stage is free. Then the block's products,
+    // each K step's followed by the next block's fragment reads of that step and a load into the free
+    // stage: the wave issues them while its MFMAs run. (us per density matrix, all of them ahead of the
+    // products / spread: FP32 n = 512 210 / 189, 1000 545 / 491, 1500 1106 / 965, 2000 2168 / 2050;
+    // FP64 512 301 / 277, 700 377 / 343, 1000 815 / 777, 1500 1861 / 1762.) full: the blocks up to
+    // i + S exist (no conditions).
     auto step = [&](auto wk, auto full, int i, int u, const Frag& cur, Frag& nxt) {
         if (full || i + 1 < nk) {
             if (full || i + S - 1 < nk) __builtin_amdgcn_s_waitcnt(0x0070 | (W::IPW * (S - 2)));
@@ -199,18 +200,34 @@ __device__ __attribute__((always_inline)) inline void wide_products(
             asm volatile("" ::: "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
-            if (full || i + S < nk) issue(i + S, u);
-            if constexpr (wk) read((u + 1) % S, nxt);
+            if constexpr (kAhead) {
+                if (full || i + S < nk) issue(i + S, u, 0, W::IPW);
+                if constexpr (wk)
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) read((u + 1) % S, s, nxt);
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (wk) multiply(cur);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            if constexpr (wk) multiply(s, cur);
+            if constexpr (!kAhead) {
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (wk)
+                    if (full || i + 1 < nk) read((u + 1) % S, s, nxt);
+                if (s < W::IPW && (full || i + S < nk)) issue(i + S, u, s, s + 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
     auto loop = [&](auto wk) {
         constexpr std::true_type yes{};
         constexpr std::false_type no{};
         Frag f0, f1;
-        if constexpr (wk) read(0, f0);
+        if constexpr (wk)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) read(0, s, f0);
         int i = 0;
         for (; i + 2 * S - 1 < nk; i += S) {
             step(wk, yes, i, 0, f0, f1);
@@ -227,7 +244,7 @@ __device__ __attribute__((always_inline)) inline void wide_products(
     };
 #pragma unroll
     for (int b = 0; b < S; ++b)
-        if (b < nk) issue(b, b);
+        if (b < nk) issue(b, b, 0, W::IPW);
     static_assert(S == 4 && W::IPW * (S - 1) < 16, "four stages unrolled, four-bit wait count");
     if (S - 1 < nk) __builtin_amdgcn_s_waitcnt(0x0070 | (W::IPW * (S - 1)));
     else __builtin_amdgcn_s_waitcnt(0x0070);
