@@ -903,7 +903,7 @@ def bench_variants(args, torch, api, models, workloads, dev):
 def bench_small(args, torch, api, models, workloads, dev):
     """The small FP64 configuration: N = 128 dense random (seed 0), kT = 0.1, mu for half filling
     (Tr D = 64, found by the library's Newton iteration in FP64), the 30-layer beta0 = 1500,
-    mu0 = 1/3 model, FP64 products in one workgroup's LDS (`k_small_f64`). One solve per step
+    mu0 = 1/3 model, FP64 products, all layers in one launch (`k_wide_resident`). One solve per step
     (launch-latency bound: one CU of 256 works); density and entropy timed."""
     import numpy as np
     m = models.load("mlsp2_L30_b1500_mu1third")
@@ -931,11 +931,11 @@ def bench_small(args, torch, api, models, workloads, dev):
                       "layers": m.L, "coefficients": m.name, "mu": mu, "newton_iterations": iters,
                       "beta_p": info["beta_p"]},
            "tflops_algorithmic": flop / (ms * 1e-3) / 1e12,
-           "roofline": {"kernel": "k_small_f64 (whole recursion in one workgroup's LDS)",
+           "roofline": {"kernel": "k_wide_resident<double> (all layers in one launch on one XCD)",
                         "bound": "latency", "achieved": flop / (ms * 1e-3) / 1e12,
                         "peak": PEAK_TFLOPS["fp64"], "unit": "TFLOP/s",
                         "frac": flop / (ms * 1e-3) / 1e12 / PEAK_TFLOPS["fp64"],
-                        "note": "one workgroup on one of the 256 CUs; the step is the launch "
+                        "note": "ten workgroups on one of the eight XCDs; the step is the launch "
                                 "sequence of bounds, rescale, recursion and reduction"},
            "entropy_ms": ms_s, "trD": float(trD)}
     D_g = D.cpu().numpy()

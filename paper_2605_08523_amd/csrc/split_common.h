@@ -147,7 +147,7 @@ __device__ inline int xcd_tile(int b, int ntiles) {
 
 // Compile-time shape of one kernel configuration. DMA = 1: operands go from global memory straight
 // to LDS (no register staging), in unpadded rows whose 16-byte chunks are XOR-swizzled.
-// NS = 3: three-part BF16 split (three operand arrays per panel), register-staged loop only.
+// NS = 3: three-part BF16 split (three operand arrays per panel).
 template <int BM_, int WM_, int WN_, int BK_, int EC_, int STAGES_, int DMA_ = 0, int NS_ = 2>
 struct Cfg {
     static constexpr int BM = BM_, WM = WM_, WN = WN_, BK = BK_, EC = EC_, STAGES = STAGES_;
@@ -614,11 +614,7 @@ template <class C>
 __device__ inline void kloop3(const uint16_t* __restrict__ hin, const uint16_t* __restrict__ min,
                               const uint16_t* __restrict__ lin, int64_t np, int64_t I0, int64_t J0,
                               int kb0, int kb1, Acc<C>& acc, uint16_t* smem) {
-    static_assert(C::NS == 3, "three-part split");
-    if constexpr (C::DMA) {
-        kloop_dma<true, C>(hin, min, lin, np, I0, J0, kb0, kb1, acc, smem);
-        return;
-    }
+    static_assert(C::NS == 3 && !C::DMA, "three-part split, register-staged");
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = tid >> 6;
@@ -807,7 +803,7 @@ struct EpiPre {
 // The epilogue of a tile in the direct layer form, all layers but the last: the same values as epi_chunk
 // in a third of its instructions, which a workgroup alone on its CU waits for one by one (us per
 // density matrix with a launch per layer, 26 layers, against epi_chunk: n = 128 159 / 213,
-// 256 189 / 246, 1001 427 / 469).
+// 256 189 / 246, 1001 427 / 469; on 128 x 128 tiles 2048 1099 / 1145).
 // Addresses are one lane offset plus scalars; the parts split once travel through LDS, in the place of
 // the product they came from, for the mirror tile; 1/s is folded into a (a power of two); a diagonal
 // tile writes both triangles of X, A and the operands itself, its lower elements from the transposed

@@ -86,3 +86,22 @@ def test_giveup_is_reported(api, paper_model, n, prec):
     D, _, _, info = api.expand_density(H, 0.1, 0.1, paper_model, prec=prec, ws=ws, want_info=True)
     assert info["rc"] == 0 and torch.equal(D, good)
     ws.close()
+
+
+@pytest.mark.parametrize("n,prec", [(50, "fp64"), (70, "fp32"), (150, "fp64"), (300, "fp16x2"), (600, "bf16x2")])
+def test_captured_replays_equal_the_eager_call(api, paper_model, n, prec):
+    print(f"case capture n={n} {prec}", flush=True)
+    H = torch.from_numpy(W.random_dense(n, 17)).cuda()
+    out = torch.float64 if prec == "fp64" else torch.float32
+    want, tr, tr2, _ = api.expand_density_noalloc(H, 0.05, 0.1, paper_model, prec=prec, out_dtype=out)
+    want, tr = want.clone(), tr.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        D, trc, _, _ = api.expand_density_noalloc(H, 0.05, 0.1, paper_model, prec=prec, out_dtype=out)
+    for _ in range(4):
+        D.zero_()
+        other = api.expand_density(H, 0.0, 0.1, paper_model, prec=prec, ws=api.workspace(n))[0]
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(D, want) and trc.item() == tr.item() and not torch.equal(other, want)
