@@ -216,20 +216,23 @@ __device__ inline void zero(Acc<C>& acc) {
 // Direct-to-LDS form of the K loop (C::DMA): each lane's buffer_load_dwordx4 ... lds moves one 16-byte
 // chunk, and the 64 chunks of one instruction land in 1 KiB of LDS in lane order. A stage holds the
 // 2 NS BM x BK operand panels (A parts, then B parts) in unpadded rows; chunk c of row r sits at
-// position c ^ ((r / RP) % CPR) of its row (RP rows per 128 bytes), so the eight rows that a
-// quarter-wave's fragment read touches fall on distinct banks. The stages form a ring: while block
-// kb is multiplied, the next STAGES - 1 blocks are in flight, so a short K loop whose operands come
-// from beyond the L2 (another XCD wrote them) pays that latency once and not per block. A wave alone
-// on its SIMD pays for every instruction between its MFMAs, so the loop has few: the loads' addresses
-// are one lane offset plus a scalar, the fragments' a fixed register plus a constant (the stages are
-// unrolled), and each step's fragments are read during the step before, across the block boundary
-// too. The barrier there is a bare s_barrier after an explicit wait for this wave's own loads of the
-// next block (a full __syncthreads would also drain everything else in flight) and its fragment
-// reads of the current one, whose stage is refilled after it. AUX: cache policy of the operand
-// loads. SEG > 0: the blocks are summed in segments of SEG, each from zero, and the segments' sums
-// added (a long K loop then rounds like the stream-K schedules' partial sums, not like one chain).
-// Blocks, K steps and products are taken in the order of the register-staged loops, so an element's
-// sum (SEG = 0) does not depend on the form. Ends with a barrier.
+// position c ^ ((r / RP) % CPR) of its row (RP rows per 256 bytes, the width of the 64 banks), so the
+// sixteen rows that a quarter-wave's fragment read touches fall on distinct banks. (RP rows per 128
+// bytes: n = 1700, two 64 x 64 workgroups per CU, 789 us per density matrix instead of 760, 5500 12.95
+// ms instead of 12.85. Launches that hand over inside an XCD, AUX != 0, keep that: their few blocks
+// are not bound by the reads, and the offsets cost 2 of the 157 us of n = 256.) The stages form a
+// ring: while block kb is multiplied, the next STAGES - 1 blocks are in flight, so a short K loop
+// whose operands come from beyond the L2 (another XCD wrote them) pays that latency once and not per
+// block. A wave alone on its SIMD pays for every instruction between its MFMAs, so the loop has few:
+// the loads' addresses are one lane offset plus a scalar, the fragments' a fixed register plus a
+// constant (the stages are unrolled), and each step's fragments are read during the step before,
+// across the block boundary too. The barrier there is a bare s_barrier after an explicit wait for this
+// wave's own loads of the next block (a full __syncthreads would also drain everything else in flight)
+// and its fragment reads of the current one, whose stage is refilled after it. AUX: cache policy of
+// the operand loads. SEG > 0: the blocks are summed in segments of SEG, each from zero, and the
+// segments' sums added (a long K loop then rounds like the stream-K schedules' partial sums, not like
+// one chain). Blocks, K steps and products are taken in the order of the register-staged loops, so an
+// element's sum (SEG = 0) does not depend on the form. Ends with a barrier.
 template <bool BF, class C, int SEG = 0, int AUX = 0>
 __device__ __attribute__((always_inline)) inline void kloop_dma(
     const uint16_t* __restrict__ hin, const uint16_t* __restrict__ min,
@@ -239,12 +242,12 @@ __device__ __attribute__((always_inline)) inline void kloop_dma(
     typedef __attribute__((address_space(3))) const unsigned char lds_char;
     typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
     constexpr int NS = C::NS, S = C::STAGES;
-    constexpr int CPR = C::BK / 8, RP = 8 / CPR, RPI = 64 / CPR;
+    constexpr int CPR = C::BK / 8, RP = (AUX ? 8 : 16) / CPR, RPI = 64 / CPR;
     constexpr int IPA = C::BM / RPI;                          // 1-KiB loads per panel and stage
     constexpr int NW = C::NT / 64, IPW = 2 * NS * IPA / NW;   // loads per wave and stage
     constexpr int ROW = 2 * C::BK, PANEL = C::BM * ROW, STAGE = 2 * NS * PANEL;   // bytes
     static_assert(IPA % NW == 0, "a wave's load q is in panel NW q / IPA");
-    static_assert((RPI / RP) % CPR == 0 && 32 / RP % CPR == 0, "chunk positions depend on the lane only");
+    static_assert(NW * RPI / RP % CPR == 0 && 32 / RP % CPR == 0, "chunk positions depend on wave and lane only");
     static_assert(IPW * (S - 1) < 64, "in-flight loads fit the wait counter");
     static_assert(SEG % S == 0, "segments are whole turns of the ring");
     int tid = threadIdx.x;
@@ -254,7 +257,7 @@ __device__ __attribute__((always_inline)) inline void kloop_dma(
     const int wm = wave / C::WN, wn = wave % C::WN;
     const uint32_t row_bytes = (uint32_t)(2 * np);
     const uint32_t lane_off =
-        (lane / CPR) * row_bytes + (((lane % CPR) ^ ((lane / CPR / RP) % CPR)) << 4);
+        (lane / CPR) * row_bytes + (((lane % CPR) ^ (((wave * RPI + lane / CPR) / RP) % CPR)) << 4);
     __amdgpu_buffer_rsrc_t rs[2 * NS];
 #pragma unroll
     for (int a = 0; a < 2 * NS; ++a) {
