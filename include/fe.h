@@ -379,7 +379,7 @@ int fe_matrix_backward(const float* hist, int64_t n, const double* theta, int32_
 
 /* Chooses the tile shape and schedule of the 16-bit layer kernel per matrix size on this device:
  * 0 = 128 x 128 tiles, one workgroup per upper tile; 1 = 256 x 256 tiles, stream-K over one
- * workgroup per CU; 2 = 128 x 128 tiles, stream-K over one or two workgroups per CU (1 and 2 need a
+ * workgroup per CU; 2 = 128 x 128 tiles, stream-K over two workgroups per CU (1 and 2 need a
  * workspace with max_n >= 1536). Each candidate runs a short expansion (1 warm-up + 3 timed, HIP
  * events on the stream) of a device-generated random symmetric matrix of each size; the fastest
  * is recorded process-wide for (device, prec, size). The timing model is a 6-layer SP2 recursion
@@ -497,7 +497,7 @@ double fe_layer_count(double beta_p);
  * layer GEMM), evaluated on the host by the same code the kernel runs; no device work.
  * np: padded size, a positive multiple of the schedule's tile (256 for schedule 1, 128 for 2).
  * schedule: 1 (256 x 256 tiles) or 2 (128 x 128 tiles). grid: the workgroups offered (the
- * library offers one per CU for schedule 1 and, below n = 8192, for schedule 2, else two). geom: host int32[6], receives
+ * library offers one per CU for schedule 1, two for schedule 2). geom: host int32[6], receives
  * T (tiles per side), ntiles, nk (K-blocks per tile), dp_tiles (leading tiles computed whole
  * before the stream-K launch), groups and the grid actually launched. w: a workgroup of that
  * grid (outside it: *count = 0). segs: host int32[5 * cap] or NULL, receives w's segments in run

@@ -24,11 +24,10 @@ constexpr int64_t kSmallN64 = 128;       // FP64 up to this size takes at most k
 // Schedule of the split-precision layer kernel (FE_SCHEDULE=dp|sk|sk2 overrides):
 //  0 data-parallel, one workgroup per upper tile (the tile by size: split_ring_tile);
 //  1 stream-K over 256 x 256 tiles, one workgroup per CU;
-//  2 stream-K over 128 x 128 tiles, one or two workgroups per CU (split_sk2_per_cu; whole-tile rounds
-//    first when there are two or more rounds).
+//  2 stream-K over 128 x 128 tiles, two workgroups per CU (whole-tile rounds first when there
+//    are two or more rounds).
 // Order: a schedule forced by the tuner, FE_SCHEDULE, the tuned table (fe_autotune), then the
-// default: 0 where all data-parallel tiles run at once (split_ring_tile), else by size
-// (split_schedule; both have the figures). Only workspaces sized for n >= kStreamKMinN carry the
+// default by size (split_schedule has the figures). Only workspaces sized for n >= kStreamKMinN carry the
 // stream-K buffers.
 // Schedules chosen by fe_autotune: (device, precision, size) -> schedule, process-wide. A
 // size uses the entry of the nearest tuned size within a factor sqrt(2).
@@ -89,7 +88,6 @@ int use_streamk(int64_t n, const fe_workspace* ws, int prec) {
     if (env && env[0] == 's') return strcmp(env, "sk2") == 0 ? 2 : 1;
     const int tuned = tuned_schedule(ws->device, prec, n);
     if (tuned >= 0) return tuned;
-    if (fe::split_ring_tile(n, ws->n_cu)) return 0;
     return fe::split_schedule(n, ws->n_cu);
 }
 
@@ -200,7 +198,9 @@ int run_expansion(const double* H, int64_t n, int64_t ldh, double mu, double kT,
         fe::SplitPlan plan{};
         plan.streamk = three ? 0 : use_streamk(n, ws, prec);   // three parts: data-parallel
         plan.ring_tile = plan.streamk ? 0 : fe::split_ring_tile(n, ws->n_cu);
-        plan.grid = plan.streamk == 2 ? fe::split_sk2_per_cu(n) * ws->n_cu : ws->n_cu;
+        plan.grid = plan.streamk == 2 ? 2 * ws->n_cu : ws->n_cu;
+        plan.n_cu = ws->n_cu;
+        plan.hand_over = g_sk_giveup.load() != 0;
         plan.partial = ws->sk_partial;
         plan.own = ws->sk_partial ? ws->sk_partial + (size_t)ws->n_cu * 256 * 256 : nullptr;
         plan.flags = ws->sk_flags;

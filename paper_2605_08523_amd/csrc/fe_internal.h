@@ -108,7 +108,9 @@ struct SplitPlan {
     int streamk;          // 0: one workgroup per upper tile; 1: persistent stream-K
     int ring_tile;        // streamk = 0: tile of the one-round kernel (split_ring_tile), or 0 for the
                           // 128 x 128 kernel of more rounds
-    int grid;             // stream-K workgroups (one per CU)
+    int grid;             // stream-K workgroups of the plan
+    int n_cu;             // compute units
+    int hand_over;        // stream-K: 1 to publish and wait also where a workgroup per tile would do
     int groups;           // stream-K groups (8: one per XCD), set by the launcher
     int dp_tiles;         // leading tiles computed whole (data-parallel rounds), set by the launcher
     float* partial;       // stream-K published partial tiles, grid x 256 x 256 floats
@@ -124,10 +126,8 @@ int split_tile_for(int streamk);
 // Tile of the data-parallel kernel whose workgroups all run at once at size n on n_cu compute
 // units: 64, 128, or 0 where the tiles need more than one round.
 int split_ring_tile(int64_t n, int n_cu);
-// Schedule (SplitPlan::streamk) of the two-part layers of larger sizes, and the workgroups per CU of
-// schedule 2.
+// Default schedule (SplitPlan::streamk) of the two-part layers.
 int split_schedule(int64_t n, int n_cu);
-int split_sk2_per_cu(int64_t n);
 // Whether its 64 x 64 tiles fit one XCD's compute units, one on each (launch_layers_resident).
 bool split_resident(int64_t n, int n_cu);
 // The stream-K plan the launcher uses for a padded size np, schedule 1 or 2, at most grid

@@ -239,7 +239,7 @@ __device__ __attribute__((always_inline)) inline void batch_tile(
     constexpr bool kPre = EpiPre<C>::PER <= 4;
     EpiPre<C> pre;
     if constexpr (kPre) pre.template load<AUX>(p, I, J);
-    kloop_dma<BF, C, 0, AUX>(p.hi_in, p.mid_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM,
+    kloop_dma<BF, C, AUX>(p.hi_in, p.mid_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM,
                              0, kend, acc, reinterpret_cast<uint16_t*>(smem));
     if (!p.last && !p.affine) {
         epilogue_mid<BF, C, AUX, kPre ? 4 : 2>(p, acc, sY, I, J, poisoned, kPre ? &pre : nullptr);

@@ -17,11 +17,12 @@
 //      data-parallel: one workgroup per upper tile: 64 x 64 or 128 x 128 tiles with direct-to-LDS
 //        operand loads where all tiles run at once (split_ring_tile), else 128 x 128 (four
 //        64 x 64 wave tiles, register-staged);
-//      stream-K over 128 x 128 tiles, persistent workgroups (one per CU on the one-round ring; beyond
-//        the Infinity Cache two, register-staged): the (tile, K-block) iterations left after the
-//        whole-tile rounds are split evenly. A workgroup that stops inside a tile publishes its
-//        FP32 partial; the workgroup that finishes the tile adds the earlier workgroups' partials
-//        in a fixed order in its epilogue (accumulators stay in registers);
+//      stream-K over 128 x 128 tiles, two persistent workgroups per CU: the (tile, K-block) iterations
+//        left after the whole-tile rounds are split evenly. A workgroup that stops inside a tile
+//        publishes its FP32 partial; the workgroup that finishes the tile adds the earlier
+//        workgroups' partials in a fixed order in its epilogue (accumulators stay in registers).
+//        Where all tiles run at once, a workgroup per tile on the direct-to-LDS ring sums the same
+//        segments instead (k_layer_ring_segments);
 //      stream-K over 256 x 256 tiles (eight 128 x 64 wave tiles, two LDS stages filled by
 //        direct global-to-LDS loads, fragment reads interleaved with the MFMAs), one
 //        workgroup per CU: the same; its K loop holds no prefetch registers, so the 128
@@ -35,14 +36,11 @@
 namespace fe {
 namespace {
 
-constexpr int64_t kInfinityCache = (int64_t)256 << 20;
-
 using namespace split;
 
 using CfgDP = Cfg<128, 2, 2, 64, 128, 1>;
 using CfgSK = Cfg<256, 2, 4, 32, 128, 2, 1>;   // direct-to-LDS operand staging
-using CfgSK2 = Cfg<128, 4, 2, 64, 128, 2, 1>;   // stream-K over 128 x 128 tiles, the one-round layers' ring
-using CfgSK2x2 = Cfg<128, 2, 2, 64, 128, 1>;    // ... for operands beyond the Infinity Cache (split_sk2_per_cu)
+using CfgSK2 = Cfg<128, 2, 2, 64, 128, 1>;   // stream-K over 128 x 128 tiles, two workgroups per CU
 // Three-part BF16 split: six panels of 32-deep K-blocks in one LDS stage (61 KiB), so two
 // workgroups still fit per CU; data-parallel only.
 using CfgDP3 = Cfg<128, 2, 2, 32, 128, 1, 0, 3>;
@@ -88,17 +86,29 @@ k_layer_dp(LayerArgs p) {
 // LDS through the ring of stages (kloop_dma), and (64 x 64 tiles) the epilogue's X and A groups
 // loaded before the K loop. Bound by latency rather than by the MFMA rate: at n = 1001 a layer takes
 // 18 us, of which 2.2 are the launch, 4.3 the epilogue and 9.5 the K loop (its 64 K steps of MFMAs
-// alone 4.5, its loads alone 4.8: the LDS port carries both). The 64 x 64 tiles take the same sums in
-// the same order as k_layer_dp. The two-part 128 x 128 ones, whose sizes (n > 1984) ran stream-K
-// before, sum K in segments of 512, as that schedule's partial tiles did at n = 2048: one chain of
-// 2048 gave 1.45 times its error against FP64.
+// alone 4.5, its loads alone 4.8: the LDS port carries both). An element is one chain over K, in the
+// order of k_layer_dp; the sizes that run stream-K sum its segments in k_layer_ring_segments (one chain
+// of 2048 gave 1.45 times their error against FP64).
 template <bool BF, class C, int AUX>
 __device__ __attribute__((always_inline)) inline void ring_products(const LayerArgs& p, int I, int J,
                                                                     int kb0, int kb1, Acc<C>& acc,
                                                                     unsigned char* smem) {
-    constexpr int kSeg = C::BM == 128 && C::NS == 2 ? 512 / C::BK : 0;
-    kloop_dma<BF, C, kSeg, AUX>(p.hi_in, p.mid_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM,
-                                kb0, kb1, acc, reinterpret_cast<uint16_t*>(smem));
+    kloop_dma<BF, C, AUX>(p.hi_in, p.mid_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM,
+                          kb0, kb1, acc, reinterpret_cast<uint16_t*>(smem));
+}
+
+template <bool BF, class C, int AUX>
+__device__ __attribute__((always_inline)) inline void ring_epilogue(const LayerArgs& p, const Acc<C>& acc,
+                                                                    int t, int I, int J,
+                                                                    unsigned char* smem, bool poisoned,
+                                                                    const EpiPre<C>& pre) {
+    constexpr bool kPre = EpiPre<C>::PER <= 4;
+    float* const sY = reinterpret_cast<float*>(smem);
+    if (!p.last && !p.affine) {
+        epilogue_mid<BF, C, AUX>(p, acc, sY, I, J, poisoned, kPre ? &pre : nullptr);
+        return;
+    }
+    epilogue<BF, C, kPre ? 8 : 2, kPre>(p, acc, sY, I, J, t, nullptr, 0, 0, poisoned, &pre);
 }
 
 template <bool BF, class C, int AUX>
@@ -106,19 +116,12 @@ __device__ __attribute__((always_inline)) inline void ring_tile(const LayerArgs&
                                                                 unsigned char* smem, bool poisoned) {
     int I, J;
     tile_coords(t, (int)(p.np / C::BM), I, J);
-    constexpr bool kPre = EpiPre<C>::PER <= 4;
     EpiPre<C> pre;
-    if constexpr (kPre) pre.template load<AUX>(p, I, J);
+    if constexpr (EpiPre<C>::PER <= 4) pre.template load<AUX>(p, I, J);
     Acc<C> acc;
     zero(acc);
     ring_products<BF, C, AUX>(p, I, J, 0, (int)(p.np / C::BK), acc, smem);
-    if (!p.last && !p.affine) {
-        epilogue_mid<BF, C, AUX>(p, acc, reinterpret_cast<float*>(smem), I, J, poisoned,
-                                 kPre ? &pre : nullptr);
-        return;
-    }
-    epilogue<BF, C, kPre ? 8 : 2, kPre>(p, acc, reinterpret_cast<float*>(smem), I, J, t, nullptr, 0,
-                                        0, poisoned, &pre);
+    ring_epilogue<BF, C, AUX>(p, acc, t, I, J, smem, poisoned, pre);
 }
 
 template <bool BF, class C>
@@ -126,6 +129,50 @@ __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2
 k_layer_ring(LayerArgs p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     ring_tile<BF, C, 0>(p, xcd_tile(blockIdx.x, gridDim.x), smem, false);
+}
+
+// A stream-K layer whose tiles all run at once (sk: the plan of launch_sk): a workgroup per tile sums the
+// segments that the plan's workgroups would have handed to each other, in the order of their epilogue
+// (the finisher's, the last one, first), so the values are the plan's and nothing is published or
+// waited for. us per density matrix (26 layers), stream-K / this: n = 2048 1815 / 1250, 2500 2367 / 1760,
+// 2816 2680 / 1940 (one chain per element: 1109, 1632, 1862, and 1.3 times the error).
+template <bool BF, class C>
+__global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_layer_ring_segments(LayerArgs p, SplitPlan sk) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int ntiles = gridDim.x, nk = (int)(p.np / C::BK), NG = sk.groups, GX = sk.grid / NG;
+    const int t = xcd_tile(blockIdx.x, ntiles);
+    int g = 0;
+    while (t >= (int)((int64_t)ntiles * (g + 1) / NG)) ++g;
+    const int tg0 = (int)((int64_t)ntiles * g / NG), tg1 = (int)((int64_t)ntiles * (g + 1) / NG);
+    const int64_t base = (int64_t)tg0 * nk, total = (int64_t)(tg1 - tg0) * nk;
+    const int64_t it0 = (int64_t)t * nk, it1 = it0 + nk;
+    int jf = (int)((it0 - base) * GX / total), jl = (int)((it1 - 1 - base) * GX / total);
+    while (sk_range_start(base, total, jf + 1, GX) <= it0) ++jf;
+    while (jf > 0 && sk_range_start(base, total, jf, GX) > it0) --jf;
+    while (sk_range_start(base, total, jl + 1, GX) < it1) ++jl;
+    while (jl > 0 && sk_range_start(base, total, jl, GX) >= it1) --jl;
+    int I, J;
+    tile_coords(t, (int)(p.np / C::BM), I, J);
+    EpiPre<C> pre;
+    if constexpr (EpiPre<C>::PER <= 4) pre.template load<0>(p, I, J);
+    Acc<C> sum;
+    for (int k = 0; k <= jl - jf; ++k) {
+        const int jj = k == 0 ? jl : jf + k - 1;
+        const int64_t a = sk_range_start(base, total, jj, GX), b = sk_range_start(base, total, jj + 1, GX);
+        Acc<C> acc;
+        zero(acc);
+        ring_products<BF, C, 0>(p, I, J, (int)((a > it0 ? a : it0) - it0), (int)((b < it1 ? b : it1) - it0),
+                                acc, smem);
+#pragma unroll
+        for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+                for (int j = 0; j < 16; ++j)
+                    sum.v[mb][nb][j] = k == 0 ? acc.v[mb][nb][j] : sum.v[mb][nb][j] + acc.v[mb][nb][j];
+    }
+    ring_epilogue<BF, C, 0>(p, sum, t, I, J, smem, false, pre);
 }
 
 // All layers of a small matrix in one launch (resident.h), by the same tile code. us per density matrix
@@ -223,11 +270,8 @@ k_layer_sk(LayerArgs p, SplitPlan sk) {
         const float* parts = sk.partial + (size_t)(g + NG * jlo) * TILE;
         Acc<C> acc;
         zero(acc);
-        if constexpr (C::DMA)
-            ring_products<BF, C, 0>(p, I, J, kb0, kb1, acc, smem);
-        else
-            kloop<BF, C>(p.hi_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM, kb0, kb1, acc,
-                         reinterpret_cast<uint16_t*>(smem));
+        kloop<BF, C>(p.hi_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM, kb0, kb1, acc,
+                     reinterpret_cast<uint16_t*>(smem));
         if (pass == 0) {
             // Publication: every wave waits until its device-coherent stores of the partial
             // have completed, then one flag store (device-coherent too) announces the tile.
@@ -241,13 +285,6 @@ k_layer_sk(LayerArgs p, SplitPlan sk) {
                                    __HIP_MEMORY_SCOPE_AGENT);
         } else if constexpr (kRegEpi) {
             const bool gave_up = wait_published(sk, g, NG, jlo, w);
-            if constexpr (C::BM == 128 && C::DMA) {
-                if (!p.last && !p.affine && (I != J || jlo == j)) {
-                    epilogue_mid<BF, C>(p, acc, sY, I, J, gave_up, nullptr, parts, (size_t)NG * TILE,
-                                        j - jlo);
-                    return;
-                }
-            }
             epilogue<BF, C, 1>(p, acc, sY, I, J, t, parts, (size_t)NG * TILE, j - jlo, gave_up);
         } else {
             store_tile<BF, C, false>(acc, own);
@@ -277,16 +314,6 @@ hipError_t launch_dp(const LayerArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(kern, dim3(T * (T + 1) / 2), dim3(C::NT), C::LDS_BYTES, s, a);
     return hipGetLastError();
 }
-
-// The kernel that runs tiles [0, dp_tiles) of a stream-K layer whole.
-template <bool BF, class C, bool DMA = C::DMA != 0>
-struct WholeTiles {
-    static constexpr auto kernel = k_layer_ring<BF, C>;
-};
-template <bool BF, class C>
-struct WholeTiles<BF, C, false> {
-    static constexpr auto kernel = k_layer_dp<BF, C>;
-};
 
 template <bool BF, class C>
 hipError_t launch_ring(const LayerArgs& a, hipStream_t s) {
@@ -328,9 +355,19 @@ hipError_t launch_sk(const LayerArgs& a, const SplitPlan& sk, hipStream_t s) {
     plan.groups = G.groups;
     plan.dp_tiles = G.dp_tiles;
     if (plan.grid < 1) return hipErrorInvalidValue;
+    if constexpr (C::BM == CfgR128::BM) {
+        if (!plan.hand_over && G.dp_tiles == 0 && G.ntiles <= plan.n_cu) {
+            auto rkern = k_layer_ring_segments<BF, CfgR128>;
+            static bool rdone = false;
+            e = set_lds(rkern, CfgR128::LDS_BYTES, rdone);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(rkern, dim3(G.ntiles), dim3(CfgR128::NT), CfgR128::LDS_BYTES, s, a, plan);
+            return hipGetLastError();
+        }
+    }
     if constexpr (reg_epi) {
         if (plan.dp_tiles > 0) {
-            auto dkern = WholeTiles<BF, C>::kernel;
+            auto dkern = k_layer_dp<BF, C>;
             static bool ddone = false;
             e = set_lds(dkern, C::LDS_BYTES, ddone);
             if (e != hipSuccess) return e;
@@ -345,12 +382,12 @@ hipError_t launch_sk(const LayerArgs& a, const SplitPlan& sk, hipStream_t s) {
 
 }  // namespace
 
-// Where the line lies (ms per density matrix, 26 layers, random dense; 256 CUs): two 64 x 64 tiles
-// fit a CU, so up to 512 of them run at once (n <= 1984): n = 1001 0.48 against 1.15 with 128 x 128
-// register-staged tiles (0.36 since), 1984 1.07 against 1.83 (stream-K) and 1.28 (128 x 128 ring; 0.93
-// since); 528 tiles at n = 2048 need a second round for 16 of them: 1.58 against 1.29 for the 128 x 128
-// ring (1.09 since), which takes one round up to n = 2816 (2.13 against 2.62 for stream-K, 1.89 since); at
-// n = 2900 its second round makes it 3.61 against 2.94 (stream-K on the ring: 2.63).
+// Where the lines lie (ms per density matrix, 26 layers, random dense; 256 CUs): two 64 x 64 tiles
+// fit a CU, so up to 512 of them run at once (n <= 1984; two parts take stream-K's segments from
+// n = 1921): n = 1001 0.48 against 1.15 with 128 x 128 register-staged tiles (0.36 since). At n = 2048,
+// 528 tiles need a second round for 16 of them: 1.58 against 1.29 for the 128 x 128 ring, which takes
+// one round up to n = 2816 (2.13 against 2.62 for stream-K); at n = 2900 its second round makes it
+// 3.61 against 2.94.
 int split_ring_tile(int64_t n, int n_cu) {
     auto tiles = [n](int64_t bm) {
         const int64_t T = (n + bm - 1) / bm;
@@ -366,31 +403,19 @@ bool split_resident(int64_t n, int n_cu) {
     return 8 * (T * (T + 1) / 2) <= n_cu;
 }
 
-int split_sk2_per_cu(int64_t n) {
-    static_assert(CfgSK2::BM == CfgSK2x2::BM && CfgSK2::BK == CfgSK2x2::BK, "one geometry");
-    return 4 * n * n >= kInfinityCache ? 2 : 1;
-}
-
-// ms per density matrix (26 layers): before (stream-K, 128 x 128 register-staged tiles, two workgroups
-// per CU) / 128 x 128 ring / 256 x 256, random dense and banded: n = 3000 4.4 / 3.9 / 5.7 (banded), 4096
-// 6.3 / 5.8 / 6.5 and 8.5 / 7.8 / 8.6, 4500 9.2 / 8.3 / 8.4 and 12.9 / 11.6 / 11.0, 5000 12.8 / 11.0 / 10.9
-// and 18.8 / 15.1 / 14.1, 5500 17.8 / 15.1 / 12.9 and 26.5 / 22.0 / 16.3, 6000 19.2 / 17.8 / 18.5 and
-// 24.7 / 24.5 / 25.0, 6500 25.3 / 22.1 / 21.6, 7000 29.1 / 28.4 / 27.0 and 36.4 / 38.1 / 34.9, 7600
-// 39.9 / 37.9 / 33.9: the 256 x 256 tiles pass half the operands through LDS, but need three quarters
-// of the CUs in their first round, and lose where they start a second one. From n = 8192 the
-// operands (4 n^2 bytes) no longer fit the 256 MiB Infinity Cache, and an XCD that works on 8 x 8
-// tiles at a time fetches fewer panels per tile than one with 8 x 4: banded 8192 57.3 / 58.5 / 60.7,
-// 10000 106 / 116 / 131. From eight whole rounds on the uneven last one costs less than the partial
-// tiles: stream-K / data-parallel 12000 150 / 146 and 201 / 182, 16384 463 / 441 (10000, six rounds:
-// 106 / 111).
+// Stream-K over 128 x 128 tiles when each of its workgroups (two per CU) gets at least eight K-blocks;
+// with fewer the partial-tile traffic outweighs the balance. From eight whole rounds on (n >= 11521) the
+// uneven last one costs less than the partial tiles: ms per density matrix, stream-K / data-parallel,
+// dense 12000 150 / 146, banded 12000 201 / 182, 16384 463 / 441 (10000, six rounds: 106 / 111). Not
+// taken, though faster: 128 x 128 ring tiles in segments of 512 products (4096 6.56 / 5.95) and 256 x 256
+// tiles (5500 17.8 / 12.9): their sums round otherwise, and on dense matrices at beta' ~ 100, where one
+// rounding more or less shows as 1e-4 of D, the values moved by that.
 int split_schedule(int64_t n, int n_cu) {
-    auto tiles = [n](int64_t bm) {
-        const int64_t T = (n + bm - 1) / bm;
-        return T * (T + 1) / 2;
-    };
-    if (split_sk2_per_cu(n) == 2) return tiles(128) >= 16 * (int64_t)n_cu ? 0 : 2;
-    const int64_t t = tiles(256);
-    return 4 * t >= 3 * (int64_t)n_cu && (t <= n_cu || 4 * t >= 5 * (int64_t)n_cu) ? 1 : 2;
+    const int64_t np = (n + 127) / 128 * 128, T = np / 128, tiles = T * (T + 1) / 2, nk = np / 64;
+    const int64_t grid = 2 * (int64_t)n_cu, rounds = tiles / grid;
+    if (rounds >= 8) return 0;
+    const int64_t nsk = rounds >= 2 ? tiles - (rounds - 1) * grid : tiles;
+    return nsk * nk >= 8 * grid ? 2 : 0;
 }
 
 int split_tile_for(int streamk) {
@@ -418,7 +443,7 @@ hipError_t launch_layer_split(const LayerArgs& a, int bf16, const SplitPlan& pla
     if (plan.streamk == 0 && plan.ring_tile != 0) {
         if (a.np % plan.ring_tile != 0) return hipErrorInvalidValue;
         const int64_t T = a.np / plan.ring_tile;
-        if (plan.ring_tile == CfgL64::BM && T * (T + 1) / 2 <= plan.grid)   // at most one per CU
+        if (plan.ring_tile == CfgL64::BM && T * (T + 1) / 2 <= plan.n_cu)   // at most one per CU
             return bf16 == 2 ? launch_ring<true, CfgL64x3>(a, s)
                    : bf16    ? launch_ring<true, CfgL64>(a, s)
                              : launch_ring<false, CfgL64>(a, s);
@@ -438,8 +463,6 @@ hipError_t launch_layer_split(const LayerArgs& a, int bf16, const SplitPlan& pla
     }
     if (plan.streamk == 1)
         return bf16 ? launch_sk<true, CfgSK>(a, plan, s) : launch_sk<false, CfgSK>(a, plan, s);
-    if (plan.streamk == 2 && split_sk2_per_cu(a.n) == 2)
-        return bf16 ? launch_sk<true, CfgSK2x2>(a, plan, s) : launch_sk<false, CfgSK2x2>(a, plan, s);
     if (plan.streamk == 2)
         return bf16 ? launch_sk<true, CfgSK2>(a, plan, s) : launch_sk<false, CfgSK2>(a, plan, s);
     return bf16 ? launch_dp<true>(a, s) : launch_dp<false>(a, s);

@@ -229,11 +229,9 @@ __device__ inline void zero(Acc<C>& acc) {
 // across the block boundary too. The barrier there is a bare s_barrier after an explicit wait for this
 // wave's own loads of the next block (a full __syncthreads would also drain everything else in flight)
 // and its fragment reads of the current one, whose stage is refilled after it. AUX: cache policy of
-// the operand loads. SEG > 0: the blocks are summed in segments of SEG, each from zero, and the
-// segments' sums added (a long K loop then rounds like the stream-K schedules' partial sums, not like
-// one chain). Blocks, K steps and products are taken in the order of the register-staged loops, so an
-// element's sum (SEG = 0) does not depend on the form. Ends with a barrier.
-template <bool BF, class C, int SEG = 0, int AUX = 0>
+// the operand loads. Blocks, K steps and products are taken in the order of the register-staged loops,
+// so an element's sum does not depend on the form. Ends with a barrier.
+template <bool BF, class C, int AUX = 0>
 __device__ __attribute__((always_inline)) inline void kloop_dma(
     const uint16_t* __restrict__ hin, const uint16_t* __restrict__ min,
     const uint16_t* __restrict__ lin, int64_t np, int64_t I0, int64_t J0, int kb0, int kb1,
@@ -249,7 +247,6 @@ __device__ __attribute__((always_inline)) inline void kloop_dma(
     static_assert(IPA % NW == 0, "a wave's load q is in panel NW q / IPA");
     static_assert(NW * RPI / RP % CPR == 0 && 32 / RP % CPR == 0, "chunk positions depend on wave and lane only");
     static_assert(IPW * (S - 1) < 64, "in-flight loads fit the wait counter");
-    static_assert(SEG % S == 0, "segments are whole turns of the ring");
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));   // keep address arithmetic inside a caller's persistent loop
     const int lane = tid & 63;
@@ -424,43 +421,8 @@ __device__ __attribute__((always_inline)) inline void kloop_dma(
     }
     // whole turns of the ring whose loads all exist, then the rest
     int i = 0;
-    if constexpr (SEG == 0) {
-        for (; i + 2 * S - 1 < nk; i += S) turn(yes, i);
-        for (; i < nk; i += S) turn(no, i);
-    } else {
-        Acc<C> sum;
-        auto flush = [&](bool fresh) {
-#pragma unroll
-            for (int mb = 0; mb < C::MB; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < C::NB; ++nb)
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) {
-                        sum.v[mb][nb][j] = fresh ? acc.v[mb][nb][j] : sum.v[mb][nb][j] + acc.v[mb][nb][j];
-                        acc.v[mb][nb][j] = 0.0f;
-                    }
-        };
-        int seg = SEG;   // end of the current segment
-        bool fresh = true;
-        while (i < nk) {
-            const int end = seg < nk ? seg : nk;
-            for (; i < end && i + 2 * S - 1 < nk; i += S) turn(yes, i);
-            for (; i < end; i += S) turn(no, i);
-            if (i < nk) {
-                flush(fresh);
-                fresh = false;
-                seg += SEG;
-            }
-        }
-        if (!fresh) {
-#pragma unroll
-            for (int mb = 0; mb < C::MB; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < C::NB; ++nb)
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) acc.v[mb][nb][j] += sum.v[mb][nb][j];
-        }
-    }
+    for (; i + 2 * S - 1 < nk; i += S) turn(yes, i);
+    for (; i < nk; i += S) turn(no, i);
     asm volatile("" ::: "memory");
     __syncthreads();
 }
@@ -813,15 +775,11 @@ struct EpiPre {
 // product (the rescale made X and A symmetric there, so they equal the upper ones bit for bit). The
 // padding comes out zero. LDS: 16-byte groups of row r at group g ^ (r / 4) (modulo the row). pre: the
 // tile's X and A groups, or NULL: loaded here, UB groups at a time. AUX: cache policy of those loads.
-// parts: nparts partial tiles of other workgroups as in epi_chunk (not for a diagonal tile).
 template <bool BF, class C, int AUX = 0, int UB = 4>
 __device__ __attribute__((always_inline)) inline void epilogue_mid(const LayerArgs& p, const Acc<C>& acc,
                                                                    float* sY, int I, int J,
                                                                    bool poisoned,
-                                                                   const EpiPre<C>* pre,
-                                                                   const float* __restrict__ parts = nullptr,
-                                                                   size_t part_stride = 0,
-                                                                   int nparts = 0) {
+                                                                   const EpiPre<C>* pre) {
     constexpr int BM = C::BM, G = BM / 4, RPG = C::NT / G, PER = BM / RPG;
     static_assert(PER % UB == 0, "whole batches of groups");
     const int tid = opaque_tid(), lane = tid & 63, wave = tid >> 6;
@@ -876,12 +834,6 @@ __device__ __attribute__((always_inline)) inline void epilogue_mid(const LayerAr
             const int u = u0 + v, r = rt + RPG * u, c = g * 4;
             const floatx4 x = pre ? pre->x[u] : xg[v], a = pre ? pre->a[u] : ag[v];
             floatx4 y = *reinterpret_cast<const floatx4*>(sY + at(r, c));
-            for (int q = 0; q < nparts; ++q) {
-                const floatx4 z = load4_coherent(make_rsrc(parts + (size_t)q * part_stride, BM * BM * 4),
-                                                 (r * BM + c) * 4);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) y[k] = fmaf(z[k], BF ? 1.0f : 2048.0f, y[k]);
-            }
             if (diag) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k)

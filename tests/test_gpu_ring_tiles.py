@@ -2,9 +2,7 @@
 edges of their tiles and of the sizes they are chosen for (n <= 1984 and n <= 2816 on 256 compute
 units): they take the same products in the same order as the batch's register-staged 128 x 128
 kernel, so D is bitwise that of a batch of one. The traces are FP64 sums of the same values in
-another order: n^2 additions of at most 1 each, 2^-53 relative each. The two-part 128 x 128 tiles
-add their products in segments of 512 along K: against FP64 their D is no further off than the
-batch kernel's one chain."""
+another order: n^2 additions of at most 1 each, 2^-53 relative each."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -33,14 +31,6 @@ def test_bitwise_equal_to_the_batch_kernel(api, paper_model, monkeypatch, n, pre
     plan = api.BatchPlan([dict(H=H, mu=0.05, kT=0.1)], paper_model, prec=prec)
     plan.launch()
     torch.cuda.synchronize()
-    if 1984 < n <= 2816 and prec != "bf16x3":
-        f, v = torch.linalg.eigh(H)
-        ref = (v * torch.sigmoid((0.05 - f) / 0.1)) @ v.T
-        e = [float(torch.linalg.norm(x.double() - ref)) for x in (D, plan.D[0])]
-        print(f"n={n} {prec} |dD|_F ring {e[0]:.3e} batch {e[1]:.3e}", flush=True)
-        assert torch.equal(D, D.T) and e[0] <= e[1]
-        plan.close()
-        return
     assert torch.equal(D, plan.D[0])
     tol = 2.0 ** -53 * n * n
     assert abs(float(tr) - float(plan.tr[0, 0])) <= tol * n
