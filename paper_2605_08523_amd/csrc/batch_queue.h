@@ -48,8 +48,11 @@ hipError_t launch_batch_queue_reset(const BatchQueue& Q, int count, hipStream_t 
 // One pass over every layer of every matrix (q.layer, q.parity and q.map unused) on `grid`
 // workgroups: the number of queues times the longest queue (the hardware deals consecutive
 // workgroups to consecutive XCDs, so each XCD gets the same number).
+// staged (128 x 128 tiles): operands through registers and a workgroup per item, for batches of many
+// operands (k_batched.hip); the per-layer launch likewise.
 hipError_t launch_batch_queue(const BatchLayerArgs& q, const BatchQueue& Q, int64_t grid, int bf16,
-                              int tile, hipStream_t s);
+                              int tile, int staged, hipStream_t s);
+hipError_t launch_batch_layer_staged(const BatchLayerArgs& q, int grid, int bf16, hipStream_t s);
 // Whether the queue launch's assumptions hold on the current device with nq XCDs: consecutive
 // workgroups run on consecutive XCDs (round-robin, from whichever XCD the dispatch starts at), and
 // each reads its XCD's id from the hardware (a probe launch; synchronizes).

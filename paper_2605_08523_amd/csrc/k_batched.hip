@@ -26,6 +26,18 @@ using CfgB64 = Cfg<64, 2, 2, 64, 64, 2, 1>;
 // Three-part BF16 split: six panels of 32-deep K-blocks per stage.
 using CfgB3 = Cfg<128, 4, 2, 32, 128, 3, 1, 3>;
 using CfgB3x64 = Cfg<64, 2, 2, 32, 64, 3, 1, 3>;
+// Batches of 64 MiB of operands and more (staged launches): 128 x 128 tiles staged through registers,
+// two workgroups of eight 32 x 64 waves per CU, so that one multiplies while the other's epilogue waits
+// for memory. In the queue each takes one item and leaves, which also lets the next one start beside an
+// epilogue's last stores (a loop over items like the ring's: 100 matrices 3.76, 400 15.5 ms). ms per
+// batch of matrices of n 64 ... 768 (40 layers), ring / staged: 100 (90 MiB) 3.77 / 3.20, 200 8.02 / 7.16,
+// 400 17.0 / 15.6, 1024 (1 GiB) 42.6 / 39.4; 60 (50 MiB) 1.68 on the ring. The epilogue keeps two groups
+// of loads in flight per thread (register budget of four waves per SIMD).
+using CfgBx2 = Cfg<128, 4, 2, 64, 128, 1>;
+using CfgB3x2 = Cfg<128, 4, 2, 32, 128, 1, 0, 3>;
+constexpr int kBatchEpiGroups = 2;
+template <class C>
+constexpr int kBatchWaves = C::DMA ? 2 : 4;   // per SIMD
 template <class C>
 constexpr int kPerCu = C::LDS_BYTES > 80 * 1024 ? 1 : 2;   // workgroups per CU
 
@@ -236,6 +248,16 @@ __device__ __attribute__((always_inline)) inline void batch_tile(
     // diagonal there), and the padded part of the tile is not stored: they are skipped.
     const int kend = (int)((p.n + C::BK - 1) / C::BK);
     float* const sY = reinterpret_cast<float*>(smem);
+    if constexpr (!C::DMA) {
+        if constexpr (C::NS == 3)
+            kloop3<C>(p.hi_in, p.mid_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM, 0, kend,
+                      acc, reinterpret_cast<uint16_t*>(smem));
+        else
+            kloop<BF, C>(p.hi_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM, 0, kend, acc,
+                         reinterpret_cast<uint16_t*>(smem));
+        epilogue<BF, C, kBatchEpiGroups>(p, acc, sY, I, J, t, nullptr, 0, 0, poisoned);
+        return;
+    } else {
     constexpr bool kPre = EpiPre<C>::PER <= 4;
     EpiPre<C> pre;
     if constexpr (kPre) pre.template load<AUX>(p, I, J);
@@ -249,7 +271,8 @@ __device__ __attribute__((always_inline)) inline void batch_tile(
         asm volatile("buffer_inv sc1\n\ts_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     }
-    epilogue<BF, C, kPre ? 8 : 2, kPre>(p, acc, sY, I, J, t, nullptr, 0, 0, poisoned, &pre);
+    epilogue<BF, C, kPre ? 8 : kBatchEpiGroups, kPre>(p, acc, sY, I, J, t, nullptr, 0, 0, poisoned, &pre);
+    }
 }
 
 // One layer for every upper tile of every matrix. Workgroup g takes the (matrix, tile) of its slot
@@ -259,7 +282,7 @@ __device__ __attribute__((always_inline)) inline void batch_tile(
 // a map it finds its matrix by binary search over the tile prefix sums.
 template <bool BF, class C>
 __global__ void __launch_bounds__(C::NT)
-__attribute__((amdgpu_waves_per_eu(2, 2)))
+__attribute__((amdgpu_waves_per_eu(kBatchWaves<C>, kBatchWaves<C>)))
 k_batch_layer(BatchLayerArgs q) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int g = blockIdx.x;
@@ -289,10 +312,11 @@ k_batch_layer(BatchLayerArgs q) {
 // the abort flag, after which no wait blocks; such an item is computed with NaN outputs.
 template <bool BF, class C>
 __global__ void __launch_bounds__(C::NT)
-__attribute__((amdgpu_waves_per_eu(2, 2)))
+__attribute__((amdgpu_waves_per_eu(kBatchWaves<C>, kBatchWaves<C>)))
 k_batch_queue(BatchLayerArgs q, BatchQueue Q, const BatchMat* __restrict__ mats,
               const int32_t* __restrict__ Ls, const float* __restrict__ coef) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int AUX = C::DMA ? kCoherentLoad : 0;
     __shared__ int4 s_item;
     __shared__ int s_gave_up;
     int x;
@@ -332,13 +356,18 @@ k_batch_queue(BatchLayerArgs q, BatchQueue Q, const BatchMat* __restrict__ mats,
             // nothing of the above is in flight beside the item's counted loads
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
+        // Plain loads follow: lines of the matrix that this CU's L1 holds from before its producers'
+        // stores are stale (agent scope: the workgroup-scope invalidate leaves the L1 alone when a
+        // workgroup's waves share one CU).
+        if constexpr (AUX == 0)
+            if (threadIdx.x < 64) asm volatile("buffer_inv sc1\n\ts_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         const int mat = __builtin_amdgcn_readfirstlane(s_item.x);
         if (mat < 0) return;   // the queue is exhausted; whole workgroup leaves
         const int t = __builtin_amdgcn_readfirstlane(s_item.y);
         const int layer = __builtin_amdgcn_readfirstlane(s_item.z);
         const bool gave_up = __builtin_amdgcn_readfirstlane(s_gave_up) != 0;
-        batch_tile<BF, C, kCoherentLoad>(q, mats, Ls, coef, mat, t, layer, gave_up, smem);
+        batch_tile<BF, C, AUX>(q, mats, Ls, coef, mat, t, layer, gave_up, smem);
         // This wave's stores of the item have completed (in the XCD's L2). The memory clobber keeps
         // the compiler from sinking any of them below the wait.
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -346,8 +375,9 @@ k_batch_queue(BatchLayerArgs q, BatchQueue Q, const BatchMat* __restrict__ mats,
         if (threadIdx.x == 0) {
             __hip_atomic_fetch_add(Q.done + mat * kQueueLine, 1, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
-            it = take();
+            if constexpr (C::DMA) it = take();
         }
+        if constexpr (!C::DMA) return;
     }
 }
 
@@ -457,6 +487,13 @@ hipError_t launch_batch_layer(const BatchLayerArgs& q, int grid, int bf16, int t
                      : launch_layer_t<false, CfgB>(q, grid, s);
 }
 
+hipError_t launch_batch_layer_staged(const BatchLayerArgs& q, int grid, int bf16, hipStream_t s) {
+    if (grid < 1) return hipErrorInvalidValue;
+    return bf16 == 2 ? launch_layer_t<true, CfgB3x2>(q, grid, s)
+           : bf16    ? launch_layer_t<true, CfgBx2>(q, grid, s)
+                     : launch_layer_t<false, CfgBx2>(q, grid, s);
+}
+
 template <bool BF, class C>
 hipError_t queue_t(const BatchLayerArgs& q, const BatchQueue& Q, int64_t grid, hipStream_t s) {
     auto kern = k_batch_queue<BF, C>;
@@ -468,13 +505,15 @@ hipError_t queue_t(const BatchLayerArgs& q, const BatchQueue& Q, int64_t grid, h
         if (e != hipSuccess) return e;
         done = true;
     }
-    // as many workgroups as run at once (the same number on every XCD)
-    int dev = 0, cus = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    const int64_t slots = std::max((int64_t)Q.nq, (int64_t)kPerCu<C> * cus / Q.nq * Q.nq);
-    if (grid > slots) grid = slots;
+    if constexpr (C::DMA) {
+        // as many workgroups as run at once (the same number on every XCD)
+        int dev = 0, cus = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess) return e;
+        const int64_t slots = std::max((int64_t)Q.nq, (int64_t)kPerCu<C> * cus / Q.nq * Q.nq);
+        if (grid > slots) grid = slots;
+    }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s, q, Q, q.mats,
                        q.cf.L, q.cf.coef);
     return hipGetLastError();
@@ -488,13 +527,17 @@ hipError_t launch_batch_queue_reset(const BatchQueue& Q, int count, hipStream_t 
 }
 
 hipError_t launch_batch_queue(const BatchLayerArgs& q, const BatchQueue& Q, int64_t grid, int bf16,
-                              int tile, hipStream_t s) {
+                              int tile, int staged, hipStream_t s) {
     if (grid < 1 || grid > 0x7fffffff) return hipErrorInvalidValue;
     if (tile == 64)
         return bf16 == 2 ? queue_t<true, CfgB3x64>(q, Q, grid, s)
                : bf16    ? queue_t<true, CfgB64>(q, Q, grid, s)
                          : queue_t<false, CfgB64>(q, Q, grid, s);
     if (tile != 128) return hipErrorInvalidValue;
+    if (staged)
+        return bf16 == 2 ? queue_t<true, CfgB3x2>(q, Q, grid, s)
+               : bf16    ? queue_t<true, CfgBx2>(q, Q, grid, s)
+                         : queue_t<false, CfgBx2>(q, Q, grid, s);
     return bf16 == 2 ? queue_t<true, CfgB3>(q, Q, grid, s)
            : bf16    ? queue_t<true, CfgB>(q, Q, grid, s)
                      : queue_t<false, CfgB>(q, Q, grid, s);
