@@ -1,7 +1,8 @@
-"""Stream-K over 128 x 128 ring tiles (two-part splits, n > 1920) at the edges of its forms: a workgroup
-per tile that sums the plan's segments itself (n <= 2816 on 256 compute units), and the plan with
-hand-overs beyond, with whole-tile rounds first at n = 5700. Segments added in a fixed order, so D is the same on every
-call, within the expansion's accuracy bar of FP64, and for FP16x2 no further off than one chain."""
+"""Stream-K over 128 x 128 tiles (two-part splits, n > 1920) at the edges of its forms: a workgroup per
+ring tile that sums the plan's segments itself (n <= 2816 on 256 compute units), and the plan with
+hand-overs beyond, with whole-tile rounds first at n = 5700. Segments are added in a fixed order, so D
+is the same on every call, within the expansion's accuracy bar of FP64, and for FP16x2 no further off
+than one chain."""
 import pytest
 
 pytestmark = pytest.mark.gpu
