@@ -513,6 +513,10 @@ int fe_streamk_segments(int64_t np, int32_t schedule, int32_t grid, int32_t w, i
  * as a wait that timed out would. Every kernel still exits normally; the tiles finished after a
  * give-up are NaN, the traces NaN, and the rescale info status FE_ERR_HIP. */
 int fe_debug_streamk_giveup(int32_t enable);
+/* The same for one wait of the launch that runs all layers of a small matrix: that of work item `item`
+ * (layer-major over the upper tiles; the splits' are 64 x 64, FP32's and FP64's 32 x 32), or none if
+ * item < 0. The item's tile and every later layer come out as NaN. */
+int fe_debug_resident_giveup(int32_t item);
 
 /* Host-side view of the queue launch's work tables (no device work; for tests of the layout the
  * kernel relies on): matrices of padded sizes np[i] (multiples of tile) running L[i] layers, in

@@ -107,6 +107,7 @@ SIGNATURES = {
     "fe_streamk_segments": (_I32, [_I64, _I32, _I32, _I32, C.POINTER(_I32), C.POINTER(_I32), _I32,
                                    C.POINTER(_I32)]),
     "fe_debug_streamk_giveup": (_I32, [_I32]),
+    "fe_debug_resident_giveup": (_I32, [_I32]),
     "fe_debug_batch_queue_giveup": (_I32, [_I32]),
     "fe_batch_queue_layout": (_I32, [_I32, C.POINTER(_I64), C.POINTER(_I32), _I32, _I32,
                                      C.POINTER(_I32), _I64, C.POINTER(_I32), C.POINTER(_I64)]),
@@ -486,6 +487,12 @@ def layer_events_read():
 def debug_streamk_giveup(enable: bool) -> None:
     """fe_debug_streamk_giveup: make every stream-K wait give up (failure-handling tests)."""
     _check(lib().fe_debug_streamk_giveup(1 if enable else 0))
+
+
+def debug_resident_giveup(item: int) -> None:
+    """fe_debug_resident_giveup: make the wait of one work item of the launch that runs all layers of a
+    small matrix give up (failure-handling tests); -1 for none."""
+    _check(lib().fe_debug_resident_giveup(int(item)))
 
 
 def batch_queue_layout(np_list, L_list, tile: int, nq: int):

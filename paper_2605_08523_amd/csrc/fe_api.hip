@@ -40,6 +40,8 @@ std::mutex g_tune_mu;
 std::vector<TunedEntry> g_tuned;
 // fe_debug_streamk_giveup: stream-K waits expect a flag value that is never written
 std::atomic<int> g_sk_giveup{0};
+// fe_debug_resident_giveup: the one item of a resident launch whose wait gives up
+std::atomic<int> g_res_stuck{fe::kNoItem};
 // fe_debug_layer_events: HIP events around each layer launch of the split path (the last call's)
 std::mutex g_ev_mu;
 bool g_ev_on = false;
@@ -96,9 +98,9 @@ fe::ResidentArgs resident_args(fe_workspace* ws, int which, int L) {
     fe::ResidentArgs R{};
     R.ctl = ws->ctl + which * fe::kResInts;
     R.L = L;
-    const bool giveup = g_sk_giveup.load() != 0;
-    R.spin_limit = giveup ? 64 : (1 << 23);   // ~0.6 us per poll: ~5 s
-    R.need_offset = giveup ? (1 << 30) : 0;
+    R.stuck = g_sk_giveup.load() != 0 ? fe::kEveryItem : g_res_stuck.load();
+    // ~0.6 us per poll: ~5 s
+    R.spin_limit = R.stuck == fe::kNoItem ? 1 << 23 : R.stuck == fe::kEveryItem ? 64 : 1 << 16;
     return R;
 }
 
@@ -783,6 +785,11 @@ int fe_debug_layer_events_read(double* ms, int32_t cap, int32_t* count) {
 
 int fe_debug_streamk_giveup(int32_t enable) {
     g_sk_giveup.store(enable ? 1 : 0);
+    return FE_OK;
+}
+
+int fe_debug_resident_giveup(int32_t item) {
+    g_res_stuck.store(item >= 0 ? item : fe::kNoItem);
     return FE_OK;
 }
 

@@ -15,7 +15,9 @@
 // hardware deals to one XCD; if it did not, fewer would stay). Producers' stores complete in the
 // L2 (vmcnt(0) in every wave, then a barrier) before the item is counted; readers load with sc1,
 // which does not take the CU's L1's word for it. Waits are bounded (~5 s): one that gives up sets
-// the error flag, and its item and all later ones come out as NaN.
+// the error flag, and its item comes out as NaN and is not counted. The layers after it then never have
+// their count, so every wait of theirs gives up too (the flag ends it) and all of them come out as NaN:
+// none starts on what a late workgroup has yet to store.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -32,8 +34,9 @@ struct ResidentArgs {
     int32_t* ctl;      // kResInts ints, zero before the launch
     int ntiles, L;
     int spin_limit;    // polls before a wait gives up
-    int need_offset;   // 0, or (to test the give-up path) a count never reached
+    int stuck;         // to test the give-up path: the item whose wait cannot end (kNoItem, kEveryItem)
 };
+constexpr int kNoItem = -1, kEveryItem = -2;
 
 // Calls item(layer, tile, gave_up) for every item this workgroup gets; item may use all threads and
 // barriers. Items end with all their stores complete.
@@ -61,7 +64,7 @@ __device__ __attribute__((always_inline)) inline void resident_items(const Resid
     while (t < total) {
         const int layer = t / R.ntiles, tile = t - layer * R.ntiles;
         if (threadIdx.x == 0) {
-            const int need = layer * R.ntiles + R.need_offset;
+            const int need = t == R.stuck || R.stuck == kEveryItem ? INT32_MAX : layer * R.ntiles;
             int spins = 0, bad = 0;
             // The next ticket now: its trip runs beside the wait (the holder of a ticket may be busy
             // with a smaller one), and it is back before the item's loads, whose waits count on
@@ -83,11 +86,12 @@ __device__ __attribute__((always_inline)) inline void resident_items(const Resid
             s_bad = bad;
         }
         __syncthreads();
-        item(layer, tile, __builtin_amdgcn_readfirstlane(s_bad) != 0);
+        const bool gave_up = __builtin_amdgcn_readfirstlane(s_bad) != 0;
+        item(layer, tile, gave_up);
         if (threadIdx.x == 0) s_ticket = next;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (threadIdx.x == 0)
+        if (threadIdx.x == 0 && !gave_up)
             __hip_atomic_fetch_add(R.ctl + kResDone, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         t = __builtin_amdgcn_readfirstlane(s_ticket);
     }
