@@ -262,8 +262,8 @@ int fe_batch_plan_retile(fe_batch_plan* plan, int32_t tile);
  * fails, plans fall back to FE_BATCH_LAUNCH_LAYERS: one grouped launch per layer over all upper
  * tiles of all matrices. Both forms run the same per-tile arithmetic in the same order, so they
  * give bitwise equal results. If a wait gives up (it never should: every wait is on earlier items of
- * the same queue, all held by running workgroups), the matrix's outputs are NaN and its status
- * FE_ERR_HIP. The queue launch holds 16 B of device tables per work item (upper tiles x layers,
+ * the same queue, all held by running workgroups), the item's tile, every later layer of the matrix and
+ * so its traces are NaN and its status is FE_ERR_HIP. The queue launch holds 16 B of device tables per work item (upper tiles x layers,
  * summed over the matrices and both passes), allocated with the plan. */
 #define FE_BATCH_LAUNCH_LAYERS 0
 #define FE_BATCH_LAUNCH_QUEUE  1
@@ -532,6 +532,9 @@ int fe_batch_queue_layout(int32_t count, const int64_t* np, const int32_t* L, in
  * the rest at once. Every kernel still exits normally; every matrix of such a plan gets NaN
  * outputs and status FE_ERR_HIP. */
 int fe_debug_batch_queue_giveup(int32_t enable);
+/* The same for one wait per matrix and pass: that of the first tile of layer `layer`, in plans built
+ * while it is set; none if layer < 0. That tile and every later layer come out as NaN. */
+int fe_debug_batch_queue_giveup_layer(int32_t layer);
 
 /* Per-launch timing of the layer kernel with HIP events on the call's stream (process-wide; for
  * the roofline measurement of Sec. V.A's layer product): while enabled, every expansion on the

@@ -109,6 +109,7 @@ SIGNATURES = {
     "fe_debug_streamk_giveup": (_I32, [_I32]),
     "fe_debug_resident_giveup": (_I32, [_I32]),
     "fe_debug_batch_queue_giveup": (_I32, [_I32]),
+    "fe_debug_batch_queue_giveup_layer": (_I32, [_I32]),
     "fe_batch_queue_layout": (_I32, [_I32, C.POINTER(_I64), C.POINTER(_I32), _I32, _I32,
                                      C.POINTER(_I32), _I64, C.POINTER(_I32), C.POINTER(_I64)]),
     "fe_debug_layer_events": (_I32, [_I32]),
@@ -517,6 +518,12 @@ def debug_batch_queue_giveup(enable: bool) -> None:
     """fe_debug_batch_queue_giveup: batch plans built while enabled make every queue-launch wait
     give up (failure-handling tests)."""
     _check(lib().fe_debug_batch_queue_giveup(1 if enable else 0))
+
+
+def debug_batch_queue_giveup_layer(layer: int) -> None:
+    """fe_debug_batch_queue_giveup_layer: batch plans built while set make the wait of the first tile of
+    that layer give up, for every matrix (failure-handling tests); -1 for none."""
+    _check(lib().fe_debug_batch_queue_giveup_layer(int(layer)))
 
 
 # ---- batches -----------------------------------------------------------------------------

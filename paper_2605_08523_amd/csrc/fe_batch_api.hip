@@ -47,6 +47,8 @@ namespace {
 
 // fe_debug_batch_queue_giveup: every wait of the queue launch expects a count never reached
 std::atomic<int> g_queue_giveup{0};
+// fe_debug_batch_queue_giveup_layer: the waits of this layer's first tiles, or none (-1)
+std::atomic<int> g_queue_stuck{-1};
 
 int check_item(const fe_batch_item& it, int i) {
     if (!it.H) return fail(FE_ERR_ARG, "batch item " + std::to_string(i) + ": H is NULL");
@@ -516,9 +518,14 @@ int build_plan(fe_batch_plan* plan, int want) {
     const bool queued = plan->launch == FE_BATCH_LAUNCH_QUEUE;
     if (queued) {
         const std::vector<int> queue_of = deal_queues(mats, tile, nq);
-        const PassQueues pd = make_queues(mats, queue_of, td.L, td.max_L, tile, nq);
+        PassQueues pd = make_queues(mats, queue_of, td.L, td.max_L, tile, nq);
         PassQueues pe;
         if (!ent.empty()) pe = make_queues(mats, queue_of, te.L, te.max_L, tile, nq);
+        const int stuck = g_queue_stuck.load();
+        if (stuck >= 0)
+            for (PassQueues* p : {&pd, &pe})
+                for (size_t i = 0; i < p->items.size(); i += 4)
+                    if (p->items[i + 1] == 0 && p->items[i + 2] == stuck) p->items[i + 3] = 1 << 30;
         if (pd.longest * nq > 0x7fffffff || pe.longest * nq > 0x7fffffff)
             return fail(FE_ERR_WORKSPACE, "batch has too many work items for one queue launch");
         const size_t id = al(pd.items.size() * 4), ie = al(pe.items.size() * 4);
@@ -545,7 +552,8 @@ int build_plan(fe_batch_plan* plan, int want) {
             v.q.done = counters + fe::kQueueLine * nq;
             v.q.err = counters + fe::kQueueLine * ((int64_t)nq + count);
             const bool giveup = g_queue_giveup.load() != 0;
-            v.q.spin_limit = giveup ? 64 : (1 << 23);   // ~0.6 us per poll: ~5 s
+            // ~0.6 us per poll: ~5 s
+            v.q.spin_limit = giveup ? 64 : stuck >= 0 ? 1 << 16 : 1 << 23;
             v.q.need_offset = giveup ? (1 << 30) : 0;
             v.grid = longest * nq;
         };
@@ -851,6 +859,11 @@ int fe_batch_queue_layout(int32_t count, const int64_t* np, const int32_t* L, in
 
 int fe_debug_batch_queue_giveup(int32_t enable) {
     g_queue_giveup.store(enable ? 1 : 0);
+    return FE_OK;
+}
+
+int fe_debug_batch_queue_giveup_layer(int32_t layer) {
+    g_queue_stuck.store(layer >= 0 ? layer : -1);
     return FE_OK;
 }
 

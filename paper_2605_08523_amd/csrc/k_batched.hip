@@ -309,7 +309,9 @@ k_batch_layer(BatchLayerArgs q) {
 // BatchQueue): each workgroup takes tickets of its XCD's queue until that is exhausted; it waits until
 // the item's matrix has completed its previous layer, computes the item, and once every wave's stores of
 // it have completed counts it done. The wait is bounded: one that gives up marks the matrix and raises
-// the abort flag, after which no wait blocks; such an item is computed with NaN outputs.
+// the abort flag, after which no wait blocks; such an item is computed with NaN outputs and not counted,
+// so the matrix's next layers never have their count and give up too, instead of starting on what a
+// late workgroup has yet to store.
 template <bool BF, class C>
 __global__ void __launch_bounds__(C::NT)
 __attribute__((amdgpu_waves_per_eu(kBatchWaves<C>, kBatchWaves<C>)))
@@ -373,8 +375,9 @@ k_batch_queue(BatchLayerArgs q, BatchQueue Q, const BatchMat* __restrict__ mats,
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (threadIdx.x == 0) {
-            __hip_atomic_fetch_add(Q.done + mat * kQueueLine, 1, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+            if (!gave_up)
+                __hip_atomic_fetch_add(Q.done + mat * kQueueLine, 1, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
             if constexpr (C::DMA) it = take();
         }
         if constexpr (!C::DMA) return;

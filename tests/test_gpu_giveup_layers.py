@@ -39,3 +39,28 @@ def test_resident_layers_after_a_giveup(api, paper_model, n, prec, tiles):
     D, _, _, info = api.expand_density(H, 0.1, 0.1, paper_model, prec=prec, ws=ws, want_info=True)
     assert info["rc"] == 0 and torch.equal(D, good)
     ws.close()
+
+
+@pytest.mark.parametrize("ns,tile,prec", [((300, 130, 520), 64, "fp16x2"), ((300, 130, 520), 128, "fp16x2"),
+                                          ((300, 130, 520), 128, "bf16x3"), ((768,) * 30, 128, "fp16x2"),
+                                          ((768,) * 30, 128, "bf16x3")])
+def test_batch_layers_after_a_giveup(api, paper_model, ns, tile, prec):
+    print(f"case {len(ns)} matrices tile={tile} {prec}", flush=True)   # 30: the staged launch
+    mats = [dict(H=torch.from_numpy(W.random_dense(n, n + b)).cuda(), mu=0.02, kT=0.1)
+            for b, n in enumerate(ns)]
+    plan = api.BatchPlan(mats, paper_model, prec=prec)
+    api.debug_batch_queue_giveup_layer(paper_model.L - 2)
+    try:
+        plan.set_launch("queue")
+        plan.retile(tile)
+    finally:
+        api.debug_batch_queue_giveup_layer(-1)
+    plan.launch()
+    torch.cuda.synchronize()
+    assert plan.status.tolist() == [api.FE_ERR_HIP] * len(ns) and torch.isnan(plan.tr).all().item()
+    assert all(torch.isnan(d).all().item() for d in plan.D)
+    plan.retile(tile)
+    plan.launch()
+    torch.cuda.synchronize()
+    assert plan.status.tolist() == [0] * len(ns) and not any(torch.isnan(d).any().item() for d in plan.D)
+    plan.close()
