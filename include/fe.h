@@ -507,6 +507,12 @@ double fe_layer_count(double beta_p);
 int fe_streamk_segments(int64_t np, int32_t schedule, int32_t grid, int32_t w, int32_t* geom,
                         int32_t* segs, int32_t cap, int32_t* count);
 
+/* The same plan by tile: the K-block segments of upper tile t (dp_tiles <= t < ntiles) in the order in
+ * which their sums are added. segs: host int32[2 * cap] or NULL, receives (kb0, kb1) per segment; count:
+ * host, their number. */
+int fe_streamk_tile_segments(int64_t np, int32_t schedule, int32_t grid, int32_t t, int32_t* segs,
+                             int32_t cap, int32_t* count);
+
 /* Test hook for failure handling (process-wide): while enabled, every stream-K wait of the layer
  * kernel, and every wait of the launch that runs all layers of a small matrix, waits for a flag
  * value that no workgroup writes and gives up after a short bounded spin,

@@ -106,6 +106,7 @@ SIGNATURES = {
                                          _P, _I32, _I64, _P, _P, C.POINTER(fe_rescale_info), _P]),
     "fe_streamk_segments": (_I32, [_I64, _I32, _I32, _I32, C.POINTER(_I32), C.POINTER(_I32), _I32,
                                    C.POINTER(_I32)]),
+    "fe_streamk_tile_segments": (_I32, [_I64, _I32, _I32, _I32, C.POINTER(_I32), _I32, C.POINTER(_I32)]),
     "fe_debug_streamk_giveup": (_I32, [_I32]),
     "fe_debug_resident_giveup": (_I32, [_I32]),
     "fe_debug_batch_queue_giveup": (_I32, [_I32]),
@@ -468,6 +469,16 @@ def streamk_segments(np_: int, schedule: int, grid: int, w: int):
                                      C.byref(cnt)))
     g = dict(zip(("T", "ntiles", "nk", "dp_tiles", "groups", "grid"), list(geom)))
     return g, segs[:cnt.value]
+
+
+def streamk_tile_segments(np_: int, schedule: int, grid: int, t: int):
+    """fe_streamk_tile_segments: the segments (kb0, kb1) of upper tile t in the order of their sum."""
+    cap = 2 * grid + 1
+    segs = (C.c_int32 * (2 * cap))()
+    cnt = C.c_int32()
+    _check(lib().fe_streamk_tile_segments(int(np_), int(schedule), int(grid), int(t), segs, cap,
+                                          C.byref(cnt)))
+    return [(segs[2 * i], segs[2 * i + 1]) for i in range(cnt.value)]
 
 
 def layer_events(enable: bool) -> None:

@@ -21,7 +21,8 @@ namespace {
 constexpr int64_t kStreamKMinN = 1536;   // workspaces for n >= this carry stream-K buffers
 constexpr int64_t kSmallN64 = 128;       // FP64 up to this size takes at most kResMaxL layers
 
-// Schedule of the split-precision layer kernel (FE_SCHEDULE=dp|sk|sk2 overrides):
+// Schedule of the split-precision layer kernel (FE_SCHEDULE=dp|sk|sk2|sk2-handover overrides; the last is
+// sk2 with the kernel that publishes and waits also where a workgroup per tile would do):
 //  0 data-parallel, one workgroup per upper tile (the tile by size: split_ring_tile);
 //  1 stream-K over 256 x 256 tiles, one workgroup per CU;
 //  2 stream-K over 128 x 128 tiles, two workgroups per CU (whole-tile rounds first when there
@@ -87,7 +88,7 @@ int use_streamk(int64_t n, const fe_workspace* ws, int prec) {
     if (t_forced_schedule >= 0) return t_forced_schedule;
     const char* env = getenv("FE_SCHEDULE");
     if (env && env[0] == 'd') return 0;
-    if (env && env[0] == 's') return strcmp(env, "sk2") == 0 ? 2 : 1;
+    if (env && env[0] == 's') return strncmp(env, "sk2", 3) == 0 ? 2 : 1;
     const int tuned = tuned_schedule(ws->device, prec, n);
     if (tuned >= 0) return tuned;
     return fe::split_schedule(n, ws->n_cu);
@@ -202,7 +203,8 @@ int run_expansion(const double* H, int64_t n, int64_t ldh, double mu, double kT,
         plan.ring_tile = plan.streamk ? 0 : fe::split_ring_tile(n, ws->n_cu);
         plan.grid = plan.streamk == 2 ? 2 * ws->n_cu : ws->n_cu;
         plan.n_cu = ws->n_cu;
-        plan.hand_over = g_sk_giveup.load() != 0;
+        const char* sched = getenv("FE_SCHEDULE");
+        plan.hand_over = g_sk_giveup.load() != 0 || (sched && strcmp(sched, "sk2-handover") == 0);
         plan.partial = ws->sk_partial;
         plan.own = ws->sk_partial ? ws->sk_partial + (size_t)ws->n_cu * 256 * 256 : nullptr;
         plan.flags = ws->sk_flags;
@@ -758,6 +760,28 @@ int fe_streamk_segments(int64_t np, int32_t schedule, int32_t grid, int32_t w, i
         }
         ++k;
     });
+    *count = k;
+    return FE_OK;
+}
+
+int fe_streamk_tile_segments(int64_t np, int32_t schedule, int32_t grid, int32_t t, int32_t* segs,
+                             int32_t cap, int32_t* count) {
+    if (!count) return fail(FE_ERR_ARG, "count is required");
+    *count = 0;
+    int32_t geom[6], k = 0;
+    const int rc = fe_streamk_segments(np, schedule, grid, -1, geom, nullptr, 0, &k);
+    if (rc != FE_OK) return rc;
+    if (t < geom[3] || t >= geom[1]) return fail(FE_ERR_ARG, "not a stream-K tile of this plan");
+    auto put = [&](int i, int kb0, int kb1) {
+        if (segs && i < cap) {
+            segs[2 * i] = kb0;
+            segs[2 * i + 1] = kb1;
+        }
+        k = i + 1;
+    };
+    const fe::SkGeometry G = fe::split_sk_geometry(np, schedule, grid);
+    if (fe::sk_fits_32(G)) fe::sk_tile_segments<uint32_t>(G, t, put);
+    else fe::sk_tile_segments<int64_t>(G, t, put);
     *count = k;
     return FE_OK;
 }

@@ -133,45 +133,38 @@ k_layer_ring(LayerArgs p) {
 
 // A stream-K layer whose tiles all run at once (sk: the plan of launch_sk): a workgroup per tile sums the
 // segments that the plan's workgroups would have handed to each other, in the order of their epilogue
-// (the finisher's, the last one, first), so the values are the plan's and nothing is published or
+// (sk_tile_segments), so the values are the plan's and nothing is published or
 // waited for. us per density matrix (26 layers), stream-K / this: n = 2048 1815 / 1250, 2500 2367 / 1760,
 // 2816 2680 / 1940 (one chain per element: 1109, 1632, 1862, and 1.3 times the error).
 template <bool BF, class C>
 __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_layer_ring_segments(LayerArgs p, SplitPlan sk) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int ntiles = gridDim.x, nk = (int)(p.np / C::BK), NG = sk.groups, GX = sk.grid / NG;
-    const int t = xcd_tile(blockIdx.x, ntiles);
-    int g = 0;
-    while (t >= (int)((int64_t)ntiles * (g + 1) / NG)) ++g;
-    const int tg0 = (int)((int64_t)ntiles * g / NG), tg1 = (int)((int64_t)ntiles * (g + 1) / NG);
-    const int64_t base = (int64_t)tg0 * nk, total = (int64_t)(tg1 - tg0) * nk;
-    const int64_t it0 = (int64_t)t * nk, it1 = it0 + nk;
-    int jf = (int)((it0 - base) * GX / total), jl = (int)((it1 - 1 - base) * GX / total);
-    while (sk_range_start(base, total, jf + 1, GX) <= it0) ++jf;
-    while (jf > 0 && sk_range_start(base, total, jf, GX) > it0) --jf;
-    while (sk_range_start(base, total, jl + 1, GX) < it1) ++jl;
-    while (jl > 0 && sk_range_start(base, total, jl, GX) >= it1) --jl;
+    SkGeometry G;
+    G.T = (int)(p.np / C::BM);
+    G.ntiles = gridDim.x;
+    G.nk = (int)(p.np / C::BK);
+    G.dp_tiles = 0;
+    G.groups = sk.groups;
+    G.grid = sk.grid;
+    const int t = xcd_tile(blockIdx.x, G.ntiles);
     int I, J;
-    tile_coords(t, (int)(p.np / C::BM), I, J);
+    tile_coords(t, G.T, I, J);
     EpiPre<C> pre;
     if constexpr (EpiPre<C>::PER <= 4) pre.template load<0>(p, I, J);
     Acc<C> sum;
-    for (int k = 0; k <= jl - jf; ++k) {
-        const int jj = k == 0 ? jl : jf + k - 1;
-        const int64_t a = sk_range_start(base, total, jj, GX), b = sk_range_start(base, total, jj + 1, GX);
+    sk_tile_segments<uint32_t>(G, t, [&](int i, int kb0, int kb1) {
         Acc<C> acc;
         zero(acc);
-        ring_products<BF, C, 0>(p, I, J, (int)((a > it0 ? a : it0) - it0), (int)((b < it1 ? b : it1) - it0),
-                                acc, smem);
+        ring_products<BF, C, 0>(p, I, J, kb0, kb1, acc, smem);
 #pragma unroll
         for (int mb = 0; mb < C::MB; ++mb)
 #pragma unroll
             for (int nb = 0; nb < C::NB; ++nb)
 #pragma unroll
                 for (int j = 0; j < 16; ++j)
-                    sum.v[mb][nb][j] = k == 0 ? acc.v[mb][nb][j] : sum.v[mb][nb][j] + acc.v[mb][nb][j];
-    }
+                    sum.v[mb][nb][j] = i == 0 ? acc.v[mb][nb][j] : sum.v[mb][nb][j] + acc.v[mb][nb][j];
+    });
     ring_epilogue<BF, C, 0>(p, sum, t, I, J, smem, false, pre);
 }
 
@@ -356,7 +349,7 @@ hipError_t launch_sk(const LayerArgs& a, const SplitPlan& sk, hipStream_t s) {
     plan.dp_tiles = G.dp_tiles;
     if (plan.grid < 1) return hipErrorInvalidValue;
     if constexpr (C::BM == CfgR128::BM) {
-        if (!plan.hand_over && G.dp_tiles == 0 && G.ntiles <= plan.n_cu) {
+        if (!plan.hand_over && G.dp_tiles == 0 && G.ntiles <= plan.n_cu && sk_fits_32(G)) {
             auto rkern = k_layer_ring_segments<BF, CfgR128>;
             static bool rdone = false;
             e = set_lds(rkern, CfgR128::LDS_BYTES, rdone);

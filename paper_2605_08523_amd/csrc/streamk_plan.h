@@ -1,6 +1,6 @@
 // Work split of the stream-K schedules of the 16-bit layer kernel, shared by the kernel (device)
-// and by the host (the launcher, and fe_streamk_segments, which lets a CPU test walk the same
-// code that the kernel runs).
+// and by the host (the launcher, and fe_streamk_segments and fe_streamk_tile_segments, which let a CPU
+// test walk the same code that the kernels run).
 //
 // The upper tiles [dp_tiles, ntiles) of one layer, times their nk K-blocks each, form a list of
 // (tile, K-block) iterations. The grid is split into `groups` groups (8: one per XCD, since the
@@ -92,6 +92,39 @@ __host__ __device__ __attribute__((always_inline)) inline void sk_walk(const SkG
             it += kb1 - kb0;
         }
     }
+}
+
+// The segments [kb0, kb1) of upper tile t >= dp_tiles in the order in which the workgroup that finishes
+// it adds them (its own, the last, first; then the published partials by workgroup index);
+// f(i, kb0, kb1) is called for the i-th. A kernel that sums them itself gives the plan's values.
+// Int: 32 bits where sk_fits_32 (a runtime 64-bit division is a hundred instructions).
+template <class Int, class F>
+__host__ __device__ __attribute__((always_inline)) inline void sk_tile_segments(const SkGeometry& G, int t,
+                                                                                F&& f) {
+    const Int nk = G.nk, t0 = G.dp_tiles, nsk = G.ntiles - G.dp_tiles;
+    const Int NG = G.groups, GX = G.grid / G.groups;
+    Int g = 0;
+    while ((Int)t >= t0 + nsk * (g + 1) / NG) ++g;
+    const Int tg0 = t0 + nsk * g / NG, tg1 = t0 + nsk * (g + 1) / NG;
+    const Int total = (tg1 - tg0) * nk, it0 = ((Int)t - tg0) * nk, it1 = it0 + nk;   // from tg0's first block
+    auto start = [&](Int jj) { return total * jj / GX; };
+    // the workgroups of the group whose ranges hold the tile's first and last block
+    Int jf = it0 * GX / total, jl = (it1 - 1) * GX / total;
+    while (start(jf + 1) <= it0) ++jf;
+    while (jf > 0 && start(jf) > it0) --jf;
+    while (start(jl + 1) < it1) ++jl;
+    while (jl > 0 && start(jl) >= it1) --jl;
+    for (Int i = 0; i <= jl - jf; ++i) {
+        const Int jj = i == 0 ? jl : jf + i - 1;
+        const Int a = start(jj), b = start(jj + 1);
+        f((int)i, (int)((a > it0 ? a : it0) - it0), (int)((b < it1 ? b : it1) - it0));
+    }
+}
+// Whether its products fit 32 bits: blocks of a group times its workgroups, tiles times groups.
+__host__ __device__ inline bool sk_fits_32(const SkGeometry& G) {
+    const int64_t nsk = G.ntiles - G.dp_tiles, per = (nsk + G.groups - 1) / G.groups;
+    return (per + 1) * G.nk * (G.grid / G.groups + 1) < ((int64_t)1 << 31) &&
+           nsk * (G.groups + 1) < ((int64_t)1 << 31);
 }
 
 }  // namespace fe
