@@ -220,7 +220,7 @@ typedef struct fe_batch_plan fe_batch_plan;
  * of 128), uploads the descriptors (synchronously) and captures the launch sequence into a HIP
  * graph: batched bounds and rescale, the layers (all in one queue launch, or one grouped launch
  * per layer: fe_batch_plan_set_launch), per-matrix traces, then the entropy pass if mS is not NULL (mS must share beta0 and
- * mu0 with m). Precision: FE_PREC_FP16X2, FE_PREC_BF16X2 or FE_PREC_BF16X3 (128 x 128 tiles only;
+ * mu0 with m). Precision: FE_PREC_FP16X2, FE_PREC_BF16X2 or FE_PREC_BF16X3 (plan tile 128 only;
  * 20 instead of 16 B of the arena per padded element). status: device int32[count] or NULL,
  * receives each item's rescale status (FE_OK, FE_WARN_BETA_CLAMPED, FE_ERR_DOMAIN,
  * FE_ERR_NONFINITE); items with an error get NaN outputs. A workspace holds one batch layout: a
@@ -247,7 +247,8 @@ int fe_batch_plan_launch(fe_batch_plan* plan, void* stream);
 /* Rebuilds the plan (layout, tables, captured graph) with layer tiles of `tile` x `tile`, tile
  * 128 or 64 (less padding for small matrices, more LDS traffic per flop). A new plan's tile is 128,
  * and until one of this function and the autotuner is called its kernel takes the 128 x 128 tiles in
- * 64 x 64 pieces where the sizes make that less work. Results differ from the other tile size at
+ * 64 x 64 pieces where the sizes make that less work (fe_batch_plan_kernel_tile tells). The tile of an
+ * FE_PREC_BF16X3 plan stays 128. Results differ from the other tile size at
  * most by the order of FP32 sums. Waits for the device first (a launch of the plan may be in flight), then
  * replaces the captured graph; on failure the plan is left empty and its launches fail. */
 int fe_batch_plan_retile(fe_batch_plan* plan, int32_t tile);
@@ -273,7 +274,8 @@ int fe_batch_plan_retile(fe_batch_plan* plan, int32_t tile);
 int fe_batch_plan_set_launch(fe_batch_plan* plan, int32_t launch);
 
 /* Autotunes the plan's tile size and launch form: builds it with each tile size (128 and 64;
- * FE_PREC_BF16X3 plans have the 128 x 128 tile only) under each launch form (the queue launch
+ * FE_PREC_BF16X3 plans: 128, whole and, where a new plan would take them, in 64 x 64 pieces) under each
+ * launch form (the queue launch
  * where the device allows it, and the per-layer launches), times three replays of each on
  * `stream` (after a warm-up) and keeps the fastest pair. tile (host, may be NULL) receives the
  * chosen tile size, ms (host, 2 entries, may be NULL) the ms per replay for tiles 128 and 64 (the
@@ -283,6 +285,9 @@ int fe_batch_plan_set_launch(fe_batch_plan* plan, int32_t launch);
 int fe_batch_plan_autotune(fe_batch_plan* plan, void* stream, int32_t* tile, double* ms);
 /* The plan's current layer tile size and launch form (host outputs, each may be NULL). */
 int fe_batch_plan_get(const fe_batch_plan* plan, int32_t* tile, int32_t* launch);
+/* The tile size that the plan's layer kernel runs (host): the plan's tile, or 64 where a plan of tile
+ * 128 takes its tiles in 64 x 64 pieces. */
+int fe_batch_plan_kernel_tile(const fe_batch_plan* plan, int32_t* tile);
 int fe_batch_plan_destroy(fe_batch_plan* plan);
 
 /* One-shot batch: create a plan, launch it on `stream`, wait for the stream, destroy the plan. */

@@ -88,6 +88,7 @@ SIGNATURES = {
     "fe_batch_plan_retile": (_I32, [_P, _I32]),
     "fe_batch_plan_set_launch": (_I32, [_P, _I32]),
     "fe_batch_plan_get": (_I32, [_P, C.POINTER(_I32), C.POINTER(_I32)]),
+    "fe_batch_plan_kernel_tile": (_I32, [_P, C.POINTER(_I32)]),
     "fe_batch_plan_autotune": (_I32, [_P, _P, C.POINTER(_I32), C.POINTER(_D)]),
     "fe_autotune": (_I32, [C.POINTER(_I64), _I32, _I32, C.POINTER(_I32), C.POINTER(_D), _P, _P]),
     "fe_autotune_input": (_I32, [_P, _I64, _I64, _D, _D, C.POINTER(fe_model), _I32, C.POINTER(_I32),
@@ -673,6 +674,14 @@ class BatchPlan:
         """fe_batch_plan_get: the layer tile size (128 or 64)."""
         tile = C.c_int32()
         _check(lib().fe_batch_plan_get(self._p, C.byref(tile), None))
+        return tile.value
+
+    @property
+    def kernel_tile(self) -> int:
+        """fe_batch_plan_kernel_tile: the tile size that the layer kernel runs (64 also where a plan of
+        tile 128 takes its tiles in 64 x 64 pieces)."""
+        tile = C.c_int32()
+        _check(lib().fe_batch_plan_kernel_tile(self._p, C.byref(tile)))
         return tile.value
 
     def autotune(self):

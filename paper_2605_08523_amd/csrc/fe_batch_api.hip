@@ -23,8 +23,9 @@ using namespace fehost;
 struct fe_batch_plan {
     uint64_t gen = 0;       // workspace layout generation this plan was built for
     int count = 0;
-    int tile = 128;         // tile size of the layer kernel (128 or 64)
+    int tile = 128;         // tile size of the plan (128 or 64)
     bool by_size = true;    // 128 not asked for: tiles in 64 x 64 pieces where that is less work
+    int kernel_tile = 128;  // tile size of the layer kernel
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     fe_workspace* ws = nullptr;
@@ -373,17 +374,18 @@ int tile_by_size(const std::vector<fe_batch_item>& items, int max_L) {
     return w128 > 1.3 * w64 && tiles64 * max_L <= (double)(1 << 22) ? 64 : 128;
 }
 
+int tile_by_size(const fe_batch_plan& plan) {
+    int max_L = 1;
+    for (const fe_model& m : plan.dens) max_L = std::max(max_L, (int)m.L);
+    for (const fe_model& m : plan.ent) max_L = std::max(max_L, (int)m.L);
+    return tile_by_size(plan.items, max_L);
+}
+
 // Builds and captures `plan` for its stored inputs with layer tiles of `want` (128 or 64): item i
 // runs model dens[model[i]] (and ent[model[i]] for the entropy pass when ent is non-empty).
 int build_plan(fe_batch_plan* plan, int want) {
     release_plan(plan);
-    int tile = want;
-    if (want == 128 && plan->by_size) {
-        int max_L = 1;
-        for (const fe_model& m : plan->dens) max_L = std::max(max_L, (int)m.L);
-        for (const fe_model& m : plan->ent) max_L = std::max(max_L, (int)m.L);
-        tile = tile_by_size(plan->items, max_L);
-    }
+    const int tile = want == 128 && plan->by_size ? tile_by_size(*plan) : want;
     const fe_batch_item* items = plan->items.data();
     const int count = plan->count;
     const std::vector<int>& model = plan->model;
@@ -477,6 +479,7 @@ int build_plan(fe_batch_plan* plan, int want) {
     const std::vector<LayerLaunch> ll_e = launches_of(km_e);
 
     plan->tile = want;
+    plan->kernel_tile = tile;
     // device tables: [density coef | L | d0 | shift0 | entropy ...], 256-byte aligned parts
     auto al = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t cd = al(td.coef.size() * 4), ld = al(td.L.size() * 4), dd = al(td.d0.size() * 4);
@@ -735,7 +738,7 @@ int fe_batch_plan_retile(fe_batch_plan* plan, int32_t tile) {
     if (!plan) return fail(FE_ERR_ARG, "invalid plan");
     if (tile != 64 && tile != 128) return fail(FE_ERR_ARG, "tile must be 64 or 128");
     if (tile == 64 && plan->prec == FE_PREC_BF16X3)
-        return fail(FE_ERR_ARG, "the three-part BF16 split runs 128 x 128 tiles only");
+        return fail(FE_ERR_ARG, "the tile of a three-part BF16 plan is 128 (taken in 64 x 64 pieces by size)");
     FE_HIP(hipDeviceSynchronize());   // a launch of the old graph may still be reading its tables
     plan->by_size = false;
     return build_plan(plan, tile);
@@ -769,24 +772,29 @@ int fe_batch_plan_autotune(fe_batch_plan* plan, void* stream, int32_t* tile, dou
         const int rc = queue_support(&nq, &queue_ok);
         if (rc != FE_OK) return rc;
     }
-    // candidates: tile x launch form (the three-part split has the 128 x 128 tile only)
+    // candidates: tile x launch form. A three-part plan's tile is 128, whole or, where a new plan would
+    // take them, in 64 x 64 pieces (for two parts that is tile 64).
     struct Cand {
         int tile, launch;
+        bool by_size;
         double ms;
     };
     std::vector<Cand> cands;
-    plan->by_size = false;
-    for (int t : {128, 64}) {
-        if (t == 64 && plan->prec == FE_PREC_BF16X3) continue;
-        if (queue_ok) cands.push_back({t, FE_BATCH_LAUNCH_QUEUE, NAN});
-        cands.push_back({t, FE_BATCH_LAUNCH_LAYERS, NAN});
-    }
+    const bool three = plan->prec == FE_PREC_BF16X3;
+    auto add = [&](int t, bool by_size) {
+        if (queue_ok) cands.push_back({t, FE_BATCH_LAUNCH_QUEUE, by_size, NAN});
+        cands.push_back({t, FE_BATCH_LAUNCH_LAYERS, by_size, NAN});
+    };
+    add(128, false);
+    if (!three) add(64, false);
+    else if (tile_by_size(*plan) == 64) add(128, true);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     FE_HIP(hipEventCreate(&e0));
     hipError_t e = hipEventCreate(&e1);
     int rc = FE_OK;
     for (size_t c = 0; c < cands.size() && rc == FE_OK && e == hipSuccess; ++c) {
         plan->launch = cands[c].launch;
+        plan->by_size = cands[c].by_size;
         rc = build_plan(plan, cands[c].tile);
         if (rc != FE_OK) break;
         for (int rep = 0; rep < 4 && e == hipSuccess; ++rep) {   // one warm-up, three timed
@@ -802,7 +810,8 @@ int fe_batch_plan_autotune(fe_batch_plan* plan, void* stream, int32_t* tile, dou
     (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     if (e != hipSuccess || rc != FE_OK) {
-        // leave the plan usable: the default form at 128 x 128
+        // leave the plan usable: the default form
+        plan->by_size = true;
         plan->launch = queue_ok ? plan->default_launch : FE_BATCH_LAUNCH_LAYERS;
         (void)build_plan(plan, 128);
         return e != hipSuccess ? hip_fail(e, "batch autotune") : rc;
@@ -818,8 +827,9 @@ int fe_batch_plan_autotune(fe_batch_plan* plan, void* stream, int32_t* tile, dou
         }
     }
     if (tile) *tile = cands[best].tile;
-    if (plan->tile == cands[best].tile && plan->launch == cands[best].launch) return FE_OK;
+    if (best + 1 == cands.size()) return FE_OK;   // the one built last
     plan->launch = cands[best].launch;
+    plan->by_size = cands[best].by_size;
     return build_plan(plan, cands[best].tile);
 }
 
@@ -827,6 +837,12 @@ int fe_batch_plan_get(const fe_batch_plan* plan, int32_t* tile, int32_t* launch)
     if (!plan) return fail(FE_ERR_ARG, "invalid plan");
     if (tile) *tile = plan->tile;
     if (launch) *launch = plan->launch;
+    return FE_OK;
+}
+
+int fe_batch_plan_kernel_tile(const fe_batch_plan* plan, int32_t* tile) {
+    if (!plan || !tile) return fail(FE_ERR_ARG, "plan and tile are required");
+    *tile = plan->kernel_tile;
     return FE_OK;
 }
 
