@@ -383,14 +383,15 @@ int fe_matrix_backward(const float* hist, int64_t n, const double* theta, int32_
 /* ---- schedule autotuner -------------------------------------------------------------------- */
 
 /* Chooses the tile shape and schedule of the 16-bit layer kernel per matrix size on this device:
- * 0 = 128 x 128 tiles, one workgroup per upper tile; 1 = 256 x 256 tiles, stream-K over one
- * workgroup per CU; 2 = 128 x 128 tiles, stream-K over two workgroups per CU (1 and 2 need a
+ * 0 = one workgroup per upper tile (64 x 64 or 128 x 128 tiles by size); 1 = 256 x 256 tiles,
+ * stream-K over one workgroup per CU; 2 = 128 x 128 tiles, stream-K over two workgroups per CU (1 and 2 need a
  * workspace with max_n >= 1536). Each candidate runs a short expansion (1 warm-up + 3 timed, HIP
  * events on the stream) of a device-generated random symmetric matrix of each size; the fastest
  * is recorded process-wide for (device, prec, size). The timing model is a 6-layer SP2 recursion
  * with a small accumulator weight on every layer (the accumulator epilogue runs every second
  * layer, as in trained models). Later expansions of a size within a factor
- * sqrt(2) of a tuned one use its schedule (FE_SCHEDULE still overrides). sizes: host, count
+ * sqrt(2) of a tuned one whose tiles run in the same form (all at once as 64 x 64 or as 128 x 128
+ * tiles, or in several rounds) use its schedule (FE_SCHEDULE still overrides). sizes: host, count
  * entries, each <= ws max_n. choice (host, count, may be NULL) receives the chosen schedules, ms
  * (host, 3 x count, may be NULL) each candidate's time per expansion (NaN if not run). prec:
  * FE_PREC_FP16X2 or FE_PREC_BF16X2. Allocates one n_max x n_max FP64 matrix for the call;

@@ -31,7 +31,10 @@ constexpr int64_t kSmallN64 = 128;       // FP64 up to this size takes at most k
 // default by size (split_schedule has the figures). Only workspaces sized for n >= kStreamKMinN carry the
 // stream-K buffers.
 // Schedules chosen by fe_autotune: (device, precision, size) -> schedule, process-wide. A
-// size uses the entry of the nearest tuned size within a factor sqrt(2).
+// size uses the entry of the nearest tuned size within a factor sqrt(2) whose one-round tile is its own
+// (split_ring_tile: 64, 128 or none), for that tile decides which kernels the schedules stand for: 0 is
+// the ring up to the last size of one round (n = 2816: 1862 us against stream-K's 1940) and the
+// register-staged tiles in uneven rounds beyond (2900: 3.61 ms against 2.94).
 struct TunedEntry {
     int device, prec;
     int64_t n;
@@ -68,12 +71,14 @@ bool layer_events_on() {
 constexpr uint32_t kNeverEpoch = 0xFFFFFFFFu;   // no launch publishes this value
 thread_local int t_forced_schedule = -1;   // set by the tuner around its timing runs
 
-int tuned_schedule(int device, int prec, int64_t n) {
+int tuned_schedule(int device, int prec, int64_t n, int n_cu) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     int best = -1;
     double dist = 0.5;   // |log2(n / n_tuned)|
     for (const TunedEntry& t : g_tuned) {
-        if (t.device != device || t.prec != prec) continue;
+        if (t.device != device || t.prec != prec ||
+            fe::split_ring_tile(t.n, n_cu) != fe::split_ring_tile(n, n_cu))
+            continue;
         const double d = fabs(log2((double)n / (double)t.n));
         if (d <= dist) {
             dist = d;
@@ -89,7 +94,7 @@ int use_streamk(int64_t n, const fe_workspace* ws, int prec) {
     const char* env = getenv("FE_SCHEDULE");
     if (env && env[0] == 'd') return 0;
     if (env && env[0] == 's') return strncmp(env, "sk2", 3) == 0 ? 2 : 1;
-    const int tuned = tuned_schedule(ws->device, prec, n);
+    const int tuned = tuned_schedule(ws->device, prec, n, ws->n_cu);
     if (tuned >= 0) return tuned;
     return fe::split_schedule(n, ws->n_cu);
 }
