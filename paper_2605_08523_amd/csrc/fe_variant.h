@@ -52,11 +52,14 @@ struct SquareSplit {
 };
 SquareSplit square_split(int ntiles, int nk, int slots);
 constexpr int64_t kSquarePartTile = 128 * 128;   // floats per partial tile
+// Whether operands start on 16 bytes: the ring tiles load them in 16-byte chunks straight to LDS. The
+// caller's scratch may start on any float; then the register-staged tiles run (launch_square_combine does not).
+bool square_aligned(const void* operands);
 hipError_t launch_square(const uint16_t* hi, const uint16_t* lo, int64_t np, float* out, int bf16,
                          int slots, float* parts, hipStream_t s);
 // That and the combine a after it in one launch, where the tiles run at once (split_ring_tile(np, n_cu)
-// is not 0): x takes the place of a.term[tx] and a.acc_src and is stored in x_out unless NULL; a.hi and
-// a.lo are other buffers than hi and lo; not the first or last combine.
+// is not 0) and the operands are square_aligned: x takes the place of a.term[tx] and a.acc_src and is
+// stored in x_out unless NULL; a.hi and a.lo are other buffers than hi and lo; not the first or last combine.
 hipError_t launch_square_combine(const uint16_t* hi, const uint16_t* lo, const CombineArgs& a, int tx,
                                  float* x_out, int n_cu, hipStream_t s);
 

@@ -102,7 +102,7 @@ int fe_expand_density_variant(const double* H, int64_t n, int64_t ldh, double mu
     // Where the tiles run at once a squaring and the next layer's combine are one launch, and the operands
     // alternate between two buffers; the second lies where the squaring's partial tiles would be (a
     // round of slots, so two tiles per CU: at least as large).
-    const bool fused = fe::split_ring_tile(np, slots / 2) != 0 &&
+    const bool fused = fe::split_ring_tile(np, slots / 2) != 0 && fe::square_aligned(hi) &&
                        2 * e * sizeof(uint16_t) <= (size_t)slots * fe::kSquarePartTile * sizeof(float);
     uint16_t* const ops[2] = {hi, reinterpret_cast<uint16_t*>(parts)};
     // Layer i's combine, and the squaring of its operand into x_dst if nothing follows in one launch.

@@ -546,7 +546,7 @@ hipError_t launch_square_combine_t(const uint16_t* hi, const uint16_t* lo, const
 template <bool BF>
 hipError_t launch_square_t(const uint16_t* hi, const uint16_t* lo, int64_t np, float* out,
                            int slots, float* parts, hipStream_t s) {
-    switch (split_ring_tile(np, slots / 2)) {
+    switch (square_aligned(hi) ? split_ring_tile(np, slots / 2) : 0) {
         case 64:
             return lone_tiles(np, slots / 2) ? launch_square_ring<BF, CfgQ64L>(hi, lo, np, out, s)
                                              : launch_square_ring<BF, CfgQ64>(hi, lo, np, out, s);
@@ -605,6 +605,8 @@ SquareSplit square_split(int ntiles, int nk, int slots) {
     return sp;
 }
 
+bool square_aligned(const void* operands) { return reinterpret_cast<uintptr_t>(operands) % 16 == 0; }
+
 hipError_t launch_square(const uint16_t* hi, const uint16_t* lo, int64_t np, float* out, int bf16,
                          int slots, float* parts, hipStream_t s) {
     if (np % CfgQ::BM != 0) return hipErrorInvalidValue;
@@ -614,8 +616,8 @@ hipError_t launch_square(const uint16_t* hi, const uint16_t* lo, int64_t np, flo
 
 hipError_t launch_square_combine(const uint16_t* hi, const uint16_t* lo, const CombineArgs& a, int tx,
                                  float* x_out, int n_cu, hipStream_t s) {
-    if (a.np % CfgQ::BM != 0 || a.out || a.acc_first || a.nterm < 1 || a.nterm > kCombineMaxTerms ||
-        a.nacc < 0 || a.nacc > kCombineMaxAcc || hi == a.hi || lo == a.lo)
+    if (a.np % CfgQ::BM != 0 || !square_aligned(hi) || !square_aligned(lo) || a.out || a.acc_first ||
+        a.nterm < 1 || a.nterm > kCombineMaxTerms || a.nacc < 0 || a.nacc > kCombineMaxAcc || hi == a.hi || lo == a.lo)
         return hipErrorInvalidValue;
     switch (split_ring_tile(a.np, n_cu)) {
         case 64:
