@@ -100,46 +100,52 @@ def timed(fn, steps, warmup, torch):
     return e0.elapsed_time(e1) / steps     # ms per call
 
 
-KERNEL_SOURCES = ("fe_api.hip", "fe_internal.h", "k_layer_split.hip", "split_common.h")
+KERNEL_SOURCES = ("fe_api.hip", "fe_internal.h", "k_layer_split.hip", "split_common.h", "streamk_plan.h")
 COUNTER_SUMMARY = os.path.join(ROOT, "profiles", "k_layer_split_counters_anderson4096.md")
 SQ_SUMMARY = os.path.join(ROOT, "profiles", "k_layer_split_sq_counters_anderson4096.md")
 TRACE_SUMMARY = os.path.join(ROOT, "profiles", "k_layer_split_anderson4096_fp16x2.md")
 
 
-def _profile_record(path, tag):
-    """The JSON record after `tag:` in a committed profile summary, or None if it is missing or
-    the layer kernel's sources changed since the counters were taken (SHA-256 over them)."""
+def layer_kernel(schedule, prec):
+    """The layer kernel of a schedule at N = 4096, as the profile summaries name it."""
+    form = {"sk2x128": "k_layer_sk<{},128>", "sk256": "k_layer_sk<{},256>", "dp128": "k_layer_dp<{},128>"}
+    return form[schedule].format({"fp16x2": "fp16", "bf16x2": "bf16"}[prec])
+
+
+def _profile_record(path, tag, kernel=None):
+    """The first JSON record after `tag:` in a committed profile summary that was taken with the layer
+    kernel's present sources (SHA-256 over them) and, if `kernel` is given, of that kernel; else None."""
     import hashlib
-    try:
-        line = next(l for l in open(path) if l.startswith(tag + ":"))
-        rec = json.loads(line.split(":", 1)[1])
-    except (OSError, StopIteration, ValueError):
-        return None
     h = hashlib.sha256()
     for f in KERNEL_SOURCES:
         with open(os.path.join(ROOT, "paper_2605_08523_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
-    return rec if h.hexdigest() == rec.get("source_sha256") else None
+    try:
+        recs = [json.loads(l.split(":", 1)[1]) for l in open(path) if l.startswith(tag + ":")]
+    except (OSError, ValueError):
+        return None
+    for rec in recs:
+        if rec.get("source_sha256") == h.hexdigest() and kernel in (None, rec.get("kernel")):
+            return rec
+    return None
 
 
-def measured_traffic():
-    """HBM bytes per layer launch from the committed rocprofv3 FETCH_SIZE/WRITE_SIZE summary
-    (copy-calibrated), or None if the layer kernel's sources changed since it was taken."""
-    rec = _profile_record(COUNTER_SUMMARY, "traffic_json")
+def measured_traffic(kernel=None):
+    """HBM bytes per launch of `kernel` from the committed rocprofv3 FETCH_SIZE/WRITE_SIZE summary
+    (copy-calibrated), or None if there is none of it with the present sources."""
+    rec = _profile_record(COUNTER_SUMMARY, "traffic_json", kernel)
     return rec["bytes_per_launch"] if rec else None
 
 
-def measured_profile():
-    """The rocprofv3 kernel-trace average of the layer kernel and the event figure of the same
-    session, from the committed summary (None if the layer kernel's sources changed since)."""
-    rec = _profile_record(TRACE_SUMMARY, "trace_json")
-    return rec
+def measured_profile(kernel=None):
+    """The rocprofv3 kernel-trace average of `kernel` and the event figure of the same session, from the
+    committed summary (None as above)."""
+    return _profile_record(TRACE_SUMMARY, "trace_json", kernel)
 
 
-def measured_pipe_busy():
-    """Clock and MFMA-pipe occupancy of the layer kernel from the committed SQ-counter summary
-    (None if stale)."""
-    rec = _profile_record(SQ_SUMMARY, "sq_json")
+def measured_pipe_busy(kernel=None):
+    """Clock and MFMA-pipe occupancy of `kernel` from the committed SQ-counter summary (None as above)."""
+    rec = _profile_record(SQ_SUMMARY, "sq_json", kernel)
     return {k: rec[k] for k in ("clock_ghz", "mfma_pipe_busy", "vendor_gemm_mfma_pipe_busy")} if rec else None
 
 
@@ -305,19 +311,19 @@ def main():
             "peak": peak,
             "unit": "TFLOP/s",
             "frac": achieved / peak,
-            "traffic": measured_traffic(),
+            "traffic": measured_traffic(layer_kernel(sched, args.prec)),
             "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
             "layer_ms": layer_ms,
             "executed_mfma_tflops": exec_flop_layer / (layer_ms * 1e-3) / 1e12,
             "executed_frac": exec_flop_layer / (layer_ms * 1e-3) / 1e12 / peak,
-            "sq_counters": measured_pipe_busy(),
+            "sq_counters": measured_pipe_busy(layer_kernel(sched, args.prec)),
             "schedule": sched,
             "method": (f"HIP events recorded by the library on the launch stream around each of the "
                        f"{L} layer launches of an expansion, mean over {lay['launches']} launches "
                        f"(median {lay['median']:.4f} ms); by differencing expansions, "
                        f"(t(L={L}) - t(L=1)) / {L - 1} = {layer_ms_diff:.4f} ms"),
             "layer_ms_by_differencing": layer_ms_diff,
-            "profile": measured_profile(),
+            "profile": measured_profile(layer_kernel(sched, args.prec)),
         },
         "prologue_plus_one_layer_ms": ms1,
         "autotune": tuned,
