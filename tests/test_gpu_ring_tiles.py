@@ -1,7 +1,8 @@
 """One-round data-parallel layers (64 x 64 and 128 x 128 tiles, direct-to-LDS operand ring) at the
 edges of their tiles and of the sizes they are chosen for (n <= 1984 and n <= 2816 on 256 compute
-units): they take the same products in the same order as the batch's register-staged 128 x 128
-kernel, so D is bitwise that of a batch of one. The traces are FP64 sums of the same values in
+units): they take the same products in the same order as a batch of one, whose launch form and tile
+are other ones, or the same ring tiles in another launch (the register-staged kernel is the partner at
+n = 2817 alone), so D is bitwise the batch's. The traces are FP64 sums of the same values in
 another order: n^2 additions of at most 1 each, 2^-53 relative each."""
 import pytest
 
