@@ -4,15 +4,15 @@
 // Work items are (matrix, upper tile, layer). Each matrix belongs to one XCD; XCD x's items form
 // its own queue, ordered layer-major (all items of layer 0 of its matrices, then layer 1, ...).
 // A workgroup (as many are launched as run at once) reads its XCD from the hardware and takes tickets
-// of that queue until it is exhausted. Item (m, t, l) starts once matrix m has
+// of that queue until it is exhausted (in the staged form one per workgroup). Item (m, t, l) starts once matrix m has
 // completed l x (tiles of m) items, i.e. its whole layer l - 1. Every wait is on items of smaller
 // tickets of the same queue, each held by a running workgroup (a ticket is taken only by a
 // running workgroup, which holds it until that item is done), so the smallest unfinished ticket
 // can always proceed: no deadlock, whatever the number of resident workgroups. A matrix's
 // producers and consumers share one L2 (its XCD's), so a hand-off needs the producer's stores to
-// have completed (they are then in that L2) and the consumer CU's L1 to be invalidated (one
-// invalidate per workgroup); no L2 write-back is involved. Instead of the invalidate the consumers
-// load with sc1, which does not take the L1's word for it.
+// have completed (they are then in that L2) and the consumer to get past its CU's L1: the ring's loads
+// carry sc1, which does not take the L1's word for it, and the staged form invalidates the L1 once per
+// workgroup. No L2 write-back is involved.
 //
 // The counters that workgroups poll and add to sit on a 128-byte line each: side by side, the polls and
 // additions of all XCDs met on a few lines, and a batch of 60 matrices (n 64 ... 768, 64 x 64 tiles) took
@@ -45,11 +45,13 @@ inline int64_t batch_queue_counters(int nq, int count) {
 
 // Zeroes Q's counters (a kernel, so that the plan's captured graph holds no memset node).
 hipError_t launch_batch_queue_reset(const BatchQueue& Q, int count, hipStream_t s);
-// One pass over every layer of every matrix (q.layer, q.parity and q.map unused) on `grid`
-// workgroups: the number of queues times the longest queue (the hardware deals consecutive
-// workgroups to consecutive XCDs, so each XCD gets the same number).
-// staged (128 x 128 tiles): operands through registers and a workgroup per item, for batches of many
-// operands (k_batched.hip); the per-layer launch likewise.
+// One pass over every layer of every matrix (q.layer, q.parity and q.map unused) on at most `grid`
+// workgroups, the number of queues times the longest queue (the hardware deals consecutive
+// workgroups to consecutive XCDs, so each XCD gets the same number): as many as run at once, each of which
+// loops over the queue.
+// staged (128 x 128 tiles): operands through registers, `grid` workgroups of one item each and an L1
+// invalidate before the item's plain loads, for batches of many operands (k_batched.hip); the per-layer
+// launch likewise.
 hipError_t launch_batch_queue(const BatchLayerArgs& q, const BatchQueue& Q, int64_t grid, int bf16,
                               int tile, int staged, hipStream_t s);
 hipError_t launch_batch_layer_staged(const BatchLayerArgs& q, int grid, int bf16, hipStream_t s);

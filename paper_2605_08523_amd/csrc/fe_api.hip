@@ -33,8 +33,8 @@ constexpr int64_t kSmallN64 = 128;       // FP64 up to this size takes at most k
 // Schedules chosen by fe_autotune: (device, precision, size) -> schedule, process-wide. A
 // size uses the entry of the nearest tuned size within a factor sqrt(2) whose one-round tile is its own
 // (split_ring_tile: 64, 128 or none), for that tile decides which kernels the schedules stand for: 0 is
-// the ring up to the last size of one round (n = 2816: 1862 us against stream-K's 1940) and the
-// register-staged tiles in uneven rounds beyond (2900: 3.61 ms against 2.94).
+// the ring up to the last size of one round (n = 2816: 1.90 ms against 1.97 for stream-K's segments) and
+// the register-staged tiles in uneven rounds beyond (2900: 3.32 ms against 2.98).
 struct TunedEntry {
     int device, prec;
     int64_t n;

@@ -358,8 +358,10 @@ void release_plan(fe_batch_plan* plan) {
 }
 
 // Tile of the layer kernel of a plan that leaves it open. Small matrices waste much of their 128 x 128
-// tiles; a 64 x 64 tile takes about 1.33 times as long per element (its operand panels pass through
-// LDS twice as often). us per batch with 128 / 64 tiles, and their ratio of work: 60 matrices of
+// tiles; a 64 x 64 tile takes longer per element (its operand panels pass through LDS twice as often). The
+// rule compares the tiles that hold data; the kernel also runs the 64 x 64 tiles between the last of those
+// and the padded size (a multiple of 128), so the line is fitted to times that include them, not derived.
+// us per batch with 128 / 64 tiles, and the ratio of that work: 60 matrices of
 // n 64 ... 768 1367 / 1513 (1.19), 30 of 16 ... 768 630 / 730 (1.22), 8 of 128 ... 768 634 / 771 (1.25);
 // 60 of 128 ... 384 719 / 672 (1.36), 12 of 128 ... 512 400 / 372 (1.37), 30 of 64 ... 256 311 / 228 (1.38).
 // The work table of the queue launch (16 bytes per item) bounds it: at most 64 MiB with 64 x 64 tiles.

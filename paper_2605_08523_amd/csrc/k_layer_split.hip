@@ -134,8 +134,9 @@ k_layer_ring(LayerArgs p) {
 // A stream-K layer whose tiles all run at once (sk: the plan of launch_sk): a workgroup per tile sums the
 // segments that the plan's workgroups would have handed to each other, in the order of their epilogue
 // (sk_tile_segments), so the values are the plan's and nothing is published or
-// waited for. us per density matrix (26 layers), stream-K / this: n = 2048 1815 / 1250, 2500 2367 / 1760,
-// 2816 2680 / 1940 (one chain per element: 1109, 1632, 1862, and 1.3 times the error).
+// waited for. us per density matrix (26 layers), stream-K / this: n = 2048 1874 / 1218, 2500 2399 / 1771,
+// 2816 2629 / 1967 (one chain per element: 1086, 1640, 1895, and 1.3 times the error). With 64-bit divisions
+// in the walk 2048 took 1245.
 template <bool BF, class C>
 __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_layer_ring_segments(LayerArgs p, SplitPlan sk) {
@@ -378,9 +379,9 @@ hipError_t launch_sk(const LayerArgs& a, const SplitPlan& sk, hipStream_t s) {
 // Where the lines lie (ms per density matrix, 26 layers, random dense; 256 CUs): two 64 x 64 tiles
 // fit a CU, so up to 512 of them run at once (n <= 1984; two parts take stream-K's segments from
 // n = 1921): n = 1001 0.48 against 1.15 with 128 x 128 register-staged tiles (0.36 since). At n = 2048,
-// 528 tiles need a second round for 16 of them: 1.58 against 1.29 for the 128 x 128 ring, which takes
-// one round up to n = 2816 (2.13 against 2.62 for stream-K); at n = 2900 its second round makes it
-// 3.61 against 2.94.
+// 528 tiles need a second round for 16 of them: 1.58 against 1.09 for the 128 x 128 ring, which takes
+// one round up to n = 2816 (1.90 against 2.63 for stream-K); at n = 2900 a second round makes it
+// 3.61 on the ring and 3.32 register-staged against 2.98.
 int split_ring_tile(int64_t n, int n_cu) {
     auto tiles = [n](int64_t bm) {
         const int64_t T = (n + bm - 1) / bm;
@@ -399,7 +400,9 @@ bool split_resident(int64_t n, int n_cu) {
 // Stream-K over 128 x 128 tiles when each of its workgroups (two per CU) gets at least eight K-blocks;
 // with fewer the partial-tile traffic outweighs the balance. From eight whole rounds on (n >= 11521) the
 // uneven last one costs less than the partial tiles: ms per density matrix, stream-K / data-parallel,
-// dense 12000 150 / 146, banded 12000 201 / 182, 16384 463 / 441 (10000, six rounds: 106 / 111). Not
+// dense 12000 150 / 146, banded 12000 201 / 182, 16384 463 / 441 (10000, six rounds: 106 / 111). Only the
+// last two rounds were summed in segments; |dD|_F against an FP64 recursion, data-parallel over stream-K:
+// dense 11600 1.001, 12800 1.000, 16384 1.000, banded 11600 and 16384 1.000, BF16x2 dense 12000 1.001. Not
 // taken, though faster: 128 x 128 ring tiles in segments of 512 products (4096 6.56 / 5.95) and 256 x 256
 // tiles (5500 17.8 / 12.9): their sums round otherwise, and on dense matrices at beta' ~ 100, where one
 // rounding more or less shows as 1e-4 of D, the values moved by that.
