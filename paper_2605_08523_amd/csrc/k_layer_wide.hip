@@ -18,38 +18,17 @@
 #include <type_traits>
 
 #include "fe_internal.h"
+#include "mfma_wide.h"
 #include "resident.h"
 #include "split_common.h"
 
 namespace fe {
 namespace {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef double doublex4 __attribute__((ext_vector_type(4)));
-
-template <typename T>
-struct Mfma;
-
-// v_mfma_f32_16x16x4f32: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16];
-// acc[i] of lane l holds D[4 (l / 16) + i][l % 16].
-template <>
-struct Mfma<float> {
-    using vec = floatx4;
-    __device__ static vec mma(float a, float b, vec c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    __device__ static int crow(int lane, int i) { return 4 * (lane >> 4) + i; }
-};
-
-// v_mfma_f64_16x16x4f64: the same operands; acc[i] of lane l holds D[4 i + l / 16][l % 16].
-template <>
-struct Mfma<double> {
-    using vec = doublex4;
-    __device__ static vec mma(double a, double b, vec c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    __device__ static int crow(int lane, int i) { return 4 * i + (lane >> 4); }
-};
+using split::wave_sum;
+using wide::doublex4;
+using wide::floatx4;
+using wide::Mfma;
 
 constexpr int kPad = 64;      // padding unit of the matrices (a multiple of every tile)
 constexpr int NT = 256;       // 4 waves, 2 x 2
@@ -68,11 +47,6 @@ struct WCfg {
     static constexpr size_t EPI = (size_t)BM * LDY * sizeof(double);
     static constexpr size_t LDS = (size_t)S * STAGE > EPI ? (size_t)S * STAGE : EPI;
 };
-
-__device__ inline double wave_sum(double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 // a y + b x + c with the roundings spelled out: the order the compiler picks for the plain expression
 // varies from kernel to kernel, and in FP32 that alone moves a trained gradient by 2.5e-5.

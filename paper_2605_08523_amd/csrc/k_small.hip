@@ -13,34 +13,15 @@
 // np + 4 elements: a fragment read (16 rows x 4 k) then touches every bank once per 256 bytes.
 #include <math.h>
 
-#include <type_traits>
-
 #include "fe_internal.h"
+#include "mfma_wide.h"
 #include "rescale_params.h"
+#include "split_common.h"
 
 namespace fe {
 namespace {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef double doublex4 __attribute__((ext_vector_type(4)));
-
-__device__ inline double wave_sum(double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// Lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]; acc[i] of lane l holds column l % 16 of row
-// crow(l, i).
-__device__ inline floatx4 mma(float a, float b, floatx4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-__device__ inline doublex4 mma(double a, double b, doublex4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-template <typename T>
-__device__ inline int crow(int lane, int i) {
-    return sizeof(T) == 8 ? 4 * i + (lane >> 4) : 4 * (lane >> 4) + i;
-}
+using split::wave_sum;
 
 template <typename T, int NB>
 struct SmallCfg {
@@ -56,7 +37,8 @@ struct SmallCfg {
 template <typename T, int NB>
 __global__ void __launch_bounds__((SmallCfg<T, NB>::NT)) k_small(SmallArgs p) {
     using C = SmallCfg<T, NB>;
-    using vec = typename std::conditional<sizeof(T) == 8, doublex4, floatx4>::type;
+    using M = wide::Mfma<T>;
+    using vec = typename M::vec;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     T* const X0 = reinterpret_cast<T*>(smem);
     double* const sH = reinterpret_cast<double*>(smem + C::BUF);
@@ -131,7 +113,7 @@ __global__ void __launch_bounds__((SmallCfg<T, NB>::NT)) k_small(SmallArgs p) {
     int row[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        row[k] = I * 16 + crow<T>(lane, k);
+        row[k] = I * 16 + M::crow(lane, k);
         x[k] = mine ? start(row[k], col) : (T)0;
         acc_d[k] = (T)p.theta[3] * x[k];
     }
@@ -150,7 +132,7 @@ __global__ void __launch_bounds__((SmallCfg<T, NB>::NT)) k_small(SmallArgs p) {
             b[s] = fb[buf * BUFE + 4 * s];
         }
 #pragma unroll
-        for (int s = 0; s < 4 * NB; ++s) y = mma(a[s], b[s], y);
+        for (int s = 0; s < 4 * NB; ++s) y = M::mma(a[s], b[s], y);
         return y;
     };
     auto value = [&](const double* th, const vec& y, int k) -> T {
