@@ -231,7 +231,7 @@ int enqueue_pass(fe_workspace* ws, int count, int64_t max_np, const fe::BatchCoe
                  const std::vector<LayerLaunch>& launches, const QueueLaunch* queue, double alpha,
                  int entropy, int bf, int tile, int staged, int32_t* status, hipStream_t s) {
     if (!entropy) FE_HIP(fe::launch_batch_bounds(ws->bmats, count, max_np, ws->bparams, s));
-    FE_HIP(fe::launch_batch_rescale(ws->bmats, count, max_np, ws->bparams, alpha, cf, bf, s));
+    FE_HIP(fe::launch_batch_rescale(ws->bmats, count, max_np, ws->bparams, alpha, cf, bf, !staged, s));
     if (queue) {
         fe::BatchLayerArgs q{};
         q.mats = ws->bmats;

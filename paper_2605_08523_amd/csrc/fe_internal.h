@@ -247,8 +247,10 @@ constexpr int kBatchPad = 128;   // batch matrices are padded to a multiple of t
 hipError_t launch_batch_bounds(const BatchMat* mats, int count, int64_t max_n, Params* P,
                                hipStream_t s);
 // bf16 (here and below): 0 FP16x2, 1 BF16x2, 2 three-part BF16 (BatchMat mid[] set).
+// mirror: X and A below the diagonal of a diagonal tile mirror what lies above it (for the ring tiles,
+// whose epilogue updates both; the register-staged tiles read neither there).
 hipError_t launch_batch_rescale(const BatchMat* mats, int count, int64_t max_np, const Params* P,
-                                double alpha, BatchCoef cf, int bf16, hipStream_t s);
+                                double alpha, BatchCoef cf, int bf16, int mirror, hipStream_t s);
 // One layer over `grid` workgroups: with q.map, the slots of the map (the tiles of the matrices
 // whose model has more than q.layer layers, each matrix on one XCD); without, the first `grid`
 // tiles of the grouped grid.
