@@ -49,12 +49,12 @@ hipError_t launch_batch_queue_reset(const BatchQueue& Q, int count, hipStream_t 
 // workgroups, the number of queues times the longest queue (the hardware deals consecutive
 // workgroups to consecutive XCDs, so each XCD gets the same number): as many as run at once, each of which
 // loops over the queue.
-// staged (128 x 128 tiles): operands through registers, `grid` workgroups of one item each and an L1
-// invalidate before the item's plain loads, for batches of many operands (k_batched.hip); the per-layer
-// launch likewise.
+// big, 128 x 128 tiles: operands staged through registers, `grid` workgroups of one item each and an L1
+// invalidate before the item's plain loads, for batches of many operands (k_batched.hip). big, 64 x 64 tiles
+// (two parts): matrices past kLeanMaxNp. The per-layer launch likewise.
 hipError_t launch_batch_queue(const BatchLayerArgs& q, const BatchQueue& Q, int64_t grid, int bf16,
-                              int tile, int staged, hipStream_t s);
-hipError_t launch_batch_layer_staged(const BatchLayerArgs& q, int grid, int bf16, hipStream_t s);
+                              int tile, int big, hipStream_t s);
+hipError_t launch_batch_layer_big(const BatchLayerArgs& q, int grid, int bf16, int tile, hipStream_t s);
 // Whether the queue launch's assumptions hold on the current device with nq XCDs: consecutive
 // workgroups run on consecutive XCDs (round-robin, from whichever XCD the dispatch starts at), and
 // each reads its XCD's id from the hardware (a probe launch; synchronizes).

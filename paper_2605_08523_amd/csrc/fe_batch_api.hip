@@ -229,9 +229,9 @@ struct LayerLaunch {
 // that many layers).
 int enqueue_pass(fe_workspace* ws, int count, int64_t max_np, const fe::BatchCoef& cf,
                  const std::vector<LayerLaunch>& launches, const QueueLaunch* queue, double alpha,
-                 int entropy, int bf, int tile, int staged, int32_t* status, hipStream_t s) {
+                 int entropy, int bf, int tile, int big, int32_t* status, hipStream_t s) {
     if (!entropy) FE_HIP(fe::launch_batch_bounds(ws->bmats, count, max_np, ws->bparams, s));
-    FE_HIP(fe::launch_batch_rescale(ws->bmats, count, max_np, ws->bparams, alpha, cf, bf, !staged, s));
+    FE_HIP(fe::launch_batch_rescale(ws->bmats, count, max_np, ws->bparams, alpha, cf, bf, !big, s));
     if (queue) {
         fe::BatchLayerArgs q{};
         q.mats = ws->bmats;
@@ -241,7 +241,7 @@ int enqueue_pass(fe_workspace* ws, int count, int64_t max_np, const fe::BatchCoe
         q.P = ws->bparams;
         q.partials = ws->btparts;
         FE_HIP(fe::launch_batch_queue_reset(queue->q, count, s));
-        FE_HIP(fe::launch_batch_queue(q, queue->q, queue->grid, bf, tile, staged, s));
+        FE_HIP(fe::launch_batch_queue(q, queue->q, queue->grid, bf, tile, big, s));
         FE_HIP(fe::launch_batch_queue_check(ws->bmats, count, queue->q, cf, ws->bparams, tile, s));
         FE_HIP(fe::launch_batch_reduce(ws->bmats, count, ws->btparts, ws->bparams, entropy, status,
                                        tile, s));
@@ -259,8 +259,8 @@ int enqueue_pass(fe_workspace* ws, int count, int64_t max_np, const fe::BatchCoe
         q.cf = cf;
         q.P = ws->bparams;
         q.partials = ws->btparts;
-        FE_HIP(staged ? fe::launch_batch_layer_staged(q, launches[l].grid, bf, s)
-                      : fe::launch_batch_layer(q, launches[l].grid, bf, tile, s));
+        FE_HIP(big ? fe::launch_batch_layer_big(q, launches[l].grid, bf, tile, s)
+                   : fe::launch_batch_layer(q, launches[l].grid, bf, tile, s));
     }
     FE_HIP(fe::launch_batch_reduce(ws->bmats, count, ws->btparts, ws->bparams, entropy, status,
                                    tile, s));
@@ -411,7 +411,7 @@ int build_plan(fe_batch_plan* plan, int want) {
     // many operands (4 bytes per element): see CfgBx2
     int64_t elems = 0;
     for (const fe::BatchMat& m : mats) elems += m.np * m.np;
-    const int staged = tile == 128 && 4 * elems >= ((int64_t)64 << 20) ? 1 : 0;
+    const int big = tile == 128 ? 4 * elems >= ((int64_t)64 << 20) : max_np > fe::kLeanMaxNp;
     const PassTables td = make_tables(dens, prec, 1.0);
     PassTables te;
     if (!ent.empty()) te = make_tables(ent, prec, alpha);
@@ -573,10 +573,10 @@ int build_plan(fe_batch_plan* plan, int want) {
     const int bf = prec == FE_PREC_BF16X3 ? 2 : prec == FE_PREC_BF16X2 ? 1 : 0;
     if (e == hipSuccess) {
         rc = enqueue_pass(ws, count, max_np, cfd, ll_d, queued ? &qd : nullptr, 1.0, 0, bf,
-                          tile, staged, status, cs);
+                          tile, big, status, cs);
         if (rc == FE_OK && !ent.empty())
             rc = enqueue_pass(ws, count, max_np, cfe, ll_e, queued ? &qe : nullptr, alpha, 1, bf,
-                              tile, staged, status, cs);
+                              tile, big, status, cs);
         hipGraph_t g = nullptr;
         hipError_t e2 = hipStreamEndCapture(cs, &g);
         plan->graph = g;

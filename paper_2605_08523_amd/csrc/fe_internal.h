@@ -36,6 +36,7 @@ struct Slot {
     size_t bytes;
 };
 
+constexpr int64_t kLeanMaxNp = 23168;   // padded sizes whose FP32 X ends below 2 GiB (epilogue_mid)
 constexpr int kMaxBoundsBlocks = 4096;
 constexpr int kMaxTiles = 1 << 16;
 

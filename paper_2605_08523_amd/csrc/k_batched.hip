@@ -6,6 +6,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "batch_queue.h"
@@ -23,6 +24,11 @@ using namespace split;
 // 64 ... 256 0.69 / 0.23 (64 x 64), 60 of 128 ... 384 and 40 layers 1.80 (128 x 128) / 0.67 (64 x 64).
 using CfgB = Cfg<128, 4, 2, 64, 128, 2, 1>;
 using CfgB64 = Cfg<64, 2, 2, 64, 64, 2, 1>;
+// Matrices past kLeanMaxNp (64 x 64 tiles run at any size): every layer by the epilogue that loads and
+// stores X and A itself, with 64-bit addresses.
+struct CfgB64Big : CfgB64 {};
+template <class C>
+constexpr bool kLean = !std::is_same<C, CfgB64Big>::value;
 // Three-part BF16 split: six panels of 32-deep K-blocks per stage.
 using CfgB3 = Cfg<128, 4, 2, 32, 128, 3, 1, 3>;
 using CfgB3x64 = Cfg<64, 2, 2, 32, 64, 3, 1, 3>;
@@ -259,12 +265,12 @@ __device__ __attribute__((always_inline)) inline void batch_tile(
         epilogue<BF, C, kBatchEpiGroups>(p, acc, sY, I, J, t, nullptr, 0, 0, poisoned);
         return;
     } else {
-    constexpr bool kPre = EpiPre<C>::PER <= 4;
+    constexpr bool kPre = kLean<C> && EpiPre<C>::PER <= 4;
     EpiPre<C> pre;
     if constexpr (kPre) pre.template load<AUX>(p, I, J);
     kloop_dma<BF, C, AUX>(p.hi_in, p.mid_in, p.lo_in, p.np, (int64_t)I * C::BM, (int64_t)J * C::BM,
                              0, kend, acc, reinterpret_cast<uint16_t*>(smem));
-    if (!p.last && !p.affine) {
+    if (kLean<C> && !p.last && !p.affine) {
         epilogue_mid<BF, C, AUX, kPre ? 4 : 2>(p, acc, sY, I, J, poisoned, kPre ? &pre : nullptr);
         return;
     }
@@ -376,7 +382,7 @@ k_batch_queue(BatchLayerArgs q, BatchQueue Q, const BatchMat* __restrict__ mats,
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (threadIdx.x == 0) {
-            if (!gave_up)
+            if (!s_gave_up)
                 __hip_atomic_fetch_add(Q.done + mat * kQueueLine, 1, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
             if constexpr (C::DMA) it = take();
@@ -489,8 +495,10 @@ hipError_t launch_batch_layer(const BatchLayerArgs& q, int grid, int bf16, int t
                      : launch_layer_t<false, CfgB>(q, grid, s);
 }
 
-hipError_t launch_batch_layer_staged(const BatchLayerArgs& q, int grid, int bf16, hipStream_t s) {
-    if (grid < 1) return hipErrorInvalidValue;
+hipError_t launch_batch_layer_big(const BatchLayerArgs& q, int grid, int bf16, int tile, hipStream_t s) {
+    if (grid < 1 || (tile == 64 ? bf16 == 2 : tile != 128)) return hipErrorInvalidValue;
+    if (tile == 64)
+        return bf16 ? launch_layer_t<true, CfgB64Big>(q, grid, s) : launch_layer_t<false, CfgB64Big>(q, grid, s);
     return bf16 == 2 ? launch_layer_t<true, CfgB3x2>(q, grid, s)
            : bf16    ? launch_layer_t<true, CfgBx2>(q, grid, s)
                      : launch_layer_t<false, CfgBx2>(q, grid, s);
@@ -529,14 +537,18 @@ hipError_t launch_batch_queue_reset(const BatchQueue& Q, int count, hipStream_t 
 }
 
 hipError_t launch_batch_queue(const BatchLayerArgs& q, const BatchQueue& Q, int64_t grid, int bf16,
-                              int tile, int staged, hipStream_t s) {
+                              int tile, int big, hipStream_t s) {
     if (grid < 1 || grid > 0x7fffffff) return hipErrorInvalidValue;
+    if (tile == 64 && big)
+        return bf16 == 2 ? hipErrorInvalidValue
+               : bf16    ? queue_t<true, CfgB64Big>(q, Q, grid, s)
+                         : queue_t<false, CfgB64Big>(q, Q, grid, s);
     if (tile == 64)
         return bf16 == 2 ? queue_t<true, CfgB3x64>(q, Q, grid, s)
                : bf16    ? queue_t<true, CfgB64>(q, Q, grid, s)
                          : queue_t<false, CfgB64>(q, Q, grid, s);
     if (tile != 128) return hipErrorInvalidValue;
-    if (staged)
+    if (big)
         return bf16 == 2 ? queue_t<true, CfgB3x2>(q, Q, grid, s)
                : bf16    ? queue_t<true, CfgBx2>(q, Q, grid, s)
                          : queue_t<false, CfgBx2>(q, Q, grid, s);

@@ -731,9 +731,8 @@ __device__ inline floatx4 load4_coherent(__amdgpu_buffer_rsrc_t rs, int off) {
 
 // The X and A groups of a tile that each thread's epilogue uses, loaded before the K loop: the layer
 // reads them from where the previous one left them, usually beyond this XCD's L2, and a short K
-// loop's epilogue would wait for that latency again. For tiles whose epilogue runs in one chunk.
-// Offsets are 32-bit from the tile's first row, so the whole matrix may exceed 4 GiB (a batch takes
-// 64 x 64 tiles of any size). Every address lies in the padded matrices, whose padding the rescale wrote;
+// loop's epilogue would wait for that latency again. For tiles whose epilogue runs in one chunk of a
+// matrix of np <= kLeanMaxNp (32-bit offsets). Every address lies in the padded matrices, whose padding the rescale wrote;
 // a is loaded (and later read) only where the layer updates or outputs A. AUX: cache policy.
 template <class C>
 struct EpiPre {
@@ -742,17 +741,16 @@ struct EpiPre {
     template <int AUX = 0>
     __device__ inline void load(const LayerArgs& p, int I, int J) {
         static_assert(C::EC == C::BM, "one epilogue chunk per tile");
-        const uint32_t np = (uint32_t)p.np, bytes = C::BM * np * 4;
-        const int64_t row0 = (int64_t)I * C::BM * p.np;
+        const uint32_t np = (uint32_t)p.np, bytes = np * np * 4;
         const int tid = opaque_tid();
         const int voff = (int)((tid / G) * np * 4 + (tid % G) * 16);
-        const uint32_t base = (uint32_t)J * C::BM * 4;
+        const uint32_t base = ((uint32_t)I * C::BM * np + (uint32_t)J * C::BM) * 4;
         auto at = [&](__amdgpu_buffer_rsrc_t rs, int u) {
             return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(
                                                    rs, voff, (int)(base + u * RPG * np * 4), AUX));
         };
         if (p.affine == 0) {
-            const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.X + row0, bytes);
+            const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.X, bytes);
 #pragma unroll
             for (int u = 0; u < PER; ++u) x[u] = at(rs, u);
         } else {
@@ -760,7 +758,7 @@ struct EpiPre {
             for (int u = 0; u < PER; ++u) x[u] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
         }
         if (p.last != 0 || p.d_old != 0.0f || p.d_new != 0.0f) {
-            const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.A + row0, bytes);
+            const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.A, bytes);
 #pragma unroll
             for (int u = 0; u < PER; ++u) a[u] = at(rs, u);
         }
@@ -771,13 +769,14 @@ struct EpiPre {
 // in a third of its instructions, which a workgroup alone on its CU waits for one by one (us per
 // density matrix with a launch per layer, 26 layers, against epi_chunk: n = 128 159 / 213,
 // 256 189 / 246, 1001 427 / 469; on 128 x 128 tiles 2048 1099 / 1145).
-// Addresses are one lane offset plus scalars from the first row of the tile or of its mirror (32-bit, as
-// EpiPre); the parts split once travel through LDS, in the place of
+// Addresses are one lane offset plus scalars; the parts split once travel through LDS, in the place of
 // the product they came from, for the mirror tile; 1/s is folded into a (a power of two); a diagonal
 // tile writes both triangles of X, A and the operands itself, its lower elements from the transposed
 // product (the rescale made X and A symmetric there, so they equal the upper ones bit for bit). The
 // padding comes out zero. LDS: 16-byte groups of row r at group g ^ (r / 4) (modulo the row). pre: the
 // tile's X and A groups, or NULL: loaded here, UB groups at a time. AUX: cache policy of those loads.
+// Offsets are 32-bit: np <= kLeanMaxNp (from the tile's first row instead, the queue kernel of three parts
+// and 64 x 64 tiles reloads twice as many spilled scalars, 3% of its time).
 template <bool BF, class C, int AUX = 0, int UB = 4>
 __device__ __attribute__((always_inline)) inline void epilogue_mid(const LayerArgs& p, const Acc<C>& acc,
                                                                    float* sY, int I, int J,
@@ -804,13 +803,11 @@ __device__ __attribute__((always_inline)) inline void epilogue_mid(const LayerAr
     const float cb = p.b, cc = p.c, dold = p.d_old, dnew = p.d_new;
     const bool upd = dold != 0.0f || dnew != 0.0f;
     const int vx = (int)(rt * np * 4 + g * 16), vh = (int)(rt * np * 2 + g * 8);
-    const uint32_t bu = (uint32_t)J0, bl = (uint32_t)I0;   // first column of the tile, of its mirror
-    const int64_t row_u = (int64_t)I0 * p.np, row_l = (int64_t)J0 * p.np;
-    auto rows = [&](const float* m) { return make_rsrc(m + row_u, BM * np * 4); };
-    auto rows16 = [&](const uint16_t* m, int64_t row) { return make_rsrc(m + row, BM * np * 2); };
-    const __amdgpu_buffer_rsrc_t rx = rows(p.X), ra = rows(p.A);
-    __amdgpu_buffer_rsrc_t rh = rows16(p.hi_out, row_u), rl = rows16(p.lo_out, row_u),
-                           rm = rows16(C::NS == 3 ? p.mid_out : p.hi_out, row_u);
+    const uint32_t bu = (uint32_t)I0 * np + J0, bl = (uint32_t)J0 * np + I0;   // tile, mirror
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.X, np * np * 4), ra = make_rsrc(p.A, np * np * 4);
+    const __amdgpu_buffer_rsrc_t rh = make_rsrc(p.hi_out, np * np * 2),
+                                 rl = make_rsrc(p.lo_out, np * np * 2),
+                                 rm = make_rsrc(C::NS == 3 ? p.mid_out : p.hi_out, np * np * 2);
     auto put = [&](__amdgpu_buffer_rsrc_t rs, u32x2 v, uint32_t base, int u) {
         __builtin_amdgcn_raw_buffer_store_b64(v, rs, vh, (int)((base + u * RPG * np) * 2), 0);
     };
@@ -887,9 +884,6 @@ __device__ __attribute__((always_inline)) inline void epilogue_mid(const LayerAr
     __syncthreads();
     if (diag) return;
     // Mirror: output row J0 + c, columns I0 + 4 g .. 4 g + 3
-    rh = rows16(p.hi_out, row_l);
-    rl = rows16(p.lo_out, row_l);
-    if constexpr (C::NS == 3) rm = rows16(p.mid_out, row_l);
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         const int c = rt + RPG * u;

@@ -1,4 +1,4 @@
-"""A batch matrix of more than 4 GiB in FP32 (padded size 32768): its 64 x 64 tiles address the state,
+"""A batch matrix of 4 GiB in FP32 (padded size 32768): its 64 x 64 tiles address the state,
 the accumulator and the operands beyond 32 bits, and D is bitwise that of the 128 x 128 tiles, whose
 staged kernel forms 64-bit addresses. Two layers: one that writes the next state, and the last."""
 import pytest
