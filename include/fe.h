@@ -247,7 +247,7 @@ int fe_batch_plan_launch(fe_batch_plan* plan, void* stream);
 /* Rebuilds the plan (layout, tables, captured graph) with layer tiles of `tile` x `tile`, tile
  * 128 or 64 (less padding for small matrices, more LDS traffic per flop). A new plan's tile is 128,
  * and until one of this function and the autotuner is called its kernel takes the 128 x 128 tiles in
- * 64 x 64 pieces where the sizes make that less work (fe_batch_plan_kernel_tile tells). The tile of an
+ * 64 x 64 pieces where the sizes make that faster (fe_batch_default_tile; fe_batch_plan_kernel_tile tells). The tile of an
  * FE_PREC_BF16X3 plan stays 128. Results differ from the other tile size at
  * most by the order of FP32 sums. Waits for the device first (a launch of the plan may be in flight), then
  * replaces the captured graph; on failure the plan is left empty and its launches fail. */
@@ -288,6 +288,11 @@ int fe_batch_plan_get(const fe_batch_plan* plan, int32_t* tile, int32_t* launch)
 /* The tile size that the plan's layer kernel runs (host): the plan's tile, or 64 where a plan of tile
  * 128 takes its tiles in 64 x 64 pieces. */
 int fe_batch_plan_kernel_tile(const fe_batch_plan* plan, int32_t* tile);
+/* The rule behind it (host, no device work; for tests): the tile, 64 or 128, that the kernel of an untuned plan
+ * runs for `count` matrices of sizes n[] with up to max_L layers, created in the given launch form, at precision
+ * prec on a device of n_cu compute units. */
+int fe_batch_default_tile(int32_t count, const int64_t* n, int32_t max_L, int32_t launch, int32_t prec,
+                          int32_t n_cu, int32_t* tile);
 int fe_batch_plan_destroy(fe_batch_plan* plan);
 
 /* One-shot batch: create a plan, launch it on `stream`, wait for the stream, destroy the plan. */

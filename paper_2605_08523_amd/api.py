@@ -89,6 +89,7 @@ SIGNATURES = {
     "fe_batch_plan_set_launch": (_I32, [_P, _I32]),
     "fe_batch_plan_get": (_I32, [_P, C.POINTER(_I32), C.POINTER(_I32)]),
     "fe_batch_plan_kernel_tile": (_I32, [_P, C.POINTER(_I32)]),
+    "fe_batch_default_tile": (_I32, [_I32, C.POINTER(_I64), _I32, _I32, _I32, _I32, C.POINTER(_I32)]),
     "fe_batch_plan_autotune": (_I32, [_P, _P, C.POINTER(_I32), C.POINTER(_D)]),
     "fe_autotune": (_I32, [C.POINTER(_I64), _I32, _I32, C.POINTER(_I32), C.POINTER(_D), _P, _P]),
     "fe_autotune_input": (_I32, [_P, _I64, _I64, _D, _D, C.POINTER(fe_model), _I32, C.POINTER(_I32),
@@ -524,6 +525,15 @@ def batch_queue_layout(np_list, L_list, tile: int, nq: int):
                                        items.ctypes.data_as(C.POINTER(C.c_int32)), n.value,
                                        qoff.ctypes.data_as(C.POINTER(C.c_int32)), C.byref(n)))
     return items[:n.value], qoff
+
+
+def batch_default_tile(sizes, layers: int, launch: str, prec: str = "fp16x2", n_cu: int = 256) -> int:
+    """fe_batch_default_tile: the tile that the kernel of an untuned batch plan runs (host only)."""
+    n = (C.c_int64 * len(sizes))(*[int(v) for v in sizes])
+    tile = C.c_int32()
+    _check(lib().fe_batch_default_tile(len(sizes), n, int(layers), BATCH_LAUNCH[launch], PREC[prec],
+                                       int(n_cu), C.byref(tile)))
+    return tile.value
 
 
 def debug_batch_queue_giveup(enable: bool) -> None:

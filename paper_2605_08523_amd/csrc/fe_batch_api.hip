@@ -24,7 +24,7 @@ struct fe_batch_plan {
     uint64_t gen = 0;       // workspace layout generation this plan was built for
     int count = 0;
     int tile = 128;         // tile size of the plan (128 or 64)
-    bool by_size = true;    // 128 not asked for: tiles in 64 x 64 pieces where that is less work
+    bool by_size = true;    // 128 not asked for: tiles in 64 x 64 pieces where that is faster (batch_tile)
     int kernel_tile = 128;  // tile size of the layer kernel
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -357,30 +357,61 @@ void release_plan(fe_batch_plan* plan) {
     plan->queues = nullptr;
 }
 
-// Tile of the layer kernel of a plan that leaves it open. Small matrices waste much of their 128 x 128
-// tiles; a 64 x 64 tile takes longer per element (its operand panels pass through LDS twice as often). The
-// rule compares the tiles that hold data; the kernel also runs the 64 x 64 tiles between the last of those
-// and the padded size (a multiple of 128), so the line is fitted to times that include them, not derived.
-// us per batch with 128 / 64 tiles, and the ratio of that work: 60 matrices of
-// n 64 ... 768 1367 / 1513 (1.19), 30 of 16 ... 768 630 / 730 (1.22), 8 of 128 ... 768 634 / 771 (1.25);
-// 60 of 128 ... 384 719 / 672 (1.36), 12 of 128 ... 512 400 / 372 (1.37), 30 of 64 ... 256 311 / 228 (1.38).
-// The work table of the queue launch (16 bytes per item) bounds it: at most 64 MiB with 64 x 64 tiles.
-int tile_by_size(const std::vector<fe_batch_item>& items, int max_L) {
-    double w128 = 0.0, w64 = 0.0, tiles64 = 0.0;
-    for (const fe_batch_item& it : items) {
-        const double n = (double)it.n, T = (double)((it.n + 127) / 128), t = (double)((it.n + 63) / 64);
-        w128 += 0.5 * T * (T + 1.0) * 4.0 * n;
-        w64 += 0.5 * t * (t + 1.0) * n;
-        tiles64 += T * (2.0 * T + 1.0);
-    }
-    return w128 > 1.3 * w64 && tiles64 * max_L <= (double)(1 << 22) ? 64 : 128;
-}
+// Whether the layers of a batch take the register-staged 128 x 128 launches (many operands, 4 bytes per
+// element: see CfgBx2).
+bool staged_size(int64_t elems) { return 4 * elems >= ((int64_t)64 << 20); }
 
+// Tile of the layer kernel of a plan that leaves it open, created in the given launch form: 64 x 64 tiles have more
+// workgroups (two per CU) with less padding, 128 x 128 ones half the operand traffic per element. np is a
+// multiple of 128 for both, so a matrix of T x T tiles of 128 has T (2 T + 1) upper ones of 64. Measured
+// ms per batch with 128 / 64 over batches of one size (26 layers, two parts unless stated, 256 CUs):
+//  - all 64 x 64 tiles of an XCD at once (launch per layer: of every XCD; queue: on average): always 64.
+//    12 x 140 0.28 / 0.22, 24 x 300 0.39 / 0.32, 8 x 500 0.45 / 0.34, 5 x 520 0.52 / 0.39; past it with a
+//    launch per layer 128: 9 x 500 0.50 / 0.54, 14 x 520 0.56 / 0.66; and 128 in batches of up to 1.75 such
+//    rounds whose largest matrix alone is more than one (n > 640): it sets the time, 4 x 700 0.57 / 0.66;
+//  - batches of the staged launches: 128. 288 x 140 0.99 / 1.41, 128 x 300 (three parts) 3.81 / 4.36,
+//    72 x 400 1.38 / 1.67, 128 x 520 3.19 / 4.05 (against it: 1000 x 250 7.08 / 6.29);
+//  - between them by the ratio of work, 2 (T + 1) / (2 T + 1): 1.33, 1.2, 1.14, 1.11, 1.09 ... 800 x 70 0.96 /
+//    0.87, 200 x 200 0.97 / 0.95, 40 x 300 0.46 / 0.44, 88 x 300 0.99 / 0.95 (three parts 1.24 / 1.33), 20 x 400
+//    0.49 / 0.47, 32 x 400 0.65 / 0.68 (three parts 20 x 500 0.77 / 0.79), 12 x 520 0.55 / 0.56.
+// The work table of the queue launch (16 bytes per item) bounds it: at most 64 MiB with 64 x 64 tiles.
+int batch_tile(std::vector<int64_t> n, int max_L, int launch, bool three, int cus) {
+    std::sort(n.begin(), n.end(), [](int64_t x, int64_t y) { return x > y; });
+    double w128 = 0.0, w64 = 0.0, tiles = 0.0;
+    int64_t elems = 0, at_once[kXcds] = {};
+    double load[kXcds] = {};
+    for (int64_t v : n) {
+        const int64_t np = round_up(v, (int64_t)fe::kBatchPad), T = np / 128, t64 = T * (2 * T + 1);
+        elems += np * np;
+        w128 += 2.0 * T * (T + 1) * v;
+        w64 += (double)t64 * v;
+        tiles += (double)t64;
+        const int x = (int)(std::min_element(load, load + kXcds) - load);   // dealt as deal_queues does
+        load[x] += (double)t64 * np;
+        at_once[x] += t64;
+    }
+    if (staged_size(elems) || tiles * max_L > (double)(1 << 22)) return 128;
+    const double slots = 2.0 * cus / kXcds;   // 64 x 64 workgroups of an XCD
+    if (launch == FE_BATCH_LAUNCH_LAYERS)
+        return (double)*std::max_element(at_once, at_once + kXcds) <= slots ? 64 : 128;
+    const double rounds = tiles / kXcds / slots;
+    const int64_t T0 = round_up(n[0], (int64_t)fe::kBatchPad) / 128;
+    if (rounds <= 1.75 && T0 * (2 * T0 + 1) > slots) return 128;
+    if (rounds <= 1.0) return 64;
+    const double line = three ? (rounds <= 1.75 ? 1.14 : 1.16) : (rounds <= 1.75 ? 1.10 : 1.13);
+    return w128 > line * w64 ? 64 : 128;
+}
+// In the form chosen at creation, so that the traces, summed by tile, do not change with set_launch.
 int tile_by_size(const fe_batch_plan& plan) {
-    int max_L = 1;
+    int max_L = 1, dev = 0, cus = 0;
     for (const fe_model& m : plan.dens) max_L = std::max(max_L, (int)m.L);
     for (const fe_model& m : plan.ent) max_L = std::max(max_L, (int)m.L);
-    return tile_by_size(plan.items, max_L);
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        cus = 256;
+    std::vector<int64_t> n;
+    for (const fe_batch_item& it : plan.items) n.push_back(it.n);
+    return batch_tile(n, max_L, plan.default_launch, plan.prec == FE_PREC_BF16X3, cus);
 }
 
 // Builds and captures `plan` for its stored inputs with layer tiles of `want` (128 or 64): item i
@@ -408,10 +439,9 @@ int build_plan(fe_batch_plan* plan, int want) {
     int64_t tiles = 0, max_np = 0;
     std::vector<fe::BatchMat> mats = layout(items, order, model, dens, ws, tile, prec, &tiles, &max_np);
     if (tiles > ws->batch_tiles) return fail(FE_ERR_WORKSPACE, "batch has too many tiles for the workspace");
-    // many operands (4 bytes per element): see CfgBx2
     int64_t elems = 0;
     for (const fe::BatchMat& m : mats) elems += m.np * m.np;
-    const int big = tile == 128 ? 4 * elems >= ((int64_t)64 << 20) : max_np > fe::kLeanMaxNp;
+    const int big = tile == 128 ? staged_size(elems) : max_np > fe::kLeanMaxNp;
     const PassTables td = make_tables(dens, prec, 1.0);
     PassTables te;
     if (!ent.empty()) te = make_tables(ent, prec, alpha);
@@ -845,6 +875,17 @@ int fe_batch_plan_get(const fe_batch_plan* plan, int32_t* tile, int32_t* launch)
 int fe_batch_plan_kernel_tile(const fe_batch_plan* plan, int32_t* tile) {
     if (!plan || !tile) return fail(FE_ERR_ARG, "plan and tile are required");
     *tile = plan->kernel_tile;
+    return FE_OK;
+}
+
+int fe_batch_default_tile(int32_t count, const int64_t* n, int32_t max_L, int32_t launch, int32_t prec,
+                          int32_t n_cu, int32_t* tile) {
+    if (count < 1 || !n || !tile || max_L < 1 || n_cu < 1) return fail(FE_ERR_ARG, "bad arguments");
+    if (launch != FE_BATCH_LAUNCH_LAYERS && launch != FE_BATCH_LAUNCH_QUEUE)
+        return fail(FE_ERR_ARG, "launch must be FE_BATCH_LAUNCH_LAYERS or FE_BATCH_LAUNCH_QUEUE");
+    for (int i = 0; i < count; ++i)
+        if (n[i] < 1) return fail(FE_ERR_ARG, "n must be >= 1");
+    *tile = batch_tile({n, n + count}, max_L, launch, prec == FE_PREC_BF16X3, n_cu);
     return FE_OK;
 }
 

@@ -1,5 +1,5 @@
-"""Which tile the layer kernel of a batch plan runs: 64 x 64 pieces by size on both sides of the line,
-what retile asked for afterwards, and what the tuner chose. A three-part BF16 plan's tuner times the
+"""Which tile the layer kernel of a batch plan runs: 64 x 64 pieces by size on both sides of its lines,
+the same whichever launch form is set, what retile asked for afterwards, and what the tuner chose. A three-part BF16 plan's tuner times the
 pieces too, so tuning cannot lose the faster form that a new plan starts with (30 matrices of one or two
 tiles: 1.3 times as fast); the result is the same."""
 import ctypes
@@ -27,13 +27,17 @@ def batch(ns):
 
 
 @pytest.mark.parametrize("prec", ["fp16x2", "bf16x3"])
-@pytest.mark.parametrize("n,tile", [(64, 64), (256, 128), (513, 64), (641, 128)])
-def test_tile_by_size(api, paper_model, n, tile, prec):
-    print(f"case n={n} {prec}", flush=True)
-    plan = api.BatchPlan(batch([n, n]), paper_model, prec=prec)
-    assert plan.tile == 128 and plan.kernel_tile == tile
-    plan.set_launch("queue")
-    assert plan.kernel_tile == tile
+@pytest.mark.parametrize("n,count,form,tile", [(64, 2, "layers", 64), (640, 2, "layers", 64), (641, 2, "layers", 128),
+                                               (500, 9, "layers", 128), (500, 13, "queue", 64),
+                                               (500, 40, "queue", 128)])
+def test_tile_by_size(api, paper_model, n, count, form, tile, prec):
+    print(f"case n={n} count={count} {prec}", flush=True)
+    plan = api.BatchPlan(batch([n] * count), paper_model, prec=prec)
+    assert plan.launch_form == form
+    assert api.batch_default_tile([n] * count, paper_model.L, form, prec) == tile
+    for other in (form, "layers", "queue"):
+        assert plan.tile == 128 and plan.kernel_tile == tile
+        plan.set_launch(other)
     plan.retile(128)
     assert plan.tile == 128 and plan.kernel_tile == 128
     if prec == "fp16x2":
