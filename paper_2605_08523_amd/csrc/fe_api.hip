@@ -93,7 +93,7 @@ int use_streamk(int64_t n, const fe_workspace* ws, int prec) {
     if (t_forced_schedule >= 0) return t_forced_schedule;
     const char* env = getenv("FE_SCHEDULE");
     if (env && env[0] == 'd') return 0;
-    if (env && env[0] == 's') return strncmp(env, "sk2", 3) == 0 ? 2 : 1;
+    if (env && env[0] == 's') return strcmp(env, "sk2") == 0 || strcmp(env, "sk2-handover") == 0 ? 2 : 1;
     const int tuned = tuned_schedule(ws->device, prec, n, ws->n_cu);
     if (tuned >= 0) return tuned;
     return fe::split_schedule(n, ws->n_cu);

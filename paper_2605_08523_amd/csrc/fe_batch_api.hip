@@ -401,6 +401,7 @@ int batch_tile(std::vector<int64_t> n, int max_L, int launch, bool three, int cu
     const double line = three ? (rounds <= 1.75 ? 1.14 : 1.16) : (rounds <= 1.75 ? 1.10 : 1.13);
     return w128 > line * w64 ? 64 : 128;
 }
+
 // In the form chosen at creation, so that the traces, summed by tile, do not change with set_launch.
 int tile_by_size(const fe_batch_plan& plan) {
     int max_L = 1, dev = 0, cus = 0;
